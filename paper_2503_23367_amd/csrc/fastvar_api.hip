@@ -196,13 +196,27 @@ struct Rope {
     const float* sin;
 };
 
+// The arrival counters of the split-K scratch (GEMM) and of the key-range split (attention) must be zero
+// before the first kernel that uses them; every such kernel leaves them zero again, so once per
+// entry-point call is enough: the call's first LayerNorm launch does it.
+fv::ZeroCounters split_counters(void* ws, const BlockPlan& bp) {
+    fv::ZeroCounters zc;
+    char* base = static_cast<char*>(ws);
+    if (bp.sk_bytes) { zc.a = reinterpret_cast<int32_t*>(base + bp.off_sk); zc.na = bp.sk_counters; }
+    if (bp.asplit_bytes) { zc.b = reinterpret_cast<int32_t*>(base + bp.off_asplit); zc.nb = bp.asplit_counters; }
+    return zc;
+}
+
 // Attention half of the block on the kept tokens: h1 = x[idx] + proj(attn(LN1(x[idx]))).
 // Scratch used: a, q, rows of the block plan.
 // `scatter`: h1_out is a [B, N, D] map and row m goes to the kept token's own row of it.
+// `clear`: this is the call's first use of the scratch, so its counters have to be cleared.
 void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                   const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* h1_out, void* ws,
-                  hipStream_t st, bool scatter = false, const Fill* fill = nullptr, const Rope* rope = nullptr) {
+                  hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
+                  const Rope* rope = nullptr) {
     const BlockPlan bp = block_plan(d, B, k);
+    const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
     void* buf_a = base + bp.off_a;
     void* buf_q = base + bp.off_q;
@@ -214,11 +228,11 @@ void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const 
     if (idx && fill)
         fv::launch_gather_layernorm_fill(x, idx, B, N, k, d->D, w->ln1_g, w->ln1_b, d->ln_eps, rows, buf_a,
                                          fill->rank, fill->cache_map, fill->hc, fill->wc, fill->h, fill->w,
-                                         fill->y_out, st);
+                                         fill->y_out, zc, st);
     else if (idx)
-        fv::launch_gather_layernorm(x, idx, B, N, k, d->D, w->ln1_g, w->ln1_b, d->ln_eps, rows, buf_a, st);
+        fv::launch_gather_layernorm(x, idx, B, N, k, d->D, w->ln1_g, w->ln1_b, d->ln_eps, rows, buf_a, zc, st);
     else
-        fv::launch_layernorm(x, M, d->D, w->ln1_g, w->ln1_b, d->ln_eps, buf_a, st);
+        fv::launch_layernorm(x, M, d->D, w->ln1_g, w->ln1_b, d->ln_eps, buf_a, zc, st);
     mark(st, FASTVAR_STAGE_LN1);
     // q | k | v = a1 * Wqkv^T + b ; k, v appended to the caches at [L0, L0+k)
     fv::GemmArgs g{};
@@ -255,9 +269,10 @@ void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const 
 // `scatter_rows`: y is a [B, N, D] map and row m goes to row scatter_rows[m] of it (the absolute row of
 // the kept token, as left in the plan's row list by the gather).
 void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
-                 const fastvar_block_weights* w, void* y, void* ws, hipStream_t st, bool scatter = false,
+                 const fastvar_block_weights* w, void* y, void* ws, hipStream_t st, bool clear, bool scatter = false,
                  const Fill* fill = nullptr) {
     const BlockPlan bp = block_plan(d, B, k);
+    const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
     void* buf_q = base + bp.off_q;
     void* buf_u = base + bp.off_u;
@@ -269,11 +284,11 @@ void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const
     if (idx && fill)
         fv::launch_gather_layernorm_fill(src, idx, B, N, k, d->D, w->ln2_g, w->ln2_b, d->ln_eps, rows, buf_q,
                                          fill->rank, fill->cache_map, fill->hc, fill->wc, fill->h, fill->w,
-                                         fill->y_out, st);
+                                         fill->y_out, zc, st);
     else if (idx)
-        fv::launch_gather_layernorm(src, idx, B, N, k, d->D, w->ln2_g, w->ln2_b, d->ln_eps, rows, buf_q, st);
+        fv::launch_gather_layernorm(src, idx, B, N, k, d->D, w->ln2_g, w->ln2_b, d->ln_eps, rows, buf_q, zc, st);
     else
-        fv::launch_layernorm(src, M, d->D, w->ln2_g, w->ln2_b, d->ln_eps, buf_q, st);
+        fv::launch_layernorm(src, M, d->D, w->ln2_g, w->ln2_b, d->ln_eps, buf_q, zc, st);
     mark(st, FASTVAR_STAGE_LN2);
     // u = gelu(a2 * W1^T + b1)
     fv::GemmArgs f1{};
@@ -292,26 +307,13 @@ void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const
     mark(st, FASTVAR_STAGE_FC2);
 }
 
-// `scatter`: y is the [B, N, D] output map and the kept tokens' outputs go straight to their own rows
-// (the row list written by the gather of the attention half is still in the plan when FC2 runs).
-// The arrival counters of the split-K scratch (GEMM) and of the key-range split (attention) must be zero
-// before the first kernel that uses them; every such kernel leaves them zero again, so once per
-// entry-point call is enough.
-void zero_splitk_counters(void* ws, const fastvar_dims* d, int B, int k, hipStream_t st) {
-    if (k <= 0) return;
-    const BlockPlan bp = block_plan(d, B, k);
-    if (bp.sk_bytes)
-        fv::launch_zero_i32(reinterpret_cast<int32_t*>(static_cast<char*>(ws) + bp.off_sk), bp.sk_counters, st);
-    if (bp.asplit_bytes)
-        fv::launch_zero_i32(reinterpret_cast<int32_t*>(static_cast<char*>(ws) + bp.off_asplit), bp.asplit_counters, st);
-}
-
 void enqueue_block(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                    const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* y, void* ws,
-                   hipStream_t st, bool scatter = false, const Fill* fill = nullptr, const Rope* rope = nullptr) {
+                   hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
+                   const Rope* rope = nullptr) {
     void* buf_h1 = static_cast<char*>(ws) + block_plan(d, B, k).off_h1;
-    enqueue_attn(x, N, idx, B, k, d, w, kc, vc, L0, L_cap, buf_h1, ws, st, false, idx ? fill : nullptr, rope);
-    enqueue_ffn(buf_h1, 0, nullptr, B, k, d, w, y, ws, st, scatter && idx);
+    enqueue_attn(x, N, idx, B, k, d, w, kc, vc, L0, L_cap, buf_h1, ws, st, clear, false, idx ? fill : nullptr, rope);
+    enqueue_ffn(buf_h1, 0, nullptr, B, k, d, w, y, ws, st, false, scatter && idx);
 }
 
 int check_ffn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* dims,
@@ -431,9 +433,8 @@ int fastvar_block_forward_pruned(const void* x, int N, const int32_t* idx, int B
                                ws_bytes);
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
-    zero_splitk_counters(ws, dims, B, k, static_cast<hipStream_t>(stream));
     enqueue_block(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_kept_out, ws,
-                  static_cast<hipStream_t>(stream));
+                  static_cast<hipStream_t>(stream), true);
     return launch_status();
 }
 
@@ -458,9 +459,8 @@ int fastvar_block_forward_pruned_rope(const void* x, int N, const int32_t* idx, 
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
     const Rope rope{rope_cos, rope_sin};
-    zero_splitk_counters(ws, dims, B, k, static_cast<hipStream_t>(stream));
     enqueue_block(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_kept_out, ws,
-                  static_cast<hipStream_t>(stream), false, nullptr, &rope);
+                  static_cast<hipStream_t>(stream), true, false, nullptr, &rope);
     return launch_status();
 }
 
@@ -531,14 +531,14 @@ int fastvar_step(const void* x, const int32_t* sched_h, const int32_t* sched_w, 
     if (rc) return rc;
 
     hipStream_t st = static_cast<hipStream_t>(stream);
-    zero_splitk_counters(ws_blk, dims, B, k, st);
     fv::launch_select(x, B, N, D, k, idx_out, rank, nullptr, ws_sel, fv::select_plan(B, N, D), st);
     // Restoration has no launch of its own: the pruned rows of y_out are filled by extra workgroups of the
     // gather + LayerNorm launch, the kept rows are written by the block's last GEMM.  With nothing kept
     // the step is the upsampled cache.
     const Fill fill{rank, cache_map, hc, wc, h, w, y_out};
     if (k > 0)
-        enqueue_block(x, N, idx_out, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_out, ws_blk, st, true, &fill);
+        enqueue_block(x, N, idx_out, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_out, ws_blk, st, true, true,
+                      &fill);
     else
         fv::launch_restore(nullptr, rank, B, k, cache_map, hc, wc, h, w, D, y_out, st);
     rc = launch_status();
@@ -610,13 +610,13 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h, const int32_t* sch
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const fv::SelectPlan sp = fv::select_plan(B, N, D);
-    zero_splitk_counters(ws_blk, dims, B, k, st);
     for (int l = 0; l < n_layers; ++l) {
         const fastvar_layer& ly = layers[l];
         const void* src = l == 0 ? x : dst_of(l - 1);
         void* dst = dst_of(l);
         if (dense) {
-            enqueue_block(src, N, nullptr, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk, st);
+            enqueue_block(src, N, nullptr, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk, st,
+                          l == 0);
         } else {
             fv::launch_select(src, B, N, D, k, idx_out, rank, nullptr, ws_sel, sp, st);
             mark(st, FASTVAR_STAGE_SELECT);
@@ -624,7 +624,7 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h, const int32_t* sch
             const Fill fill{rank, ly.cache_map, hc, wc, h, w, dst};
             if (k > 0) {
                 enqueue_block(src, N, idx_out, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk,
-                              st, true, &fill);
+                              st, l == 0, true, &fill);
             } else {
                 fv::launch_restore(nullptr, rank, B, k, ly.cache_map, hc, wc, h, w, D, dst, st);
                 mark(st, FASTVAR_STAGE_RESTORE);
@@ -690,9 +690,8 @@ int fastvar_attn_forward_pruned(const void* x, int N, const int32_t* idx, int B,
                                ws_bytes);
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
-    zero_splitk_counters(ws, dims, B, k, static_cast<hipStream_t>(stream));
     enqueue_attn(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, h_kept_out, ws,
-                 static_cast<hipStream_t>(stream));
+                 static_cast<hipStream_t>(stream), true);
     return launch_status();
 }
 
@@ -702,8 +701,7 @@ int fastvar_ffn_forward_pruned(const void* x, int N, const int32_t* idx, int B, 
     const int rc = check_ffn(x, N, idx, B, k, dims, weights, y_kept_out, ws, ws_bytes);
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
-    zero_splitk_counters(ws, dims, B, k, static_cast<hipStream_t>(stream));
-    enqueue_ffn(x, N, idx, B, k, dims, weights, y_kept_out, ws, static_cast<hipStream_t>(stream));
+    enqueue_ffn(x, N, idx, B, k, dims, weights, y_kept_out, ws, static_cast<hipStream_t>(stream), true);
     return launch_status();
 }
 
@@ -757,20 +755,18 @@ int fastvar_step_sublayer(const void* x, const int32_t* sched_h, const int32_t* 
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const fv::SelectPlan sp = fv::select_plan(B, N, D);
-    zero_splitk_counters(ws_blk, dims, B, k_attn, st);
     fv::launch_select(x, B, N, D, k_attn, idx_attn_out, rank, nullptr, ws_sel, sp, st);
     // each half's restoration rides in its own gather launch (pruned rows) and last GEMM (kept rows)
     const Fill fill_a{rank, cache_map_attn, hc, wc, h, w, x_mid};
     if (k_attn > 0)
         enqueue_attn(x, N, idx_attn_out, B, k_attn, dims, weights, k_cache, v_cache, L0, L_cap, x_mid, ws_blk, st, true,
-                     &fill_a);
+                     true, &fill_a);
     else
         fv::launch_restore(nullptr, rank, B, k_attn, cache_map_attn, hc, wc, h, w, D, x_mid, st);
     fv::launch_select(x_mid, B, N, D, k_ffn, idx_ffn_out, rank, nullptr, ws_sel, sp, st);
-    zero_splitk_counters(ws_blk, dims, B, k_ffn, st);   // the two halves lay the scratch out for their own k
     const Fill fill_f{rank, cache_map_ffn, hc, wc, h, w, y_out};
     if (k_ffn > 0)
-        enqueue_ffn(x_mid, N, idx_ffn_out, B, k_ffn, dims, weights, y_out, ws_blk, st, true, &fill_f);
+        enqueue_ffn(x_mid, N, idx_ffn_out, B, k_ffn, dims, weights, y_out, ws_blk, st, true, true, &fill_f);   // (the halves lay the scratch out for their own k)
     else
         fv::launch_restore(nullptr, rank, B, k_ffn, cache_map_ffn, hc, wc, h, w, D, y_out, st);
     rc = launch_status();
@@ -787,9 +783,9 @@ int fastvar_layernorm(const void* in, const int32_t* idx, int B, int N, int k, i
         return FASTVAR_EALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (idx)
-        fv::launch_gather_layernorm(in, idx, B, N, k, D, gamma, beta, eps, nullptr, out, st);
+        fv::launch_gather_layernorm(in, idx, B, N, k, D, gamma, beta, eps, nullptr, out, fv::ZeroCounters{}, st);
     else
-        fv::launch_layernorm(in, B * k, D, gamma, beta, eps, out, st);
+        fv::launch_layernorm(in, B * k, D, gamma, beta, eps, out, fv::ZeroCounters{}, st);
     return launch_status();
 }
 

@@ -732,11 +732,6 @@ void launch_cfg(GemmParams& p, hipStream_t stream) {
         <<<dim3(grid, SK ? p.splits : 1), 64 * WGM * WGN * KG, smem, stream>>>(p);
 }
 
-__global__ void zero_i32_kernel(int32_t* p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
 // Tuning builds only (-DFASTVAR_DEV_KNOBS, never the product library, which reads no environment and keeps
 // no state): FASTVAR_GEMM_CFG (all epilogues) or FASTVAR_GEMM_CFG<e> (epilogue e = 0, 1, 2) forces a tile
 // configuration; unset means the heuristic below.
@@ -889,10 +884,6 @@ SplitKPlan gemm_splitk_plan(int M, int N, int K) {
     sk.counter_bytes = sk.splits > 1 ? (size_t)kSplitKMaxTiles * 8 : 0;   // arrivals, then ready counts
     sk.bytes = sk.splits > 1 ? sk.counter_bytes + (size_t)sk.tiles * sk.splits * sk.tile_m * sk.tile_n * 4 : 0;
     return sk;
-}
-
-void launch_zero_i32(int32_t* p, int n, hipStream_t stream) {
-    if (n > 0) zero_i32_kernel<<<(n + 255) / 256, 256, 0, stream>>>(p, n);
 }
 
 void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {

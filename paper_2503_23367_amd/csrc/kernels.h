@@ -46,22 +46,31 @@ void launch_residual_accumulate(const float* r_prev, int hp, int wp, const void*
                                 float* r_out, hipStream_t stream);
 
 // ---- block pieces ----
+// Arrival counters in the caller's scratch that have to be zero before the call's first GEMM or attention launch
+// (the split-K areas; every kernel that uses them leaves them zero again).  The call's first LayerNorm launch
+// clears them on the side, which costs nothing measurable; a launch of their own cost 2.7 us each.
+struct ZeroCounters {
+    int32_t* a = nullptr;
+    int na = 0;
+    int32_t* b = nullptr;
+    int nb = 0;
+};
 // xk = x[idx] (optional copy out) and a = LayerNorm(xk); one wave per row.
 // rows_out (optional, int32 [B*k]) receives the absolute source row b*N + idx[m] of
 // every kept token, for later gathers of the same rows.
 void launch_gather_layernorm(const void* x, const int32_t* idx, int B, int N, int k, int D,
                              const void* gamma, const void* beta, float eps, int32_t* rows_out,
-                             void* a_out, hipStream_t stream);
+                             void* a_out, const ZeroCounters& zc, hipStream_t stream);
 // The same launch carrying the restoration's fill as well (Sec. 3.3, Eq. 6): extra workgroups write every
 // pruned row (rank[b,n] < 0) of y_out [B, N, D] from cache_map [B, hc*wc, D] resampled to h x w (N = h*w).
 // y_out must not be x.  Kept rows of y_out are not touched.
 void launch_gather_layernorm_fill(const void* x, const int32_t* idx, int B, int N, int k, int D, const void* gamma,
                                   const void* beta, float eps, int32_t* rows_out, void* a_out, const int32_t* rank,
                                   const void* cache_map, int hc, int wc, int h, int w, void* y_out,
-                                  hipStream_t stream);
+                                  const ZeroCounters& zc, hipStream_t stream);
 // a = LayerNorm(rows of `in`), M rows.
 void launch_layernorm(const void* in, int M, int D, const void* gamma, const void* beta, float eps,
-                      void* a_out, hipStream_t stream);
+                      void* a_out, const ZeroCounters& zc, hipStream_t stream);
 
 enum GemmEpilogue {
     EPI_QKV = 0,       // +bias; q -> q_out [M, D]; k, v -> caches at positions L0 + t
@@ -113,9 +122,6 @@ struct SplitKPlan {
     size_t bytes;          // counters + partial tiles
 };
 SplitKPlan gemm_splitk_plan(int M, int N, int K);
-// zero the n counters at the head of a split-K scratch area
-void launch_zero_i32(int32_t* p, int n, hipStream_t stream);
-
 // cos / sin tables [h*w, dh/2] fp32 of the axial 2-D rotary embedding (see rope.hip).
 void launch_rope2d_table(int h, int w, int dh, double base, int ref_h, int ref_w, float* cos_out, float* sin_out,
                          hipStream_t stream);

@@ -95,13 +95,21 @@ __device__ __forceinline__ void layernorm_row(const bf16_t* __restrict__ in, con
     }
 }
 
+// the launch's threads clear the counters between them (see ZeroCounters)
+__device__ __forceinline__ void clear_counters(const ZeroCounters& zc) {
+    const int at = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+    for (int i = at; i < zc.na; i += step) zc.a[i] = 0;
+    for (int i = at; i < zc.nb; i += step) zc.b[i] = 0;
+}
+
 template <int CH>
 __global__ __launch_bounds__(256) void layernorm_rows_kernel(const bf16_t* __restrict__ in,
                                                              const int32_t* __restrict__ idx, int N, int k,
                                                              int M, int D, const bf16_t* __restrict__ gamma,
                                                              const bf16_t* __restrict__ beta, float eps,
                                                              int32_t* __restrict__ rows_out,
-                                                             bf16_t* __restrict__ out) {
+                                                             bf16_t* __restrict__ out, const ZeroCounters zc) {
+    clear_counters(zc);
     layernorm_row<CH>(in, idx, N, k, M, D, gamma, beta, eps, rows_out, out, blockIdx.x * 4 + (threadIdx.x >> 6));
 }
 
@@ -124,7 +132,8 @@ __global__ __launch_bounds__(256) void gather_layernorm_fill_kernel(const bf16_t
                                                                     const bf16_t* __restrict__ beta, float eps,
                                                                     int32_t* __restrict__ rows_out,
                                                                     bf16_t* __restrict__ out, int ln_blocks,
-                                                                    const FillParams f) {
+                                                                    const FillParams f, const ZeroCounters zc) {
+    clear_counters(zc);
     if ((int)blockIdx.x < ln_blocks) {
         layernorm_row<CH>(in, idx, N, k, M, D, gamma, beta, eps, rows_out, out, blockIdx.x * 4 + (threadIdx.x >> 6));
         return;
@@ -144,13 +153,13 @@ __global__ __launch_bounds__(256) void gather_layernorm_fill_kernel(const bf16_t
 }
 
 void dispatch(const void* in, const int32_t* idx, int N, int k, int M, int D, const void* gamma,
-              const void* beta, float eps, int32_t* rows_out, void* out, hipStream_t stream) {
+              const void* beta, float eps, int32_t* rows_out, void* out, const ZeroCounters& zc, hipStream_t stream) {
     const dim3 grid((M + 3) / 4), block(256);
     const int ch = (D + 511) / 512;
 #define FV_LN_CASE(CHV)                                                                                  \
     layernorm_rows_kernel<CHV><<<grid, block, 0, stream>>>(                                              \
         static_cast<const bf16_t*>(in), idx, N, k, M, D, static_cast<const bf16_t*>(gamma),              \
-        static_cast<const bf16_t*>(beta), eps, rows_out, static_cast<bf16_t*>(out))
+        static_cast<const bf16_t*>(beta), eps, rows_out, static_cast<bf16_t*>(out), zc)
     if (ch <= 1) FV_LN_CASE(1);
     else if (ch <= 2) FV_LN_CASE(2);
     else if (ch <= 4) FV_LN_CASE(4);
@@ -162,14 +171,15 @@ void dispatch(const void* in, const int32_t* idx, int N, int k, int M, int D, co
 }  // namespace
 
 void launch_gather_layernorm(const void* x, const int32_t* idx, int B, int N, int k, int D, const void* gamma,
-                             const void* beta, float eps, int32_t* rows_out, void* a_out, hipStream_t stream) {
-    dispatch(x, idx, N, k, B * k, D, gamma, beta, eps, rows_out, a_out, stream);
+                             const void* beta, float eps, int32_t* rows_out, void* a_out, const ZeroCounters& zc,
+                             hipStream_t stream) {
+    dispatch(x, idx, N, k, B * k, D, gamma, beta, eps, rows_out, a_out, zc, stream);
 }
 
 void launch_gather_layernorm_fill(const void* x, const int32_t* idx, int B, int N, int k, int D, const void* gamma,
                                   const void* beta, float eps, int32_t* rows_out, void* a_out, const int32_t* rank,
                                   const void* cache_map, int hc, int wc, int h, int w, void* y_out,
-                                  hipStream_t stream) {
+                                  const ZeroCounters& zc, hipStream_t stream) {
     const int M = B * k;
     const int ln_blocks = (M + 3) / 4;
     FillParams f;
@@ -183,7 +193,7 @@ void launch_gather_layernorm_fill(const void* x, const int32_t* idx, int B, int 
 #define FV_LNF_CASE(CHV)                                                                                 \
     gather_layernorm_fill_kernel<CHV><<<grid, block, 0, stream>>>(                                       \
         static_cast<const bf16_t*>(x), idx, N, k, M, D, static_cast<const bf16_t*>(gamma),               \
-        static_cast<const bf16_t*>(beta), eps, rows_out, static_cast<bf16_t*>(a_out), ln_blocks, f)
+        static_cast<const bf16_t*>(beta), eps, rows_out, static_cast<bf16_t*>(a_out), ln_blocks, f, zc)
     if (ch <= 1) FV_LNF_CASE(1);
     else if (ch <= 2) FV_LNF_CASE(2);
     else if (ch <= 4) FV_LNF_CASE(4);
@@ -193,8 +203,8 @@ void launch_gather_layernorm_fill(const void* x, const int32_t* idx, int B, int 
 }
 
 void launch_layernorm(const void* in, int M, int D, const void* gamma, const void* beta, float eps, void* a_out,
-                      hipStream_t stream) {
-    dispatch(in, nullptr, 0, 1, M, D, gamma, beta, eps, nullptr, a_out, stream);
+                      const ZeroCounters& zc, hipStream_t stream) {
+    dispatch(in, nullptr, 0, 1, M, D, gamma, beta, eps, nullptr, a_out, zc, stream);
 }
 
 }  // namespace fv
