@@ -531,14 +531,16 @@ int fastvar_step(const void* x, const int32_t* sched_h, const int32_t* sched_w, 
     if (rc) return rc;
 
     hipStream_t st = static_cast<hipStream_t>(stream);
-    fv::launch_select(x, B, N, D, k, idx_out, rank, nullptr, ws_sel, fv::select_plan(B, N, D), st);
+    // With every token kept (k == N) the block runs without an index list and its output is the map.
+    const bool pruned = k > 0 && k < N;
+    fv::launch_select(x, B, N, D, k, idx_out, pruned ? rank : nullptr, nullptr, ws_sel, fv::select_plan(B, N, D), st);
     // Restoration has no launch of its own: the pruned rows of y_out are filled by extra workgroups of the
     // gather + LayerNorm launch, the kept rows are written by the block's last GEMM.  With nothing kept
     // the step is the upsampled cache.
     const Fill fill{rank, cache_map, hc, wc, h, w, y_out};
     if (k > 0)
-        enqueue_block(x, N, idx_out, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_out, ws_blk, st, true, true,
-                      &fill);
+        enqueue_block(x, N, pruned ? idx_out : nullptr, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_out, ws_blk,
+                      st, true, true, &fill);
     else
         fv::launch_restore(nullptr, rank, B, k, cache_map, hc, wc, h, w, D, y_out, st);
     rc = launch_status();
@@ -618,7 +620,7 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h, const int32_t* sch
             enqueue_block(src, N, nullptr, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk, st,
                           l == 0);
         } else {
-            fv::launch_select(src, B, N, D, k, idx_out, rank, nullptr, ws_sel, sp, st);
+            fv::launch_select(src, B, N, D, k, idx_out, k > 0 ? rank : nullptr, nullptr, ws_sel, sp, st);
             mark(st, FASTVAR_STAGE_SELECT);
             // restoration rides in the block's first launch (pruned rows) and its last (kept rows)
             const Fill fill{rank, ly.cache_map, hc, wc, h, w, dst};
@@ -755,18 +757,22 @@ int fastvar_step_sublayer(const void* x, const int32_t* sched_h, const int32_t* 
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const fv::SelectPlan sp = fv::select_plan(B, N, D);
-    fv::launch_select(x, B, N, D, k_attn, idx_attn_out, rank, nullptr, ws_sel, sp, st);
+    // (a half that keeps every token runs without an index list: its output is the map)
+    const bool pruned_a = k_attn > 0 && k_attn < N, pruned_f = k_ffn > 0 && k_ffn < N;
+    fv::launch_select(x, B, N, D, k_attn, idx_attn_out, pruned_a ? rank : nullptr, nullptr, ws_sel, sp, st);
     // each half's restoration rides in its own gather launch (pruned rows) and last GEMM (kept rows)
     const Fill fill_a{rank, cache_map_attn, hc, wc, h, w, x_mid};
     if (k_attn > 0)
-        enqueue_attn(x, N, idx_attn_out, B, k_attn, dims, weights, k_cache, v_cache, L0, L_cap, x_mid, ws_blk, st, true,
-                     true, &fill_a);
+        enqueue_attn(x, N, pruned_a ? idx_attn_out : nullptr, B, k_attn, dims, weights, k_cache, v_cache, L0, L_cap,
+                     x_mid, ws_blk, st, true, true, &fill_a);
     else
         fv::launch_restore(nullptr, rank, B, k_attn, cache_map_attn, hc, wc, h, w, D, x_mid, st);
-    fv::launch_select(x_mid, B, N, D, k_ffn, idx_ffn_out, rank, nullptr, ws_sel, sp, st);
+    fv::launch_select(x_mid, B, N, D, k_ffn, idx_ffn_out, pruned_f ? rank : nullptr, nullptr, ws_sel, sp, st);
     const Fill fill_f{rank, cache_map_ffn, hc, wc, h, w, y_out};
     if (k_ffn > 0)
-        enqueue_ffn(x_mid, N, idx_ffn_out, B, k_ffn, dims, weights, y_out, ws_blk, st, true, true, &fill_f);   // (the halves lay the scratch out for their own k)
+        // (the halves lay the scratch out for their own k: its counters are cleared again)
+        enqueue_ffn(x_mid, N, pruned_f ? idx_ffn_out : nullptr, B, k_ffn, dims, weights, y_out, ws_blk, st, true, pruned_f,
+                    &fill_f);
     else
         fv::launch_restore(nullptr, rank, B, k_ffn, cache_map_ffn, hc, wc, h, w, D, y_out, st);
     rc = launch_status();

@@ -24,15 +24,15 @@ inline void raise_lds_limit_once(std::once_flag& once, Kernel kernel, size_t byt
 
 // ---- selection (Sec. 3.3, Eq. 4-5) ----
 struct SelectPlan {
-    int col_tiles;     // column tiles of 512
-    int n_chunks;      // row chunks of the column-sum pass
+    int n_chunks;        // row chunks of the column-sum pass
     int rows_per_chunk;
     size_t off_partial;  // fp64 [B, n_chunks, D]
-    size_t off_mean;     // fp64 [B, D]
     size_t off_score;    // fp32 [B, N]
     size_t bytes;
 };
 SelectPlan select_plan(int B, int N, int D);
+// idx [B, k] and rank [B, N] (optional); with k == 0 or k == N the result does not depend on x and only
+// score_out, if asked for, is computed from it.
 void launch_select(const void* x, int B, int N, int D, int k, int32_t* idx, int32_t* rank,
                    float* score_out, void* ws, const SelectPlan& plan, hipStream_t stream);
 

@@ -2,23 +2,21 @@
 // the token positions, squared distance of every token from it, and the k
 // highest-scoring tokens per sample.
 //
-// Four launches, all bit-reproducible (no floating-point atomics):
-//   colsum_partial   fp64 column sums of row chunks           (HBM bound: reads x once)
-//   colsum_finalize  fixed-order sum of the chunk partials / N (tiny)
-//   score            fp64 sum_c (x - mean)^2 per token, one wave per token,
-//                    mean staged in LDS, rounded once to fp32  (re-reads x, mostly from cache)
-//   topk             one workgroup per sample: MSB-first radix select on the
-//                    order-preserving bit pattern of the fp32 score, then an
-//                    ordered compaction (ties to the lowest index)
+// Three launches, all bit-reproducible (no floating-point atomics):
+//   colsum   fp64 column sums of a few long row chunks            (HBM bound: reads x once)
+//   score    every workgroup adds the chunk sums to the mean by itself (a few
+//            chunks only, so that this stays cheap), then fp64
+//            sum_c (x - mean)^2 per token, rounded once to fp32    (re-reads x, mostly from cache)
+//   topk     one workgroup per sample: radix select on the
+//            order-preserving bit pattern of the fp32 score, then an
+//            ordered compaction (ties to the lowest index)
+// A selection that keeps every token or none does not depend on the scores: one fill launch.
 #include "common.h"
 #include "kernels.h"
 
 namespace fv {
 
 namespace {
-
-constexpr int kColsPerWave = 512;  // 64 lanes x 8 bf16 (one 16-byte load per lane)
-constexpr int kRedStride = 72;     // padded [j][lane] stride of the LDS reduction buffer
 
 __device__ __forceinline__ void add8(double (&acc)[8], const uint4& v) {
     acc[0] += (double)bf16_lo(v.x);
@@ -31,15 +29,20 @@ __device__ __forceinline__ void add8(double (&acc)[8], const uint4& v) {
     acc[7] += (double)bf16_hi(v.w);
 }
 
-// grid (col_tiles, n_chunks, B), block 256.  Wave w of a block sums rows
-// r0+w, r0+w+4, ... of its chunk for the block's 512 columns; the four waves
-// are then combined through LDS in a fixed order.
-__global__ __launch_bounds__(256) void colsum_partial_kernel(const bf16_t* __restrict__ x,
-                                                             double* __restrict__ partial, int N, int D,
-                                                             int rows_per_chunk, int n_chunks) {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int col = blockIdx.x * kColsPerWave + lane * 8;
+// grid (ceil(D/64), n_chunks, B), block 256: column sums of the row chunk for 64 columns (eight lanes read the
+// 128 bytes of a row, 32 rows per pass, eight passes of loads in flight), combined through LDS in a fixed order.
+// Few, long chunks: the launch after this one sums them in every workgroup, which it can only do cheaply for a
+// handful (4096 x 2048: 8 chunks, 128 KB of partials), and that takes a launch of its own (4.7 us) off the
+// selection; 256 workgroups with 64 KB in flight each read x as fast as more and shorter ones.
+constexpr int kColTile = 64;
+constexpr int kColRows = 32;      // rows of a pass
+constexpr int kMaxChunks = 16;
+__global__ __launch_bounds__(256) void colsum_kernel(const bf16_t* __restrict__ x, double* __restrict__ partial, int N,
+                                                     int D, int rows_per_chunk, int n_chunks) {
+    __shared__ double red[kColRows][kColTile];
+    __shared__ double red4[4][kColTile];
+    const int c8 = threadIdx.x & 7, rr = threadIdx.x >> 3;
+    const int col = blockIdx.x * kColTile + c8 * 8;
     const int b = blockIdx.z;
     const int r0 = blockIdx.y * rows_per_chunk;
     const int r1 = min(r0 + rows_per_chunk, N);
@@ -47,77 +50,37 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const bf16_t* __res
     double acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.0;
-
     if (col < D) {
         const bf16_t* base = x + (size_t)b * N * D + col;
-        int r = r0 + wave;
-        for (; r + 12 < r1; r += 16) {
-            const uint4 v0 = *reinterpret_cast<const uint4*>(base + (size_t)(r + 0) * D);
-            const uint4 v1 = *reinterpret_cast<const uint4*>(base + (size_t)(r + 4) * D);
-            const uint4 v2 = *reinterpret_cast<const uint4*>(base + (size_t)(r + 8) * D);
-            const uint4 v3 = *reinterpret_cast<const uint4*>(base + (size_t)(r + 12) * D);
-            add8(acc, v0);
-            add8(acc, v1);
-            add8(acc, v2);
-            add8(acc, v3);
+        int r = r0 + rr;
+        for (; r + 7 * kColRows < r1; r += 8 * kColRows) {
+            uint4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const uint4*>(base + (size_t)(r + u * kColRows) * D);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) add8(acc, v[u]);
         }
-        for (; r < r1; r += 4) {
+        for (; r < r1; r += kColRows) {
             const uint4 v0 = *reinterpret_cast<const uint4*>(base + (size_t)r * D);
             add8(acc, v0);
         }
     }
-
-    __shared__ double red[4][8 * kRedStride];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) red[wave][j * kRedStride + lane] = acc[j];
+    for (int j = 0; j < 8; ++j) red[rr][c8 * 8 + j] = acc[j];
     __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const int cl = threadIdx.x + e * 256;  // column inside the tile
-        const int at = (cl & 7) * kRedStride + (cl >> 3);
-        const double s = ((red[0][at] + red[1][at]) + red[2][at]) + red[3][at];
-        const int c = blockIdx.x * kColsPerWave + cl;
-        if (c < D) partial[((size_t)b * n_chunks + blockIdx.y) * D + c] = s;
-    }
-}
-
-// grid (ceil(D/64), B), block 1024: mean[b,c] = (sum of the chunk partials) / N.
-// Thread (c = t%64, g = t/64) sums every 16th chunk starting at g, ascending (eight
-// independent loads at a time); the sixteen partial sums of a column are then
-// added in a fixed order.
-constexpr int kFinGroups = 16;
-__global__ __launch_bounds__(64 * kFinGroups) void colsum_finalize_kernel(const double* __restrict__ partial,
-                                                                          double* __restrict__ mean, int N, int D,
-                                                                          int n_chunks) {
-    __shared__ double part[kFinGroups][64];
     const int cl = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int c = blockIdx.x * 64 + cl;
-    const int b = blockIdx.y;
     double s = 0.0;
-    if (c < D) {
-        const double* p = partial + (size_t)b * n_chunks * D + c;
-        int y = g;
-        for (; y + 7 * kFinGroups < n_chunks; y += 8 * kFinGroups) {
-            double a[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) a[j] = p[(size_t)(y + j * kFinGroups) * D];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) s += a[j];
-        }
-        for (; y < n_chunks; y += kFinGroups) s += p[(size_t)y * D];
-    }
-    part[g][cl] = s;
+    for (int j = 0; j < kColRows / 4; ++j) s += red[g * (kColRows / 4) + j][cl];
+    red4[g][cl] = s;
     __syncthreads();
-    if (g == 0 && c < D) {
-        double t = part[0][cl];
-#pragma unroll
-        for (int j = 1; j < kFinGroups; ++j) t += part[j][cl];
-        mean[(size_t)b * D + c] = t / (double)N;
+    if (g == 0) {
+        const int c = blockIdx.x * kColTile + cl;
+        if (c < D)
+            partial[((size_t)b * n_chunks + blockIdx.y) * D + c] =
+                ((red4[0][cl] + red4[1][cl]) + red4[2][cl]) + red4[3][cl];
     }
 }
-
-constexpr int kScoreRowsPerBlock = 16;  // 8 waves x 2 rows: two waves per SIMD cover each other's fp64 chains and loads
-constexpr int kScoreThreads = 512;
 
 __device__ __forceinline__ void sqdev8(double& acc, const uint4& v, const double* mu /* stride 64 */) {
     double d;
@@ -131,45 +94,66 @@ __device__ __forceinline__ void sqdev8(double& acc, const uint4& v, const double
     d = (double)bf16_hi(v.w) - mu[7 * 64]; acc = fma(d, d, acc);
 }
 
-// grid (ceil(N/16), B), block 512, dynamic LDS = round_up(D,512) doubles.
-// The mean is staged in LDS as [group of 512 cols][j = col%8][lane = (col%512)/8]
-// so that the 64 lanes of a wave read consecutive doubles.
+// grid (ceil(N/rows_per_wg), B), block 512 (eight waves, two per SIMD to cover each other's fp64 chains), dynamic
+// LDS = CH*512 doubles.  The mean (sum of the chunk partials / N) is staged in LDS as
+// [group of 512 cols][j = col%8][lane = (col%512)/8] so that the 64 lanes of a wave read consecutive doubles.  A
+// wave scores two tokens at a time; its first two tokens' loads go out before the mean is summed.
+// CH: 512-column groups of a row (D <= 512*CH).
+constexpr int kScoreThreads = 512;
+constexpr int kScoreRowsPerPass = kScoreThreads / 64 * 2;
+template <int CH>
 __global__ __launch_bounds__(kScoreThreads) void score_kernel(const bf16_t* __restrict__ x,
-                                                    const double* __restrict__ mean,
-                                                    float* __restrict__ score, int N, int D) {
+                                                              const double* __restrict__ partial, int n_chunks,
+                                                              float* __restrict__ score, int N, int D, int passes) {
     extern __shared__ double mu_s[];
     const int b = blockIdx.y;
-    for (int c = threadIdx.x; c < D; c += kScoreThreads) {
-        const int g = c >> 9, r = c & 511;
-        mu_s[g * 512 + (r & 7) * 64 + (r >> 3)] = mean[(size_t)b * D + c];
-    }
-    __syncthreads();
-
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int groups = (D + 511) >> 9;
-    {
-        const int n0 = blockIdx.x * kScoreRowsPerBlock + wave * 2;
-        const int n1 = n0 + 1;
-        const bool ok0 = n0 < N, ok1 = n1 < N;
-        const bf16_t* row0 = x + ((size_t)b * N + (ok0 ? n0 : 0)) * D;
-        const bf16_t* row1 = x + ((size_t)b * N + (ok1 ? n1 : 0)) * D;
-        double acc0 = 0.0, acc1 = 0.0;
-        for (int g = 0; g < groups; ++g) {
+    const int n_first = blockIdx.x * passes * kScoreRowsPerPass + wave * 2;
+    uint4 v0[CH], v1[CH];
+    auto fetch = [&](int n0) {
+        const bf16_t* row0 = x + ((size_t)b * N + min(n0, N - 1)) * D;
+        const bf16_t* row1 = x + ((size_t)b * N + min(n0 + 1, N - 1)) * D;
+#pragma unroll
+        for (int g = 0; g < CH; ++g) {
             const int col = g * 512 + lane * 8;
             if (col < D) {
-                const uint4 v0 = *reinterpret_cast<const uint4*>(row0 + col);
-                const uint4 v1 = *reinterpret_cast<const uint4*>(row1 + col);
-                const double* mu = mu_s + g * 512 + lane;
-                sqdev8(acc0, v0, mu);
-                sqdev8(acc1, v1, mu);
+                v0[g] = *reinterpret_cast<const uint4*>(row0 + col);
+                v1[g] = *reinterpret_cast<const uint4*>(row1 + col);
             }
         }
+    };
+    fetch(n_first);
+    const double* pb = partial + (size_t)b * n_chunks * D;
+    for (int c = threadIdx.x; c < D; c += kScoreThreads) {
+        double a[kMaxChunks];
+#pragma unroll
+        for (int y = 0; y < kMaxChunks; ++y) a[y] = y < n_chunks ? pb[(size_t)y * D + c] : 0.0;
+        double s = a[0];
+#pragma unroll
+        for (int y = 1; y < kMaxChunks; ++y) s += a[y];
+        const int g = c >> 9, r = c & 511;
+        mu_s[g * 512 + (r & 7) * 64 + (r >> 3)] = s / (double)N;
+    }
+    __syncthreads();
+    for (int ps = 0; ps < passes; ++ps) {
+        const int n0 = n_first + ps * kScoreRowsPerPass;
+        if (n0 >= N) return;
+        double acc0 = 0.0, acc1 = 0.0;
+#pragma unroll
+        for (int g = 0; g < CH; ++g) {
+            if (g * 512 + lane * 8 < D) {
+                const double* mu = mu_s + g * 512 + lane;
+                sqdev8(acc0, v0[g], mu);
+                sqdev8(acc1, v1[g], mu);
+            }
+        }
+        if (ps + 1 < passes) fetch(n0 + kScoreRowsPerPass);
         acc0 = wave_sum(acc0);
         acc1 = wave_sum(acc1);
         if (lane == 0) {
-            if (ok0) score[(size_t)b * N + n0] = (float)acc0;
-            if (ok1) score[(size_t)b * N + n1] = (float)acc1;
+            score[(size_t)b * N + n0] = (float)acc0;
+            if (n0 + 1 < N) score[(size_t)b * N + n0 + 1] = (float)acc1;
         }
     }
 }
@@ -180,137 +164,184 @@ __device__ __forceinline__ uint32_t float_key(float f) {
     return u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u);
 }
 
-constexpr int kTopkThreads = 1024;
+// Set bits of a wave mask below this lane's own.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
 
-// grid (B), block 1024, dynamic LDS = N uint32 keys.
+constexpr int kTopkThreads = 1024;
+constexpr int kTopkWaves = kTopkThreads / 64;
+constexpr int kBins = 1024;      // one per thread
+constexpr int kBinCopies = 8;
+constexpr int kMaxCand = 256;
+
+// grid (B), block 1024, 0 < k < N <= 1024*E: wave w owns the 64*E tokens from w*64*E on, lane l of it every 64th of
+// them (loads and stores are contiguous over a wave), with the keys in registers.
+//   1. smallest and largest key; the range between them is cut into at most 1024 equal bins (a power of two wide)
+//   2. histogram, one scan for the bin that holds the k-th largest key
+//   3. that bin usually holds a few keys: they are ranked against each other directly.  If it holds more than
+//      256, its range is cut into bins again (a map of equal scores ends with bins one key wide).
+//   4. ordered compaction of the kept tokens (ties to the lowest index)
+// Equal-width bins over the keys' own range spread the scores of a map over hundreds of bins, so the histogram's
+// LDS atomics seldom meet and one pass nearly always leaves a few candidates; 8-bit digits below the common
+// leading bits piled a whole wave onto a handful of bins and took three to four passes.  Neighbouring tokens of a
+// smooth map still have neighbouring scores: every bin has eight counters in different banks, one per lane % 8
+// (4096 scores 10.3 -> ~6 us, 16384 scores 28.6 -> ~8 us).
+template <int E>
 __global__ __launch_bounds__(kTopkThreads) void topk_kernel(const float* __restrict__ score, int N, int k,
                                                             int32_t* __restrict__ idx,
                                                             int32_t* __restrict__ rank) {
-    extern __shared__ uint32_t keys[];
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t sel[2];
-    __shared__ uint32_t wave_tot[kTopkThreads / 64];
+    __shared__ __attribute__((aligned(16))) uint32_t hist[kBins * kBinCopies];   // bin r: keys of the r-th highest range
+    __shared__ uint32_t wave_a[kTopkWaves], wave_b[kTopkWaves];
+    __shared__ uint32_t sel[3];
+    __shared__ uint32_t cand[kMaxCand];
+    __shared__ uint32_t n_cand;
 
     const int b = blockIdx.x;
     const int t = threadIdx.x;
-    for (int n = t; n < N; n += kTopkThreads) keys[n] = float_key(score[(size_t)b * N + n]);
-
-    // ---- radix select: T = key of the k-th largest, need = how many keys equal to T are kept.
-    // Scores of one map usually share their leading bits (same sign, nearby
-    // exponents); those bits are found first (AND / OR over all keys) and the
-    // 8-bit digit passes only walk the bits below them, which also keeps the
-    // LDS histogram atomics from piling onto a single bin.
-    uint32_t prefix = 0, mask = 0, k_rem = (uint32_t)k;
-    if (k > 0) {
-        uint32_t all_and = 0xFFFFFFFFu, all_or = 0u;
-        for (int n = t; n < N; n += kTopkThreads) {  // this thread's own entries: no barrier needed yet
-            const uint32_t key = keys[n];
-            all_and &= key;
-            all_or |= key;
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            all_and &= __shfl_xor(all_and, o, 64);
-            all_or |= __shfl_xor(all_or, o, 64);
-        }
-        if ((t & 63) == 0) { wave_tot[t >> 6] = all_and; hist[t >> 6] = all_or; }
-        __syncthreads();
-        for (int wv = 0; wv < kTopkThreads / 64; ++wv) { all_and &= wave_tot[wv]; all_or |= hist[wv]; }
-        __syncthreads();
-        const uint32_t differ = all_and ^ all_or;           // bits that are not common to all keys
-        const int top = differ ? 32 - __clz(differ) : 0;     // number of low bits that may differ
-        mask = top >= 32 ? 0u : (0xFFFFFFFFu << top);
-        prefix = all_and & mask;
-        for (int shift = top - 8; shift > -8; shift -= 8) {
-            const int sh = shift < 0 ? 0 : shift;
-            const uint32_t dmask = shift < 0 ? ((1u << (shift + 8)) - 1u) : 255u;  // last pass may be narrower
-            if (t < 256) hist[t] = 0;
-            __syncthreads();
-            for (int n = t; n < N; n += kTopkThreads) {
-                const uint32_t key = keys[n];
-                if ((key & mask) == prefix) atomicAdd(&hist[(key >> sh) & dmask], 1u);
-            }
-            __syncthreads();
-            if (t < 64) {
-                const uint32_t h0 = hist[4 * t + 0], h1 = hist[4 * t + 1];
-                const uint32_t h2 = hist[4 * t + 2], h3 = hist[4 * t + 3];
-                const uint32_t tot = h0 + h1 + h2 + h3;
-                uint32_t incl = tot;  // becomes sum over lanes >= t
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const uint32_t v = __shfl_down(incl, o, 64);
-                    if (t + o < 64) incl += v;
-                }
-                const uint32_t c3 = incl - tot;  // keys in bins above 4t+3
-                const uint32_t c2 = c3 + h3, c1 = c2 + h2, c0 = c1 + h1;
-                if (c3 < k_rem && k_rem <= c3 + h3) { sel[0] = 4 * t + 3; sel[1] = k_rem - c3; }
-                else if (c2 < k_rem && k_rem <= c2 + h2) { sel[0] = 4 * t + 2; sel[1] = k_rem - c2; }
-                else if (c1 < k_rem && k_rem <= c1 + h1) { sel[0] = 4 * t + 1; sel[1] = k_rem - c1; }
-                else if (c0 < k_rem && k_rem <= c0 + h0) { sel[0] = 4 * t + 0; sel[1] = k_rem - c0; }
-            }
-            __syncthreads();
-            prefix |= sel[0] << sh;
-            mask |= dmask << sh;
-            k_rem = sel[1];
-        }
-    } else {
-        __syncthreads();
-        prefix = 0xFFFFFFFFu;  // nothing is greater; need = 0 keeps no tie
-        k_rem = 0;
-    }
-    const uint32_t T = prefix, need = k_rem;
-
-    // ---- ordered compaction: thread t owns tokens [t*E, (t+1)*E)
-    const int E = (N + kTopkThreads - 1) / kTopkThreads;
-    const int lo = min(t * E, N), hi = min(lo + E, N);
-    uint32_t cnt = 0;  // (greater << 16) | equal ; both totals <= 32768
-    for (int n = lo; n < hi; ++n) {
-        const uint32_t key = keys[n];
-        cnt += (key > T ? 0x10000u : 0u) + (key == T ? 1u : 0u);
-    }
-    uint32_t incl = cnt;
     const int lane = t & 63, wave = t >> 6;
+    const int n0 = wave * (64 * E) + lane;       // token of register j: n0 + 64*j
+    const float* sc = score + (size_t)b * N;
+    uint32_t key[E];
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t v = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += v;
+    for (int j = 0; j < E; ++j) key[j] = n0 + 64 * j < N ? max(float_key(sc[n0 + 64 * j]), 1u) : 0u;   // 0: no token
+    uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        kmin = min(kmin, key[j] - 1u);
+        kmax = max(kmax, key[j]);
     }
-    if (lane == 63) wave_tot[wave] = incl;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, 64));
+        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, 64));
+    }
+    if (lane == 0) { wave_a[wave] = kmin; wave_b[wave] = kmax; }
     __syncthreads();
-    uint32_t before = incl - cnt;
-    for (int wv = 0; wv < wave; ++wv) before += wave_tot[wv];
-    uint32_t gt_before = before >> 16, eq_before = before & 0xFFFFu;
-    for (int n = lo; n < hi; ++n) {
-        const uint32_t key = keys[n];
-        int pos = -1;
-        if (key > T) {
-            pos = (int)(gt_before + min(eq_before, need));
-            ++gt_before;
-        } else if (key == T) {
-            if (eq_before < need) pos = (int)(gt_before + eq_before);
-            ++eq_before;
+#pragma unroll
+    for (int wv = 0; wv < kTopkWaves; ++wv) { kmin = min(kmin, wave_a[wv]); kmax = max(kmax, wave_b[wv]); }
+    kmin += 1u;
+
+    // ---- T = key of the k-th largest, need = how many keys equal to T are kept
+    uint32_t T, need, k_rem = (uint32_t)k;
+    for (;;) {
+        const uint32_t range = kmax - kmin;
+        const int shift = range < (uint32_t)kBins ? 0 : 32 - __clz(range) - 10;     // range >> shift < 1024
+        static_assert(kBins == 1024 && kBins == kTopkThreads && kBinCopies == 8, "ten bits of bin index, a thread per bin");
+        reinterpret_cast<uint4*>(hist)[t] = make_uint4(0, 0, 0, 0);
+        reinterpret_cast<uint4*>(hist)[t + kTopkThreads] = make_uint4(0, 0, 0, 0);
+        if (t == 0) n_cand = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+            if (key[j] - kmin <= kmax - kmin)
+                atomicAdd(&hist[(kBins - 1 - ((key[j] - kmin) >> shift)) * kBinCopies + (lane & 7)], 1u);
+        __syncthreads();
+        const uint4 ha = reinterpret_cast<const uint4*>(hist)[2 * t], hb = reinterpret_cast<const uint4*>(hist)[2 * t + 1];
+        const uint32_t here = ((ha.x + ha.y) + (ha.z + ha.w)) + ((hb.x + hb.y) + (hb.z + hb.w));
+        uint32_t incl = here;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t v = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += v;
         }
-        if (pos >= 0) idx[(size_t)b * k + pos] = n;
-        if (rank) rank[(size_t)b * N + n] = pos;
+        if (lane == 63) wave_a[wave] = incl;
+        __syncthreads();
+        uint32_t before = incl - here;
+#pragma unroll
+        for (int wv = 0; wv < kTopkWaves; ++wv) before += wv < wave ? wave_a[wv] : 0u;
+        if (before < k_rem && k_rem <= before + here) { sel[0] = t; sel[1] = k_rem - before; sel[2] = here; }
+        __syncthreads();
+        const uint32_t count = sel[2];
+        kmin += (uint32_t)(kBins - 1 - sel[0]) << shift;
+        kmax = min(kmax - kmin, (1u << shift) - 1u) + kmin;   // (the highest bin may reach past the largest key)
+        k_rem = sel[1];
+        if (shift == 0) { T = kmin; need = k_rem; break; }
+        if (count <= kMaxCand) {
+#pragma unroll
+            for (int j = 0; j < E; ++j)
+                if (key[j] - kmin <= kmax - kmin) cand[atomicAdd(&n_cand, 1u)] = key[j];
+            __syncthreads();
+            if (t < (int)count) {
+                const uint32_t mine = cand[t];
+                uint32_t above = 0, equal = 0;
+#pragma unroll 8
+                for (uint32_t i = 0; i < count; ++i) {
+                    const uint32_t c = cand[i];
+                    above += c > mine ? 1u : 0u;
+                    equal += c == mine ? 1u : 0u;
+                }
+                if (above < k_rem && k_rem <= above + equal) { sel[0] = mine; sel[1] = k_rem - above; }
+            }
+            __syncthreads();
+            T = sel[0];
+            need = sel[1];
+            break;
+        }
     }
+
+    // ---- ordered compaction
+    uint32_t total = 0;  // (greater << 16) | equal ; both at most 32768
+#pragma unroll
+    for (int j = 0; j < E; ++j) total += (key[j] > T ? 0x10000u : 0u) + (key[j] == T ? 1u : 0u);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) total += (uint32_t)__shfl_xor((int)total, o, 64);
+    if (lane == 0) wave_b[wave] = total;
+    __syncthreads();
+    uint32_t before = 0;
+#pragma unroll
+    for (int wv = 0; wv < kTopkWaves; ++wv) before += wv < wave ? wave_b[wv] : 0u;
+    // the first tokens equal to T, in order, are kept until `need` of them are
+    uint32_t kept = (before >> 16) + min(before & 0xFFFFu, need), eq_seen = before & 0xFFFFu;
+    const bool has_eq = __any((total & 0xFFFFu) != 0u) && eq_seen < need;
+    int32_t* const idx_b = idx + (size_t)b * k;
+    int32_t* const rank_b = rank ? rank + (size_t)b * N : nullptr;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+        const int n = n0 + 64 * j;
+        bool keep = key[j] > T;
+        if (has_eq) {
+            const uint64_t m_eq = __ballot(key[j] == T);
+            keep = keep || (key[j] == T && eq_seen + lanes_below(m_eq) < need);
+            eq_seen += (uint32_t)__popcll(m_eq);
+        }
+        const uint64_t m = __ballot(keep);
+        const int pos = (int)(kept + lanes_below(m));
+        kept += (uint32_t)__popcll(m);
+        if (keep) idx_b[pos] = n;
+        if (rank_b && n < N) rank_b[n] = keep ? pos : -1;
+    }
+}
+
+// Every token kept (all = true): idx and rank are the identity; none kept: rank is -1 everywhere.
+__global__ __launch_bounds__(256) void trivial_selection_kernel(int N, long total, bool all, int32_t* __restrict__ idx,
+                                                                int32_t* __restrict__ rank) {
+    const long i = (long)blockIdx.x * 256 + threadIdx.x;
+    if (i >= total) return;
+    const int n = (int)(i % N);
+    if (all) idx[i] = n;
+    if (rank) rank[i] = all ? n : -1;
 }
 
 }  // namespace
 
 SelectPlan select_plan(int B, int N, int D) {
     SelectPlan p;
-    p.col_tiles = (D + kColsPerWave - 1) / kColsPerWave;
-    // 32 rows per chunk (8 per wave) lets a wave issue all of its loads at once;
-    // the chunk count is capped at 256 so the fp64 partials stay a small
-    // fraction of x (1/8 of its bytes at 32 rows per chunk, less beyond).
+    // As few row chunks as give the column sums a workgroup per CU, in powers of two up to sixteen, none shorter
+    // than one pass.
+    const long tiles = (long)((D + kColTile - 1) / kColTile) * B;
+    int chunks = 1;
+    while (chunks < kMaxChunks && tiles * chunks < 240 && (N + 2 * chunks - 1) / (2 * chunks) >= kColRows) chunks *= 2;
+    p.rows_per_chunk = ((N + chunks - 1) / chunks + kColRows - 1) / kColRows * kColRows;
+    p.n_chunks = (N + p.rows_per_chunk - 1) / p.rows_per_chunk;
+    // The size of the area is part of the interface (callers keep buffers of it, and the static entry point
+    // accepts what fits into its array): partial sums of 32-row chunks, at most 256 of them, then mean and scores.
+    // The kernels use the head of the first part and the scores.
     int rows = 32;
     while ((N + rows - 1) / rows > 256) rows *= 2;
-    p.rows_per_chunk = rows;
-    p.n_chunks = (N + rows - 1) / rows;
     size_t off = 0;
     p.off_partial = off;
-    off += (size_t)B * p.n_chunks * D * sizeof(double);
-    p.off_mean = off;
+    off += (size_t)B * ((N + rows - 1) / rows) * D * sizeof(double);
     off += (size_t)B * D * sizeof(double);
     p.off_score = off;
     off += (((size_t)B * N * sizeof(float)) + 255) & ~(size_t)255;
@@ -320,21 +351,41 @@ SelectPlan select_plan(int B, int N, int D) {
 
 void launch_select(const void* x, int B, int N, int D, int k, int32_t* idx, int32_t* rank, float* score_out,
                    void* ws, const SelectPlan& plan, hipStream_t stream) {
+    const bool trivial = k == 0 || k == N;
+    if (trivial && (k > 0 || rank)) {
+        const long total = (long)B * N;
+        trivial_selection_kernel<<<(unsigned)((total + 255) / 256), 256, 0, stream>>>(N, total, k > 0, idx, rank);
+    }
+    if (trivial && !score_out) return;
     char* w = static_cast<char*>(ws);
     double* partial = reinterpret_cast<double*>(w + plan.off_partial);
-    double* mean = reinterpret_cast<double*>(w + plan.off_mean);
     float* score = score_out ? score_out : reinterpret_cast<float*>(w + plan.off_score);
     const bf16_t* xb = static_cast<const bf16_t*>(x);
 
-    colsum_partial_kernel<<<dim3(plan.col_tiles, plan.n_chunks, B), 256, 0, stream>>>(
+    colsum_kernel<<<dim3((D + kColTile - 1) / kColTile, plan.n_chunks, B), 256, 0, stream>>>(
         xb, partial, N, D, plan.rows_per_chunk, plan.n_chunks);
-    colsum_finalize_kernel<<<dim3((D + 63) / 64, B), 64 * kFinGroups, 0, stream>>>(partial, mean, N, D, plan.n_chunks);
-    const size_t mu_bytes = (size_t)plan.col_tiles * 512 * sizeof(double);
-    score_kernel<<<dim3((N + kScoreRowsPerBlock - 1) / kScoreRowsPerBlock, B), kScoreThreads, mu_bytes, stream>>>(
-        xb, mean, score, N, D);
-    static std::once_flag once;  // maps above 16K tokens need more than the default 64 KB of dynamic LDS
-    raise_lds_limit_once(once, &topk_kernel, 32768 * sizeof(uint32_t));
-    topk_kernel<<<dim3(B), kTopkThreads, (size_t)N * sizeof(uint32_t), stream>>>(score, N, k, idx, rank);
+    // one pass of 16 tokens per workgroup while that gives few workgroups; the mean is summed once per workgroup,
+    // so beyond two rounds of them (two fit a CU) a workgroup takes more passes
+    int passes = 1;
+    while (passes < 8 && (long)B * ((N + passes * kScoreRowsPerPass - 1) / (passes * kScoreRowsPerPass)) > 512) passes *= 2;
+    const dim3 sgrid((N + passes * kScoreRowsPerPass - 1) / (passes * kScoreRowsPerPass), B);
+#define FV_SCORE_CASE(CHV)                                                                                          score_kernel<CHV><<<sgrid, kScoreThreads, (size_t)CHV * 512 * sizeof(double), stream>>>(xb, partial,                                                                                                   plan.n_chunks, score, N, D, passes)
+    const int ch = (D + 511) / 512;
+    if (ch <= 1) FV_SCORE_CASE(1);
+    else if (ch <= 2) FV_SCORE_CASE(2);
+    else if (ch <= 4) FV_SCORE_CASE(4);
+    else if (ch <= 8) FV_SCORE_CASE(8);
+    else FV_SCORE_CASE(16);   // D <= 8192, checked by the caller
+#undef FV_SCORE_CASE
+    if (trivial) return;
+#define FV_TOPK_CASE(EV) topk_kernel<EV><<<dim3(B), kTopkThreads, 0, stream>>>(score, N, k, idx, rank)
+    if (N <= 1024) FV_TOPK_CASE(1);
+    else if (N <= 2048) FV_TOPK_CASE(2);
+    else if (N <= 4096) FV_TOPK_CASE(4);
+    else if (N <= 8192) FV_TOPK_CASE(8);
+    else if (N <= 16384) FV_TOPK_CASE(16);
+    else FV_TOPK_CASE(32);   // N <= 32768, checked by the caller
+#undef FV_TOPK_CASE
 }
 
 }  // namespace fv
