@@ -231,7 +231,7 @@ void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const 
                                          fill->y_out, zc, st);
     else if (idx)
         fv::launch_gather_layernorm(x, idx, B, N, k, d->D, w->ln1_g, w->ln1_b, d->ln_eps, rows, buf_a, zc, st);
-    else
+    else if (!fv::gemm_takes_layernorm(M, d->D))
         fv::launch_layernorm(x, M, d->D, w->ln1_g, w->ln1_b, d->ln_eps, buf_a, zc, st);
     mark(st, FASTVAR_STAGE_LN1);
     // q | k | v = a1 * Wqkv^T + b ; k, v appended to the caches at [L0, L0+k)
@@ -240,6 +240,9 @@ void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const 
     g.q_out = buf_q; g.k_cache = kc; g.v_cache = vc;
     g.D = d->D; g.H = d->H; g.dh = d->dh; g.k_tokens = k; g.L0 = L0; g.L_cap = L_cap;
     g.splitk_ws = sk;
+    if (!idx && fv::gemm_takes_layernorm(M, d->D)) {   // few rows: the product normalises them itself
+        g.A = x; g.ln_g = w->ln1_g; g.ln_b = w->ln1_b; g.ln_eps = d->ln_eps; g.zero = zc;
+    }
     if (rope) {   // q and the new keys are turned by the angles of each kept token's own slot
         g.rope_cos = rope->cos; g.rope_sin = rope->sin; g.rope_rows = idx ? rows : nullptr; g.rope_N = N;
     }
@@ -287,7 +290,7 @@ void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const
                                          fill->y_out, zc, st);
     else if (idx)
         fv::launch_gather_layernorm(src, idx, B, N, k, d->D, w->ln2_g, w->ln2_b, d->ln_eps, rows, buf_q, zc, st);
-    else
+    else if (!fv::gemm_takes_layernorm(M, d->D))
         fv::launch_layernorm(src, M, d->D, w->ln2_g, w->ln2_b, d->ln_eps, buf_q, zc, st);
     mark(st, FASTVAR_STAGE_LN2);
     // u = gelu(a2 * W1^T + b1)
@@ -295,6 +298,9 @@ void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const
     f1.A = buf_q; f1.W = w->w_fc1; f1.bias = w->b_fc1; f1.M = M; f1.N = d->F; f1.K = d->D;
     f1.out = buf_u; f1.k_tokens = k;
     f1.splitk_ws = sk;
+    if (!idx && fv::gemm_takes_layernorm(M, d->D)) {
+        f1.A = src; f1.ln_g = w->ln2_g; f1.ln_b = w->ln2_b; f1.ln_eps = d->ln_eps; f1.zero = zc;
+    }
     fv::launch_gemm(fv::EPI_BIAS_GELU, f1, st);
     mark(st, FASTVAR_STAGE_FC1);
     // y = s + u * W2^T + b2

@@ -843,6 +843,12 @@ void launch_epi(GemmParams& p, hipStream_t stream) {
 
 SplitKPlan gemm_splitk_plan(int M, int N, int K) {
     SplitKPlan sk;
+    if (M <= kSkinnyRows) {   // skinny.hip: no exchange between workgroups
+        sk.splits = 1;
+        sk.tiles = sk.shape = sk.tile_m = sk.tile_n = 0;
+        sk.counter_bytes = sk.bytes = 0;
+        return sk;
+    }
     // Up to 256 rows the tiles are 64x64 (eight stages): at those row counts the GEMMs stream their weights,
     // and what counts is how many workgroups pull on them.  Measured inside 32-block steps of the large model
     // (us per launch, 144 / 256 rows): out-proj 13.1 / 14.1 against 21.0 / 21.1 with 128x128 tiles on four
@@ -887,6 +893,10 @@ SplitKPlan gemm_splitk_plan(int M, int N, int K) {
 }
 
 void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {
+    if (a.M <= kSkinnyRows) {
+        launch_gemm_skinny(epi, a, stream);
+        return;
+    }
     GemmParams p;
     p.A = static_cast<const bf16_t*>(a.A);
     p.W = static_cast<const bf16_t*>(a.W);

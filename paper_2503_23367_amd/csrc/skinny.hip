@@ -1,0 +1,299 @@
+// GEMMs of at most kSkinnyRows rows (the first scales of a schedule): C[m,n] = sum_k A[m,k] * W[n,k], with the
+// same fused epilogues as gemm.hip and, for the QKV and FC1 products, the LayerNorm of the rows in front.
+//
+// At these row counts a block is one pass over its weights (100 MB for the large model), and the time goes to what
+// surrounds that pass: a launch per LayerNorm, rings that fill and drain, partial tiles that travel through
+// memory between workgroups.  So nothing is staged here: a workgroup owns CW output columns over the whole K
+// range, its waves take K in turns of 64, and every lane loads its weights straight from memory into the
+// registers of a 16x16x32 MFMA operand, all loads of a wave in flight at once (a weight is used by one wave
+// only, so LDS would add a trip and save nothing).  The waves' sums meet in LDS, in wave order; nothing is
+// exchanged between workgroups.
+//
+// LN: the rows' operand fragments are loaded first and the weights right behind them, so mean, variance (two passes
+// in fp32, the values rounded to bf16 as a LayerNorm launch would round them) and the normalised operand are computed
+// while the weights are on their way.  Every workgroup repeats this for its columns; that is 16 rows from L2.
+//
+// Measured on eight blocks of the large model (805 MB of weights): one row 454 -> 358 us, 16 rows 469 -> 436; the small
+// model 304 -> 225, 318 -> 289.  Beyond 16 rows it loses (25 rows in two groups 660 against 474 us: every workgroup reads
+// the rows' operands from L2, and they no longer fit beside the weights in registers), hence kSkinnyRows.
+//
+// CW = 16 fills the operand with 16 weight rows.  CW = 8 (outputs of few columns: out-proj, FC2) gives half of the
+// operand's rows to a second K half of the same eight columns, which doubles the number of workgroups: the matrix
+// instructions, one per half, waste half of their rows, and have the time.
+#include "common.h"
+#include "kernels.h"
+
+namespace fv {
+
+namespace {
+
+constexpr int EPI_QKV_ROPE = 3;
+constexpr bool is_qkv(int epi) { return epi == EPI_QKV || epi == EPI_QKV_ROPE; }
+
+// v * sigma(2u), u = sqrt(2/pi) (v + 0.044715 v^3): the form gemm.hip uses
+__device__ __forceinline__ float gelu_fast(float v) {
+    constexpr float c1 = -1.4426950408889634f * 1.5957691216057308f;
+    constexpr float c3 = c1 * 0.044715f;
+    const float e = __builtin_amdgcn_exp2f(v * fmaf(c3, v * v, c1));
+    return v * __builtin_amdgcn_rcpf(1.0f + e);
+}
+
+__device__ __forceinline__ void unpack8(const u32x4_t& v, float (&f)[8]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { f[2 * j] = bf16_lo(v[j]); f[2 * j + 1] = bf16_hi(v[j]); }
+}
+
+__device__ __forceinline__ u32x4_t load16(const void* p) { return *reinterpret_cast<const u32x4_t*>(p); }
+
+__device__ __forceinline__ f32x4_t mfma16(const u32x4_t& w, const u32x4_t& a, const f32x4_t& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, a), c,
+                                                   0, 0, 0);
+}
+
+// Lane l of a wave: operand row r = l % 16 (weight row n0 + r, or token row r of a 16-row group) and K octets
+// q = l / 16 of a 64-wide turn: elements [16 q, 16 q + 16) in two 16-byte loads, one per MFMA (K may be taken in any
+// order as long as both operands agree; this one makes a turn's two loads of a row one 128-byte line).
+// U: turns a wave has in flight.  Turns past the end load the last one and are skipped by a wave-uniform branch around
+// the MFMA, not around the load: with loads in branches the compiler can no longer count what is in flight, and waits for all.
+// Results: lane l holds columns n0 + 4 q + 0..3 of token row r.
+template <int EPI, bool LN, int CW, int NW, int U>
+__global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
+    constexpr int KH = CW == 8 ? 2 : 1;               // K halves side by side in the weight operand
+    __shared__ f32x4_t red[NW][64];
+    __shared__ float stat[2][NW][16];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int r = lane & 15, q = lane >> 4;
+    const int n0 = blockIdx.x * CW;
+    const int turns = p.K >> 6;
+    const int half = (turns + KH - 1) / KH;           // turns of the first K half
+
+    if (LN && blockIdx.x == 0) {                      // (the launch stands in for the call's first LayerNorm)
+        for (int i = threadIdx.x; i < p.zero.na; i += 64 * NW) p.zero.a[i] = 0;
+        for (int i = threadIdx.x; i < p.zero.nb; i += 64 * NW) p.zero.b[i] = 0;
+    }
+
+    // this lane's weight row, and the turn its K half starts at
+    const int wh = KH == 2 ? r >> 3 : 0;
+    const bf16_t* const wrow = static_cast<const bf16_t*>(p.W) +
+                               (size_t)min(n0 + (KH == 2 ? (r & 7) : r), p.N - 1) * p.K + 16 * q;
+    // (rows past M repeat the last one; their results are dropped)
+    const bf16_t* const arow = static_cast<const bf16_t*>(p.A) + (size_t)min(r, p.M - 1) * p.K + 16 * q;
+
+    // what the epilogue reads (this lane's four columns of row m) goes out ahead of everything else, without a branch
+    const int m = r, mc = min(m, p.M - 1);
+    const int n = n0 + 4 * q, nc = min(n, p.N - 4);
+    const u32x2_t bias = *reinterpret_cast<const u32x2_t*>(static_cast<const bf16_t*>(p.bias ? p.bias : p.W) + nc);
+    u32x2_t res = {0u, 0u};
+    size_t orow = (size_t)mc;
+    if (EPI == EPI_BIAS_RES) {
+        const size_t rrow = p.res_rows ? (size_t)p.res_rows[mc] : (size_t)mc;
+        if (p.out_rows) orow = (size_t)p.out_rows[mc];
+        res = *reinterpret_cast<const u32x2_t*>(static_cast<const bf16_t*>(p.residual) + rrow * p.N + nc);
+    }
+
+    f32x4_t acc[KH];
+#pragma unroll
+    for (int h = 0; h < KH; ++h) acc[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    if constexpr (LN) {
+        static_assert(!LN || CW == 16, "one K range");
+        // K <= 64 * NW * U: the wave's whole share is in registers; gain and shift, the same for all rows, go
+        // through LDS (in registers they would cost a second workgroup per CU, and the QKV and FC1 grids of the large
+        // model are one and a half to two workgroups per CU)
+        __shared__ u32x4_t gb[2][8 * NW * U];
+        const int octets = p.K >> 3;                  // 16-byte chunks of a row: at most 8 * NW * U
+        u32x4_t a[U][2], w[U][2];
+        static_assert(2 * 8 * U <= 64, "a thread fetches one chunk");
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) a[i][c] = load16(arow + min(wave + NW * i, turns - 1) * 64 + 8 * c);
+        // thread t fetches chunk t of [gain | shift]
+        const int t0 = threadIdx.x;
+        const int chunk = min(t0 < octets ? t0 : t0 - octets, octets - 1);
+        const u32x4_t gv = load16(static_cast<const bf16_t*>(t0 < octets ? p.ln_g : p.ln_b) + chunk * 8);
+        __builtin_amdgcn_sched_barrier(0);            // loads complete in order: the weights go out last
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) w[i][c] = load16(wrow + min(wave + NW * i, turns - 1) * 64 + 8 * c);
+        __builtin_amdgcn_sched_barrier(0);
+        if (t0 < 2 * octets) gb[t0 < octets ? 0 : 1][chunk] = gv;
+        float mean = 0.f, rstd = 0.f;
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+            float s = 0.f;
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+                if (wave + NW * i < turns) {
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        float v[8];
+                        unpack8(a[i][c], v);
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            if (pass == 0) s += v[j];
+                            else { const float d = v[j] - mean; s = fmaf(d, d, s); }
+                        }
+                    }
+                }
+            s += __shfl_xor(s, 16, 64);
+            s += __shfl_xor(s, 32, 64);
+            if (q == 0) stat[pass][wave][r] = s;
+            // the barrier by hand: __syncthreads() would wait for the weights in flight as well
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            s = 0.f;
+#pragma unroll
+            for (int x = 0; x < NW; ++x) s += stat[pass][x][r];
+            if (pass == 0) mean = s / (float)p.K;
+            else rstd = 1.0f / sqrtf(s / (float)p.K + p.ln_eps);
+        }
+        // normalised in place while the weights are still on their way
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (wave + NW * i < turns) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const int at = (wave + NW * i) * 8 + 2 * q + c;
+                    float gm[8], bt[8], v[8];
+                    unpack8(gb[0][at], gm);
+                    unpack8(gb[1][at], bt);
+                    unpack8(a[i][c], v);
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) v[j] = (v[j] - mean) * rstd * gm[j] + bt[j];
+                    a[i][c] = u32x4_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]),
+                                      pack_bf16x2(v[6], v[7])};
+                }
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (wave + NW * i < turns) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) acc[0] = mfma16(w[i][c], a[i][c], acc[0]);
+            }
+    } else {
+        for (int base = 0; base < half; base += NW * U) {
+            u32x4_t w[U][2], a[U][KH][2];
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const int t = min(base + wave + NW * i, half - 1);
+#pragma unroll
+                for (int c = 0; c < 2; ++c) w[i][c] = load16(wrow + min(t + wh * half, turns - 1) * 64 + 8 * c);
+            }
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const int t = min(base + wave + NW * i, half - 1);
+#pragma unroll
+                for (int h = 0; h < KH; ++h)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+                        a[i][h][c] = load16(arow + min(t + h * half, turns - 1) * 64 + 8 * c);
+            }
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const int t = base + wave + NW * i;
+#pragma unroll
+                for (int h = 0; h < KH; ++h)
+                    if (t < half && t + h * half < turns) {
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) acc[h] = mfma16(w[i][c], a[i][h][c], acc[h]);
+                    }
+            }
+        }
+    }
+
+    if (KH == 2) {
+        // columns 0-7 of the first half are in lanes 0-31 of its results, those of the second half in lanes
+        // 32-63 of its own (each MFMA's other half multiplied mismatched K ranges and is dropped)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[0][j] += __shfl_xor(acc[KH - 1][j], 32, 64);
+    }
+    red[wave][lane] = acc[0];
+    __syncthreads();
+    if (wave != 0 || m >= p.M || (KH == 2 && q >= 2) || n >= p.N) return;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (p.bias) { v[0] = bf16_lo(bias.x); v[1] = bf16_hi(bias.x); v[2] = bf16_lo(bias.y); v[3] = bf16_hi(bias.y); }
+    f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < NW; ++x) sum += red[x][lane];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] += sum[j];
+
+    if (EPI == EPI_BIAS_GELU) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = gelu_fast(v[j]);
+    }
+    if (EPI == EPI_BIAS_RES) {
+        v[0] += bf16_lo(res.x); v[1] += bf16_hi(res.x);
+        v[2] += bf16_lo(res.y); v[3] += bf16_hi(res.y);
+    }
+    bf16_t* dst;
+    if (is_qkv(EPI)) {
+        const int sec = n / p.D, f = n - sec * p.D, hh = f / p.dh, d = f - hh * p.dh;
+        const int bq = m / p.k_tokens, tq = m - bq * p.k_tokens;
+        if (sec == 2) {
+            bf16_t* const vc =
+                static_cast<bf16_t*>(p.v_cache) + (((size_t)bq * p.H + hh) * p.dh + d) * p.L_cap + p.L0 + tq;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) vc[(size_t)j * p.L_cap] = (bf16_t)f32_to_bf16_bits(v[j]);
+            return;
+        }
+        if (EPI == EPI_QKV_ROPE) {
+            const int slot = p.rope_rows ? p.rope_rows[m] % p.rope_N : tq;
+            const size_t at = (size_t)slot * (p.dh >> 1) + (d >> 1);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const float cs = p.rope_cos[at + j], sn = p.rope_sin[at + j], x = v[2 * j], y = v[2 * j + 1];
+                v[2 * j] = x * cs - y * sn;
+                v[2 * j + 1] = x * sn + y * cs;
+            }
+        }
+        if (sec == 0) dst = static_cast<bf16_t*>(p.q_out) + (size_t)m * p.D + f;
+        else dst = static_cast<bf16_t*>(p.k_cache) + (((size_t)bq * p.H + hh) * p.L_cap + p.L0 + tq) * p.dh + d;
+    } else {
+        dst = static_cast<bf16_t*>(p.out) + orow * p.N + n;
+    }
+    *reinterpret_cast<u32x2_t*>(dst) = u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+}
+
+template <int EPI, bool LN, int CW, int NW, int U>
+void launch(const GemmArgs& a, hipStream_t st) {
+    skinny_kernel<EPI, LN, CW, NW, U><<<(a.N + CW - 1) / CW, 64 * NW, 0, st>>>(a);
+}
+
+// Sixteen columns per workgroup where that gives every CU a workgroup or the rows' LayerNorm is repeated in each,
+// else eight.  Turns in flight and waves: so that a wave has its whole share in flight at once (K up to 2048 eight
+// waves, longer ones sixteen).
+template <int EPI>
+void launch_epi(const GemmArgs& a, hipStream_t st) {
+    constexpr int W = kSkinnyWaves, U = kSkinnyTurns;
+    if constexpr (EPI != EPI_BIAS_RES) {
+        if (a.ln_g) {
+            if (a.K <= 64 * W * U / 2) launch<EPI, true, 16, W, U / 2>(a, st);
+            else launch<EPI, true, 16, W, U>(a, st);
+            return;
+        }
+    }
+    if (a.N >= 16 * 256 && a.N % 16 == 0) launch<EPI, false, 16, W, U>(a, st);
+    else if (a.K <= 64 * W * U) launch<EPI, false, 8, W, U / 2>(a, st);
+    else launch<EPI, false, 8, 2 * W, U>(a, st);
+}
+
+}  // namespace
+
+void launch_gemm_skinny(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {
+    switch (epi) {
+        case EPI_QKV:
+            if (a.rope_cos) launch_epi<EPI_QKV_ROPE>(a, stream);
+            else launch_epi<EPI_QKV>(a, stream);
+            break;
+        case EPI_BIAS_RES: launch_epi<EPI_BIAS_RES>(a, stream); break;
+        case EPI_BIAS_GELU: launch_epi<EPI_BIAS_GELU>(a, stream); break;
+    }
+}
+
+}  // namespace fv

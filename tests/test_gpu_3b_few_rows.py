@@ -1,0 +1,66 @@
+"""GPU parity of the products of few rows (up to 16: a workgroup owns 8 or 16 output columns and its waves share K),
+at the edges of the row group (16), column tiles and K turns (64 wide, an odd number of them, more than one
+round), with and without the LayerNorm in front (every token kept, up to 2048 columns).
+Same bars as test_gpu_3_components.py and test_gpu_4_block.py."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fastvar_oracle as O
+from paper_2503_23367_amd import binding as fb
+from paper_2503_23367_amd import synth
+from gpu_util import DEV, cache_rows, empty_ws, from_dev_bf16, make_caches, max_rel, to_dev_bf16, upload_weights
+from test_gpu_3_components import rnd
+from test_gpu_4_block import branch_error
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M", [1, 15, 16, 17, 32, 33])
+@pytest.mark.parametrize("N,K", [(64, 64), (72, 192), (200, 2048), (136, 2112), (72, 8256), (4112, 576), (4104, 1088)])
+@pytest.mark.parametrize("epi", [fb.EPI_BIAS_RES, fb.EPI_BIAS_GELU])
+def test_gemm_few_rows(M, N, K, epi):
+    rng = np.random.default_rng(M * 7 + N * 3 + K + epi)
+    A, W = rnd(rng, M, K), rnd(rng, N, K, scale=0.2)
+    bias, res = rnd(rng, N), rnd(rng, M, N)
+    guard = 4096   # untouched elements behind the output
+    out = torch.full((M * N + guard,), float("nan"), dtype=torch.bfloat16, device=DEV)
+    fb.fastvar_gemm_bf16(to_dev_bf16(A), to_dev_bf16(W), to_dev_bf16(bias), to_dev_bf16(res), M, N, K, epi, out)
+    torch.cuda.synchronize()
+    lin = O.linear(A, W, bias)
+    ref = lin + res if epi == fb.EPI_BIAS_RES else O.gelu(lin)
+    got = from_dev_bf16(out)
+    assert np.isnan(got[M * N:]).all()
+    assert max_rel(got[:M * N].reshape(M, N), ref) <= 2.0 ** -7, (M, N, K, epi)
+
+
+@pytest.mark.parametrize("dims", [synth.BlockDims(D=64, H=1, dh=64, F=64), synth.BlockDims(D=192, H=3, dh=64, F=320),
+                                  synth.BlockDims(D=1088, H=17, dh=64, F=1088), synth.D30, synth.INF2B,
+                                  synth.BlockDims(D=2176, H=17, dh=128, F=2240)], ids=lambda d: f"D{d.D}")
+@pytest.mark.parametrize("B,N,L0", [(1, 1, 0), (2, 8, 3), (1, 17, 300), (4, 8, 21), (3, 11, 40)])
+def test_block_all_tokens_kept_without_an_index_list(dims, B, N, L0):
+    print(f"[few rows] D={dims.D} B={B} N={N} L0={L0}", flush=True)
+    L_cap = (L0 + N + 7) // 8 * 8 + 8
+    x_np = synth.token_map(5, B, 1, N, dims.D)
+    W = synth.block_weights(5, dims)
+    kp, vp = synth.kv_prior(5, B, L0, dims.H, dims.dh)
+    d = fb.make_dims(dims.D, dims.H, dims.dh, dims.F)
+    wt, ws_struct = upload_weights(W)
+    x = to_dev_bf16(x_np)
+    kc, vc = make_caches(kp, vp, L_cap)
+    y, h1 = (torch.full((B, N, dims.D), float("nan"), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    ws = empty_ws(fb.fastvar_block_workspace_bytes(d, B, N))
+    ws.fill_(0xFF)
+    fb.fastvar_attn_forward_pruned(x, N, None, B, N, d, ws_struct, kc, vc, L0, L_cap, h1, ws)
+    kc, vc = make_caches(kp, vp, L_cap)
+    ws.fill_(0xFF)
+    fb.fastvar_block_forward_pruned(x, N, None, B, N, d, ws_struct, kc, vc, L0, L_cap, y, ws)
+    torch.cuda.synchronize()
+    yo, kn, vn, parts = O.block_forward_pruned(x_np, W, dims.H, kp, vp, return_parts=True)
+    got, mid = from_dev_bf16(y), from_dev_bf16(h1)
+    mid64 = mid.astype(np.float64)
+    ffn = O.ffn_sublayer_pruned(mid64, W)
+    kg, vg = cache_rows(kc, vc, L0, L0 + N)
+    assert max(max_rel(got, yo), max_rel(mid, parts["h1"]), max_rel(kg, kn), max_rel(vg, vn),
+               branch_error(mid, x_np, parts["h1"] - x_np, parts["h1"]),
+               branch_error(got, mid64, ffn - mid64, ffn)) <= 2e-2
