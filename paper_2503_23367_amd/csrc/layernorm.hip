@@ -7,6 +7,7 @@
 // workgroups of the same launch write them while the first ones normalise the kept rows.
 #include "common.h"
 #include "kernels.h"
+#include "launch_math.h"
 #include "resample.h"
 
 namespace fv {
@@ -95,11 +96,12 @@ __device__ __forceinline__ void layernorm_row(const bf16_t* __restrict__ in, con
     }
 }
 
-// the launch's threads clear the counters between them (see ZeroCounters)
+// the launch's first workgroups clear the counters between them (see ZeroCounters)
 __device__ __forceinline__ void clear_counters(const ZeroCounters& zc) {
-    const int at = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
-    for (int i = at; i < zc.na; i += step) zc.a[i] = 0;
-    for (int i = at; i < zc.nb; i += step) zc.b[i] = 0;
+    if (!clears_counters(blockIdx.x)) return;
+    const CounterShare s = counter_share(blockIdx.x, threadIdx.x, gridDim.x);
+    for (int i = s.first; i < zc.na; i += s.step) zc.a[i] = 0;
+    for (int i = s.first; i < zc.nb; i += s.step) zc.b[i] = 0;
 }
 
 template <int CH>
@@ -154,7 +156,7 @@ __global__ __launch_bounds__(256) void gather_layernorm_fill_kernel(const bf16_t
 
 void dispatch(const void* in, const int32_t* idx, int N, int k, int M, int D, const void* gamma,
               const void* beta, float eps, int32_t* rows_out, void* out, const ZeroCounters& zc, hipStream_t stream) {
-    const dim3 grid((M + 3) / 4), block(256);
+    const dim3 grid((M + 3) / 4), block(kClearThreads);
     const int ch = (D + 511) / 512;
 #define FV_LN_CASE(CHV)                                                                                  \
     layernorm_rows_kernel<CHV><<<grid, block, 0, stream>>>(                                              \
@@ -188,7 +190,7 @@ void launch_gather_layernorm_fill(const void* x, const int32_t* idx, int B, int 
     f.y_out = static_cast<bf16_t*>(y_out);
     f.hc = hc; f.wc = wc; f.h = h; f.w = w;
     f.blocks_per_sample = (N + 4 * kFillRowsPerWave - 1) / (4 * kFillRowsPerWave);
-    const dim3 grid(ln_blocks + B * f.blocks_per_sample), block(256);
+    const dim3 grid(ln_blocks + B * f.blocks_per_sample), block(kClearThreads);
     const int ch = (D + 511) / 512;
 #define FV_LNF_CASE(CHV)                                                                                 \
     gather_layernorm_fill_kernel<CHV><<<grid, block, 0, stream>>>(                                       \
