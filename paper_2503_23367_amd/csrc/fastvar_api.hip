@@ -223,6 +223,7 @@ void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const 
     int32_t* rows = reinterpret_cast<int32_t*>(base + bp.off_rows);
     void* sk = bp.sk_bytes ? base + bp.off_sk : nullptr;
     const int M = B * k;
+    const bool ln_in_gemm = !idx && fv::few_rows_layernorm(M, 3 * d->D, d->D);
 
     // a1 = LN1(x[idx]); without an index list every token is kept, in order
     if (idx && fill)
@@ -231,7 +232,7 @@ void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const 
                                          fill->y_out, zc, st);
     else if (idx)
         fv::launch_gather_layernorm(x, idx, B, N, k, d->D, w->ln1_g, w->ln1_b, d->ln_eps, rows, buf_a, zc, st);
-    else if (!fv::gemm_takes_layernorm(M, d->D))
+    else if (!ln_in_gemm)
         fv::launch_layernorm(x, M, d->D, w->ln1_g, w->ln1_b, d->ln_eps, buf_a, zc, st);
     mark(st, FASTVAR_STAGE_LN1);
     // q | k | v = a1 * Wqkv^T + b ; k, v appended to the caches at [L0, L0+k)
@@ -240,7 +241,7 @@ void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const 
     g.q_out = buf_q; g.k_cache = kc; g.v_cache = vc;
     g.D = d->D; g.H = d->H; g.dh = d->dh; g.k_tokens = k; g.L0 = L0; g.L_cap = L_cap;
     g.splitk_ws = sk;
-    if (!idx && fv::gemm_takes_layernorm(M, d->D)) {   // few rows: the product normalises them itself
+    if (ln_in_gemm) {   // few rows: the product normalises them itself
         g.A = x; g.ln_g = w->ln1_g; g.ln_b = w->ln1_b; g.ln_eps = d->ln_eps; g.zero = zc;
     }
     if (rope) {   // q and the new keys are turned by the angles of each kept token's own slot
@@ -282,6 +283,7 @@ void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const
     int32_t* rows = reinterpret_cast<int32_t*>(base + bp.off_rows);
     void* sk = bp.sk_bytes ? base + bp.off_sk : nullptr;
     const int M = B * k;
+    const bool ln_in_gemm = !idx && fv::few_rows_layernorm(M, d->F, d->D);
 
     // a2 = LN2(s)
     if (idx && fill)
@@ -290,7 +292,7 @@ void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const
                                          fill->y_out, zc, st);
     else if (idx)
         fv::launch_gather_layernorm(src, idx, B, N, k, d->D, w->ln2_g, w->ln2_b, d->ln_eps, rows, buf_q, zc, st);
-    else if (!fv::gemm_takes_layernorm(M, d->D))
+    else if (!ln_in_gemm)
         fv::launch_layernorm(src, M, d->D, w->ln2_g, w->ln2_b, d->ln_eps, buf_q, zc, st);
     mark(st, FASTVAR_STAGE_LN2);
     // u = gelu(a2 * W1^T + b1)
@@ -298,7 +300,7 @@ void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const
     f1.A = buf_q; f1.W = w->w_fc1; f1.bias = w->b_fc1; f1.M = M; f1.N = d->F; f1.K = d->D;
     f1.out = buf_u; f1.k_tokens = k;
     f1.splitk_ws = sk;
-    if (!idx && fv::gemm_takes_layernorm(M, d->D)) {
+    if (ln_in_gemm) {
         f1.A = src; f1.ln_g = w->ln2_g; f1.ln_b = w->ln2_b; f1.ln_eps = d->ln_eps; f1.zero = zc;
     }
     fv::launch_gemm(fv::EPI_BIAS_GELU, f1, st);

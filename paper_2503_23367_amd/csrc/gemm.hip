@@ -839,16 +839,8 @@ void launch_epi(GemmParams& p, hipStream_t stream) {
     }
 }
 
-}  // namespace
-
-SplitKPlan gemm_splitk_plan(int M, int N, int K) {
+SplitKPlan tiled_splitk_plan(int M, int N, int K) {
     SplitKPlan sk;
-    if (M <= kSkinnyRows) {   // skinny.hip: no exchange between workgroups
-        sk.splits = 1;
-        sk.tiles = sk.shape = sk.tile_m = sk.tile_n = 0;
-        sk.counter_bytes = sk.bytes = 0;
-        return sk;
-    }
     // Up to 256 rows the tiles are 64x64 (eight stages): at those row counts the GEMMs stream their weights,
     // and what counts is how many workgroups pull on them.  Measured inside 32-block steps of the large model
     // (us per launch, 144 / 256 rows): out-proj 13.1 / 14.1 against 21.0 / 21.1 with 128x128 tiles on four
@@ -892,8 +884,20 @@ SplitKPlan gemm_splitk_plan(int M, int N, int K) {
     return sk;
 }
 
+}  // namespace
+
+SplitKPlan gemm_splitk_plan(int M, int N, int K) {
+    SplitKPlan sk = tiled_splitk_plan(M, N, K);
+    if (few_rows_product(M, N, K, sk.splits > 1)) {   // skinny.hip: no exchange between workgroups
+        sk.splits = 1;
+        sk.tiles = sk.shape = sk.tile_m = sk.tile_n = 0;
+        sk.counter_bytes = sk.bytes = 0;
+    }
+    return sk;
+}
+
 void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {
-    if (a.M <= kSkinnyRows) {
+    if (few_rows_product(a.M, a.N, a.K, a.splitk_ws && tiled_splitk_plan(a.M, a.N, a.K).splits > 1)) {
         launch_gemm_skinny(epi, a, stream);
         return;
     }

@@ -9,6 +9,8 @@
 
 #include <mutex>
 
+#include "launch_math.h"
+
 namespace fv {
 
 // Raises a kernel's dynamic-LDS limit: a per-function attribute that has to be set once per process before
@@ -102,7 +104,7 @@ struct GemmArgs {
     // Optional scratch for the split-K path of shapes with few output tiles (gemm_splitk_plan):
     // [counters | partial tiles]; the counters must be zero on entry and are zero again on exit.
     void* splitk_ws = nullptr;
-    // Optional (EPI_QKV, EPI_BIAS_GELU; only where gemm_takes_layernorm says so): the rows of A are normalised on
+    // Optional (EPI_QKV, EPI_BIAS_GELU; only where few_rows_layernorm says so): the rows of A are normalised on
     // the way in, and the call's arrival counters cleared, as the LayerNorm launch this replaces would.
     const void* ln_g = nullptr;
     const void* ln_b = nullptr;
@@ -111,13 +113,8 @@ struct GemmArgs {
 };
 void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream);
 
-// GEMMs of few rows (skinny.hip; launch_gemm routes there).
-constexpr int kSkinnyRows = 16;    // most rows (one 16x16 operand; see there)
-constexpr int kSkinnyWaves = 8;    // waves that share a workgroup's K range
-constexpr int kSkinnyTurns = 4;    // 64-wide K turns a wave has in flight
+// GEMMs of few rows (skinny.hip); launch_gemm routes there what few_rows_product (launch_math.h) gives it.
 void launch_gemm_skinny(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream);
-// A LayerNorm over K columns fits in front of such a product: a wave holds its share of the rows in registers.
-inline bool gemm_takes_layernorm(int M, int K) { return M <= kSkinnyRows && K <= 64 * kSkinnyWaves * kSkinnyTurns; }
 
 // Split-K plan for a GEMM shape with few output tiles (few rows: the small scales of a schedule, where
 // a block is nothing but streaming its weights once): the K range is cut into `splits` slices that run

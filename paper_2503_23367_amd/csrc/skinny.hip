@@ -1,4 +1,4 @@
-// GEMMs of at most kSkinnyRows rows (the first scales of a schedule): C[m,n] = sum_k A[m,k] * W[n,k], with the
+// GEMMs of at most kFewRowsMax rows (the first scales of a schedule): C[m,n] = sum_k A[m,k] * W[n,k], with the
 // same fused epilogues as gemm.hip and, for the QKV and FC1 products, the LayerNorm of the rows in front.
 //
 // At these row counts a block is one pass over its weights (100 MB for the large model), and the time goes to what
@@ -13,15 +13,17 @@
 // in fp32, the values rounded to bf16 as a LayerNorm launch would round them) and the normalised operand are computed
 // while the weights are on their way.  Every workgroup repeats this for its columns; that is 16 rows from L2.
 //
-// Measured on eight blocks of the large model (805 MB of weights): one row 454 -> 358 us, 16 rows 469 -> 436; the small
-// model 304 -> 225, 318 -> 289.  Beyond 16 rows it loses (25 rows in two groups 660 against 474 us: every workgroup reads
-// the rows' operands from L2, and they no longer fit beside the weights in registers), hence kSkinnyRows.
+// Eight blocks of the large model (805 MB of weights), against the tiled products: one row 465 -> 366 us, 16 rows 471 -> 411;
+// of the 512 px model 479 -> 337, 495 -> 391; of the small model 305 -> 200, 318 -> 237.  Beyond 16 rows it loses (25 rows in two
+// groups 660 against 474 us: every workgroup reads the rows' operands from L2, and they no longer fit beside the
+// weights in registers), hence kFewRowsMax; launch_math.h says which shapes of up to 16 rows come here.
 //
 // CW = 16 fills the operand with 16 weight rows.  CW = 8 (outputs of few columns: out-proj, FC2) gives half of the
 // operand's rows to a second K half of the same eight columns, which doubles the number of workgroups: the matrix
 // instructions, one per half, waste half of their rows, and have the time.
 #include "common.h"
 #include "kernels.h"
+#include "launch_math.h"
 
 namespace fv {
 
@@ -265,22 +267,22 @@ void launch(const GemmArgs& a, hipStream_t st) {
     skinny_kernel<EPI, LN, CW, NW, U><<<(a.N + CW - 1) / CW, 64 * NW, 0, st>>>(a);
 }
 
-// Sixteen columns per workgroup where that gives every CU a workgroup or the rows' LayerNorm is repeated in each,
-// else eight.  Turns in flight and waves: so that a wave has its whole share in flight at once (K up to 2048 eight
-// waves, longer ones sixteen).
+template <int EPI, bool LN, int CW, int NW, int U>
+void launch_turns(int turns, const GemmArgs& a, hipStream_t st) {
+    if constexpr (U > 1)
+        if (turns < U) return launch_turns<EPI, LN, CW, NW, U - 1>(turns, a, st);
+    launch<EPI, LN, CW, NW, U>(a, st);
+}
+
 template <int EPI>
 void launch_epi(const GemmArgs& a, hipStream_t st) {
-    constexpr int W = kSkinnyWaves, U = kSkinnyTurns;
-    if constexpr (EPI != EPI_BIAS_RES) {
-        if (a.ln_g) {
-            if (a.K <= 64 * W * U / 2) launch<EPI, true, 16, W, U / 2>(a, st);
-            else launch<EPI, true, 16, W, U>(a, st);
-            return;
-        }
-    }
-    if (a.N >= 16 * 256 && a.N % 16 == 0) launch<EPI, false, 16, W, U>(a, st);
-    else if (a.K <= 64 * W * U) launch<EPI, false, 8, W, U / 2>(a, st);
-    else launch<EPI, false, 8, 2 * W, U>(a, st);
+    constexpr int W = kFewRowsWaves, U = kFewRowsTurns;
+    const FewRowsPlan p = few_rows_plan(a.N, a.K, a.ln_g != nullptr);
+    if constexpr (EPI != EPI_BIAS_RES)
+        if (a.ln_g) return launch_turns<EPI, true, 16, W, U>(p.turns, a, st);
+    if (p.cols == 16) launch_turns<EPI, false, 16, W, U>(p.turns, a, st);
+    else if (p.waves == W) launch_turns<EPI, false, 8, W, U>(p.turns, a, st);
+    else launch_turns<EPI, false, 8, 2 * W, U>(p.turns, a, st);
 }
 
 }  // namespace

@@ -34,6 +34,24 @@ def test_gemm_few_rows(M, N, K, epi):
     assert max_rel(got[:M * N].reshape(M, N), ref) <= 2.0 ** -7, (M, N, K, epi)
 
 
+@pytest.mark.parametrize("M", [1, 8, 13, 16])
+@pytest.mark.parametrize("N,K", [(72, 512), (72, 1088), (72, 2112), (72, 4800), (72, 8064), (4112, 64), (4112, 1600),
+                                 (4112, 2112), (4096, 4096), (2304, 2304), (12304, 128), (16400, 576)])
+def test_gemm_few_rows_turns_in_flight(M, N, K):
+    """One to four turns in flight for eight and sixteen waves, one and two rounds of them, and shapes on both sides of the
+    rule that sends wide outputs to the tiled product."""
+    test_gemm_few_rows(M, N, K, fb.EPI_BIAS_RES)
+
+
+@pytest.mark.parametrize("B,N,L0", [(1, 5, 12), (3, 4, 7), (1, 16, 9)])
+@pytest.mark.parametrize("dims", [synth.D16, synth.BlockDims(D=640, H=10, dh=64, F=2560), synth.BlockDims(D=1536, H=12, dh=128, F=6144),
+                                  synth.BlockDims(D=2176, H=17, dh=128, F=8704)], ids=lambda d: f"D{d.D}")
+def test_block_that_mixes_few_row_and_tiled_products(dims, B, N, L0):
+    """LayerNorm in front of one product and split K in another (1536 columns, more than eight rows), every product tiled but
+    two (2176 columns), one to three turns in flight."""
+    test_block_all_tokens_kept_without_an_index_list(dims, B, N, L0)
+
+
 @pytest.mark.parametrize("dims", [synth.BlockDims(D=64, H=1, dh=64, F=64), synth.BlockDims(D=192, H=3, dh=64, F=320),
                                   synth.BlockDims(D=1088, H=17, dh=64, F=1088), synth.D30, synth.INF2B,
                                   synth.BlockDims(D=2176, H=17, dh=128, F=2240)], ids=lambda d: f"D{d.D}")

@@ -1,4 +1,4 @@
-"""Index and plan arithmetic of the launches (csrc/launch_math.h), compiled with the host compiler and checked at sizes
+"""Index, plan and routing arithmetic of the launches (csrc/launch_math.h), compiled with the host compiler and checked at sizes
 that no GPU test launches."""
 import ctypes as C
 import os
@@ -20,6 +20,15 @@ void share(unsigned block, unsigned thread, unsigned blocks, int* out) {
     out[0] = s.first;
     out[1] = s.step;
 }
+void plan(int N, int K, int layernorm, int* out) {
+    const fv::FewRowsPlan p = fv::few_rows_plan(N, K, layernorm);
+    out[0] = p.cols;
+    out[1] = p.waves;
+    out[2] = p.turns;
+    out[3] = fv::few_rows_share(K, p.cols);
+}
+int few_rows(int M, int N, int K, int split_k) { return fv::few_rows_product(M, N, K, split_k); }
+int few_rows_ln(int M, int N, int K) { return fv::few_rows_layernorm(M, N, K); }
 }
 """
 
@@ -63,3 +72,42 @@ def test_counter_shares_stay_in_range_and_cover_every_counter_once(math, blocks)
                     if first >= n:
                         break
         assert seen == [1] * n
+
+
+@pytest.mark.parametrize("layernorm", [0, 1])
+@pytest.mark.parametrize("N", [64, 2048, 2304, 4096, 4104, 24576])
+def test_few_rows_turns_past_the_end_are_less_than_one_a_wave_and_round(math, N, layernorm):
+    """A wave whose turns are used up loads the last one again: four turns in flight for every K loaded 64 for 18."""
+    for K in range(64, 2049 if layernorm else 33000, 64):
+        out = (C.c_int * 4)()
+        math.plan(N, K, layernorm, out)
+        cols, waves, turns, share = out
+        assert (cols, waves) in ((16, 8), (8, 8), (8, 16)) and 1 <= turns <= 4 and share == -(-K // (64 * (16 // cols)))
+        if layernorm:
+            assert cols == 16 and waves * turns >= share   # the rows of a wave's whole share stay in registers
+        rounds = -(-share // (waves * turns))
+        assert rounds * waves * turns - share < rounds * waves, (K, waves, turns)
+
+
+# Shapes whose few-row product was measured slower than the tiled one (M, N, K, the tiled one splits K).
+TILED = [(16, 32768, 1024, 0), (8, 24576, 1024, 0), (16, 65536, 512, 0), (16, 16384, 2048, 0), (8, 16384, 2304, 0),
+         (16, 2304, 9216, 1), (1, 2304, 9216, 1), (1, 2176, 2176, 1), (12, 24576, 8192, 0), (16, 32768, 8192, 0),
+         (16, 1920, 7680, 1), (2, 5120, 20480, 1), (17, 64, 64, 0)]
+# ... and faster.
+FEW = [(1, 6144, 2048, 1), (16, 6144, 2048, 1), (16, 8192, 2048, 0), (1, 2048, 8192, 1), (8, 1920, 7680, 1),
+       (16, 1024, 4096, 1), (16, 12288, 4096, 0), (8, 16384, 4096, 0), (1, 32768, 8192, 0), (16, 64, 64, 0),
+       (16, 256, 16384, 0), (16, 4096, 1024, 0)]
+
+
+def test_few_rows_routing(math):
+    for case in TILED:
+        assert not math.few_rows(*case), case
+    for case in FEW:
+        assert math.few_rows(*case), case
+    # A block whose shapes have no split-K scratch asks without it: what the scratch's plan gave to the few-row product
+    # has to go there then too.
+    for M in range(1, 18):
+        for N in range(64, 8193, 64):
+            for K in (64, 1024, 2048, 2112, 2304, 3072, 4096, 4352, 6144, 8192, 9216, 16384, 20480, 32768):
+                assert not math.few_rows(M, N, K, 1) or math.few_rows(M, N, K, 0), (M, N, K)
+                assert not math.few_rows_ln(M, N, K) or K <= 2048 and math.few_rows(M, N, K, 1), (M, N, K)
