@@ -53,6 +53,11 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// A normalised value, wherever a LayerNorm is computed.
+__device__ __forceinline__ float layernorm_value(float v, float mean, float rstd, float gain, float shift) {
+    return fmaf((v - mean) * rstd, gain, shift);
+}
+
 // Compile-time loop: f(integral_constant<int, I>) for I in [Begin, End).
 // Used where an accumulator array must only ever be indexed by constants.
 template <int Begin, int End, class F>

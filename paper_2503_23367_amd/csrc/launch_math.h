@@ -35,9 +35,11 @@ struct FewRowsPlan {
     int cols, waves, turns;
 };
 FV_HOST_DEVICE int few_rows_share(int K, int cols) { return cols == 8 ? (K / 64 + 1) / 2 : K / 64; }
+// `layernorm`: a product that a LayerNorm can go in front of (QKV, FC1).  Up to one round of K it has one split of K
+// whether the LayerNorm is in front or, with an index list, in the gather's launch: the results are the same bits.
 FV_HOST_DEVICE FewRowsPlan few_rows_plan(int N, int K, bool layernorm) {
     FewRowsPlan p;
-    p.cols = layernorm || (N >= 16 * 256 && N % 16 == 0) ? 16 : 8;
+    p.cols = (layernorm && K <= kFewRowsRound) || (N >= 16 * 256 && N % 16 == 0) ? 16 : 8;
     p.waves = p.cols == 8 && K > kFewRowsRound ? 2 * kFewRowsWaves : kFewRowsWaves;
     // Loads are not in branches, so a wave whose turns are used up loads the last one again.  Turns in flight that
     // divide the share evenly over the rounds keep that to less than one turn a wave and round; always four of

@@ -88,7 +88,7 @@ __device__ __forceinline__ void layernorm_row(const bf16_t* __restrict__ in, con
             unpack8(braw[g], bt);
             float o[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) o[j] = (v[g][j] - mean) * rstd * gm[j] + bt[j];
+            for (int j = 0; j < 8; ++j) o[j] = layernorm_value(v[g][j], mean, rstd, gm[j], bt[j]);
             uint4 pk;
             pk.x = pack_bf16x2(o[0], o[1]);
             pk.y = pack_bf16x2(o[2], o[3]);

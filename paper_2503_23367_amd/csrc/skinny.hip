@@ -52,6 +52,30 @@ __device__ __forceinline__ f32x4_t mfma16(const u32x4_t& w, const u32x4_t& a, co
                                                    0, 0, 0);
 }
 
+// A barrier for what is in LDS: __syncthreads() would wait for the weights in flight as well.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// The sum over the 32 lanes of a half-wave, lanes 16 apart first, then 8, 4, 2 and 1, in every one of them and without a
+// trip through LDS (once lanes 8 apart agree, a rotation by 4 of 16 lanes brings the lane 4 away).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float half_wave_sum(float v) {
+    const uint32_t u = __float_as_uint(v);
+    const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // {lower, lower}, {upper, upper} of each pair of rows
+    v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    v += dpp<0x128>(v);   // row_ror:8
+    v += dpp<0x124>(v);   // row_ror:4
+    v += dpp<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+    v += dpp<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+    return v;
+}
+
 // Lane l of a wave: operand row r = l % 16 (weight row n0 + r, or token row r of a 16-row group) and K octets
 // q = l / 16 of a 64-wide turn: elements [16 q, 16 q + 16) in two 16-byte loads, one per MFMA (K may be taken in any
 // order as long as both operands agree; this one makes a turn's two loads of a row one 128-byte line).
@@ -62,7 +86,6 @@ template <int EPI, bool LN, int CW, int NW, int U>
 __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
     constexpr int KH = CW == 8 ? 2 : 1;               // K halves side by side in the weight operand
     __shared__ f32x4_t red[NW][64];
-    __shared__ float stat[2][NW][16];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r = lane & 15, q = lane >> 4;
@@ -99,7 +122,9 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
     for (int h = 0; h < KH; ++h) acc[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     if constexpr (LN) {
-        static_assert(!LN || CW == 16, "one K range");
+        static_assert(!LN || (CW == 16 && NW == 8), "one K range; eight waves, as the statistics are added up");
+        __shared__ f32x2_t stat[NW][64 + 2];
+        __shared__ float total[2][16];
         // K <= 64 * NW * U: the wave's whole share is in registers; gain and shift, the same for all rows, go
         // through LDS (in registers they would cost a second workgroup per CU, and the QKV and FC1 grids of the large
         // model are one and a half to two workgroups per CU)
@@ -125,7 +150,7 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
         float mean = 0.f, rstd = 0.f;
 #pragma unroll
         for (int pass = 0; pass < 2; ++pass) {
-            float s = 0.f;
+            f32x2_t s = {0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < U; ++i)
                 if (wave + NW * i < turns) {
@@ -135,23 +160,26 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
                         unpack8(a[i][c], v);
 #pragma unroll
                         for (int j = 0; j < 8; ++j) {
-                            if (pass == 0) s += v[j];
-                            else { const float d = v[j] - mean; s = fmaf(d, d, s); }
+                            if (pass == 0) s[c] += v[j];
+                            else { const float d = v[j] - mean; s[c] = fmaf(d, d, s[c]); }
                         }
                     }
                 }
-            s += __shfl_xor(s, 16, 64);
-            s += __shfl_xor(s, 32, 64);
-            if (q == 0) stat[pass][wave][r] = s;
-            // the barrier by hand: __syncthreads() would wait for the weights in flight as well
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            s = 0.f;
-#pragma unroll
-            for (int x = 0; x < NW; ++x) s += stat[pass][x][r];
-            if (pass == 0) mean = s / (float)p.K;
-            else rstd = 1.0f / sqrtf(s / (float)p.K + p.ln_eps);
+            stat[wave][lane] = s;
+            lds_barrier();
+            // A LayerNorm launch's wave holds octet (wave, q, c) of every 512 columns in lane 8 wave + 2 q + c and adds the
+            // lanes up by a butterfly from the top bit down.  The same tree here, so that a row's mean and deviation
+            // are the same bits with an index list (whose gather is such a launch) and without; each wave does it for
+            // two rows (eight blocks of one token 361; every wave for all of them 362; eight partial sums a row, in
+            // another order, 358).
+            const int mine = 2 * wave + (lane >> 5);
+            s = stat[(lane >> 2) & 7][16 * (lane & 3) + mine];
+            const float sum = half_wave_sum(s[0]) + half_wave_sum(s[1]);
+            if ((lane & 31) == 0)
+                total[pass][mine] = pass == 0 ? sum / (float)p.K : 1.0f / sqrtf(sum / (float)p.K + p.ln_eps);
+            lds_barrier();
+            if (pass == 0) mean = total[0][r];
+            else rstd = total[1][r];
         }
         // normalised in place while the weights are still on their way
 #pragma unroll
@@ -165,7 +193,7 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
                     unpack8(gb[1][at], bt);
                     unpack8(a[i][c], v);
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) v[j] = (v[j] - mean) * rstd * gm[j] + bt[j];
+                    for (int j = 0; j < 8; ++j) v[j] = layernorm_value(v[j], mean, rstd, gm[j], bt[j]);
                     a[i][c] = u32x4_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]),
                                       pack_bf16x2(v[6], v[7])};
                 }
@@ -277,7 +305,7 @@ void launch_turns(int turns, const GemmArgs& a, hipStream_t st) {
 template <int EPI>
 void launch_epi(const GemmArgs& a, hipStream_t st) {
     constexpr int W = kFewRowsWaves, U = kFewRowsTurns;
-    const FewRowsPlan p = few_rows_plan(a.N, a.K, a.ln_g != nullptr);
+    const FewRowsPlan p = few_rows_plan(a.N, a.K, EPI != EPI_BIAS_RES);
     if constexpr (EPI != EPI_BIAS_RES)
         if (a.ln_g) return launch_turns<EPI, true, 16, W, U>(p.turns, a, st);
     if (p.cols == 16) launch_turns<EPI, false, 16, W, U>(p.turns, a, st);

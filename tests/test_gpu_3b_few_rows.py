@@ -82,3 +82,42 @@ def test_block_all_tokens_kept_without_an_index_list(dims, B, N, L0):
     assert max(max_rel(got, yo), max_rel(mid, parts["h1"]), max_rel(kg, kn), max_rel(vg, vn),
                branch_error(mid, x_np, parts["h1"] - x_np, parts["h1"]),
                branch_error(got, mid64, ffn - mid64, ffn)) <= 2e-2
+
+
+@pytest.mark.parametrize("rope", [False, True], ids=["plain", "rope"])
+@pytest.mark.parametrize("dims", [synth.BlockDims(D=64, H=1, dh=64, F=64), synth.BlockDims(D=576, H=9, dh=64, F=2304), synth.D16,
+                                  synth.BlockDims(D=1088, H=17, dh=64, F=1088), synth.D30, synth.INF2B,
+                                  synth.BlockDims(D=2304, H=18, dh=128, F=4608)], ids=lambda d: f"D{d.D}")
+def test_identity_list_is_bit_equal_to_no_list(dims, rope):
+    """Every token kept, by an index list (LayerNorm in the gather's launch) and without one (up to 16 rows and 2048 columns
+    in front of the product): the same sums in the same order, up to 16 rows and just beyond."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(dims.D)
+
+    def rand(*shape, scale=1.0):
+        return (torch.randn(shape, generator=gen, device=DEV) * scale).to(torch.bfloat16)
+
+    D, H, dh, F = dims.D, dims.H, dims.dh, dims.F
+    wt = dict(ln1_g=1 + rand(D, scale=0.1), ln1_b=rand(D, scale=0.1), w_qkv=rand(3 * D, D, scale=0.05), b_qkv=rand(3 * D),
+              w_proj=rand(D, D, scale=0.05), b_proj=rand(D), ln2_g=1 + rand(D, scale=0.1), ln2_b=rand(D, scale=0.1),
+              w_fc1=rand(F, D, scale=0.05), b_fc1=rand(F), w_fc2=rand(D, F, scale=0.05), b_fc2=rand(D))
+    d, w = fb.make_dims(D, H, dh, F), fb.make_weights(wt)
+    for B, h, wd, L0 in ((1, 1, 1, 0), (2, 2, 2, 3), (3, 1, 5, 9), (1, 3, 3, 5), (1, 4, 4, 30), (1, 1, 17, 4)):
+        N = h * wd
+        L_cap = (L0 + N + 7) // 8 * 8
+        x, kc0, vc0 = rand(B, N, D, scale=3.0), rand(B, H, L_cap, dh), rand(B, H, dh, L_cap)
+        cos, sin = (torch.empty(N, dh // 2, device=DEV) for _ in range(2))
+        fb.fastvar_rope2d_table(h, wd, dh, 10000.0, h, wd, cos, sin)
+        ws = empty_ws(fb.fastvar_block_workspace_bytes(d, B, N))
+        got = []
+        for idx in (None, torch.arange(N, dtype=torch.int32, device=DEV).repeat(B, 1).contiguous()):
+            y, kc, vc = torch.empty_like(x), kc0.clone(), vc0.clone()
+            ws.fill_(0xFF)
+            if rope:
+                fb.fastvar_block_forward_pruned_rope(x, N, idx, B, N, d, w, cos, sin, kc, vc, L0, L_cap, y, ws)
+            else:
+                fb.fastvar_block_forward_pruned(x, N, idx, B, N, d, w, kc, vc, L0, L_cap, y, ws)
+            got.append((y, kc, vc))
+        torch.cuda.synchronize()
+        for a, b, what in zip(*got, ("y", "k", "v")):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (what, B, N, L0)
