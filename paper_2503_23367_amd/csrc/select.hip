@@ -13,6 +13,7 @@
 // A selection that keeps every token or none does not depend on the scores: one fill launch.
 #include "common.h"
 #include "kernels.h"
+#include "launch_math.h"
 
 namespace fv {
 
@@ -34,9 +35,7 @@ __device__ __forceinline__ void add8(double (&acc)[8], const uint4& v) {
 // Few, long chunks: the launch after this one sums them in every workgroup, which it can only do cheaply for a
 // handful (4096 x 2048: 8 chunks, 128 KB of partials), and that takes a launch of its own (4.7 us) off the
 // selection; 256 workgroups with 64 KB in flight each read x as fast as more and shorter ones.
-constexpr int kColTile = 64;
 constexpr int kColRows = 32;      // rows of a pass
-constexpr int kMaxChunks = 16;
 __global__ __launch_bounds__(256) void colsum_kernel(const bf16_t* __restrict__ x, double* __restrict__ partial, int N,
                                                      int D, int rows_per_chunk, int n_chunks) {
     __shared__ double red[kColRows][kColTile];
@@ -327,11 +326,7 @@ __global__ __launch_bounds__(256) void trivial_selection_kernel(int N, long tota
 
 SelectPlan select_plan(int B, int N, int D) {
     SelectPlan p;
-    // As few row chunks as give the column sums a workgroup per CU, in powers of two up to sixteen, none shorter
-    // than one pass.
-    const long tiles = (long)((D + kColTile - 1) / kColTile) * B;
-    int chunks = 1;
-    while (chunks < kMaxChunks && tiles * chunks < 240 && (N + 2 * chunks - 1) / (2 * chunks) >= kColRows) chunks *= 2;
+    const int chunks = column_chunks(N, D);
     p.rows_per_chunk = ((N + chunks - 1) / chunks + kColRows - 1) / kColRows * kColRows;
     p.n_chunks = (N + p.rows_per_chunk - 1) / p.rows_per_chunk;
     // The size of the area is part of the interface (callers keep buffers of it, and the static entry point

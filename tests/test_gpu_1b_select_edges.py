@@ -4,8 +4,11 @@ bin again), row chunks of the column sums that are not full, and widths around t
 Same bar as test_gpu_1_select.py: index sets bit-exact, scores within one fp32 rounding."""
 import numpy as np
 import pytest
+import torch
 
+from paper_2503_23367_amd import binding as fb
 from paper_2503_23367_amd import synth
+from gpu_util import DEV, empty_ws
 from test_gpu_1_select import check_against_oracle
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +39,30 @@ def test_scores_crowded_into_one_bin(N):
 def test_width_edges(D):
     x = synth.token_map(13, 2, 9, 23, D)
     check_against_oracle(x, 9, 23, 71, f"D{D}")
+
+
+@pytest.mark.parametrize("B,h,w,D", [(8, 32, 32, 1920), (3, 40, 40, 2048), (5, 16, 16, 1024), (2, 64, 64, 512)])
+def test_scores_of_a_sample_do_not_depend_on_its_batch(B, h, w, D):
+    """Bit for bit, on maps whose column sums depend on the order they are added in: eight columns hold 2^80 and -2^80 at two
+    rows, which swallow what the sums had gathered."""
+    N, k = h * w, h * w // 3
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(B)
+    x = torch.randn(B, N, D, generator=gen, device=DEV)
+    for b in range(B):
+        for c in range(0, D, D // 8):
+            x[b, torch.randperm(N, generator=gen, device=DEV)[:2], c] = torch.tensor([2.0 ** 80, -2.0 ** 80], device=DEV)
+    x = x.to(torch.bfloat16)
+
+    def scores(maps):
+        n = maps.shape[0]
+        score = torch.full((n, N), float("nan"), device=DEV)
+        idx = torch.empty(n, k, dtype=torch.int32, device=DEV)
+        fb.fastvar_select_pivotal(maps, n, h, w, D, k, idx, None, score,
+                                  empty_ws(fb.fastvar_select_workspace_bytes(n, N, D)))
+        return torch.cat([score.view(torch.int32), idx], dim=1)
+
+    whole = scores(x)
+    alone = torch.cat([scores(x[b:b + 1].contiguous()) for b in range(B)])
+    torch.cuda.synchronize()
+    assert torch.equal(whole, alone)

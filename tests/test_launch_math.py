@@ -28,6 +28,7 @@ void plan(int N, int K, int layernorm, int* out) {
     out[3] = fv::few_rows_share(K, p.cols);
 }
 int few_rows(int M, int N, int K, int split_k) { return fv::few_rows_product(M, N, K, split_k); }
+int column_chunks(int N, int D) { return fv::column_chunks(N, D); }
 int few_rows_ln(int M, int N, int K) { return fv::few_rows_layernorm(M, N, K); }
 }
 """
@@ -111,3 +112,17 @@ def test_few_rows_routing(math):
             for K in (64, 1024, 2048, 2112, 2304, 3072, 4096, 4352, 6144, 8192, 9216, 16384, 20480, 32768):
                 assert not math.few_rows(M, N, K, 1) or math.few_rows(M, N, K, 0), (M, N, K)
                 assert not math.few_rows_ln(M, N, K) or K <= 2048 and math.few_rows(M, N, K, 1), (M, N, K)
+
+
+def test_column_chunks_fit_the_scratch(math):
+    """The sums of the chunks go to the head of an area for 32-row chunks, at most 256 of them."""
+    for N in list(range(1, 700)) + [1024, 2047, 2048, 4095, 4096, 8192, 16384, 32767, 32768]:
+        for D in (8, 64, 512, 1024, 1920, 2048, 4096, 8192):
+            chunks = math.column_chunks(N, D)
+            rows = -(-N // chunks)
+            assert chunks in (1, 2, 4, 8, 16) and (chunks == 1 or rows >= 256)
+            rows = 32 * -(-rows // 32)
+            room = 32
+            while -(-N // room) > 256:
+                room *= 2
+            assert -(-N // rows) <= -(-N // room), (N, D)
