@@ -12,6 +12,7 @@ from paper_2503_23367_amd import synth
 from gpu_util import DEV, cache_rows, empty_ws, from_dev_bf16, make_caches, max_rel, to_dev_bf16, upload_weights
 from test_gpu_3_components import rnd
 from test_gpu_4_block import branch_error
+from test_gpu_9_rope import check_block_rope
 
 pytestmark = pytest.mark.gpu
 
@@ -121,3 +122,20 @@ def test_identity_list_is_bit_equal_to_no_list(dims, rope):
         torch.cuda.synchronize()
         for a, b, what in zip(*got, ("y", "k", "v")):
             assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (what, B, N, L0)
+
+
+@pytest.mark.parametrize("dims,B,N", [(synth.BlockDims(D=256, H=2, dh=128, F=512), 1, 12), (synth.BlockDims(D=256, H=2, dh=128, F=512), 3, 5),
+                                      (synth.INF2B, 1, 16)], ids=["D256_b1", "D256_b3", "D2048"])
+def test_few_rows_over_a_long_cache(dims, B, N):
+    """Attention splits the keys between workgroups (heads of 128, 2048 keys or more): its arrival counters are cleared by the
+    product with the LayerNorm in front, out of scratch that holds 0xFF."""
+    test_block_all_tokens_kept_without_an_index_list(dims, B, N, 2200)
+
+
+@pytest.mark.parametrize("name,dims,B,h,w,L0", [
+    ("D192", synth.BlockDims(D=192, H=3, dh=64, F=320), 3, 1, 5, 29), ("D1024", synth.D16, 2, 2, 4, 11),
+    ("D2048", synth.INF2B, 1, 4, 4, 14), ("D2176", synth.BlockDims(D=2176, H=17, dh=128, F=2240), 2, 2, 2, 5)],
+    ids=["D192", "D1024", "D2048", "D2176"])
+def test_rope_without_an_index_list(name, dims, B, h, w, L0):
+    """A token's slot is its row within its sample; with the LayerNorm in front of the product and, at 2176 columns, not."""
+    check_block_rope(name, dims, B, h, w, h * w, L0, (L0 + h * w + 7) // 8 * 8, seed=27)

@@ -226,11 +226,12 @@ def test_stack_equals_single_block_calls_at_the_headline_size():
     assert torch.equal(ya.view(torch.int16), cur.view(torch.int16))
 
 
-@pytest.mark.parametrize("side", [2, 8, 12, 24])
+@pytest.mark.parametrize("side", [2, 4, 5, 8, 12, 24])
 def test_structure_steps_of_the_large_model_across_layers(side):
-    """Structure steps of the 2B-class model: few rows, so every GEMM splits K between workgroups, and the
-    four GEMMs of a block (different tile counts) and the blocks of the stack reuse one scratch area whose
-    arrival counters are cleared once per call.  Three blocks through fastvar_scale_step must give the bits
+    """Structure steps of the 2B-class model.  From 25 rows on (side 5) GEMMs split K between workgroups, and the
+    GEMMs of a block (different tile counts) and the blocks of the stack reuse one scratch area whose arrival
+    counters are cleared once per call; of 16 rows (side 4) FC2 alone does, after products that split nothing
+    and carry the LayerNorm that clears the counters; of 4 rows (side 2) none does.  Three blocks through fastvar_scale_step must give the bits
     of three single-block calls; the first block is also checked against the oracle."""
     dims = synth.INF2B
     B, N, n_layers = 1, side * side, 3
