@@ -24,25 +24,6 @@ namespace fv {
 
 namespace {
 
-// GELU in its tanh form written as a sigmoid: v * sigma(2u), u = sqrt(2/pi) (v + 0.044715 v^3).
-// It deviates from the erf form by at most 3e-4 in absolute value (near |v| = 2),
-// far below the bf16 resolution of the outputs, and costs 7 instructions where
-// an erf approximation costs about 20: the epilogue is pure VALU time that no
-// MFMA overlaps.
-__device__ __forceinline__ float gelu_fast(float v) {
-    // -2u log2(e), the factor folded into the two coefficients
-    constexpr float c1 = -1.4426950408889634f * 1.5957691216057308f;
-    constexpr float c3 = c1 * 0.044715f;
-    const float v2 = v * v;
-    const float e = __builtin_amdgcn_exp2f(v * fmaf(c3, v2, c1));                         // exp(-2u)
-    return v * __builtin_amdgcn_rcpf(1.0f + e);
-}
-
-// Internal fourth epilogue: EPI_QKV with the rotary embedding of q and the new keys (an instantiation of its
-// own, so that the plain QKV GEMM carries none of its registers).
-constexpr int EPI_QKV_ROPE = 3;
-constexpr bool is_qkv(int epi) { return epi == EPI_QKV || epi == EPI_QKV_ROPE; }
-
 struct GemmParams {
     const bf16_t* A;
     const bf16_t* W;

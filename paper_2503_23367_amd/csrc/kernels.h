@@ -79,6 +79,10 @@ enum GemmEpilogue {
     EPI_BIAS_RES = 1,  // out = acc + bias + residual
     EPI_BIAS_GELU = 2  // out = gelu(acc + bias)
 };
+// Internal fourth epilogue: EPI_QKV with the rotary embedding of q and the new keys (an instantiation of its
+// own, so that the plain QKV GEMM carries none of its registers).
+constexpr int EPI_QKV_ROPE = 3;
+constexpr bool is_qkv(int epi) { return epi == EPI_QKV || epi == EPI_QKV_ROPE; }
 struct GemmArgs {
     const void* A;     // [M, K] bf16
     const void* W;     // [N, K] bf16

@@ -14,13 +14,6 @@ namespace fv {
 
 namespace {
 
-__device__ __forceinline__ void unpack8(const uint4& v, float (&f)[8]) {
-    f[0] = bf16_lo(v.x); f[1] = bf16_hi(v.x);
-    f[2] = bf16_lo(v.y); f[3] = bf16_hi(v.y);
-    f[4] = bf16_lo(v.z); f[5] = bf16_hi(v.z);
-    f[6] = bf16_lo(v.w); f[7] = bf16_hi(v.w);
-}
-
 // CH = number of 512-column groups held in registers (D <= 512*CH).
 // Row m of the output reads input row (idx ? b*N + idx[m] : m), b = m / k; that
 // row index is also written to rows_out[m] when asked for.

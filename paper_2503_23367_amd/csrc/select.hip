@@ -364,7 +364,10 @@ void launch_select(const void* x, int B, int N, int D, int k, int32_t* idx, int3
     int passes = 1;
     while (passes < 8 && (long)B * ((N + passes * kScoreRowsPerPass - 1) / (passes * kScoreRowsPerPass)) > 512) passes *= 2;
     const dim3 sgrid((N + passes * kScoreRowsPerPass - 1) / (passes * kScoreRowsPerPass), B);
-#define FV_SCORE_CASE(CHV)                                                                                          score_kernel<CHV><<<sgrid, kScoreThreads, (size_t)CHV * 512 * sizeof(double), stream>>>(xb, partial,                                                                                                   plan.n_chunks, score, N, D, passes)
+#define FV_SCORE_CASE(CHV)                                                                                 \
+    score_kernel<CHV><<<sgrid, kScoreThreads, (size_t)CHV * 512 * sizeof(double), stream>>>(xb, partial,   \
+                                                                                            plan.n_chunks, \
+                                                                                            score, N, D, passes)
     const int ch = (D + 511) / 512;
     if (ch <= 1) FV_SCORE_CASE(1);
     else if (ch <= 2) FV_SCORE_CASE(2);

@@ -29,22 +29,6 @@ namespace fv {
 
 namespace {
 
-constexpr int EPI_QKV_ROPE = 3;
-constexpr bool is_qkv(int epi) { return epi == EPI_QKV || epi == EPI_QKV_ROPE; }
-
-// v * sigma(2u), u = sqrt(2/pi) (v + 0.044715 v^3): the form gemm.hip uses
-__device__ __forceinline__ float gelu_fast(float v) {
-    constexpr float c1 = -1.4426950408889634f * 1.5957691216057308f;
-    constexpr float c3 = c1 * 0.044715f;
-    const float e = __builtin_amdgcn_exp2f(v * fmaf(c3, v * v, c1));
-    return v * __builtin_amdgcn_rcpf(1.0f + e);
-}
-
-__device__ __forceinline__ void unpack8(const u32x4_t& v, float (&f)[8]) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { f[2 * j] = bf16_lo(v[j]); f[2 * j + 1] = bf16_hi(v[j]); }
-}
-
 __device__ __forceinline__ u32x4_t load16(const void* p) { return *reinterpret_cast<const u32x4_t*>(p); }
 
 __device__ __forceinline__ f32x4_t mfma16(const u32x4_t& w, const u32x4_t& a, const f32x4_t& c) {
