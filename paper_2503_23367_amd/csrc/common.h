@@ -76,9 +76,59 @@ __device__ __forceinline__ float gelu_fast(float v) {
     return v * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
-// A normalised value, wherever a LayerNorm is computed.
-__device__ __forceinline__ float layernorm_value(float v, float mean, float rstd, float gain, float shift) {
-    return fmaf((v - mean) * rstd, gain, shift);
+// LayerNorm of one row of D <= 512*CH columns by a wave, wherever one is computed: lane l holds the octets at columns
+// 512 g + 8 l, statistics are two passes in fp32.  gain(g) and shift(g) give the lane's octet of either, store(g, v) takes
+// the rounded result.
+template <int CH, class Gain, class Shift, class Store>
+__device__ __forceinline__ void layernorm_values(const uint4 (&raw)[CH], int D, float eps, Gain&& gain, Shift&& shift,
+                                                 Store&& store) {
+    const int lane = threadIdx.x & 63;
+    float v[CH][8];
+    float sum = 0.f;
+#pragma unroll
+    for (int g = 0; g < CH; ++g) {
+        const int col = g * 512 + lane * 8;
+        if (col < D) {
+            unpack8(raw[g], v[g]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) sum += v[g][j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[g][j] = 0.f;
+        }
+    }
+    const float mean = wave_sum(sum) / (float)D;
+    float sq = 0.f;
+#pragma unroll
+    for (int g = 0; g < CH; ++g) {
+        const int col = g * 512 + lane * 8;
+        if (col < D) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float d = v[g][j] - mean;
+                sq = fmaf(d, d, sq);
+            }
+        }
+    }
+    const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)D + eps);
+#pragma unroll
+    for (int g = 0; g < CH; ++g) {
+        const int col = g * 512 + lane * 8;
+        if (col < D) {
+            float gm[8], bt[8];
+            unpack8(gain(g), gm);
+            unpack8(shift(g), bt);
+            float o[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) o[j] = fmaf((v[g][j] - mean) * rstd, gm[j], bt[j]);
+            uint4 pk;
+            pk.x = pack_bf16x2(o[0], o[1]);
+            pk.y = pack_bf16x2(o[2], o[3]);
+            pk.z = pack_bf16x2(o[4], o[5]);
+            pk.w = pack_bf16x2(o[6], o[7]);
+            store(g, pk);
+        }
+    }
 }
 
 // Compile-time loop: f(integral_constant<int, I>) for I in [Begin, End).

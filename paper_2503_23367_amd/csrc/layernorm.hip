@@ -44,52 +44,10 @@ __device__ __forceinline__ void layernorm_row(const bf16_t* __restrict__ in, con
             braw[g] = *reinterpret_cast<const uint4*>(beta + col);
         }
     }
-    float v[CH][8];
-    float sum = 0.f;
-#pragma unroll
-    for (int g = 0; g < CH; ++g) {
-        const int col = g * 512 + lane * 8;
-        if (col < D) {
-            unpack8(raw[g], v[g]);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) sum += v[g][j];
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[g][j] = 0.f;
-        }
-    }
-    const float mean = wave_sum(sum) / (float)D;
-    float sq = 0.f;
-#pragma unroll
-    for (int g = 0; g < CH; ++g) {
-        const int col = g * 512 + lane * 8;
-        if (col < D) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float d = v[g][j] - mean;
-                sq = fmaf(d, d, sq);
-            }
-        }
-    }
-    const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)D + eps);
-#pragma unroll
-    for (int g = 0; g < CH; ++g) {
-        const int col = g * 512 + lane * 8;
-        if (col < D) {
-            float gm[8], bt[8];
-            unpack8(graw[g], gm);
-            unpack8(braw[g], bt);
-            float o[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) o[j] = layernorm_value(v[g][j], mean, rstd, gm[j], bt[j]);
-            uint4 pk;
-            pk.x = pack_bf16x2(o[0], o[1]);
-            pk.y = pack_bf16x2(o[2], o[3]);
-            pk.z = pack_bf16x2(o[4], o[5]);
-            pk.w = pack_bf16x2(o[6], o[7]);
-            *reinterpret_cast<uint4*>(out + (size_t)m * D + col) = pk;
-        }
-    }
+    layernorm_values<CH>(raw, D, eps, [&](int g) { return graw[g]; }, [&](int g) { return braw[g]; },
+                         [&](int g, const uint4& v) {
+                             *reinterpret_cast<uint4*>(out + (size_t)m * D + g * 512 + lane * 8) = v;
+                         });
 }
 
 // The launch's first workgroups clear the counters between them (see ZeroCounters).  Only a call's first LayerNorm

@@ -3,18 +3,19 @@
 //
 // At these row counts a block is one pass over its weights (100 MB for the large model), and the time goes to what
 // surrounds that pass: a launch per LayerNorm, rings that fill and drain, partial tiles that travel through
-// memory between workgroups.  So nothing is staged here: a workgroup owns CW output columns over the whole K
+// memory between workgroups.  So no weights are staged here: a workgroup owns CW output columns over the whole K
 // range, its waves take K in turns of 64, and every lane loads its weights straight from memory into the
 // registers of a 16x16x32 MFMA operand, all loads of a wave in flight at once (a weight is used by one wave
 // only, so LDS would add a trip and save nothing).  The waves' sums meet in LDS, in wave order; nothing is
 // exchanged between workgroups.
 //
-// LN: the rows' operand fragments are loaded first and the weights right behind them, so mean, variance (two passes
-// in fp32, the values rounded to bf16 as a LayerNorm launch would round them) and the normalised operand are computed
-// while the weights are on their way.  Every workgroup repeats this for its columns; that is 16 rows from L2.
+// LN: the rows are loaded first and the weights right behind them; the rows are normalised, a wave a row, while the
+// weights are on their way, and reach the operands through LDS.  Every workgroup repeats this for its columns: 16 rows
+// from L2.  (Every wave normalising its own share of all sixteen operand rows, also those beyond M: eight blocks of one
+// token 357 us, this way 326.)
 //
-// Eight blocks of the large model (805 MB of weights), against the tiled products: one row 465 -> 366 us, 16 rows 471 -> 411;
-// of the 512 px model 479 -> 337, 495 -> 391; of the small model 305 -> 200, 318 -> 237.  Beyond 16 rows it loses (25 rows in two
+// Eight blocks of the large model (805 MB of weights), against the tiled products: one row 465 -> 335 us, 16 rows 472 -> 411;
+// of the 512 px model 481 -> 301, 494 -> 392; of the small model 308 -> 185, 319 -> 245.  Beyond 16 rows it loses (25 rows in two
 // groups 660 against 474 us: every workgroup reads the rows' operands from L2, and they no longer fit beside the
 // weights in registers), hence kFewRowsMax; launch_math.h says which shapes of up to 16 rows come here.
 //
@@ -41,23 +42,6 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-}
-
-// The sum over the 32 lanes of a half-wave, lanes 16 apart first, then 8, 4, 2 and 1, in every one of them and without a
-// trip through LDS (once lanes 8 apart agree, a rotation by 4 of 16 lanes brings the lane 4 away).
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-    return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float half_wave_sum(float v) {
-    const uint32_t u = __float_as_uint(v);
-    const auto s = __builtin_amdgcn_permlane16_swap(u, u, false, false);   // {lower, lower}, {upper, upper} of each pair of rows
-    v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-    v += dpp<0x128>(v);   // row_ror:8
-    v += dpp<0x124>(v);   // row_ror:4
-    v += dpp<0x4E>(v);    // quad_perm [2, 3, 0, 1]
-    v += dpp<0xB1>(v);    // quad_perm [1, 0, 3, 2]
-    return v;
 }
 
 // Lane l of a wave: operand row r = l % 16 (weight row n0 + r, or token row r of a 16-row group) and K octets
@@ -106,20 +90,27 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
     for (int h = 0; h < KH; ++h) acc[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     if constexpr (LN) {
-        static_assert(!LN || (CW == 16 && NW == 8), "one K range; eight waves, as the statistics are added up");
-        __shared__ f32x2_t stat[NW][64 + 2];
-        __shared__ float total[2][16];
-        // K <= 64 * NW * U: the wave's whole share is in registers; gain and shift, the same for all rows, go
-        // through LDS (in registers they would cost a second workgroup per CU, and the QKV and FC1 grids of the large
-        // model are one and a half to two workgroups per CU)
-        __shared__ u32x4_t gb[2][8 * NW * U];
+        static_assert(!LN || (CW == 16 && 2 * 8 * NW * U <= 64 * NW), "one K range; gain and shift fit where the sums go");
+        // The rows are normalised as a LayerNorm launch does it, by the same code: a wave has one or two of them, in
+        // registers, and leaves them in LDS, where the waves find their operands (16 bytes of padding a row: the sixteen
+        // rows of an operand in different banks).  So a row has the same bits here as with an index list, whose gather is
+        // such a launch, and its arithmetic is done once a workgroup.  Gain and shift, the same for all rows, go through
+        // LDS too: in registers they would cost a second workgroup per CU, and the QKV and FC1 grids of the large model
+        // are one and a half to two workgroups per CU.
+        extern __shared__ __attribute__((aligned(16))) bf16_t rows_s[];
+        const int stride = p.K + 8;
+        u32x4_t(*const gb)[8 * NW * U] = reinterpret_cast<u32x4_t(*)[8 * NW * U]>(&red[0][0]);
         const int octets = p.K >> 3;                  // 16-byte chunks of a row: at most 8 * NW * U
-        u32x4_t a[U][2], w[U][2];
-        static_assert(2 * 8 * U <= 64, "a thread fetches one chunk");
+        uint4 raw[2][U];
+        u32x4_t w[U][2];
 #pragma unroll
-        for (int i = 0; i < U; ++i)
+        for (int h = 0; h < 2; ++h)
+            if (wave + NW * h < p.M) {
+                const bf16_t* const src = static_cast<const bf16_t*>(p.A) + (size_t)(wave + NW * h) * p.K;
 #pragma unroll
-            for (int c = 0; c < 2; ++c) a[i][c] = load16(arow + min(wave + NW * i, turns - 1) * 64 + 8 * c);
+                for (int g = 0; g < U; ++g)
+                    raw[h][g] = *reinterpret_cast<const uint4*>(src + min(g * 512 + lane * 8, p.K - 8));
+            }
         // thread t fetches chunk t of [gain | shift]
         const int t0 = threadIdx.x;
         const int chunk = min(t0 < octets ? t0 : t0 - octets, octets - 1);
@@ -131,58 +122,22 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
             for (int c = 0; c < 2; ++c) w[i][c] = load16(wrow + min(wave + NW * i, turns - 1) * 64 + 8 * c);
         __builtin_amdgcn_sched_barrier(0);
         if (t0 < 2 * octets) gb[t0 < octets ? 0 : 1][chunk] = gv;
-        float mean = 0.f, rstd = 0.f;
+        lds_barrier();
 #pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            f32x2_t s = {0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < U; ++i)
-                if (wave + NW * i < turns) {
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        float v[8];
-                        unpack8(a[i][c], v);
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            if (pass == 0) s[c] += v[j];
-                            else { const float d = v[j] - mean; s[c] = fmaf(d, d, s[c]); }
-                        }
-                    }
-                }
-            stat[wave][lane] = s;
-            lds_barrier();
-            // A LayerNorm launch's wave holds octet (wave, q, c) of every 512 columns in lane 8 wave + 2 q + c and adds the
-            // lanes up by a butterfly from the top bit down.  The same tree here, so that a row's mean and deviation
-            // are the same bits with an index list (whose gather is such a launch) and without; each wave does it for
-            // two rows (eight blocks of one token 361; every wave for all of them 362; eight partial sums a row, in
-            // another order, 358).
-            const int mine = 2 * wave + (lane >> 5);
-            s = stat[(lane >> 2) & 7][16 * (lane & 3) + mine];
-            const float sum = half_wave_sum(s[0]) + half_wave_sum(s[1]);
-            if ((lane & 31) == 0)
-                total[pass][mine] = pass == 0 ? sum / (float)p.K : 1.0f / sqrtf(sum / (float)p.K + p.ln_eps);
-            lds_barrier();
-            if (pass == 0) mean = total[0][r];
-            else rstd = total[1][r];
-        }
-        // normalised in place while the weights are still on their way
+        for (int h = 0; h < 2; ++h)
+            if (wave + NW * h < p.M)
+                layernorm_values<U>(raw[h], p.K, p.ln_eps, [&](int g) { return gb[0][g * 64 + lane]; },
+                                    [&](int g) { return gb[1][g * 64 + lane]; },
+                                    [&](int g, const uint4& v) {
+                                        *reinterpret_cast<uint4*>(rows_s + (wave + NW * h) * stride + g * 512 + lane * 8) = v;
+                                    });
+        lds_barrier();
+        const bf16_t* const xrow = rows_s + min(r, p.M - 1) * stride + 16 * q;
+        u32x4_t a[U][2];
 #pragma unroll
         for (int i = 0; i < U; ++i)
-            if (wave + NW * i < turns) {
 #pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const int at = (wave + NW * i) * 8 + 2 * q + c;
-                    float gm[8], bt[8], v[8];
-                    unpack8(gb[0][at], gm);
-                    unpack8(gb[1][at], bt);
-                    unpack8(a[i][c], v);
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) v[j] = layernorm_value(v[j], mean, rstd, gm[j], bt[j]);
-                    a[i][c] = u32x4_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]),
-                                      pack_bf16x2(v[6], v[7])};
-                }
-            }
-        __builtin_amdgcn_sched_barrier(0);
+            for (int c = 0; c < 2; ++c) a[i][c] = load16(xrow + min(wave + NW * i, turns - 1) * 64 + 8 * c);
 #pragma unroll
         for (int i = 0; i < U; ++i)
             if (wave + NW * i < turns) {
@@ -276,7 +231,13 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
 
 template <int EPI, bool LN, int CW, int NW, int U>
 void launch(const GemmArgs& a, hipStream_t st) {
-    skinny_kernel<EPI, LN, CW, NW, U><<<(a.N + CW - 1) / CW, 64 * NW, 0, st>>>(a);
+    size_t rows_bytes = 0;
+    if constexpr (LN) {   // sixteen rows of 2048 columns: 74 KB with the sums, two workgroups in a CU's 160 KB
+        rows_bytes = (size_t)a.M * (a.K + 8) * sizeof(bf16_t);
+        static std::once_flag once;
+        raise_lds_limit_once(once, &skinny_kernel<EPI, LN, CW, NW, U>, kFewRowsMax * (512 * U + 8) * sizeof(bf16_t));
+    }
+    skinny_kernel<EPI, LN, CW, NW, U><<<(a.N + CW - 1) / CW, 64 * NW, rows_bytes, st>>>(a);
 }
 
 template <int EPI, bool LN, int CW, int NW, int U>
