@@ -198,8 +198,8 @@ int fastvar_select_pivotal(const void* x, int B, int h, int w, int D, int k,
  * memory: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same arguments, results and error codes as
  * fastvar_select_pivotal (bit for bit the same idx, rank and score), without
- * ws / ws_bytes: the column-sum partials, the mean and (when score_out is NULL)
- * the scores live in a device array of FASTVAR_SELECT_STATIC_BYTES bytes that
+ * ws / ws_bytes: the column-sum partials and (when score_out is NULL) the
+ * scores live in a device array of FASTVAR_SELECT_STATIC_BYTES bytes that
  * is part of the library's code object, one copy per GPU, held until the
  * process ends.  The call allocates nothing and frees nothing.
  *   - FASTVAR_ECAPACITY when fastvar_select_workspace_bytes(B, h*w, D) exceeds

@@ -7,9 +7,9 @@
 //   score    every workgroup adds the chunk sums to the mean by itself (a few
 //            chunks only, so that this stays cheap), then fp64
 //            sum_c (x - mean)^2 per token, rounded once to fp32    (re-reads x, mostly from cache)
-//   topk     one workgroup per sample: radix select on the
-//            order-preserving bit pattern of the fp32 score, then an
-//            ordered compaction (ties to the lowest index)
+//   topk     one workgroup per sample: equal-width bins over the range of the scores'
+//            order-preserving bit patterns, direct ranking inside the bin that the
+//            k-th falls into, then an ordered compaction (ties to the lowest index)
 // A selection that keeps every token or none does not depend on the scores: one fill launch.
 #include "common.h"
 #include "kernels.h"
@@ -34,7 +34,8 @@ __device__ __forceinline__ void add8(double (&acc)[8], const uint4& v) {
 // 128 bytes of a row, 32 rows per pass, eight passes of loads in flight), combined through LDS in a fixed order.
 // Few, long chunks: the launch after this one sums them in every workgroup, which it can only do cheaply for a
 // handful (4096 x 2048: 8 chunks, 128 KB of partials), and that takes a launch of its own (4.7 us) off the
-// selection; 256 workgroups with 64 KB in flight each read x as fast as more and shorter ones.
+// selection, for 1.5 us more in the score launch; 256 workgroups with 32 KB in flight each read x about as fast as more and
+// shorter ones (5.5 against 5.2 us).  The selection inside the step of 4096 x 2048: 27.5 -> 21.2 us in all.
 constexpr int kColRows = 32;      // rows of a pass
 __global__ __launch_bounds__(256) void colsum_kernel(const bf16_t* __restrict__ x, double* __restrict__ partial, int N,
                                                      int D, int rows_per_chunk, int n_chunks) {
@@ -185,7 +186,8 @@ constexpr int kMaxCand = 256;
 // LDS atomics seldom meet and one pass nearly always leaves a few candidates; 8-bit digits below the common
 // leading bits piled a whole wave onto a handful of bins and took three to four passes.  Neighbouring tokens of a
 // smooth map still have neighbouring scores: every bin has eight counters in different banks, one per lane % 8
-// (4096 scores 10.3 -> ~6 us, 16384 scores 28.6 -> ~8 us).
+// (the launch inside the step: 4096 scores 10.3 -> 6.8 us, 16384 scores 29 -> 15).  Beyond 16384 tokens (E = 32) a few registers
+// spill; 32761 tokens, whole selection: 119 -> 75 us all the same.
 template <int E>
 __global__ __launch_bounds__(kTopkThreads) void topk_kernel(const float* __restrict__ score, int N, int k,
                                                             int32_t* __restrict__ idx,
