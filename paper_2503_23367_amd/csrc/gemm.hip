@@ -746,7 +746,9 @@ int gemm_cfg_override(int epi) {
 //  * a part-filled last round costs less than a full one (fewer workgroups share the memory system and the
 //    power budget).
 //  * shapes that give at most 128 tiles of 128x128 (few rows) use 128x64 tiles, at most 64 use 64x64 tiles:
-//    more workgroups streaming the weights beat the better operand reuse of the larger tile.
+//    more workgroups streaming the weights beat the better operand reuse of the larger tile.  With a workgroup a CU the
+//    ring takes the LDS there is: 128x64 with eight waves and six stages (with four waves and three stages: 256 x 6144 x
+//    2048 18.6 -> 16.6 us, 256 x 8192 x 2048 18.5 -> 17.1, 576 x 2048 x 2048 17.4 -> 14.1, 960 rows 18.3 -> 15.3).
 // The choice is the candidate with the least modelled time, rounds * (fix + K tiles * per-tile), a part-filled
 // round counting 0.85 + 0.29 * fill; the constants are a least-squares fit to the in-step times of the four
 // GEMMs of fifteen workloads under each configuration (residual 7 % rms; the picks cost 0.3 % more than the
@@ -807,7 +809,7 @@ void launch_epi(GemmParams& p, hipStream_t stream) {
         case 11: launch_cfg<256, 256, 64, 2, 2, 4, 1, EPI>(p, stream); break;
         case 12: launch_cfg<256, 192, 64, 2, 4, 2, 1, EPI>(p, stream); break;
         case 16: launch_cfg<64, 64, 64, 4, 2, 2, 1, EPI>(p, stream); break;
-        case 17: launch_cfg<128, 64, 64, 3, 2, 2, 1, EPI>(p, stream); break;
+        case 17: launch_cfg<128, 64, 64, 6, 4, 2, 1, EPI>(p, stream); break;
         case 32: launch_cfg<256, 128, 64, 3, 4, 2, 1, EPI>(p, stream); break;
         case 34: launch_cfg<192, 128, 64, 3, 2, 2, 1, EPI>(p, stream); break;
         case 40: launch_cfg<128, 128, 64, 4, 2, 4, 1, EPI>(p, stream); break;
