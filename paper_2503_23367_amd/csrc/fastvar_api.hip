@@ -19,7 +19,7 @@ constexpr int kMaxWidth = 8192;  // LayerNorm keeps a row in registers; score ke
 
 struct BlockPlan {
     size_t off_a, off_q, off_h1, off_u, off_rows, off_asplit, asplit_bytes, off_sk, sk_bytes, bytes;
-    int sk_counters, asplit_counters;
+    int asplit_counters;
 };
 
 BlockPlan block_plan(const fastvar_dims* d, int B, int k) {
@@ -47,12 +47,9 @@ BlockPlan block_plan(const fastvar_dims* d, int B, int k) {
     // split-K scratch of the GEMMs (only shapes with few output tiles have any): one area, the
     // largest of the four, used by one GEMM at a time
     p.sk_bytes = 0;
-    p.sk_counters = 0;
-    const int shapes[4][2] = {{3 * d->D, d->D}, {d->D, d->D}, {d->F, d->D}, {d->D, d->F}};
-    for (const auto& nk : shapes) {
-        const fv::SplitKPlan sk = fv::gemm_splitk_plan((int)M, nk[0], nk[1]);
-        if (sk.bytes > p.sk_bytes) p.sk_bytes = sk.bytes;
-        if (sk.splits > 1) p.sk_counters = (int)(sk.counter_bytes / 4);
+    for (const bool out_proj : {true, false}) {
+        const size_t bytes = fv::gemm_splitk_plan((int)M, d->D, out_proj ? d->D : d->F, out_proj).bytes;
+        if (bytes > p.sk_bytes) p.sk_bytes = bytes;
     }
     p.off_sk = off; off += round256(p.sk_bytes);
     p.bytes = off;
@@ -196,25 +193,47 @@ struct Rope {
     const float* sin;
 };
 
-// The arrival counters of the split-K scratch (GEMM) and of the key-range split (attention) must be zero
-// before the first kernel that uses them; every such kernel leaves them zero again, so once per
-// entry-point call is enough: the call's first LayerNorm launch does it.
+// The arrival counters of the key-range split (attention) must be zero before the first kernel that uses
+// them; every such kernel leaves them zero again, so once per entry-point call is enough: the call's first
+// LayerNorm launch does it.
 fv::ZeroCounters split_counters(void* ws, const BlockPlan& bp) {
     fv::ZeroCounters zc;
-    char* base = static_cast<char*>(ws);
-    if (bp.sk_bytes) { zc.a = reinterpret_cast<int32_t*>(base + bp.off_sk); zc.na = bp.sk_counters; }
-    if (bp.asplit_bytes) { zc.b = reinterpret_cast<int32_t*>(base + bp.off_asplit); zc.nb = bp.asplit_counters; }
+    if (bp.asplit_bytes) {
+        zc.p = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + bp.off_asplit);
+        zc.n = bp.asplit_counters;
+    }
     return zc;
+}
+
+// Out-proj or FC2 on the kept tokens.  Where K is split the slices are left in scratch, and what is returned has to
+// be launched before anything reads the output or uses the scratch again: alone or with the LayerNorm of the rows.
+fv::SliceSum enqueue_residual_product(const fv::GemmArgs& g, hipStream_t st) {
+    fv::launch_gemm(fv::EPI_BIAS_RES, g, st);
+    fv::SliceSum s;
+    if (!g.slice_ws) return s;
+    const fv::SplitKPlan sk = fv::gemm_splitk_plan(g.M, g.N, g.K, g.layernorm_follows);
+    if (sk.splits == 1) return s;
+    s.slices = static_cast<const float*>(g.slice_ws);
+    s.splits = sk.splits; s.M = g.M; s.N = g.N;
+    s.residual = g.residual; s.res_rows = g.res_rows;
+    s.out = g.out; s.out_rows = g.out_rows;
+    return s;
+}
+void finish(const fv::SliceSum& s, hipStream_t st) {
+    if (!s.slices) return;
+    fv::launch_slice_sum(s, st);
+    mark(st, FASTVAR_STAGE_FC2);   // (the stopwatch knows whole blocks only)
 }
 
 // Attention half of the block on the kept tokens: h1 = x[idx] + proj(attn(LN1(x[idx]))).
 // Scratch used: a, q, rows of the block plan.
 // `scatter`: h1_out is a [B, N, D] map and row m goes to the kept token's own row of it.
 // `clear`: this is the call's first use of the scratch, so its counters have to be cleared.
-void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
+// `before`: what is left of the product that x comes from (no index list).  Returns what is left of h1.
+fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                   const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* h1_out, void* ws,
                   hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
-                  const Rope* rope = nullptr) {
+                  const Rope* rope = nullptr, const fv::SliceSum& before = {}) {
     const BlockPlan bp = block_plan(d, B, k);
     const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
@@ -232,7 +251,11 @@ void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const 
                                          fill->y_out, zc, st);
     else if (idx)
         fv::launch_gather_layernorm(x, idx, B, N, k, d->D, w->ln1_g, w->ln1_b, d->ln_eps, rows, buf_a, zc, st);
-    else if (!ln_in_gemm)
+    else if (ln_in_gemm)
+        finish(before, st);
+    else if (before.slices)
+        fv::launch_slice_sum_layernorm(before, w->ln1_g, w->ln1_b, d->ln_eps, buf_a, st);
+    else
         fv::launch_layernorm(x, M, d->D, w->ln1_g, w->ln1_b, d->ln_eps, buf_a, zc, st);
     mark(st, FASTVAR_STAGE_LN1);
     // q | k | v = a1 * Wqkv^T + b ; k, v appended to the caches at [L0, L0+k)
@@ -240,7 +263,7 @@ void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const 
     g.A = buf_a; g.W = w->w_qkv; g.bias = w->b_qkv; g.M = M; g.N = 3 * d->D; g.K = d->D;
     g.q_out = buf_q; g.k_cache = kc; g.v_cache = vc;
     g.D = d->D; g.H = d->H; g.dh = d->dh; g.k_tokens = k; g.L0 = L0; g.L_cap = L_cap;
-    g.splitk_ws = sk;
+    g.slice_ws = sk;
     if (ln_in_gemm) {   // few rows: the product normalises them itself
         g.A = x; g.ln_g = w->ln1_g; g.ln_b = w->ln1_b; g.ln_eps = d->ln_eps; g.zero = zc;
     }
@@ -263,18 +286,20 @@ void enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const 
     pj.A = buf_a; pj.W = w->w_proj; pj.bias = w->b_proj; pj.M = M; pj.N = d->D; pj.K = d->D;
     pj.out = h1_out; pj.residual = x; pj.res_rows = idx ? rows : nullptr; pj.k_tokens = k;
     pj.out_rows = (scatter && idx) ? rows : nullptr;
-    pj.splitk_ws = sk;
-    fv::launch_gemm(fv::EPI_BIAS_RES, pj, st);
+    pj.slice_ws = sk; pj.layernorm_follows = true;
+    const fv::SliceSum left = enqueue_residual_product(pj, st);
     mark(st, FASTVAR_STAGE_PROJ);
+    return left;
 }
 
 // MLP half: y = s + fc2(gelu(fc1(LN2(s)))), where s = src[idx] (rows gathered from a [B, N, D]
 // map) or, with idx == NULL, the contiguous [B*k, D] rows at src.  Scratch used: q, u, rows.
 // `scatter_rows`: y is a [B, N, D] map and row m goes to row scatter_rows[m] of it (the absolute row of
 // the kept token, as left in the plan's row list by the gather).
-void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
-                 const fastvar_block_weights* w, void* y, void* ws, hipStream_t st, bool clear, bool scatter = false,
-                 const Fill* fill = nullptr) {
+// `before`: what is left of the product that src comes from (no index list).  Returns what is left of y.
+fv::SliceSum enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
+                         const fastvar_block_weights* w, void* y, void* ws, hipStream_t st, bool clear,
+                         bool scatter = false, const Fill* fill = nullptr, const fv::SliceSum& before = {}) {
     const BlockPlan bp = block_plan(d, B, k);
     const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
@@ -292,14 +317,18 @@ void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const
                                          fill->y_out, zc, st);
     else if (idx)
         fv::launch_gather_layernorm(src, idx, B, N, k, d->D, w->ln2_g, w->ln2_b, d->ln_eps, rows, buf_q, zc, st);
-    else if (!ln_in_gemm)
+    else if (ln_in_gemm)
+        finish(before, st);
+    else if (before.slices)
+        fv::launch_slice_sum_layernorm(before, w->ln2_g, w->ln2_b, d->ln_eps, buf_q, st);
+    else
         fv::launch_layernorm(src, M, d->D, w->ln2_g, w->ln2_b, d->ln_eps, buf_q, zc, st);
     mark(st, FASTVAR_STAGE_LN2);
     // u = gelu(a2 * W1^T + b1)
     fv::GemmArgs f1{};
     f1.A = buf_q; f1.W = w->w_fc1; f1.bias = w->b_fc1; f1.M = M; f1.N = d->F; f1.K = d->D;
     f1.out = buf_u; f1.k_tokens = k;
-    f1.splitk_ws = sk;
+    f1.slice_ws = sk;
     if (ln_in_gemm) {
         f1.A = src; f1.ln_g = w->ln2_g; f1.ln_b = w->ln2_b; f1.ln_eps = d->ln_eps; f1.zero = zc;
     }
@@ -310,18 +339,21 @@ void enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const
     f2.A = buf_u; f2.W = w->w_fc2; f2.bias = w->b_fc2; f2.M = M; f2.N = d->D; f2.K = d->F;
     f2.out = y; f2.residual = src; f2.res_rows = idx ? rows : nullptr; f2.k_tokens = k;
     f2.out_rows = scatter ? rows : nullptr;
-    f2.splitk_ws = sk;
-    fv::launch_gemm(fv::EPI_BIAS_RES, f2, st);
+    f2.slice_ws = sk;
+    const fv::SliceSum left = enqueue_residual_product(f2, st);
     mark(st, FASTVAR_STAGE_FC2);
+    return left;
 }
 
-void enqueue_block(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
-                   const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* y, void* ws,
-                   hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
-                   const Rope* rope = nullptr) {
+// (`before` and what is returned as in the halves)
+fv::SliceSum enqueue_block(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
+                           const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* y, void* ws,
+                           hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
+                           const Rope* rope = nullptr, const fv::SliceSum& before = {}) {
     void* buf_h1 = static_cast<char*>(ws) + block_plan(d, B, k).off_h1;
-    enqueue_attn(x, N, idx, B, k, d, w, kc, vc, L0, L_cap, buf_h1, ws, st, clear, false, idx ? fill : nullptr, rope);
-    enqueue_ffn(buf_h1, 0, nullptr, B, k, d, w, y, ws, st, false, scatter && idx);
+    const fv::SliceSum h1 = enqueue_attn(x, N, idx, B, k, d, w, kc, vc, L0, L_cap, buf_h1, ws, st, clear, false,
+                                         idx ? fill : nullptr, rope, before);
+    return enqueue_ffn(buf_h1, 0, nullptr, B, k, d, w, y, ws, st, false, scatter && idx, nullptr, h1);
 }
 
 int check_ffn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* dims,
@@ -441,8 +473,8 @@ int fastvar_block_forward_pruned(const void* x, int N, const int32_t* idx, int B
                                ws_bytes);
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
-    enqueue_block(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_kept_out, ws,
-                  static_cast<hipStream_t>(stream), true);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    finish(enqueue_block(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_kept_out, ws, st, true), st);
     return launch_status();
 }
 
@@ -467,8 +499,9 @@ int fastvar_block_forward_pruned_rope(const void* x, int N, const int32_t* idx, 
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
     const Rope rope{rope_cos, rope_sin};
-    enqueue_block(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_kept_out, ws,
-                  static_cast<hipStream_t>(stream), true, false, nullptr, &rope);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    finish(enqueue_block(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_kept_out, ws, st, true, false,
+                         nullptr, &rope), st);
     return launch_status();
 }
 
@@ -547,8 +580,8 @@ int fastvar_step(const void* x, const int32_t* sched_h, const int32_t* sched_w, 
     // the step is the upsampled cache.
     const Fill fill{rank, cache_map, hc, wc, h, w, y_out};
     if (k > 0)
-        enqueue_block(x, N, pruned ? idx_out : nullptr, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_out, ws_blk,
-                      st, true, true, &fill);
+        finish(enqueue_block(x, N, pruned ? idx_out : nullptr, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_out,
+                             ws_blk, st, true, true, &fill), st);
     else
         fv::launch_restore(nullptr, rank, B, k, cache_map, hc, wc, h, w, D, y_out, st);
     rc = launch_status();
@@ -620,27 +653,29 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h, const int32_t* sch
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     const fv::SelectPlan sp = fv::select_plan(B, N, D);
+    fv::SliceSum left;   // of the block before (every token kept: its LayerNorm adds the slices up)
     for (int l = 0; l < n_layers; ++l) {
         const fastvar_layer& ly = layers[l];
         const void* src = l == 0 ? x : dst_of(l - 1);
         void* dst = dst_of(l);
         if (dense) {
-            enqueue_block(src, N, nullptr, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk, st,
-                          l == 0);
+            left = enqueue_block(src, N, nullptr, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk,
+                                 st, l == 0, false, nullptr, nullptr, left);
         } else {
             fv::launch_select(src, B, N, D, k, idx_out, k > 0 ? rank : nullptr, nullptr, ws_sel, sp, st);
             mark(st, FASTVAR_STAGE_SELECT);
             // restoration rides in the block's first launch (pruned rows) and its last (kept rows)
             const Fill fill{rank, ly.cache_map, hc, wc, h, w, dst};
             if (k > 0) {
-                enqueue_block(src, N, idx_out, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk,
-                              st, l == 0, true, &fill);
+                finish(enqueue_block(src, N, idx_out, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst,
+                                     ws_blk, st, l == 0, true, &fill), st);
             } else {
                 fv::launch_restore(nullptr, rank, B, k, ly.cache_map, hc, wc, h, w, D, dst, st);
                 mark(st, FASTVAR_STAGE_RESTORE);
             }
         }
     }
+    finish(left, st);
     if (capture &&
         hipMemcpyAsync(y_out, layers[n_layers - 1].cache_map, (size_t)B * N * D * 2, hipMemcpyDeviceToDevice, st) !=
             hipSuccess)
@@ -700,8 +735,8 @@ int fastvar_attn_forward_pruned(const void* x, int N, const int32_t* idx, int B,
                                ws_bytes);
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
-    enqueue_attn(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, h_kept_out, ws,
-                 static_cast<hipStream_t>(stream), true);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    finish(enqueue_attn(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, h_kept_out, ws, st, true), st);
     return launch_status();
 }
 
@@ -711,7 +746,8 @@ int fastvar_ffn_forward_pruned(const void* x, int N, const int32_t* idx, int B, 
     const int rc = check_ffn(x, N, idx, B, k, dims, weights, y_kept_out, ws, ws_bytes);
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
-    enqueue_ffn(x, N, idx, B, k, dims, weights, y_kept_out, ws, static_cast<hipStream_t>(stream), true);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    finish(enqueue_ffn(x, N, idx, B, k, dims, weights, y_kept_out, ws, st, true), st);
     return launch_status();
 }
 
@@ -771,16 +807,16 @@ int fastvar_step_sublayer(const void* x, const int32_t* sched_h, const int32_t* 
     // each half's restoration rides in its own gather launch (pruned rows) and last GEMM (kept rows)
     const Fill fill_a{rank, cache_map_attn, hc, wc, h, w, x_mid};
     if (k_attn > 0)
-        enqueue_attn(x, N, pruned_a ? idx_attn_out : nullptr, B, k_attn, dims, weights, k_cache, v_cache, L0, L_cap,
-                     x_mid, ws_blk, st, true, true, &fill_a);
+        finish(enqueue_attn(x, N, pruned_a ? idx_attn_out : nullptr, B, k_attn, dims, weights, k_cache, v_cache, L0,
+                            L_cap, x_mid, ws_blk, st, true, true, &fill_a), st);
     else
         fv::launch_restore(nullptr, rank, B, k_attn, cache_map_attn, hc, wc, h, w, D, x_mid, st);
     fv::launch_select(x_mid, B, N, D, k_ffn, idx_ffn_out, pruned_f ? rank : nullptr, nullptr, ws_sel, sp, st);
     const Fill fill_f{rank, cache_map_ffn, hc, wc, h, w, y_out};
     if (k_ffn > 0)
         // (the halves lay the scratch out for their own k: its counters are cleared again)
-        enqueue_ffn(x_mid, N, pruned_f ? idx_ffn_out : nullptr, B, k_ffn, dims, weights, y_out, ws_blk, st, true, pruned_f,
-                    &fill_f);
+        finish(enqueue_ffn(x_mid, N, pruned_f ? idx_ffn_out : nullptr, B, k_ffn, dims, weights, y_out, ws_blk, st, true,
+                           pruned_f, &fill_f), st);
     else
         fv::launch_restore(nullptr, rank, B, k_ffn, cache_map_ffn, hc, wc, h, w, D, y_out, st);
     rc = launch_status();

@@ -42,10 +42,8 @@ struct GemmParams {
     const int32_t* rope_rows;  // slot of output row m = rope_rows[m] % rope_N (NULL: its token index)
     int rope_N;
     int tiles_m, tiles_n;
-    int splits;        // split-K slices (grid.y); 1 unless the kernel is instantiated with SK
-    float* sk_part;    // [tile][slice][BM*BN] fp32 partial tiles, accumulator-register order
-    int* sk_cnt;       // [tile] arrival counters, zero between launches
-    int* sk_ready;     // [tile] slices whose partial tile is complete in memory (CF kernels), zero between launches
+    int splits;        // K slices (grid.y); 1 unless the kernel is instantiated with SLICED
+    float* slices;     // [slice][M][N] fp32 sums of the slices (SLICED)
 };
 
 // s_waitcnt immediate (gfx9 encoding): wait until at most `vm` vector-memory
@@ -69,15 +67,15 @@ __device__ __forceinline__ int swz(int row) {
 // summed through LDS at the end.  Eight waves (two per SIMD) cover each other's
 // barrier, load and LDS waits where the tile gives one wave per SIMD too little
 // independent work.
-// SK: the K range is also split between workgroups (blockIdx.y); every workgroup leaves its partial
-// tile in scratch memory, and the one that arrives last at the tile's counter adds the slices up, in
-// slice order (so the sum does not depend on who was last), and runs the epilogue.  Nobody waits.
-// CF (with SK; large partial tiles): the slices count themselves in first, only the earlier arrivers
-// store, and the last one polls for their stores: see the epilogue.
-template <int EPI, int KG, bool SK>
-constexpr bool kPersistent = !SK && KG == 1 && is_qkv(EPI);
+// SLICED: the K range is also split between workgroups (blockIdx.y), each of which leaves the fp32 sums of its
+// slice in scratch memory, row-major; the launch that follows adds the slices up (sum_slices in layernorm.hip),
+// mostly the LayerNorm that reads the rows anyway.  The slices meeting inside this launch instead (partial tiles through
+// memory, the last workgroup of a tile adding them up) cost every such product 3 to 8 us: FC2 of the large model at
+// 64 / 256 / 576 / 1152 rows 13.3 / 25.2 / 43.2 / 60.2 us that way, 9.9 / 20.2 / 29.7 / 51.6 this way.
+template <int EPI, int KG, bool SLICED>
+constexpr bool kPersistent = !SLICED && KG == 1 && is_qkv(EPI);
 
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, int KG, int EPI, bool SK = false, bool CF = false>
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, int KG, int EPI, bool SLICED = false>
 __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const GemmParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     constexpr int NWQ = WGM * WGN;             // waves per k-group
@@ -95,14 +93,12 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     static_assert(A_LD * RPI * NW == BM && W_LD * RPI * NW == BN && NW % 2 == 0, "loads must tile the stage");
     // When a stage is refilled.  EARLY: at the hand-over that frees it, all of the tile's loads at once (LPR
     // after each operand read), so they have STAGES-1 whole tiles of matrix work to land in: what a ring of two
-    // stages needs.  Otherwise spread over the k-steps of the following tile, one load per operand read: a
+    // stages needs, and all that there is room for where k-groups leave a wave few operand reads per tile.
+    // Otherwise spread over the k-steps of the following tile, one load per operand read: a
     // quarter to three quarters of a tile later, which deeper rings can afford, and gentler on the hand-over.
-#ifndef FV_GEMM_EARLY_MAX_STAGES
-#define FV_GEMM_EARLY_MAX_STAGES 2
-#endif
-    constexpr bool EARLY = STAGES <= FV_GEMM_EARLY_MAX_STAGES || KK == 1;
+    constexpr int LPK = KK > 1 ? (LPT + KK - 2) / (KK - 1) : LPT;   // loads of a k-step
+    constexpr bool EARLY = STAGES <= 2 || KK == 1 || LPK > MI + NI;
     constexpr int LPR = (LPT + MI + NI - 1) / (MI + NI);
-    static_assert(EARLY || (LPT + KK - 2) / (KK - 1) <= MI + NI, "one load per operand read at most");
     static_assert((STAGES - 1) * LPT <= 63, "vmcnt is 6 bits");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -126,7 +122,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     // QKV epilogue, the longest (2-byte stores into the transposed V cache): 3-4 % of the launch at 3072 to
     // 6552 rows; the other epilogues are short enough that the hardware's own hand-over from a finished
     // workgroup to the next does as well (measured: +-2 %), so they keep one workgroup per tile.
-    constexpr bool PERSIST = kPersistent<EPI, KG, SK>;
+    constexpr bool PERSIST = kPersistent<EPI, KG, SLICED>;
     const int n_tiles = p.tiles_m * p.tiles_n;
     int m0, n0;
 #define FV_TILE_COORDS(vpid_)                                                                   \
@@ -144,9 +140,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     }
     int vpid = blockIdx.x;
     FV_TILE_COORDS(vpid)
-    static_assert(!SK || KG == 1, "split-K across workgroups is written for one k-group");
-    const int n_splits = SK ? p.splits : 1;
-    const int split = SK ? (int)blockIdx.y : 0;
+    const int n_splits = SLICED ? p.splits : 1;
+    const int split = SLICED ? (int)blockIdx.y : 0;
     const int KT = p.K / BK / n_splits;          // K tiles of this workgroup
     const bf16_t* const Ab = p.A + (size_t)split * KT * BK;
     const bf16_t* const Wb = p.W + (size_t)split * KT * BK;
@@ -384,7 +379,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     // there consecutive lanes are consecutive tokens, 2-byte stores that a half-wave makes 64 contiguous bytes.
     constexpr int XCH = KG > 1 ? MI * NI * 16 * 64 * NWQ : 0;  // floats handed over by the other k-groups
     static_assert(XCH * 4 <= STAGES * (BM + BN) * BK * 2, "the k-group exchange must fit in the tile LDS");
-    if (KG > 1 || SK) {
+    if (KG > 1) {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));
         __builtin_amdgcn_s_barrier();  // every wave is done reading operand tiles: LDS is free for the exchange
@@ -420,138 +415,20 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
         }
         if (kg != 0) return;  // no barrier follows
     }
-    if (SK && CF) {
-        // Large partial tiles (256x128 fp32 = 128 KB): count first, store only if not last.  A slice counts
-        // itself in at the tile's counter; every slice but the last to arrive then leaves its partial tile,
-        // waits until its stores have been acknowledged and reports ready; the last to arrive keeps its own
-        // accumulators, polls the ready count (the others are running and past their K loops: the wait is short
-        // and always ends, and it is bounded all the same), adds the slices up in slice order and runs the
-        // epilogue.  Half the stores of the other order, and none on the last arriver's path.  (For the few-KB
-        // partials of the few-row shapes a poll costs more than the stores it saves: they keep the order below.)
-        float* part = p.sk_part + ((size_t)blockIdx.x * n_splits) * (BM * BN) + wq * 64 + lane;
-        int* flag = reinterpret_cast<int*>(smem);
-        if (tid == 0)
-            *flag = __hip_atomic_fetch_add(p.sk_cnt + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        const int arrived = *flag;
-        if (arrived != n_splits - 1) {
-            float* mine = part + (size_t)split * (BM * BN);
-            static_for<0, MI>([&](auto mi_c) {
-                constexpr int mi = decltype(mi_c)::value;
-                if (m0e + wm * WTM + mi * 32 < p.M) {
-                    static_for<0, NI * 16>([&](auto j_c) {
-                        constexpr int j = decltype(j_c)::value;
-                        __hip_atomic_store(mine + (mi * NI * 16 + j) * (NWQ * 64), acc[mi][j / 16][j % 16],
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    });
-                }
+    if constexpr (SLICED) {
+        float* const sums = p.slices + (size_t)split * p.M * p.N;
+        static_for<0, MI>([&](auto mi_c) {
+            constexpr int mi = decltype(mi_c)::value;
+            const int m = m0e + wm * WTM + mi * 32 + (lane & 31);
+            static_for<0, NI * 4>([&](auto r_c) {
+                constexpr int ni = decltype(r_c)::value / 4, g = decltype(r_c)::value % 4;
+                const int n = n0e + wn * WTN + ni * 32 + 8 * g + 4 * frag_half;
+                if (m < p.M && n < p.N)
+                    *reinterpret_cast<f32x4_t*>(sums + (size_t)m * p.N + n) =
+                        f32x4_t{acc[mi][ni][4 * g], acc[mi][ni][4 * g + 1], acc[mi][ni][4 * g + 2], acc[mi][ni][4 * g + 3]};
             });
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));   // own stores acknowledged
-            __syncthreads();
-            if (tid == 0)
-                __hip_atomic_fetch_add(p.sk_ready + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return;
-        }
-        if (tid == 0) {
-            // about a microsecond per look; the bound is never reached by a launch that is making progress
-            for (int looks = 0; looks < (1 << 20); ++looks) {
-                if (__hip_atomic_load(p.sk_ready + blockIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                    n_splits - 1)
-                    break;
-                __builtin_amdgcn_s_sleep(8);
-            }
-            // ready for the next launch
-            __hip_atomic_store(p.sk_cnt + blockIdx.x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(p.sk_ready + blockIdx.x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-        // slice order, this workgroup's own slice from its registers
-        static_for<0, MI>([&](auto mi_c) {
-            constexpr int mi = decltype(mi_c)::value;
-            if (m0e + wm * WTM + mi * 32 < p.M) {
-                float sum[NI * 16];
-                _Pragma("unroll") for (int j = 0; j < NI * 16; ++j) sum[j] = 0.f;
-                for (int sl = 0; sl < n_splits; ++sl) {
-                    if (sl == split) {
-                        static_for<0, NI * 16>([&](auto j_c) {
-                            constexpr int j = decltype(j_c)::value;
-                            sum[j] += acc[mi][j / 16][j % 16];
-                        });
-                    } else {
-                        const float* src = part + (size_t)sl * (BM * BN) + (mi * NI * 16) * (NWQ * 64);
-                        float v[NI * 16];
-                        _Pragma("unroll") for (int j = 0; j < NI * 16; ++j)
-                            v[j] = __hip_atomic_load(src + j * (NWQ * 64), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        _Pragma("unroll") for (int j = 0; j < NI * 16; ++j) sum[j] += v[j];
-                    }
-                }
-                static_for<0, NI * 16>([&](auto j_c) {
-                    constexpr int j = decltype(j_c)::value;
-                    acc[mi][j / 16][j % 16] = sum[j];
-                });
-            }
         });
-    }
-    if (SK && !CF) {
-        // Leave this slice's partial tile (register-major, lane contiguous), then count arrivals;
-        // 32-row blocks that lie entirely past M (most of the tile at the small scales) are skipped.
-        // The partial tiles and the counter are written and read with device-scope atomic accesses
-        // (relaxed): those are coherent across the chip's L2s by themselves, so no cache write-back
-        // or invalidate is needed (a device-scope fence in each of 256 workgroups costs 7 us per
-        // GEMM here).  Order: every thread waits until its own stores have been acknowledged, the
-        // barrier collects the workgroup, and only then one thread counts the workgroup in.
-        float* part = p.sk_part + ((size_t)blockIdx.x * n_splits) * (BM * BN) + wq * 64 + lane;
-        float* mine = part + (size_t)split * (BM * BN);
-        static_for<0, MI>([&](auto mi_c) {
-            constexpr int mi = decltype(mi_c)::value;
-            if (m0e + wm * WTM + mi * 32 < p.M) {
-                static_for<0, NI * 16>([&](auto j_c) {
-                    constexpr int j = decltype(j_c)::value;
-                    __hip_atomic_store(mine + (mi * NI * 16 + j) * (NWQ * 64), acc[mi][j / 16][j % 16],
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                });
-            }
-        });
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));   // own stores acknowledged
-        int* flag = reinterpret_cast<int*>(smem);
-        __syncthreads();
-        if (tid == 0)
-            *flag = __hip_atomic_fetch_add(p.sk_cnt + blockIdx.x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        const int arrived = *flag;
-        __syncthreads();                 // the flag's LDS word is staging memory below
-        if (arrived != n_splits - 1) return;
-        // sum the slices in slice order; several slices' loads in flight at a time (128 registers' worth)
-        static_for<0, MI>([&](auto mi_c) {
-            constexpr int mi = decltype(mi_c)::value;
-            if (m0e + wm * WTM + mi * 32 < p.M) {
-                float sum[NI * 16];
-                _Pragma("unroll") for (int j = 0; j < NI * 16; ++j) sum[j] = 0.f;
-                constexpr int SG = 8 / NI > 0 ? 8 / NI : 1;
-                for (int s0 = 0; s0 < n_splits; s0 += SG) {
-                    float v[SG][NI * 16];
-                    _Pragma("unroll") for (int g = 0; g < SG; ++g) {
-                        const int sl = min(s0 + g, n_splits - 1);
-                        const float* src = part + (size_t)sl * (BM * BN) + (mi * NI * 16) * (NWQ * 64);
-                        _Pragma("unroll") for (int j = 0; j < NI * 16; ++j)
-                            v[g][j] = __hip_atomic_load(src + j * (NWQ * 64), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
-                    _Pragma("unroll") for (int g = 0; g < SG; ++g) {
-                        if (s0 + g < n_splits) {
-                            _Pragma("unroll") for (int j = 0; j < NI * 16; ++j) sum[j] += v[g][j];
-                        }
-                    }
-                }
-                static_for<0, NI * 16>([&](auto j_c) {
-                    constexpr int j = decltype(j_c)::value;
-                    acc[mi][j / 16][j % 16] = sum[j];
-                });
-            }
-        });
-        if (tid == 0)   // ready for the next launch
-            __hip_atomic_store(p.sk_cnt + blockIdx.x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
     }
     const int lrow = lane & 31;            // output row inside a 32-row block
     static_for<0, MI>([&](auto mi_c) {
@@ -693,24 +570,24 @@ inline int compute_units() {
     return cus[dev];
 }
 
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, int KG, int EPI, bool SK = false, bool CF = false>
+template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, int KG, int EPI, bool SLICED = false>
 void launch_cfg(GemmParams& p, hipStream_t stream) {
     constexpr size_t smem = (size_t)STAGES * (BM + BN) * BK * sizeof(bf16_t);
     p.tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
     static std::once_flag once;  // raising the dynamic-LDS limit is per function, once per process
-    raise_lds_limit_once(once, &gemm_nt_kernel<BM, BN, BK, STAGES, WGM, WGN, KG, EPI, SK, CF>, smem);
-    if (!SK) p.splits = 1;
+    raise_lds_limit_once(once, &gemm_nt_kernel<BM, BN, BK, STAGES, WGM, WGN, KG, EPI, SLICED>, smem);
+    if (!SLICED) p.splits = 1;
     // one round of workgroups when there are more tiles than the chip holds at a time (the kernel then walks
     // the rest itself); as many workgroups per CU as fit into its 160 KB of LDS
     int grid = p.tiles_m * p.tiles_n;
-    if (kPersistent<EPI, KG, SK>) {
+    if (kPersistent<EPI, KG, SLICED>) {
         constexpr int per_cu = (int)((160u << 10) / smem) > 0 ? (int)((160u << 10) / smem) : 1;
         const int slots = compute_units() * per_cu;
         if (grid > slots && slots % 8 == 0) grid = slots;
     }
-    gemm_nt_kernel<BM, BN, BK, STAGES, WGM, WGN, KG, EPI, SK, CF>
-        <<<dim3(grid, SK ? p.splits : 1), 64 * WGM * WGN * KG, smem, stream>>>(p);
+    gemm_nt_kernel<BM, BN, BK, STAGES, WGM, WGN, KG, EPI, SLICED>
+        <<<dim3(grid, SLICED ? p.splits : 1), 64 * WGM * WGN * KG, smem, stream>>>(p);
 }
 
 // Tuning builds only (-DFASTVAR_DEV_KNOBS, never the product library, which reads no environment and keeps
@@ -745,17 +622,20 @@ int gemm_cfg_override(int epi) {
 //    tile count come out even (3072 rows x 2048 columns = 256 tiles).
 //  * a part-filled last round costs less than a full one (fewer workgroups share the memory system and the
 //    power budget).
-//  * shapes that give at most 128 tiles of 128x128 (few rows) use 128x64 tiles, at most 64 use 64x64 tiles:
-//    more workgroups streaming the weights beat the better operand reuse of the larger tile.  With a workgroup a CU the
-//    ring takes the LDS there is: 128x64 with eight waves and six stages (with four waves and three stages: 256 x 6144 x
-//    2048 18.6 -> 16.6 us, 256 x 8192 x 2048 18.5 -> 17.1, 576 x 2048 x 2048 17.4 -> 14.1, 960 rows 18.3 -> 15.3).
+//  * shapes that give at most 128 tiles of 128x128 (few rows) are bound by what a CU pulls in (about 37 bytes a
+//    nanosecond of what misses the L2, 110 of what hits it), so more workgroups on smaller tiles beat the better
+//    operand reuse of the larger ones, and, with a workgroup a CU, rings take the LDS there is: 128x64 tiles with
+//    eight waves and six stages (128x64 with four waves and three: 256 x 6144 x 2048 18.6 -> 16.6 us, 576 x 2048 x 2048
+//    17.3 -> 14.0, 960 rows 18.3 -> 15.4), at most 64: 64x64 tiles with eight stages (64 x 6144 x 2048 13.7 with four,
+//    13.2 with eight), or 64x32 ones where these are at most a round (64 x 6144 x 2048 13.2 -> 11.2, 25 rows 11.4 -> 9.3; but
+//    128 rows, a round and a half, 13.1 -> 19.2).
 // The choice is the candidate with the least modelled time, rounds * (fix + K tiles * per-tile), a part-filled
 // round counting 0.85 + 0.29 * fill; the constants are a least-squares fit to the in-step times of the four
 // GEMMs of fifteen workloads under each configuration (residual 7 % rms; the picks cost 0.3 % more than the
 // best measured configuration of every shape would).
 int gemm_choose_cfg(bool qkv, int M, int N, int K) {
     const long tiles128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-    if (tiles128 <= 64) return 16;
+    if (tiles128 <= 64) return (long)((M + 63) / 64) * ((N + 31) / 32) <= 256 ? 18 : 16;
     if (tiles128 <= 128) return 17;
     struct Cand { int cfg, bm, bn, slots; double fix, per_kt; };
     const Cand cands[] = {
@@ -791,25 +671,12 @@ void launch_epi(GemmParams& p, hipStream_t stream) {
     int cfg = gemm_choose_cfg(is_qkv(EPI), p.M, p.N, p.K);
     constexpr int knob = EPI == EPI_QKV_ROPE ? (int)EPI_QKV : EPI;
     if (gemm_cfg_override(knob) >= 0) cfg = gemm_cfg_override(knob);
-    if (p.sk_part && gemm_cfg_override(knob) < 0) {
-        // few output tiles: split K between workgroups (the caller sized the scratch with the same plan)
-        const SplitKPlan sk = gemm_splitk_plan(p.M, p.N, p.K);
-        if (sk.splits > 1) {
-            p.splits = sk.splits;
-            if (sk.shape == 0) launch_cfg<64, 64, 64, 8, 2, 2, 1, EPI, true>(p, stream);
-            // (128x128: two long slices run best on the eight-wave four-stage tile, four short ones on the
-            // four-wave three-stage one: FC2 at 576 / 960 rows 48.9 -> 46.5 / 49.6 -> 48.0 us, at 400 rows 33.9 vs 35.1)
-            else if (sk.shape == 1 && sk.splits == 2) launch_cfg<128, 128, 64, 4, 2, 4, 1, EPI, true>(p, stream);
-            else if (sk.shape == 1) launch_cfg<128, 128, 64, 3, 2, 2, 1, EPI, true>(p, stream);
-            else launch_cfg<256, 128, 64, 3, 4, 2, 1, EPI, true, true>(p, stream);
-            return;
-        }
-    }
     switch (cfg) {
         case 11: launch_cfg<256, 256, 64, 2, 2, 4, 1, EPI>(p, stream); break;
         case 12: launch_cfg<256, 192, 64, 2, 4, 2, 1, EPI>(p, stream); break;
-        case 16: launch_cfg<64, 64, 64, 4, 2, 2, 1, EPI>(p, stream); break;
+        case 16: launch_cfg<64, 64, 64, 8, 2, 2, 1, EPI>(p, stream); break;
         case 17: launch_cfg<128, 64, 64, 6, 4, 2, 1, EPI>(p, stream); break;
+        case 18: launch_cfg<64, 32, 64, 8, 2, 1, 2, EPI>(p, stream); break;
         case 32: launch_cfg<256, 128, 64, 3, 4, 2, 1, EPI>(p, stream); break;
         case 34: launch_cfg<192, 128, 64, 3, 2, 2, 1, EPI>(p, stream); break;
         case 40: launch_cfg<128, 128, 64, 4, 2, 4, 1, EPI>(p, stream); break;
@@ -822,65 +689,59 @@ void launch_epi(GemmParams& p, hipStream_t stream) {
     }
 }
 
-SplitKPlan tiled_splitk_plan(int M, int N, int K) {
-    SplitKPlan sk;
-    // Up to 256 rows the tiles are 64x64 (eight stages): at those row counts the GEMMs stream their weights,
-    // and what counts is how many workgroups pull on them.  Measured inside 32-block steps of the large model
-    // (us per launch, 144 / 256 rows): out-proj 13.1 / 14.1 against 21.0 / 21.1 with 128x128 tiles on four
-    // slices, FC2 23.4 / 28.4 against 31.4 / 35.3.  Above that, 128x128 tiles split K only where K is long
-    // (FC2): with K = 2048 a slice is 8-16 K tiles and the summing costs more than it saves (out-proj at
-    // 400 / 576 rows: 21.3 / 23.8 split, 14.9 / 20.6 whole).
-    const bool small = M <= 256;
-    sk.shape = small ? 0 : 1;
-    const int t = small ? 64 : 128;
-    sk.tile_m = sk.tile_n = t;
-    sk.tiles = ((M + t - 1) / t) * ((N + t - 1) / t);
-    sk.splits = 1;
-    const int KT = K / 64;
-    const int min_kt = small ? 2 : 4;   // K tiles a slice must keep
-    // a short K range is over before the slices' summing would pay for itself
-    static_assert(kSplitKMaxTiles >= 128 && (kSplitKMaxTiles * 4) % 256 == 0, "covers the tile-count limit below");
-    if (K >= (small ? 2048 : 4096) && sk.tiles <= 128)
-        while (sk.splits < (small ? 8 : 4) && sk.tiles * sk.splits * 2 <= 256 &&
-               KT % (sk.splits * 2) == 0 && KT / (sk.splits * 2) >= min_kt)
-            sk.splits *= 2;   // (more slices than that cost more to sum than they save)
-    if (sk.splits == 1 && !small && K >= 8192 && KT % 2 == 0) {
-        // A long K over a narrow output with a few too many rows for the above (FC2 at 1100-1500 rows): 128x128
-        // tiles would fill a little over half of the chip, at the lowest efficiency of the tile shapes; 256x128
-        // tiles on two K slices fill two thirds to three quarters of it and run the main loop a quarter faster,
-        // and with the count-first exchange (see the kernel) their 128 KB partial tiles cost less than that
-        // gain: 1152 rows 68.7 -> 60.2 us.  With more tiles the exchanged bytes win: 1638 rows 70.1 -> 69.1,
-        // 2048 rows 73.1 -> 79.7 (32 MB of partial tiles); those stay on 128x128 tiles unsplit.
-        const int tiles = ((M + 255) / 256) * ((N + 127) / 128);
-        if (tiles * 2 >= 160 && tiles * 2 <= 192) {
-            sk.shape = 2;
-            sk.tile_m = 256; sk.tile_n = 128;
-            sk.tiles = tiles;
-            sk.splits = 2;
-        }
+void launch_sliced(const SplitKPlan& sk, GemmParams& p, hipStream_t stream) {
+    p.splits = sk.splits;
+    switch (sk.cfg) {
+        case 16: launch_cfg<64, 64, 64, 8, 2, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
+        case 17: launch_cfg<128, 64, 64, 6, 4, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
+        case 34: launch_cfg<192, 128, 64, 3, 2, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
+        default: launch_cfg<128, 128, 64, 4, 2, 4, 1, EPI_BIAS_RES, true>(p, stream); break;   // 40
     }
-    // The counter area has one size for every shape (the most tiles the conditions above admit): the
-    // GEMMs of a block share one scratch area, and a partial tile of one must never land on a counter
-    // of another.
-    sk.counter_bytes = sk.splits > 1 ? (size_t)kSplitKMaxTiles * 8 : 0;   // arrivals, then ready counts
-    sk.bytes = sk.splits > 1 ? sk.counter_bytes + (size_t)sk.tiles * sk.splits * sk.tile_m * sk.tile_n * 4 : 0;
-    return sk;
 }
 
 }  // namespace
 
-SplitKPlan gemm_splitk_plan(int M, int N, int K) {
-    SplitKPlan sk = tiled_splitk_plan(M, N, K);
-    if (few_rows_product(M, N, K, sk.splits > 1)) {   // skinny.hip: no exchange between workgroups
-        sk.splits = 1;
-        sk.tiles = sk.shape = sk.tile_m = sk.tile_n = 0;
-        sk.counter_bytes = sk.bytes = 0;
-    }
-    return sk;
+// Whether the K of an out-proj or FC2 product is cut into slices, and on which tile.  Few output tiles leave CUs idle and
+// make each of the others walk all of K; slices fill the chip, at the price of their fp32 sums going through memory.
+// The candidate with the least modelled time (us): 4.7 to launch, fill and drain; the K tiles of a slice, at what one takes on a
+// full round of 256 workgroups; the slices' bytes at 5 TB/s out and 6.2 TB/s back in, and where no LayerNorm follows
+// that would read the rows anyway (FC2 has one behind it in a stack and none in a single step: half) the launch that adds
+// them up, 3.1.  Unsplit, the tiled product's own choice, at the same per-tile times.  Against 30 products of the large model
+// at 25 to 1152 rows the model is off by 9 % rms, and its picks are the fastest measured, or within 5 % of it.
+SplitKPlan gemm_splitk_plan(int M, int N, int K, bool layernorm_follows) {
+    SplitKPlan best;
+    if (few_rows_product(M, N, K, few_rows_tiled_splits(N, K))) return best;   // skinny.hip
+    struct Cand { int cfg, bm, bn, max_splits; double per_kt; };
+    const Cand cands[] = {{16, 64, 64, 8, 0.27}, {17, 128, 64, 4, 0.40}, {40, 128, 128, 4, 0.50}, {34, 192, 128, 4, 0.66}};
+    const int KT = K / 64;
+    const auto rounds = [](long wgs) {
+        const long full = wgs / 256, rem = wgs - full * 256;
+        return (double)full + (rem ? 0.85 + 0.15 * (double)rem / 256.0 : 0.0);
+    };
+    const auto tiles = [&](const Cand& c) { return (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); };
+    double least = 1e30;
+    const int whole = gemm_choose_cfg(false, M, N, K);
+    if (whole != 16 && whole != 17 && whole != 18 && whole != 40 && whole != 34) return best;   // rows enough for wide tiles
+    for (const Cand& c : cands)
+        if (c.cfg == whole || (whole == 18 && c.cfg == 16)) least = 4.7 + rounds(tiles(c)) * KT * (whole == 17 ? 0.33 : c.per_kt);
+    for (const Cand& c : cands)
+        for (int s = 2; s <= c.max_splits; s *= 2) {
+            if (KT % s != 0 || KT / s < 4 || tiles(c) * s > 256) continue;
+            const double bytes = 4.0 * s * M * N;
+            const double t = 4.7 + rounds(tiles(c) * s) * (KT / s) * c.per_kt + bytes / 5.0e6 + bytes / 6.2e6 +
+                             (layernorm_follows ? 0.0 : 1.5);
+            if (t < least) {
+                least = t;
+                best.splits = s;
+                best.cfg = c.cfg;
+                best.bytes = (size_t)s * M * N * 4;
+            }
+        }
+    return best;
 }
 
 void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {
-    if (few_rows_product(a.M, a.N, a.K, a.splitk_ws && tiled_splitk_plan(a.M, a.N, a.K).splits > 1)) {
+    if (few_rows_product(a.M, a.N, a.K, a.slice_ws && few_rows_tiled_splits(a.N, a.K))) {
         launch_gemm_skinny(epi, a, stream);
         return;
     }
@@ -900,15 +761,12 @@ void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {
     p.rope_cos = a.rope_cos; p.rope_sin = a.rope_sin; p.rope_rows = a.rope_rows; p.rope_N = a.rope_N;
     p.tiles_m = p.tiles_n = 0;
     p.splits = 1;
-    p.sk_part = nullptr;
-    p.sk_cnt = nullptr;
-    p.sk_ready = nullptr;
-    if (a.splitk_ws) {
-        const SplitKPlan sk = gemm_splitk_plan(a.M, a.N, a.K);
+    p.slices = static_cast<float*>(a.slice_ws);
+    if (a.slice_ws && epi == EPI_BIAS_RES) {
+        const SplitKPlan sk = gemm_splitk_plan(a.M, a.N, a.K, a.layernorm_follows);
         if (sk.splits > 1) {
-            p.sk_cnt = static_cast<int*>(a.splitk_ws);
-            p.sk_ready = p.sk_cnt + kSplitKMaxTiles;
-            p.sk_part = reinterpret_cast<float*>(static_cast<char*>(a.splitk_ws) + sk.counter_bytes);
+            launch_sliced(sk, p, stream);
+            return;
         }
     }
     switch (epi) {

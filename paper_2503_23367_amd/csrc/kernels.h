@@ -48,14 +48,12 @@ void launch_residual_accumulate(const float* r_prev, int hp, int wp, const void*
                                 float* r_out, hipStream_t stream);
 
 // ---- block pieces ----
-// Arrival counters in the caller's scratch that have to be zero before the call's first GEMM or attention launch
-// (the split-K areas; every kernel that uses them leaves them zero again).  The call's first LayerNorm launch
-// clears them on the side, which costs nothing measurable; a launch of their own cost 2.7 us each.
+// Arrival counters in the caller's scratch that have to be zero before the call's first attention launch
+// (its key ranges; every kernel that uses them leaves them zero again).  The call's first LayerNorm launch
+// clears them on the side, which costs nothing measurable; a launch of their own cost 2.7 us.
 struct ZeroCounters {
-    int32_t* a = nullptr;
-    int na = 0;
-    int32_t* b = nullptr;
-    int nb = 0;
+    int32_t* p = nullptr;
+    int n = 0;
 };
 // xk = x[idx] (optional copy out) and a = LayerNorm(xk); one wave per row.
 // rows_out (optional, int32 [B*k]) receives the absolute source row b*N + idx[m] of
@@ -105,9 +103,11 @@ struct GemmArgs {
     const float* rope_sin = nullptr;
     const int32_t* rope_rows = nullptr;
     int rope_N = 0;
-    // Optional scratch for the split-K path of shapes with few output tiles (gemm_splitk_plan):
-    // [counters | partial tiles]; the counters must be zero on entry and are zero again on exit.
-    void* splitk_ws = nullptr;
+    // Optional scratch for the slices of a split K (EPI_BIAS_RES; gemm_splitk_plan says whether there are any and how
+    // large they are).  Split, the launch leaves its slices there and touches neither `out` nor `residual`: the
+    // launch of a SliceSum has to follow.
+    void* slice_ws = nullptr;
+    bool layernorm_follows = false;   // as in the plan that the scratch was sized by
     // Optional (EPI_QKV, EPI_BIAS_GELU; only where few_rows_layernorm says so): the rows of A are normalised on
     // the way in, and the call's arrival counters cleared, as the LayerNorm launch this replaces would.
     const void* ln_g = nullptr;
@@ -120,23 +120,28 @@ void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream);
 // GEMMs of few rows (skinny.hip); launch_gemm routes there what few_rows_product (launch_math.h) gives it.
 void launch_gemm_skinny(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream);
 
-// Split-K plan for a GEMM shape with few output tiles (few rows: the small scales of a schedule, where
-// a block is nothing but streaming its weights once): the K range is cut into `splits` slices that run
-// as separate workgroups, so that every CU streams a share of the weights; the workgroup that finishes
-// a tile last sums the slices in slice order and runs the epilogue.  Up to 256 rows use 64x64 tiles with
-// an eight-stage ring (a workgroup's whole K slice, or half of it, is in flight at once), more rows
-// 128x128 tiles where K is long; FC2-like shapes a little too tall for those, 256x128 tiles on two slices.
-// splits == 1: no scratch needed.
-constexpr int kSplitKMaxTiles = 128;   // most output tiles a split-K launch has
+// Split-K plan of an out-proj or FC2 product (EPI_BIAS_RES) of few rows: the K range is cut into `splits` slices that
+// run as separate workgroups and leave fp32 sums [splits][M][N] in scratch; splits == 1: no scratch needed.
+// layernorm_follows: a LayerNorm of the rows always comes next (out-proj) and adds the slices up on the way.
 struct SplitKPlan {
-    int splits;
-    int tiles;
-    int shape;             // 0: 64x64 tiles, 1: 128x128, 2: 256x128 (count-first exchange)
-    int tile_m, tile_n;
-    size_t counter_bytes;  // 2 x kSplitKMaxTiles ints (arrivals, ready counts) whatever the shape: GEMMs that share a scratch area share the counters
-    size_t bytes;          // counters + partial tiles
+    int splits = 1;
+    int cfg = 0;        // tile of the slices (gemm.hip)
+    size_t bytes = 0;
 };
-SplitKPlan gemm_splitk_plan(int M, int N, int K);
+SplitKPlan gemm_splitk_plan(int M, int N, int K, bool layernorm_follows);
+// What is left of a split product: out[row] = sum of the slices, in slice order, + residual (the bias is in the first slice).
+struct SliceSum {
+    const float* slices = nullptr;   // [splits][M][N]; null: nothing is left to do
+    int splits = 0, M = 0, N = 0;
+    const void* residual = nullptr;
+    const int32_t* res_rows = nullptr;   // as in GemmArgs
+    const int32_t* out_rows = nullptr;
+    void* out = nullptr;
+};
+// The sum alone, or with the LayerNorm of the rows behind it: a_out[m] = LayerNorm(out row of m).
+void launch_slice_sum(const SliceSum& s, hipStream_t stream);
+void launch_slice_sum_layernorm(const SliceSum& s, const void* gamma, const void* beta, float eps, void* a_out,
+                                hipStream_t stream);
 // cos / sin tables [h*w, dh/2] fp32 of the axial 2-D rotary embedding (see rope.hip).
 void launch_rope2d_table(int h, int w, int dh, double base, int ref_h, int ref_w, float* cos_out, float* sin_out,
                          hipStream_t stream);

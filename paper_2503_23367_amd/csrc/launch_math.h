@@ -74,6 +74,8 @@ FV_HOST_DEVICE bool few_rows_product(int M, int N, int K, bool split_k) {
     if (K < kFewRowsRound) return M == 1 || N <= (M <= 8 ? 16384 : 12288);
     return N <= (M == 1 ? 16384 : M <= 8 ? 12288 : 2048);
 }
+// The `split_k` of a block's products, which have scratch for slices.
+FV_HOST_DEVICE bool few_rows_tiled_splits(int N, int K) { return K >= 2048 && K / 64 % 2 == 0 && N <= 8192; }
 // A LayerNorm over K columns fits in front: a wave holds its share of the rows in registers.
 FV_HOST_DEVICE bool few_rows_layernorm(int M, int N, int K) {
     return K <= kFewRowsRound && few_rows_product(M, N, K, false);

@@ -62,8 +62,7 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
     const int half = (turns + KH - 1) / KH;           // turns of the first K half
 
     if (LN && blockIdx.x == 0) {                      // (the launch stands in for the call's first LayerNorm)
-        for (int i = threadIdx.x; i < p.zero.na; i += 64 * NW) p.zero.a[i] = 0;
-        for (int i = threadIdx.x; i < p.zero.nb; i += 64 * NW) p.zero.b[i] = 0;
+        for (int i = threadIdx.x; i < p.zero.n; i += 64 * NW) p.zero.p[i] = 0;
     }
 
     // this lane's weight row, and the turn its K half starts at

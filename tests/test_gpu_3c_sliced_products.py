@@ -1,0 +1,53 @@
+"""GPU parity of out-proj and FC2 where their K is cut into slices, and of the launch that adds the slices up: rows one
+short of, at and past the tiles that the plan picks, two to eight slices, one to nine 512-column groups (whole and
+part-filled), with the LayerNorm behind the sum (out-proj in a block), without (its own entry point, a block's FC2) and with the
+kept rows scattered into a map (a step).  Same bars as test_gpu_4_block.py, whose checks these are."""
+import pytest
+import torch
+
+from paper_2503_23367_amd import binding as fb
+from paper_2503_23367_amd import synth
+from gpu_util import DEV, empty_ws
+from test_gpu_4_block import check_block
+
+pytestmark = pytest.mark.gpu
+
+DIMS = [synth.BlockDims(D=448, H=7, dh=64, F=2048), synth.D16, synth.BlockDims(D=1088, H=17, dh=64, F=8192),
+        synth.BlockDims(D=4224, H=33, dh=128, F=4352)]
+
+
+@pytest.mark.parametrize("dims", DIMS, ids=lambda d: f"D{d.D}")
+@pytest.mark.parametrize("B,h,w,k", [(1, 1, 17, 17), (1, 9, 9, 63), (1, 9, 9, 65), (3, 6, 8, 43), (1, 16, 17, 257), (2, 16, 16, 193),
+                                     (1, 25, 25, 577)])
+def test_block(dims, B, h, w, k):
+    check_block(f"slices_{dims.D}", dims, B, h, w, k, 21, (21 + k + 7) // 8 * 8 + 8, seed=31)
+
+
+@pytest.mark.parametrize("dims", DIMS[:3] + [synth.INF2B], ids=lambda d: f"D{d.D}")
+@pytest.mark.parametrize("B,h,w,k", [(1, 8, 8, 31), (2, 12, 13, 70), (1, 24, 24, 400), (1, 30, 31, 929)])
+def test_step_scatters_the_rows_of_the_block(dims, B, h, w, k):
+    """The kept rows of a step's map are the block's own output for the step's index list, bit for bit."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(k)
+
+    def rand(*shape, scale=1.0):
+        return (torch.randn(shape, generator=gen, device=DEV) * scale).to(torch.bfloat16)
+
+    D, H, dh, F, N, L0 = dims.D, dims.H, dims.dh, dims.F, h * w, 19
+    wt = dict(ln1_g=1 + rand(D, scale=0.1), ln1_b=rand(D, scale=0.1), w_qkv=rand(3 * D, D, scale=0.05), b_qkv=rand(3 * D),
+              w_proj=rand(D, D, scale=0.05), b_proj=rand(D), ln2_g=1 + rand(D, scale=0.1), ln2_b=rand(D, scale=0.1),
+              w_fc1=rand(F, D, scale=0.05), b_fc1=rand(F), w_fc2=rand(D, F, scale=0.05), b_fc2=rand(D))
+    d, wts = fb.make_dims(D, H, dh, F), fb.make_weights(wt)
+    L_cap = (L0 + k + 7) // 8 * 8
+    x, cache, kc0, vc0 = rand(B, N, D), rand(B, 6, D), rand(B, H, L_cap, dh), rand(B, H, dh, L_cap)
+    y, y_kept = torch.full_like(x, float("nan")), torch.full((B, k, D), float("nan"), dtype=torch.bfloat16, device=DEV)
+    idx = torch.empty((B, k), dtype=torch.int32, device=DEV)
+    ws = empty_ws(fb.fastvar_step_workspace_bytes(d, B, N, k))
+    ws.fill_(0xFF)
+    kc, vc = kc0.clone(), vc0.clone()
+    fb.fastvar_step(x, [2, h], [3, w], 1, 0, B, k, d, wts, kc, vc, L0, L_cap, cache, y, idx, ws)
+    ws.fill_(0xFF)
+    fb.fastvar_block_forward_pruned(x, N, idx, B, k, d, wts, kc0, vc0, L0, L_cap, y_kept, ws)
+    torch.cuda.synchronize()
+    assert not y.isnan().any()
+    assert torch.equal(torch.gather(y, 1, idx.long()[..., None].expand(B, k, D)).view(torch.int16), y_kept.view(torch.int16))
