@@ -50,6 +50,8 @@ struct AttnParams {
     int q_tiles, splits, keys_per_split, full_tiles, tail_tiles;
     float* part;   // [tail tile][split][1 + DB*QB*4 vectors][QG*64 lanes][4] fp32
     int* split_cnt;   // [tail tile][kCounterStride] arrival counters, zero between launches
+    int n_wg;         // plain kernel: workgroups of its own; those behind them prefetch
+    Prefetch ahead;
     int* split_ready; // [tail tile][kCounterStride] ranges whose partial result is complete in memory, zero between launches
 };
 
@@ -115,12 +117,16 @@ __global__ __launch_bounds__(QG * KSPLIT * 64, (QB == 1 ? 2 : 1)) void attention
     // round-robin to the 8 XCDs, each with its own L2; undo that so an XCD works on
     // a contiguous run of (head, query tile) pairs: the workgroups that stream the
     // same head's K / V then share one L2 instead of pulling it into all eight.
-    int wg = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    const int n_wg = gridDim.x * gridDim.y * gridDim.z;
+    int wg = blockIdx.x;
+    const int n_wg = p.n_wg;
+    if (wg >= n_wg) {
+        prefetch_lines(p.ahead, wg - n_wg);
+        return;
+    }
     if ((n_wg & 7) == 0) wg = (wg & 7) * (n_wg >> 3) + (wg >> 3);
-    const int q_tile = wg % gridDim.x;
-    const int head = (wg / gridDim.x) % gridDim.y;
-    const int b = wg / (gridDim.x * gridDim.y);
+    const int q_tile = wg % p.q_tiles;
+    const int head = (wg / p.q_tiles) % p.H;
+    const int b = wg / (p.q_tiles * p.H);
     const int q_base = q_tile * (QG * 32 * QB) + qg * (32 * QB);
 
     const bf16_t* kc = p.kc + ((size_t)b * p.H + head) * p.L_cap * DH;
@@ -1226,15 +1232,22 @@ void launch_pipe_split(const AttnParams& p, int B, hipStream_t stream) {
 }
 
 template <int DH, int QB, int QG, int KSPLIT>
-void launch_cfg(const AttnParams& p, int B, hipStream_t stream) {
+void launch_cfg(AttnParams& p, const AttnArgs& a, hipStream_t stream) {
     constexpr size_t tile_bytes = (size_t)2 * (64 * KSPLIT * (DH / 8) + DH * (8 * KSPLIT)) * 16;
     constexpr size_t merge_bytes = KSPLIT > 1 ? (size_t)QG * (DH / 32 * 16 + 2) * QB * 64 * 4 : 0;
     constexpr size_t smem = tile_bytes > merge_bytes ? tile_bytes : merge_bytes;
     static std::once_flag once;
     raise_lds_limit_once(once, &attention_kernel<DH, QB, QG, KSPLIT>, smem);
     const int per_wg = QG * 32 * QB;
+    p.q_tiles = (p.k_tokens + per_wg - 1) / per_wg;
+    p.n_wg = p.q_tiles * p.H * a.B;
+    // A quarter of the CUs idle or more: they fetch the weights of the products behind this launch, which takes about
+    // 6.5 us and 1.45 (head dim 64: 0.6) for every tile of keys.
+    if (p.n_wg <= 192)
+        p.ahead = a.ahead.plan(256 - p.n_wg, 6.5 + (DH == 128 ? 1.45 : 0.6) * ((p.L + 64 * KSPLIT - 1) / (64 * KSPLIT)),
+                               a.B * a.k_tokens <= kFewRowsMax);
     attention_kernel<DH, QB, QG, KSPLIT>
-        <<<dim3((p.k_tokens + per_wg - 1) / per_wg, p.H, B), QG * KSPLIT * 64, smem, stream>>>(p);
+        <<<dim3(p.n_wg + p.ahead.blocks), QG * KSPLIT * 64, smem, stream>>>(p);
 }
 
 // Tuning builds only (-DFASTVAR_DEV_KNOBS, never the product library, which reads no environment and keeps
@@ -1404,23 +1417,23 @@ void launch_attention(const AttnArgs& a, hipStream_t stream) {
     if ((cfg == 5 || cfg == 6) && a.L <= 2 * (cfg == 5 ? 128 : 64)) cfg = 4;
     if (a.dh == 128) {
         switch (cfg) {
-            case 0: launch_cfg<128, 2, 4, 1>(p, a.B, stream); break;
-            case 1: launch_cfg<128, 2, 2, 2>(p, a.B, stream); break;
-            case 2: launch_cfg<128, 1, 4, 1>(p, a.B, stream); break;
-            case 3: launch_cfg<128, 1, 2, 2>(p, a.B, stream); break;
+            case 0: launch_cfg<128, 2, 4, 1>(p, a, stream); break;
+            case 1: launch_cfg<128, 2, 2, 2>(p, a, stream); break;
+            case 2: launch_cfg<128, 1, 4, 1>(p, a, stream); break;
+            case 3: launch_cfg<128, 1, 2, 2>(p, a, stream); break;
             case 5: launch_pipe<128, 2, 2>(p, a.B, stream); break;
             case 6: launch_pipe<128, 4, 1>(p, a.B, stream); break;
-            default: launch_cfg<128, 1, 4, 2>(p, a.B, stream); break;
+            default: launch_cfg<128, 1, 4, 2>(p, a, stream); break;
         }
     } else {
         switch (cfg) {
-            case 0: launch_cfg<64, 2, 4, 1>(p, a.B, stream); break;
-            case 1: launch_cfg<64, 2, 2, 2>(p, a.B, stream); break;
-            case 2: launch_cfg<64, 1, 4, 1>(p, a.B, stream); break;
-            case 3: launch_cfg<64, 1, 2, 2>(p, a.B, stream); break;
+            case 0: launch_cfg<64, 2, 4, 1>(p, a, stream); break;
+            case 1: launch_cfg<64, 2, 2, 2>(p, a, stream); break;
+            case 2: launch_cfg<64, 1, 4, 1>(p, a, stream); break;
+            case 3: launch_cfg<64, 1, 2, 2>(p, a, stream); break;
             case 5: launch_pipe<64, 2, 2>(p, a.B, stream); break;
             case 6: launch_pipe<64, 4, 1>(p, a.B, stream); break;
-            default: launch_cfg<64, 1, 4, 2>(p, a.B, stream); break;
+            default: launch_cfg<64, 1, 4, 2>(p, a, stream); break;
         }
     }
 }

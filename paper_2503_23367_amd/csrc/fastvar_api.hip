@@ -233,7 +233,7 @@ void finish(const fv::SliceSum& s, hipStream_t st) {
 fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                   const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* h1_out, void* ws,
                   hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
-                  const Rope* rope = nullptr, const fv::SliceSum& before = {}) {
+                  const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false) {
     const BlockPlan bp = block_plan(d, B, k);
     const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
@@ -279,6 +279,13 @@ fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k
     at.scale = d->softmax_scale;
     at.split_ws = bp.asplit_bytes ? base + bp.off_asplit : nullptr;
     at.split_ws_bytes = bp.asplit_bytes;
+    // (matrices under 16 MB only in a stack, and not for few rows: 16 blocks of the small model on 169 rows 775 -> 734 us with
+    // it, but its single step on 128 rows 55.8 -> 56.4 and eight blocks of it on 16 rows 241 -> 246)
+    if (2L * d->D * d->F >= 16L << 20 || (in_stack && M > fv::kFewRowsMax)) {
+        at.ahead.add(w->w_proj, 2L * d->D * d->D);
+        at.ahead.add(w->w_fc1, 2L * d->D * d->F);
+        at.ahead.add(w->w_fc2, 2L * d->D * d->F);
+    }
     fv::launch_attention(at, st);
     mark(st, FASTVAR_STAGE_ATTENTION);
     // h1 = x[idx] + o * Wp^T + bp
@@ -349,10 +356,10 @@ fv::SliceSum enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int 
 fv::SliceSum enqueue_block(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                            const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* y, void* ws,
                            hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
-                           const Rope* rope = nullptr, const fv::SliceSum& before = {}) {
+                           const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false) {
     void* buf_h1 = static_cast<char*>(ws) + block_plan(d, B, k).off_h1;
     const fv::SliceSum h1 = enqueue_attn(x, N, idx, B, k, d, w, kc, vc, L0, L_cap, buf_h1, ws, st, clear, false,
-                                         idx ? fill : nullptr, rope, before);
+                                         idx ? fill : nullptr, rope, before, in_stack);
     return enqueue_ffn(buf_h1, 0, nullptr, B, k, d, w, y, ws, st, false, scatter && idx, nullptr, h1);
 }
 
@@ -660,7 +667,7 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h, const int32_t* sch
         void* dst = dst_of(l);
         if (dense) {
             left = enqueue_block(src, N, nullptr, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk,
-                                 st, l == 0, false, nullptr, nullptr, left);
+                                 st, l == 0, false, nullptr, nullptr, left, n_layers > 1);
         } else {
             fv::launch_select(src, B, N, D, k, idx_out, k > 0 ? rank : nullptr, nullptr, ws_sel, sp, st);
             mark(st, FASTVAR_STAGE_SELECT);
@@ -668,7 +675,7 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h, const int32_t* sch
             const Fill fill{rank, ly.cache_map, hc, wc, h, w, dst};
             if (k > 0) {
                 finish(enqueue_block(src, N, idx_out, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst,
-                                     ws_blk, st, l == 0, true, &fill), st);
+                                     ws_blk, st, l == 0, true, &fill, nullptr, {}, n_layers > 1), st);
             } else {
                 fv::launch_restore(nullptr, rank, B, k, ly.cache_map, hc, wc, h, w, D, dst, st);
                 mark(st, FASTVAR_STAGE_RESTORE);

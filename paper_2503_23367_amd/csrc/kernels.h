@@ -10,6 +10,7 @@
 #include <mutex>
 
 #include "launch_math.h"
+#include "prefetch.h"
 
 namespace fv {
 
@@ -146,6 +147,27 @@ void launch_slice_sum_layernorm(const SliceSum& s, const void* gamma, const void
 void launch_rope2d_table(int h, int w, int dh, double base, int ref_h, int ref_w, float* cos_out, float* sin_out,
                          hipStream_t stream);
 
+// Matrices that the products behind a launch read, in that order.
+struct WeightsAhead {
+    const void* p[Prefetch::kRanges] = {};
+    long bytes[Prefetch::kRanges] = {};
+    int n = 0;
+    void add(const void* w, long size) { p[n] = w; bytes[n++] = size; }
+    // What a launch of `us` microseconds with `idle` idle CUs fetches of them (prefetch_plan).
+    Prefetch plan(int idle, double us, bool cut) const {
+        Prefetch f;
+        PrefetchPlan pl = prefetch_plan(bytes, n, idle, us, cut);
+        f.blocks = pl.blocks;
+        for (int i = 0; i < n && pl.bytes >= 128; ++i) {
+            const long take = bytes[i] < pl.bytes ? bytes[i] : pl.bytes;
+            f.p[i] = static_cast<const char*>(p[i]);
+            f.lines[i] = (int)(take / 128);
+            pl.bytes -= take;
+        }
+        return f;
+    }
+};
+
 struct AttnArgs {
     const void* q;        // [B*k, D] bf16 (feature = head*dh + d)
     const void* k_cache;  // [B, H, L_cap, dh]
@@ -157,6 +179,7 @@ struct AttnArgs {
     // split the key range between workgroups; without it every workgroup walks all keys.
     void* split_ws = nullptr;
     size_t split_ws_bytes = 0;   // its size: variants that need more are not considered
+    WeightsAhead ahead;          // fetched by a launch that leaves CUs idle
 };
 void launch_attention(const AttnArgs& a, hipStream_t stream);
 

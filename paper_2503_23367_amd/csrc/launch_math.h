@@ -81,6 +81,32 @@ FV_HOST_DEVICE bool few_rows_layernorm(int M, int N, int K) {
     return K <= kFewRowsRound && few_rows_product(M, N, K, false);
 }
 
+// How much of a list of matrices (bytes[0], bytes[1], ..., in the order they are read) a launch of about `us` microseconds
+// fetches ahead on its `idle` CUs, and on how many of them.  Whole matrices, as many as come in while the launch runs: 45 KB a
+// microsecond and CU, 5.6 MB for the chip.  No more CUs than that takes: the launch's own loads wait behind the others.
+// `cut`: products of few rows, whose columns are streamed by workgroups on their own, also gain from the first part of a matrix;
+// their launches are short, so less of it and from more CUs.  Eight blocks of the large model, without / with, us: one row
+// 327 / 318, 64 rows 473 / 450, 256 rows 707 / 675, 576 rows 1063 / 1005; one matrix more than this takes or one less: 64 rows
+// 497 / 482, 256 rows 712 / 682, 576 rows 1037 / 1023; 64 rows on 64 and 256 CUs instead of 128: 498 / 473.
+struct PrefetchPlan {
+    long bytes;
+    int blocks;
+};
+FV_HOST_DEVICE PrefetchPlan prefetch_plan(const long* bytes, int n, int idle, double us, bool cut) {
+    const double per_cu = (cut ? 16.0e3 : 45.0e3) * us, all = idle * per_cu, chip = (cut ? 2.0e6 : 5.6e6) * us;
+    const long budget = (long)(all < chip ? all : chip);
+    PrefetchPlan p{0, 0};
+    for (int i = 0; i < n; ++i) {
+        const long left = budget - p.bytes, take = bytes[i] <= left ? bytes[i] : cut ? left : 0;
+        p.bytes += take;
+        if (take < bytes[i]) break;
+    }
+    if (p.bytes >= 128) p.blocks = ((int)(p.bytes / per_cu) + 16) / 16 * 16;
+    if (p.blocks > idle / 8 * 8) p.blocks = idle / 8 * 8;
+    if (p.blocks <= 0) p = PrefetchPlan{0, 0};
+    return p;
+}
+
 // Row chunks of the selection's column sums, of a map of N tokens and D columns: in powers of two, as few as give the
 // launch a workgroup per CU (64 columns each; 240 of the 256 count as all), none shorter than the 256 rows that a workgroup
 // has in flight.  A function of the map alone, so that a sample's scores have the same bits in every batch.

@@ -29,6 +29,11 @@ void plan(int N, int K, int layernorm, int* out) {
 }
 int few_rows(int M, int N, int K, int split_k) { return fv::few_rows_product(M, N, K, split_k); }
 int column_chunks(int N, int D) { return fv::column_chunks(N, D); }
+void prefetch(const long* bytes, int n, int idle, double us, int cut, long* out) {
+    const fv::PrefetchPlan p = fv::prefetch_plan(bytes, n, idle, us, cut);
+    out[0] = p.bytes;
+    out[1] = p.blocks;
+}
 int few_rows_ln(int M, int N, int K) { return fv::few_rows_layernorm(M, N, K); }
 }
 """
@@ -126,3 +131,18 @@ def test_column_chunks_fit_the_scratch(math):
             while -(-N // room) > 256:
                 room *= 2
             assert -(-N // rows) <= -(-N // room), (N, D)
+
+
+@pytest.mark.parametrize("cut", [0, 1])
+def test_prefetch_plan_stays_inside_the_list_and_the_idle_units(math, cut):
+    """Whole matrices in their order (or, cut, a prefix of the bytes), never more workgroups than idle units, none for nothing."""
+    out = (C.c_long * 2)()
+    for sizes in ([], [0], [100], [8 << 20, 32 << 20, 32 << 20], [2 << 20, 8 << 20, 8 << 20], [1 << 40], [0, 0, 64], [127, 1 << 20]):
+        prefixes = {sum(sizes[:i]) for i in range(len(sizes) + 1)}
+        for idle in (-5, 0, 1, 7, 8, 64, 76, 192, 255):
+            for us in (0.0, 6.5, 7.95, 23.9, 1000.0):
+                math.prefetch((C.c_long * max(1, len(sizes)))(*sizes), len(sizes), idle, C.c_double(us), cut, out)
+                got, blocks = out
+                assert 0 <= got <= sum(sizes) and 0 <= blocks <= max(0, idle) and (got > 0) >= (blocks > 0)
+                assert blocks > 0 or got == 0
+                assert cut or got in prefixes, (sizes, idle, us, got)
