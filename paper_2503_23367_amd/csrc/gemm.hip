@@ -618,8 +618,9 @@ int gemm_cfg_override(int epi) {
 //    20 % slower than with 64-wide ones in four.
 //  * 256x256 (QKV: 256x192, N = 3D divides evenly) wins where its tiles fill whole rounds of the 256 CUs, as
 //    at 2048 kept tokens; 128x128 tiles with eight waves of 64x32 and four stages where the wide tiles would
-//    leave CUs idle (N = D: out-proj, FC2); 192x128 (four waves of 96x64, three stages) where it makes the
-//    tile count come out even (3072 rows x 2048 columns = 256 tiles).
+//    leave CUs idle (N = D: out-proj, FC2).  Between them the tile count decides: 192x128 (eight waves of 96x32, three stages;
+//    four of 96x64 take 5-7 % longer: 960 x 6144 x 2048 29.5 -> 27.6 us), 160x128 (four waves of 160x32, four stages: 2300 x 2048 x
+//    8192 is 240 such tiles, the 2300-row step 438 -> 428) and 192x256 (two stages: 1152 x 8192 x 2048 52.9 -> 46.1).
 //  * a part-filled last round costs less than a full one (fewer workgroups share the memory system and the
 //    power budget).
 //  * shapes that give at most 128 tiles of 128x128 (few rows) are bound by what a CU pulls in (about 37 bytes a
@@ -641,7 +642,9 @@ int gemm_choose_cfg(bool qkv, int M, int N, int K) {
     const Cand cands[] = {
         {qkv ? 12 : 11, 256, qkv ? 192 : 256, 256, 4.0, qkv ? 1.33 : 1.60},
         {32, 256, 128, 256, 10.3, 0.714},
-        {34, 192, 128, 256, 9.5, 0.575},
+        {34, 192, 128, 256, 8.6, 0.545},
+        {35, 160, 128, 256, 11.5, 0.46},
+        {13, 192, 256, 256, 4.0, 1.45},
         {40, 128, 128, 256, 6.2, 0.456},
         {6, 128, 128, 512, 8.0, 1.0},     // two workgroups per CU share its time
     };
@@ -650,7 +653,7 @@ int gemm_choose_cfg(bool qkv, int M, int N, int K) {
     double best = 1e30;
     for (const Cand& c : cands) {
         double per_kt = c.per_kt;
-        if (c.bm == 256 && c.bn >= 192) {
+        if (c.bn >= 192) {
             // the two-stage wide tiles lose ground on long K ranges (1.8 us per K tile at K = 8192) and were
             // never ahead on narrow outputs (N = D: eight tile columns, 4 x 1638 rows 80.7 us against 64.7 modelled
             // for 256x128)
@@ -678,7 +681,9 @@ void launch_epi(GemmParams& p, hipStream_t stream) {
         case 17: launch_cfg<128, 64, 64, 6, 4, 2, 1, EPI>(p, stream); break;
         case 18: launch_cfg<64, 32, 64, 8, 2, 1, 2, EPI>(p, stream); break;
         case 32: launch_cfg<256, 128, 64, 3, 4, 2, 1, EPI>(p, stream); break;
-        case 34: launch_cfg<192, 128, 64, 3, 2, 2, 1, EPI>(p, stream); break;
+        case 13: launch_cfg<192, 256, 64, 2, 2, 4, 1, EPI>(p, stream); break;
+        case 34: launch_cfg<192, 128, 64, 3, 2, 4, 1, EPI>(p, stream); break;
+        case 35: launch_cfg<160, 128, 64, 4, 1, 4, 1, EPI>(p, stream); break;
         case 40: launch_cfg<128, 128, 64, 4, 2, 4, 1, EPI>(p, stream); break;
 #ifdef FASTVAR_DEV_KNOBS
         case 7: launch_cfg<128, 128, 64, 3, 2, 2, 1, EPI>(p, stream); break;
@@ -695,6 +700,7 @@ void launch_sliced(const SplitKPlan& sk, GemmParams& p, hipStream_t stream) {
         case 16: launch_cfg<64, 64, 64, 8, 2, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
         case 17: launch_cfg<128, 64, 64, 6, 4, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
         case 34: launch_cfg<192, 128, 64, 3, 2, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
+        case 35: launch_cfg<160, 128, 64, 4, 1, 4, 1, EPI_BIAS_RES, true>(p, stream); break;
         default: launch_cfg<128, 128, 64, 4, 2, 4, 1, EPI_BIAS_RES, true>(p, stream); break;   // 40
     }
 }
@@ -712,7 +718,8 @@ SplitKPlan gemm_splitk_plan(int M, int N, int K, bool layernorm_follows) {
     SplitKPlan best;
     if (few_rows_product(M, N, K, few_rows_tiled_splits(N, K))) return best;   // skinny.hip
     struct Cand { int cfg, bm, bn, max_splits; double per_kt; };
-    const Cand cands[] = {{16, 64, 64, 8, 0.27}, {17, 128, 64, 4, 0.40}, {40, 128, 128, 4, 0.50}, {34, 192, 128, 4, 0.66}};
+    const Cand cands[] = {{16, 64, 64, 8, 0.27}, {17, 128, 64, 4, 0.40}, {40, 128, 128, 4, 0.50}, {35, 160, 128, 2, 0.60},
+                          {34, 192, 128, 4, 0.66}};
     const int KT = K / 64;
     const auto rounds = [](long wgs) {
         const long full = wgs / 256, rem = wgs - full * 256;
@@ -721,7 +728,7 @@ SplitKPlan gemm_splitk_plan(int M, int N, int K, bool layernorm_follows) {
     const auto tiles = [&](const Cand& c) { return (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); };
     double least = 1e30;
     const int whole = gemm_choose_cfg(false, M, N, K);
-    if (whole != 16 && whole != 17 && whole != 18 && whole != 40 && whole != 34) return best;   // rows enough for wide tiles
+    if (whole != 16 && whole != 17 && whole != 18 && whole != 40 && whole != 34 && whole != 35) return best;   // rows enough for wide tiles
     for (const Cand& c : cands)
         if (c.cfg == whole || (whole == 18 && c.cfg == 16)) least = 4.7 + rounds(tiles(c)) * KT * (whole == 17 ? 0.33 : c.per_kt);
     for (const Cand& c : cands)

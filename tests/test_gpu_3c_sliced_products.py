@@ -1,4 +1,4 @@
-"""GPU parity of out-proj and FC2 where their K is cut into slices, and of the launch that adds the slices up: rows one
+"""GPU parity of the tile shapes of the products, of out-proj and FC2 where their K is cut into slices, and of the launch that adds the slices up: rows one
 short of, at and past the tiles that the plan picks, two to eight slices, one to nine 512-column groups (whole and
 part-filled), with the LayerNorm behind the sum (out-proj in a block), without (its own entry point, a block's FC2) and with the
 kept rows scattered into a map (a step).  Same bars as test_gpu_4_block.py, whose checks these are."""
@@ -11,6 +11,27 @@ from gpu_util import DEV, empty_ws
 from test_gpu_4_block import check_block
 
 pytestmark = pytest.mark.gpu
+
+@pytest.mark.parametrize("M,N,K,epi", [
+    (731, 6144, 256, fb.EPI_BIAS_GELU), (577, 8200, 256, fb.EPI_BIAS_GELU),      # 192x128
+    (2299, 2040, 8192, fb.EPI_BIAS_RES), (2241, 2048, 8192, fb.EPI_BIAS_RES),    # 160x128
+    (1500, 4104, 64, fb.EPI_BIAS_GELU), (1345, 8192, 128, fb.EPI_BIAS_RES), (1537, 8192, 2048, fb.EPI_BIAS_GELU),   # 192x256
+    (65, 2040, 64, fb.EPI_BIAS_RES), (64, 1000, 512, fb.EPI_BIAS_GELU), (33, 8192, 2048, fb.EPI_BIAS_GELU),         # 64x32
+    (129, 6136, 448, fb.EPI_BIAS_GELU), (257, 5000, 1024, fb.EPI_BIAS_RES)])                                        # 128x64
+def test_tiles(M, N, K, epi):
+    """Rows and columns that end inside a tile, K shorter than the ring and longer, against fp32."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(M + K)
+    A, W, bias, res = (torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((M, K), (N, K), (N,), (M, N)))
+    W = (W * 0.2).contiguous()
+    out = torch.full((M * N + 4096,), float("nan"), dtype=torch.bfloat16, device=DEV)
+    fb.fastvar_gemm_bf16(A, W, bias, res, M, N, K, epi, out)
+    lin = torch.addmm(bias.float(), A.float(), W.float().T)
+    ref = lin + res.float() if epi == fb.EPI_BIAS_RES else torch.nn.functional.gelu(lin)
+    assert out[M * N:].isnan().all()
+    err = (out[:M * N].view(M, N).float() - ref).abs().max() / ref.abs().max()
+    assert err <= 2.0 ** -7, float(err)
+
 
 DIMS = [synth.BlockDims(D=448, H=7, dh=64, F=2048), synth.D16, synth.BlockDims(D=1088, H=17, dh=64, F=8192),
         synth.BlockDims(D=4224, H=33, dh=128, F=4352)]
