@@ -304,8 +304,8 @@ __global__ __launch_bounds__(QG * KSPLIT * 64, (QB == 1 ? 2 : 1)) void attention
                     k_base_ + (((i - NV_) % 2) * 32 + li) * KCH + ((2 * ((i - NV_) / 2) + hf) ^ sw_k)); \
             /* the loads go between the first SPAN_ fragment reads, evenly: early enough */       \
             /* to land before the end-of-iteration barrier */                                       \
-            if (NJ_ > 0 && i < SPAN_ && ((i + 1) * NJ_) / SPAN_ > (i * NJ_) / SPAN_)                \
-                FV_ISSUE_ONE((kt_) + 1, (kt_), JLO_ + (i * NJ_) / SPAN_)                            \
+            _Pragma("unroll") for (int j = (i * NJ_) / SPAN_; i < SPAN_ && j < ((i + 1) * NJ_) / SPAN_; ++j) \
+                FV_ISSUE_ONE((kt_) + 1, (kt_), JLO_ + j)                                            \
         }                                                                                           \
         if (HAS_PV_) {                                                                              \
             _Pragma("unroll") for (int t = 0; t < 4; ++t)                                           \
@@ -1390,19 +1390,29 @@ void launch_attention(const AttnArgs& a, hipStream_t stream) {
     }
     // Head dim 128 and more than two key tiles: the software-pipelined kernel (64 queries per wave),
     // with 128-query workgroups (two query groups x two key slices) or 256-query workgroups (four query
-    // groups), whichever needs less time for its rounds of workgroups; with fewer than 128 workgroups
-    // of 128 queries, 64-query workgroups of the plain kernel (one wave per 32 queries, keys split in two).
-    // Otherwise one wave per 32 queries, two waves per SIMD: with enough queries two 4-wave workgroups
-    // share a CU; with fewer an 8-wave workgroup splits the keys of each tile between two waves per
-    // query group.
+    // groups), whichever needs less time for its rounds of workgroups.  The plain kernel (a wave per 32 queries) otherwise, on
+    // workgroups as small as still fit a round: there the launch waits for its keys, which more CUs then pull on, a block's time in us:
+    //   one tile of 64 keys: nothing to split, 128 queries (37.9 for one token of the large model, 40.0 with 128-key tiles);
+    //   head dim 128, up to 176 workgroups of 32 queries, keys split in two: 256 queries over 521 keys 79.7 (64 queries: 81.1),
+    //     300 over 1221 117.1 (118.9); 208 workgroups of them lose (400 over 921 104.5, 102.4);
+    //   up to 256 workgroups of 64 queries, keys split in two: small model, 576 over 1497 62.9, 1024 over 2624 88.3 (128 queries on
+    //     eight waves: 67.3, 92.3), 4 x 169 of the large model over 424 123.7 (pipelined: 130); 270 of them lose (576 over 1497 of
+    //     the 512 px model 129.8, 126.4);
+    //   more: with enough queries two 4-wave workgroups of 128 share a CU; with fewer an 8-wave workgroup splits the
+    //     keys of each tile between two waves per query group.
     const long waves = (long)((a.k_tokens + 31) / 32) * a.H * a.B;
     const long wg256 = (long)((a.k_tokens + 255) / 256) * a.H * a.B;
     const long wg128 = (long)((a.k_tokens + 127) / 128) * a.H * a.B;
+    const long wg64 = (long)((a.k_tokens + 63) / 64) * a.H * a.B;
     int cfg = waves >= 1800 ? 2 : 4;
-    if (a.dh == 128 && a.L > 256) {
-        // rounds of workgroups on 256 CUs; a 256-query workgroup does twice the work about 7 % faster
+    if (a.L <= 64) cfg = 2;
+    else if (a.dh == 128 && waves <= 176) cfg = 7;
+    else if (wg64 <= 256 && (a.dh == 64 || wg128 < 128 || a.L <= 512)) cfg = 3;
+    else if (a.dh == 128 && a.L > 256) {
+        // rounds of workgroups on 256 CUs; a 256-query workgroup does twice the work about 7 % faster; too few queries for
+        // half the chip: 64-query workgroups
         const long rounds128 = (wg128 + 255) / 256, rounds256 = (wg256 + 255) / 256;
-        if (wg128 < 128) cfg = 3;   // too few queries for half the chip: 64-query workgroups, keys split in two
+        if (wg128 < 128) cfg = 3;
         else cfg = 1.86 * (double)rounds256 < (double)rounds128 ? 6 : 5;
     }
     if (a.dh == 64 && a.L >= 1024 && wg256 >= 128 && (a.k_tokens + 255) / 256 * 2 == (a.k_tokens + 127) / 128) {
@@ -1423,6 +1433,7 @@ void launch_attention(const AttnArgs& a, hipStream_t stream) {
             case 3: launch_cfg<128, 1, 2, 2>(p, a, stream); break;
             case 5: launch_pipe<128, 2, 2>(p, a.B, stream); break;
             case 6: launch_pipe<128, 4, 1>(p, a.B, stream); break;
+            case 7: launch_cfg<128, 1, 1, 2>(p, a, stream); break;
             default: launch_cfg<128, 1, 4, 2>(p, a, stream); break;
         }
     } else {
