@@ -230,10 +230,13 @@ void finish(const fv::SliceSum& s, hipStream_t st) {
 // `scatter`: h1_out is a [B, N, D] map and row m goes to the kept token's own row of it.
 // `clear`: this is the call's first use of the scratch, so its counters have to be cleared.
 // `before`: what is left of the product that x comes from (no index list).  Returns what is left of h1.
+// `ffn_follows`: the call goes on to the MLP half, whose weights may be fetched ahead; a call that does not touches
+// none of them.
 fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                   const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* h1_out, void* ws,
                   hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
-                  const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false) {
+                  const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false,
+                  bool ffn_follows = true) {
     const BlockPlan bp = block_plan(d, B, k);
     const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
@@ -283,8 +286,10 @@ fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k
     // it, but its single step on 128 rows 55.8 -> 56.4 and eight blocks of it on 16 rows 241 -> 246)
     if (2L * d->D * d->F >= 16L << 20 || (in_stack && M > fv::kFewRowsMax)) {
         at.ahead.add(w->w_proj, 2L * d->D * d->D);
-        at.ahead.add(w->w_fc1, 2L * d->D * d->F);
-        at.ahead.add(w->w_fc2, 2L * d->D * d->F);
+        if (ffn_follows) {
+            at.ahead.add(w->w_fc1, 2L * d->D * d->F);
+            at.ahead.add(w->w_fc2, 2L * d->D * d->F);
+        }
     }
     fv::launch_attention(at, st);
     mark(st, FASTVAR_STAGE_ATTENTION);
@@ -743,7 +748,8 @@ int fastvar_attn_forward_pruned(const void* x, int N, const int32_t* idx, int B,
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    finish(enqueue_attn(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, h_kept_out, ws, st, true), st);
+    finish(enqueue_attn(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, h_kept_out, ws, st, true, false, nullptr,
+                        nullptr, {}, false, false), st);
     return launch_status();
 }
 
@@ -815,7 +821,7 @@ int fastvar_step_sublayer(const void* x, const int32_t* sched_h, const int32_t* 
     const Fill fill_a{rank, cache_map_attn, hc, wc, h, w, x_mid};
     if (k_attn > 0)
         finish(enqueue_attn(x, N, pruned_a ? idx_attn_out : nullptr, B, k_attn, dims, weights, k_cache, v_cache, L0,
-                            L_cap, x_mid, ws_blk, st, true, true, &fill_a), st);
+                            L_cap, x_mid, ws_blk, st, true, true, &fill_a, nullptr, {}, false, k_ffn > 0), st);
     else
         fv::launch_restore(nullptr, rank, B, k_attn, cache_map_attn, hc, wc, h, w, D, x_mid, st);
     fv::launch_select(x_mid, B, N, D, k_ffn, idx_ffn_out, pruned_f ? rank : nullptr, nullptr, ws_sel, sp, st);

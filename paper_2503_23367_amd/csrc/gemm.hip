@@ -68,7 +68,7 @@ __device__ __forceinline__ int swz(int row) {
 // barrier, load and LDS waits where the tile gives one wave per SIMD too little
 // independent work.
 // SLICED: the K range is also split between workgroups (blockIdx.y), each of which leaves the fp32 sums of its
-// slice in scratch memory, row-major; the launch that follows adds the slices up (sum_slices in layernorm.hip),
+// slice in scratch memory, row-major; the launch that follows adds the slices up (slice_sum_kernel in layernorm.hip),
 // mostly the LayerNorm that reads the rows anyway.  The slices meeting inside this launch instead (partial tiles through
 // memory, the last workgroup of a tile adding them up) cost every such product 3 to 8 us: FC2 of the large model at
 // 64 / 256 / 576 / 1152 rows 13.3 / 25.2 / 43.2 / 60.2 us that way, 9.9 / 20.2 / 29.7 / 51.6 this way.

@@ -72,3 +72,33 @@ def test_step_scatters_the_rows_of_the_block(dims, B, h, w, k):
     torch.cuda.synchronize()
     assert not y.isnan().any()
     assert torch.equal(torch.gather(y, 1, idx.long()[..., None].expand(B, k, D)).view(torch.int16), y_kept.view(torch.int16))
+
+
+@pytest.mark.parametrize("k", [1, 24, 130])
+def test_attention_half_reads_no_mlp_weights(k):
+    """The attention half of a model whose MLP weights are not in memory yet (placeholders of 256
+    bytes): the same bits as with the whole block's weights."""
+    dims = synth.INF2B
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(k)
+
+    def rand(*shape, scale=1.0):
+        return (torch.randn(shape, generator=gen, device=DEV) * scale).to(torch.bfloat16)
+
+    D, H, dh, F, N, L0 = dims.D, dims.H, dims.dh, dims.F, 196, 19
+    wt = dict(ln1_g=1 + rand(D, scale=0.1), ln1_b=rand(D, scale=0.1), w_qkv=rand(3 * D, D, scale=0.05), b_qkv=rand(3 * D),
+              w_proj=rand(D, D, scale=0.05), b_proj=rand(D), ln2_g=1 + rand(D, scale=0.1), ln2_b=rand(D, scale=0.1),
+              w_fc1=rand(F, D, scale=0.05), b_fc1=rand(F), w_fc2=rand(D, F, scale=0.05), b_fc2=rand(D))
+    d = fb.make_dims(D, H, dh, F)
+    L_cap = (L0 + k + 7) // 8 * 8
+    x, kc0, vc0 = rand(1, N, D), rand(1, H, L_cap, dh), rand(1, H, dh, L_cap)
+    idx = torch.arange(k, dtype=torch.int32, device=DEV).view(1, k)
+    ws = empty_ws(fb.fastvar_block_workspace_bytes(d, 1, k))
+    out = []
+    for weights in (wt, dict(wt, w_fc1=torch.empty(128, dtype=torch.bfloat16, device=DEV),
+                             w_fc2=torch.empty(128, dtype=torch.bfloat16, device=DEV))):
+        kc, vc, y = kc0.clone(), vc0.clone(), torch.full((1, k, D), float("nan"), dtype=torch.bfloat16, device=DEV)
+        fb.fastvar_attn_forward_pruned(x, N, idx, 1, k, d, fb.make_weights(weights), kc, vc, L0, L_cap, y, ws)
+        out.append((y, kc, vc))
+    for a, b in zip(*out):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
