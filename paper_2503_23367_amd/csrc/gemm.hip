@@ -606,78 +606,18 @@ int gemm_cfg_override(int epi) {
 #endif
 }
 
-// Tile choice.  What the measurements on the block's shapes say (inside the running step):
-//  * what a tile's loads need is time to land.  A ring refilled during the tile after the hand-over gives them
-//    STAGES-2 tiles and a fraction: nothing to speak of with two stages, which is all that 256x256 and 256x192
-//    tiles fit into 160 KB.  Those rings are therefore refilled at the hand-over itself (one whole tile ahead:
-//    256x192 at 2048 rows 60 -> 52 us, 256x256 68 -> 61 us); rings of three and four stages, which have the
-//    time anyway, lose 3-5 % to the burst of loads at the hand-over and keep the spread refill.
-//  * 256x128 tiles with eight waves of 64x64 and three stages are as fast per output element as the wide tiles
-//    and twice as fine grained; the same tile with two stages and the spread refill, or with 32-wide K tiles in
-//    four or six stages (twice the hand-overs), is 20-25 % slower; 128x128 with 128-wide K tiles in two stages
-//    20 % slower than with 64-wide ones in four.
-//  * 256x256 (QKV: 256x192, N = 3D divides evenly) wins where its tiles fill whole rounds of the 256 CUs, as
-//    at 2048 kept tokens; 128x128 tiles with eight waves of 64x32 and four stages where the wide tiles would
-//    leave CUs idle (N = D: out-proj, FC2).  Between them the tile count decides: 192x128 (eight waves of 96x32, three stages;
-//    four of 96x64 take 5-7 % longer: 960 x 6144 x 2048 29.5 -> 27.6 us), 160x128 (four waves of 160x32, four stages: 2300 x 2048 x
-//    8192 is 240 such tiles, the 2300-row step 438 -> 428) and 192x256 (two stages: 1152 x 8192 x 2048 52.9 -> 46.1).
-//  * a part-filled last round costs less than a full one (fewer workgroups share the memory system and the
-//    power budget).
-//  * shapes that give at most 128 tiles of 128x128 (few rows) are bound by what a CU pulls in (about 37 bytes a
-//    nanosecond of what misses the L2, 110 of what hits it), so more workgroups on smaller tiles beat the better
-//    operand reuse of the larger ones, and, with a workgroup a CU, rings take the LDS there is: 128x64 tiles with
-//    eight waves and six stages (128x64 with four waves and three: 256 x 6144 x 2048 18.6 -> 16.6 us, 576 x 2048 x 2048
-//    17.3 -> 14.0, 960 rows 18.3 -> 15.4), at most 64: 64x64 tiles with eight stages (64 x 6144 x 2048 13.7 with four,
-//    13.2 with eight), or 64x32 ones where these are at most a round (64 x 6144 x 2048 13.2 -> 11.2, 25 rows 11.4 -> 9.3; but
-//    128 rows, a round and a half, 13.1 -> 19.2).
-// The choice is the candidate with the least modelled time, rounds * (fix + K tiles * per-tile), a part-filled
-// round counting 0.85 + 0.29 * fill; the constants are a least-squares fit to the in-step times of the four
-// GEMMs of fifteen workloads under each configuration (residual 7 % rms; the picks cost 0.3 % more than the
-// best measured configuration of every shape would).
-int gemm_choose_cfg(bool qkv, int M, int N, int K) {
-    const long tiles128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-    if (tiles128 <= 64) return (long)((M + 63) / 64) * ((N + 31) / 32) <= 256 ? 18 : 16;
-    if (tiles128 <= 128) return 17;
-    struct Cand { int cfg, bm, bn, slots; double fix, per_kt; };
-    const Cand cands[] = {
-        {qkv ? 12 : 11, 256, qkv ? 192 : 256, 256, 4.0, qkv ? 1.33 : 1.60},
-        {32, 256, 128, 256, 10.3, 0.714},
-        {34, 192, 128, 256, 8.6, 0.545},
-        {35, 160, 128, 256, 11.5, 0.46},
-        {13, 192, 256, 256, 4.0, 1.45},
-        {40, 128, 128, 256, 6.2, 0.456},
-        {6, 128, 128, 512, 8.0, 1.0},     // two workgroups per CU share its time
-    };
-    const double KT = (double)K / 64.0;
-    int best_cfg = 6;
-    double best = 1e30;
-    for (const Cand& c : cands) {
-        double per_kt = c.per_kt;
-        if (c.bn >= 192) {
-            // the two-stage wide tiles lose ground on long K ranges (1.8 us per K tile at K = 8192) and were
-            // never ahead on narrow outputs (N = D: eight tile columns, 4 x 1638 rows 80.7 us against 64.7 modelled
-            // for 256x128)
-            if ((N + c.bn - 1) / c.bn < 16) continue;
-            if (KT > 32.0) per_kt += 0.003 * (KT - 32.0);
-        }
-        const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-        const long full = tiles / c.slots, rem = tiles - full * c.slots;
-        const double rounds = (double)full + (rem ? 0.85 + 0.29 * (double)rem / c.slots : 0.0);
-        const double t = rounds * (c.fix + KT * per_kt);
-        if (t < best) { best = t; best_cfg = c.cfg; }
-    }
-    return best_cfg;
-}
-
 template <int EPI>
 void launch_epi(GemmParams& p, hipStream_t stream) {
-    int cfg = gemm_choose_cfg(is_qkv(EPI), p.M, p.N, p.K);
+    int cfg = gemm_choose_tile(is_qkv(EPI), p.M, p.N, p.K).cfg;
     constexpr int knob = EPI == EPI_QKV_ROPE ? (int)EPI_QKV : EPI;
     if (gemm_cfg_override(knob) >= 0) cfg = gemm_cfg_override(knob);
     switch (cfg) {
-        case 11: launch_cfg<256, 256, 64, 2, 2, 4, 1, EPI>(p, stream); break;
-        case 12: launch_cfg<256, 192, 64, 2, 4, 2, 1, EPI>(p, stream); break;
-        case 16: launch_cfg<64, 64, 64, 8, 2, 2, 1, EPI>(p, stream); break;
+        case 11:
+        case 12:
+            if constexpr (is_qkv(EPI)) launch_cfg<256, 192, 64, 2, 4, 2, 1, EPI>(p, stream);
+            else launch_cfg<256, 256, 64, 2, 2, 4, 1, EPI>(p, stream);
+            break;
+        case 16: launch_cfg<64, 64, 64, 4, 2, 2, 1, EPI>(p, stream); break;
         case 17: launch_cfg<128, 64, 64, 6, 4, 2, 1, EPI>(p, stream); break;
         case 18: launch_cfg<64, 32, 64, 8, 2, 1, 2, EPI>(p, stream); break;
         case 32: launch_cfg<256, 128, 64, 3, 4, 2, 1, EPI>(p, stream); break;
@@ -706,46 +646,6 @@ void launch_sliced(const SplitKPlan& sk, GemmParams& p, hipStream_t stream) {
 }
 
 }  // namespace
-
-// Whether the K of an out-proj or FC2 product is cut into slices, and on which tile.  Few output tiles leave CUs idle and
-// make each of the others walk all of K; slices fill the chip, at the price of their fp32 sums going through memory.
-// The candidate with the least modelled time (us): 4.7 to launch, fill and drain; the K tiles of a slice, at what one takes on a
-// full round of 256 workgroups; the slices' bytes at 5 TB/s out and 6.2 TB/s back in, and where no LayerNorm follows
-// that would read the rows anyway (FC2 has one behind it in a stack and none in a single step: half) the launch that adds
-// them up, 3.1.  Unsplit, the tiled product's own choice, at the same per-tile times.  Against 30 products of the large model
-// at 25 to 1152 rows the model is off by 9 % rms, and its picks are the fastest measured, or within 5 % of it.
-SplitKPlan gemm_splitk_plan(int M, int N, int K, bool layernorm_follows) {
-    SplitKPlan best;
-    if (few_rows_product(M, N, K, few_rows_tiled_splits(N, K))) return best;   // skinny.hip
-    struct Cand { int cfg, bm, bn, max_splits; double per_kt; };
-    const Cand cands[] = {{16, 64, 64, 8, 0.27}, {17, 128, 64, 4, 0.40}, {40, 128, 128, 4, 0.50}, {35, 160, 128, 2, 0.60},
-                          {34, 192, 128, 4, 0.66}};
-    const int KT = K / 64;
-    const auto rounds = [](long wgs) {
-        const long full = wgs / 256, rem = wgs - full * 256;
-        return (double)full + (rem ? 0.85 + 0.15 * (double)rem / 256.0 : 0.0);
-    };
-    const auto tiles = [&](const Cand& c) { return (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); };
-    double least = 1e30;
-    const int whole = gemm_choose_cfg(false, M, N, K);
-    if (whole != 16 && whole != 17 && whole != 18 && whole != 40 && whole != 34 && whole != 35) return best;   // rows enough for wide tiles
-    for (const Cand& c : cands)
-        if (c.cfg == whole || (whole == 18 && c.cfg == 16)) least = 4.7 + rounds(tiles(c)) * KT * (whole == 17 ? 0.33 : c.per_kt);
-    for (const Cand& c : cands)
-        for (int s = 2; s <= c.max_splits; s *= 2) {
-            if (KT % s != 0 || KT / s < 4 || tiles(c) * s > 256) continue;
-            const double bytes = 4.0 * s * M * N;
-            const double t = 4.7 + rounds(tiles(c) * s) * (KT / s) * c.per_kt + bytes / 5.0e6 + bytes / 6.2e6 +
-                             (layernorm_follows ? 0.0 : 1.5);
-            if (t < least) {
-                least = t;
-                best.splits = s;
-                best.cfg = c.cfg;
-                best.bytes = (size_t)s * M * N * 4;
-            }
-        }
-    return best;
-}
 
 void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {
     if (few_rows_product(a.M, a.N, a.K, a.slice_ws && few_rows_tiled_splits(a.N, a.K))) {

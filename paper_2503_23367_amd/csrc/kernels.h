@@ -121,15 +121,6 @@ void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream);
 // GEMMs of few rows (skinny.hip); launch_gemm routes there what few_rows_product (launch_math.h) gives it.
 void launch_gemm_skinny(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream);
 
-// Split-K plan of an out-proj or FC2 product (EPI_BIAS_RES) of few rows: the K range is cut into `splits` slices that
-// run as separate workgroups and leave fp32 sums [splits][M][N] in scratch; splits == 1: no scratch needed.
-// layernorm_follows: a LayerNorm of the rows always comes next (out-proj) and adds the slices up on the way.
-struct SplitKPlan {
-    int splits = 1;
-    int cfg = 0;        // tile of the slices (gemm.hip)
-    size_t bytes = 0;
-};
-SplitKPlan gemm_splitk_plan(int M, int N, int K, bool layernorm_follows);
 // What is left of a split product: out[row] = sum of the slices, in slice order, + residual (the bias is in the first slice).
 struct SliceSum {
     const float* slices = nullptr;   // [splits][M][N]; null: nothing is left to do

@@ -2,6 +2,8 @@
 // the same lines, so the arithmetic can be checked at sizes that no test would launch.
 #pragma once
 
+#include <stddef.h>
+
 #if defined(__HIPCC__)
 #define FV_HOST_DEVICE __host__ __device__ __forceinline__
 #else
@@ -79,6 +81,130 @@ FV_HOST_DEVICE bool few_rows_tiled_splits(int N, int K) { return K >= 2048 && K 
 // A LayerNorm over K columns fits in front: a wave holds its share of the rows in registers.
 FV_HOST_DEVICE bool few_rows_layernorm(int M, int N, int K) {
     return K <= kFewRowsRound && few_rows_product(M, N, K, false);
+}
+
+// Tile choice.  What the measurements on the block's shapes say (inside the running step):
+//  * what a tile's loads need is time to land.  A ring refilled during the tile after the hand-over gives them
+//    STAGES-2 tiles and a fraction: nothing to speak of with two stages, which is all that 256x256 and 256x192
+//    tiles fit into 160 KB.  Those rings are therefore refilled at the hand-over itself (one whole tile ahead:
+//    256x192 at 2048 rows 60 -> 52 us, 256x256 68 -> 61 us); rings of three and four stages, which have the
+//    time anyway, lose 3-5 % to the burst of loads at the hand-over and keep the spread refill.
+//  * 256x128 tiles with eight waves of 64x64 and three stages are as fast per output element as the wide tiles
+//    and twice as fine grained; the same tile with two stages and the spread refill, or with 32-wide K tiles in
+//    four or six stages (twice the hand-overs), is 20-25 % slower; 128x128 with 128-wide K tiles in two stages
+//    20 % slower than with 64-wide ones in four.
+//  * 256x256 (QKV: 256x192, N = 3D divides evenly) wins where its tiles fill whole rounds of the 256 CUs, as
+//    at 2048 kept tokens; 128x128 tiles with eight waves of 64x32 and four stages where the wide tiles would
+//    leave CUs idle (N = D: out-proj, FC2).  Between them the tile count decides: 192x128 (eight waves of 96x32, three stages;
+//    four of 96x64 take 5-7 % longer: 960 x 6144 x 2048 29.5 -> 27.6 us), 160x128 (four waves of 160x32, four stages: 2300 x 2048 x
+//    8192 is 240 such tiles, the 2300-row step 438 -> 428) and 192x256 (two stages: 1152 x 8192 x 2048 52.9 -> 46.1).
+//  * a part-filled last round costs less than a full one (fewer workgroups share the memory system and the
+//    power budget).
+//  * shapes that give at most 128 tiles of 128x128 (few rows) are bound by what a CU pulls in (about 37 bytes a
+//    nanosecond of what misses the L2, 110 of what hits it), so more workgroups on smaller tiles beat the better
+//    operand reuse of the larger ones: 128x64 tiles with eight waves and six stages (four waves and three stages: 256 x 6144 x
+//    2048 18.6 -> 16.6 us, 576 x 2048 x 2048 17.3 -> 14.0, 960 rows 18.3 -> 15.4), at most 64: 64x64 tiles with four stages, or
+//    64x32 ones with eight where these are at most a round (64 x 6144 x 2048 13.2 -> 11.2, 25 rows 11.4 -> 9.3; 128 rows, a
+//    round and a half, 13.1 -> 19.2) and K is more than eight tiles: up to there the sums of their two k-groups, which meet in LDS, cost
+//    what the finer split saves (24 products of K 320 to 512, weights in the cache, 1 % longer; of K 576 to 1024 5 %
+//    shorter, of 1088 to 2048 16 %, of longer ones 19 to 33 %).  64x64 tiles with eight stages, one workgroup a CU instead of two, and
+//    all of a ring's loads queued in front of the first product, take 6 % longer with weights in the cache (545 x 1024 x 1024
+//    6.5 / 7.1 us, 350 x 2048 x 2048 9.1 / 9.9), 2 to 5 % less with weights from memory and K above 1024: not kept.
+// Beyond 128 tiles the choice is the candidate with the least modelled time (us): 2.05 to launch, and for every round of its
+// workgroups, a part-filled one counting 0.777 + 0.189 * fill, fix + K tiles * per_kt, where a K tile beyond the 32nd takes
+// `longer` more; tile counts that do not divide by eight are not dealt to the XCDs in contiguous runs, and cost 4 % more, with
+// three, five or seven tile rows 10 % (there consecutive tiles of every XCD share neither operand).  The constants are a fit to 960
+// products (seven models' four products and generic ones; 100 to 16000 rows, K 64 to 16384; weights from memory and from the
+// cache) under each candidate, by the time that the picks lose: 0.4 % on the best candidate of every shape.  A fit to fifteen
+// workloads' products alone, short of K and of tile counts, cost 3 % more: 4242 x 6912 x 2304 153.1 us on 192x128 tiles, 139.3 on
+// 256x128; 3309 x 4096 x 16384 453 on 160x128, 392 on 256x256; 320 x 6336 x 192 14.9 on 192x256, 7.4 on 128x128.
+struct TileChoice {
+    int cfg;
+    double us;   // modelled
+};
+FV_HOST_DEVICE double tile_rounds(int M, int N, int bm, int bn, int slots, int splits, double part, double fill, double uneven,
+                                  double scattered) {
+    const long tile_rows = (M + bm - 1) / bm, tiles = tile_rows * ((N + bn - 1) / bn);
+    const long full = tiles * splits / slots, rem = tiles * splits - full * slots;
+    const double rounds = (double)full + (rem ? part + fill * (double)rem / slots : 0.0);
+    return tiles % 8 == 0 ? rounds : rounds * (1.0 + (tile_rows == 3 || tile_rows == 5 || tile_rows == 7 ? scattered : uneven));
+}
+FV_HOST_DEVICE TileChoice gemm_choose_tile(bool qkv, int M, int N, int K) {
+    const long tiles128 = (long)((M + 127) / 128) * ((N + 127) / 128);
+    const int KT = K / 64;
+    struct Cand { int cfg, bm, bn, slots; double fix, per_kt, longer; };
+    const Cand cands[] = {
+        {18, 64, 32, 256, 2.05, 0.161, 0.0},        // the first three by the rules above
+        {16, 64, 64, 512, 3.1, 0.250, 0.0},
+        {17, 128, 64, 256, 3.9, 0.305, 0.0},
+        {qkv ? 12 : 11, 256, qkv ? 192 : 256, 256, qkv ? 4.73 : 7.18, qkv ? 1.231 : 1.469, qkv ? -0.033 : -0.030},
+        {32, 256, 128, 256, 4.81, 0.779, -0.042},
+        {34, 192, 128, 256, 3.2, 0.660, -0.024},
+        {35, 160, 128, 256, 3.9, 0.654, -0.087},
+        {13, 192, 256, 256, 5.92, 1.239, -0.060},
+        {40, 128, 128, 256, 2.58, 0.526, -0.066},
+        {6, 128, 128, 512, 3.43, 1.001, -0.073},    // two workgroups per CU share its time
+    };
+    int from = 3, to = (int)(sizeof(cands) / sizeof(cands[0]));
+    if (tiles128 <= 64) from = (long)((M + 63) / 64) * ((N + 31) / 32) <= 256 && KT > 8 ? 0 : 1;
+    else if (tiles128 <= 128) from = 2;
+    if (from < 3) to = from + 1;
+    TileChoice best{6, 1e30};
+    for (int i = from; i < to; ++i) {
+        const Cand& c = cands[i];
+        const double rounds = tile_rounds(M, N, c.bm, c.bn, c.slots, 1, 0.777, 0.189, 0.037, 0.10);
+        const double t = 2.05 + rounds * (c.fix + KT * c.per_kt + (KT > 32 ? (KT - 32) * c.longer : 0.0));
+        if (t < best.us) best = TileChoice{c.cfg, t};
+    }
+    return best;
+}
+
+// Split-K plan of an out-proj or FC2 product (EPI_BIAS_RES) of few rows: the K range is cut into `splits` slices that
+// run as separate workgroups and leave fp32 sums [splits][M][N] in scratch; splits == 1: no scratch needed.
+// layernorm_follows: a LayerNorm of the rows always comes next (out-proj) and adds the slices up on the way.
+struct SplitKPlan {
+    int splits = 1;
+    int cfg = 0;        // tile of the slices (gemm.hip)
+    size_t bytes = 0;
+};
+// Whether the K of an out-proj or FC2 product is cut into slices, and on which tile.  Few output tiles leave CUs idle and
+// make each of the others walk all of K; slices fill the chip, at the price of their fp32 sums going through memory.
+// The candidate with the least modelled time (us): 4.7 to launch, fill and drain; the K tiles of a slice, at what one takes on a
+// full round of 256 workgroups; the slices' bytes at 5 TB/s out and 6.2 TB/s back in, and where no LayerNorm follows
+// that would read the rows anyway (FC2 has one behind it in a stack and none in a single step: half) the launch that adds
+// them up, 3.1.  Unsplit, the tiled product's own choice, at the same per-tile times.  Against 30 products of the large model
+// at 25 to 1152 rows the model is off by 9 % rms, and its picks are the fastest measured, or within 5 % of it.
+FV_HOST_DEVICE SplitKPlan gemm_splitk_plan(int M, int N, int K, bool layernorm_follows) {
+    SplitKPlan best;
+    if (few_rows_product(M, N, K, few_rows_tiled_splits(N, K))) return best;   // skinny.hip
+    struct Cand { int cfg, bm, bn, max_splits; double per_kt; };
+    const Cand cands[] = {{16, 64, 64, 8, 0.27}, {17, 128, 64, 4, 0.40}, {40, 128, 128, 4, 0.50}, {35, 160, 128, 2, 0.60},
+                          {34, 192, 128, 4, 0.66}};
+    const int KT = K / 64;
+    const auto rounds = [](long wgs) {
+        const long full = wgs / 256, rem = wgs - full * 256;
+        return (double)full + (rem ? 0.85 + 0.15 * (double)rem / 256.0 : 0.0);
+    };
+    const auto tiles = [&](const Cand& c) { return (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); };
+    double least = 1e30;
+    const int whole = gemm_choose_tile(false, M, N, K).cfg;
+    if (whole != 16 && whole != 17 && whole != 18 && whole != 40 && whole != 34 && whole != 35) return best;   // rows enough for wide tiles
+    for (const Cand& c : cands)
+        if (c.cfg == whole || (whole == 18 && c.cfg == 16)) least = 4.7 + rounds(tiles(c)) * KT * (whole == 17 ? 0.33 : c.per_kt);
+    for (const Cand& c : cands)
+        for (int s = 2; s <= c.max_splits; s *= 2) {
+            if (KT % s != 0 || KT / s < 4 || tiles(c) * s > 256) continue;
+            const double bytes = 4.0 * s * M * N;
+            const double t = 4.7 + rounds(tiles(c) * s) * (KT / s) * c.per_kt + bytes / 5.0e6 + bytes / 6.2e6 +
+                             (layernorm_follows ? 0.0 : 1.5);
+            if (t < least) {
+                least = t;
+                best.splits = s;
+                best.cfg = c.cfg;
+                best.bytes = (size_t)s * M * N * 4;
+            }
+        }
+    return best;
 }
 
 // How much of a list of matrices (bytes[0], bytes[1], ..., in the order they are read) a launch of about `us` microseconds

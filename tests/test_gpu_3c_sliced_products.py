@@ -8,18 +8,14 @@ import torch
 from paper_2503_23367_amd import binding as fb
 from paper_2503_23367_amd import synth
 from gpu_util import DEV, empty_ws
+from tile_cases import TILES
 from test_gpu_4_block import check_block
 
 pytestmark = pytest.mark.gpu
 
-@pytest.mark.parametrize("M,N,K,epi", [
-    (731, 6144, 256, fb.EPI_BIAS_GELU), (577, 8200, 256, fb.EPI_BIAS_GELU),      # 192x128
-    (2299, 2040, 8192, fb.EPI_BIAS_RES), (2241, 2048, 8192, fb.EPI_BIAS_RES),    # 160x128
-    (1500, 4104, 64, fb.EPI_BIAS_GELU), (1345, 8192, 128, fb.EPI_BIAS_RES), (1537, 8192, 2048, fb.EPI_BIAS_GELU),   # 192x256
-    (65, 2040, 64, fb.EPI_BIAS_RES), (64, 1000, 512, fb.EPI_BIAS_GELU), (33, 8192, 2048, fb.EPI_BIAS_GELU),         # 64x32
-    (129, 6136, 448, fb.EPI_BIAS_GELU), (257, 5000, 1024, fb.EPI_BIAS_RES)])                                        # 128x64
+@pytest.mark.parametrize("M,N,K,epi", [c for cases in TILES.values() for c in cases])
 def test_tiles(M, N, K, epi):
-    """Rows and columns that end inside a tile, K shorter than the ring and longer, against fp32."""
+    """Every tile shape (tile_cases.py), against fp32."""
     gen = torch.Generator(device=DEV)
     gen.manual_seed(M + K)
     A, W, bias, res = (torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((M, K), (N, K), (N,), (M, N)))

@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from tile_cases import TILES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SHIM = r"""
@@ -34,6 +36,7 @@ void prefetch(const long* bytes, int n, int idle, double us, int cut, long* out)
     out[0] = p.bytes;
     out[1] = p.blocks;
 }
+int tile(int qkv, int M, int N, int K) { return fv::gemm_choose_tile(qkv, M, N, K).cfg; }
 int few_rows_ln(int M, int N, int K) { return fv::few_rows_layernorm(M, N, K); }
 }
 """
@@ -117,6 +120,32 @@ def test_few_rows_routing(math):
             for K in (64, 1024, 2048, 2112, 2304, 3072, 4096, 4352, 6144, 8192, 9216, 16384, 20480, 32768):
                 assert not math.few_rows(M, N, K, 1) or math.few_rows(M, N, K, 0), (M, N, K)
                 assert not math.few_rows_ln(M, N, K) or K <= 2048 and math.few_rows(M, N, K, 1), (M, N, K)
+
+
+def test_tile_cases_reach_their_tiles(math):
+    for cfg, cases in TILES.items():
+        for M, N, K, _ in cases:
+            assert math.tile(0, M, N, K) == cfg, (M, N, K)
+
+
+# (qkv, M, N, K): the tile that was measured 6 % or more slower than the best one there, us
+SLOWER = [((0, 320, 6336, 192), 13), ((0, 1462, 4224, 640), 13),                       # 14.9 / 7.4, 17.5 / 14.7
+          ((0, 3309, 4096, 16384), 35), ((0, 787, 4096, 16384), 35), ((0, 10418, 2560, 8192), 34),   # 453 / 392, 142 / 112, 455 / 401
+          ((1, 4242, 6912, 2304), 34), ((1, 1095, 7680, 2560), 34),                    # 153 / 139, 59.4 / 54.2
+          ((0, 391, 256, 128), 18), ((0, 17, 560, 320), 18)]                           # 4.97 / 4.71, 5.12 / 4.75
+
+
+def test_tiles_are_not_the_ones_measured_slower(math):
+    for shape, cfg in SLOWER:
+        assert math.tile(*shape) != cfg, shape
+    # where 64x32 tiles are at most a round and K is long enough for their two k-groups, and just past either
+    for M, N, K, cfg in [(64, 8192, 576, 18), (64, 8192, 512, 16), (128, 4096, 1024, 18), (128, 4104, 1024, 16), (129, 8192, 1024, 17)]:
+        assert math.tile(0, M, N, K) == cfg, (M, N, K)
+    # every size has a tile that the launch knows
+    for M in (17, 64, 65, 191, 193, 1000, 4097, 33000, 87381):
+        for N in (8, 64, 1344, 6144, 24576, 32768):
+            for K in (64, 448, 2048, 2112, 8192, 32768):
+                assert math.tile(0, M, N, K) in TILES and math.tile(1, M, N, K) in {12, *TILES} - {11}, (M, N, K)
 
 
 def test_column_chunks_fit_the_scratch(math):
