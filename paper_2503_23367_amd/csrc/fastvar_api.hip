@@ -44,13 +44,14 @@ BlockPlan block_plan(const fastvar_dims* d, int B, int k) {
         }
     }
     p.off_asplit = off; off += round256(p.asplit_bytes);
-    // split-K scratch of the GEMMs (only shapes with few output tiles have any): one area, the
-    // largest of the four, used by one GEMM at a time
+    // slices of out-proj and FC2 (few rows only): one area, used by one product at a time, as large as the largest, in a
+    // whole block or in a half of one
     p.sk_bytes = 0;
-    for (const bool out_proj : {true, false}) {
-        const size_t bytes = fv::gemm_splitk_plan((int)M, d->D, out_proj ? d->D : d->F, out_proj).bytes;
-        if (bytes > p.sk_bytes) p.sk_bytes = bytes;
-    }
+    for (const fv::SplitKPlan& sk : {fv::gemm_splitk_plan((int)M, d->D, d->D, fv::MEET_IN_LAYERNORM),
+                                     fv::gemm_splitk_plan((int)M, d->D, d->D, fv::MEET_IN_LAUNCH),
+                                     fv::gemm_splitk_plan((int)M, d->D, d->F, fv::MEET_IN_EITHER),
+                                     fv::gemm_splitk_plan((int)M, d->D, d->F, fv::MEET_IN_LAUNCH)})
+        if (sk.bytes > p.sk_bytes) p.sk_bytes = sk.bytes;
     p.off_sk = off; off += round256(p.sk_bytes);
     p.bytes = off;
     return p;
@@ -211,7 +212,7 @@ fv::SliceSum enqueue_residual_product(const fv::GemmArgs& g, hipStream_t st) {
     fv::launch_gemm(fv::EPI_BIAS_RES, g, st);
     fv::SliceSum s;
     if (!g.slice_ws) return s;
-    const fv::SplitKPlan sk = fv::gemm_splitk_plan(g.M, g.N, g.K, g.layernorm_follows);
+    const fv::SplitKPlan sk = fv::gemm_splitk_plan(g.M, g.N, g.K, g.meet);
     if (sk.splits == 1) return s;
     s.slices = static_cast<const float*>(g.slice_ws);
     s.splits = sk.splits; s.M = g.M; s.N = g.N;
@@ -232,11 +233,12 @@ void finish(const fv::SliceSum& s, hipStream_t st) {
 // `before`: what is left of the product that x comes from (no index list).  Returns what is left of h1.
 // `ffn_follows`: the call goes on to the MLP half, whose weights may be fetched ahead; a call that does not touches
 // none of them.
+// `meet`: where the slices of a split out-proj meet; in a whole block its MLP half's LayerNorm reads h1 next.
 fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                   const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* h1_out, void* ws,
                   hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
                   const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false,
-                  bool ffn_follows = true) {
+                  bool ffn_follows = true, fv::SlicesMeet meet = fv::MEET_IN_LAUNCH) {
     const BlockPlan bp = block_plan(d, B, k);
     const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
@@ -298,7 +300,7 @@ fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k
     pj.A = buf_a; pj.W = w->w_proj; pj.bias = w->b_proj; pj.M = M; pj.N = d->D; pj.K = d->D;
     pj.out = h1_out; pj.residual = x; pj.res_rows = idx ? rows : nullptr; pj.k_tokens = k;
     pj.out_rows = (scatter && idx) ? rows : nullptr;
-    pj.slice_ws = sk; pj.layernorm_follows = true;
+    pj.slice_ws = sk; pj.meet = meet;
     const fv::SliceSum left = enqueue_residual_product(pj, st);
     mark(st, FASTVAR_STAGE_PROJ);
     return left;
@@ -311,7 +313,8 @@ fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k
 // `before`: what is left of the product that src comes from (no index list).  Returns what is left of y.
 fv::SliceSum enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                          const fastvar_block_weights* w, void* y, void* ws, hipStream_t st, bool clear,
-                         bool scatter = false, const Fill* fill = nullptr, const fv::SliceSum& before = {}) {
+                         bool scatter = false, const Fill* fill = nullptr, const fv::SliceSum& before = {},
+                         fv::SlicesMeet meet = fv::MEET_IN_LAUNCH) {
     const BlockPlan bp = block_plan(d, B, k);
     const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
@@ -351,7 +354,7 @@ fv::SliceSum enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int 
     f2.A = buf_u; f2.W = w->w_fc2; f2.bias = w->b_fc2; f2.M = M; f2.N = d->D; f2.K = d->F;
     f2.out = y; f2.residual = src; f2.res_rows = idx ? rows : nullptr; f2.k_tokens = k;
     f2.out_rows = scatter ? rows : nullptr;
-    f2.slice_ws = sk;
+    f2.slice_ws = sk; f2.meet = meet;
     const fv::SliceSum left = enqueue_residual_product(f2, st);
     mark(st, FASTVAR_STAGE_FC2);
     return left;
@@ -364,8 +367,9 @@ fv::SliceSum enqueue_block(const void* x, int N, const int32_t* idx, int B, int 
                            const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false) {
     void* buf_h1 = static_cast<char*>(ws) + block_plan(d, B, k).off_h1;
     const fv::SliceSum h1 = enqueue_attn(x, N, idx, B, k, d, w, kc, vc, L0, L_cap, buf_h1, ws, st, clear, false,
-                                         idx ? fill : nullptr, rope, before, in_stack);
-    return enqueue_ffn(buf_h1, 0, nullptr, B, k, d, w, y, ws, st, false, scatter && idx, nullptr, h1);
+                                         idx ? fill : nullptr, rope, before, in_stack, true, fv::MEET_IN_LAYERNORM);
+    return enqueue_ffn(buf_h1, 0, nullptr, B, k, d, w, y, ws, st, false, scatter && idx, nullptr, h1,
+                       fv::MEET_IN_EITHER);
 }
 
 int check_ffn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* dims,

@@ -670,7 +670,7 @@ void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {
     p.splits = 1;
     p.slices = static_cast<float*>(a.slice_ws);
     if (a.slice_ws && epi == EPI_BIAS_RES) {
-        const SplitKPlan sk = gemm_splitk_plan(a.M, a.N, a.K, a.layernorm_follows);
+        const SplitKPlan sk = gemm_splitk_plan(a.M, a.N, a.K, a.meet);
         if (sk.splits > 1) {
             launch_sliced(sk, p, stream);
             return;

@@ -108,7 +108,7 @@ struct GemmArgs {
     // large they are).  Split, the launch leaves its slices there and touches neither `out` nor `residual`: the
     // launch of a SliceSum has to follow.
     void* slice_ws = nullptr;
-    bool layernorm_follows = false;   // as in the plan that the scratch was sized by
+    SlicesMeet meet = MEET_IN_LAUNCH;
     // Optional (EPI_QKV, EPI_BIAS_GELU; only where few_rows_layernorm says so): the rows of A are normalised on
     // the way in, and the call's arrival counters cleared, as the LayerNorm launch this replaces would.
     const void* ln_g = nullptr;

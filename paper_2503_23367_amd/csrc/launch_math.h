@@ -134,9 +134,9 @@ FV_HOST_DEVICE TileChoice gemm_choose_tile(bool qkv, int M, int N, int K) {
     const int KT = K / 64;
     struct Cand { int cfg, bm, bn, slots; double fix, per_kt, longer; };
     const Cand cands[] = {
-        {18, 64, 32, 256, 2.05, 0.161, 0.0},        // the first three by the rules above
-        {16, 64, 64, 512, 3.1, 0.250, 0.0},
-        {17, 128, 64, 256, 3.9, 0.305, 0.0},
+        {18, 64, 32, 256, 2.1, 0.170, 0.0},        // the first three by the rules above, their times for the K slices below
+        {16, 64, 64, 512, 2.7, 0.270, 0.0},
+        {17, 128, 64, 256, 3.4, 0.335, 0.0},
         {qkv ? 12 : 11, 256, qkv ? 192 : 256, 256, qkv ? 4.73 : 7.18, qkv ? 1.231 : 1.469, qkv ? -0.033 : -0.030},
         {32, 256, 128, 256, 4.81, 0.779, -0.042},
         {34, 192, 128, 256, 3.2, 0.660, -0.024},
@@ -159,44 +159,42 @@ FV_HOST_DEVICE TileChoice gemm_choose_tile(bool qkv, int M, int N, int K) {
     return best;
 }
 
-// Split-K plan of an out-proj or FC2 product (EPI_BIAS_RES) of few rows: the K range is cut into `splits` slices that
-// run as separate workgroups and leave fp32 sums [splits][M][N] in scratch; splits == 1: no scratch needed.
-// layernorm_follows: a LayerNorm of the rows always comes next (out-proj) and adds the slices up on the way.
+// Plan of an out-proj or FC2 product of few rows: the K range is cut into `splits` slices that run as separate workgroups
+// and leave fp32 sums [splits][M][N] in scratch; splits == 1: no scratch needed.
 struct SplitKPlan {
     int splits = 1;
     int cfg = 0;        // tile of the slices (gemm.hip)
     size_t bytes = 0;
 };
-// Whether the K of an out-proj or FC2 product is cut into slices, and on which tile.  Few output tiles leave CUs idle and
-// make each of the others walk all of K; slices fill the chip, at the price of their fp32 sums going through memory.
-// The candidate with the least modelled time (us): 4.7 to launch, fill and drain; the K tiles of a slice, at what one takes on a
-// full round of 256 workgroups; the slices' bytes at 5 TB/s out and 6.2 TB/s back in, and where no LayerNorm follows
-// that would read the rows anyway (FC2 has one behind it in a stack and none in a single step: half) the launch that adds
-// them up, 3.1.  Unsplit, the tiled product's own choice, at the same per-tile times.  Against 30 products of the large model
-// at 25 to 1152 rows the model is off by 9 % rms, and its picks are the fastest measured, or within 5 % of it.
-FV_HOST_DEVICE SplitKPlan gemm_splitk_plan(int M, int N, int K, bool layernorm_follows) {
+// What the slices meet in.  A LayerNorm of the rows that follows anyway (out-proj of a whole block) adds them up for next to
+// nothing; where none does (a half of a block on its own), a launch of its own does, 3.0 us.  FC2 of a block has a LayerNorm
+// behind it in a stack and none in a single step; both use one plan, so that a stack has the bits of its single blocks: half.
+enum SlicesMeet { MEET_IN_LAYERNORM = 0, MEET_IN_EITHER = 1, MEET_IN_LAUNCH = 2 };
+// Whether the K of such a product is cut, and on which tile.  Few output tiles leave CUs idle and make each of the others walk
+// all of K; slices fill the chip, at the price of their sums going through memory.  The candidate with the least modelled time (us): 2.2 to
+// launch; a round of 256 workgroups at fix + K tiles of a slice * per_kt, a part-filled one 0.804 + 0.156 * fill, 3 % more where
+// the tiles do not divide evenly among the XCDs, 21 % with three, five or seven tile rows; 0.505 for every MB of slices; and the
+// meeting.  Against it the whole product at its tile's modelled time.  The constants are a fit to 480 products of seven models, 17 to 2600
+// rows, inside the calls that run them, by the time that the picks lose on the best candidate: 0.1 to 0.3 us a product.  A fit
+// to 30 products of the large model lost 0.3 to 0.9, most of it in halves on their own, whose sum it took for free (attention
+// half of 357 rows 2304 wide 56.1 us, whole 51.0; of 443 rows of the small model 30.1 / 27.1), and at seven tile rows
+// (MLP half, 813 rows 1920 wide: two slices on 128x128 tiles 82.9, whole 78.8).  160x128 tiles in four slices are not taken: a full round of
+// them is slower than the model has it (576 x 2048 x 8192 5 us behind 192x128).  192x128 tiles run on four waves here, eight in whole products:
+// between them slices differ by -0.3 to 0.5 us.
+FV_HOST_DEVICE SplitKPlan gemm_splitk_plan(int M, int N, int K, SlicesMeet meet) {
     SplitKPlan best;
     if (few_rows_product(M, N, K, few_rows_tiled_splits(N, K))) return best;   // skinny.hip
-    struct Cand { int cfg, bm, bn, max_splits; double per_kt; };
-    const Cand cands[] = {{16, 64, 64, 8, 0.27}, {17, 128, 64, 4, 0.40}, {40, 128, 128, 4, 0.50}, {35, 160, 128, 2, 0.60},
-                          {34, 192, 128, 4, 0.66}};
+    struct Cand { int cfg, bm, bn, max_splits; double fix, per_kt; };
+    const Cand cands[] = {{16, 64, 64, 8, 0.94, 0.244}, {17, 128, 64, 4, 2.07, 0.293}, {40, 128, 128, 4, 1.5, 0.492},
+                          {35, 160, 128, 2, 2.43, 0.555}, {34, 192, 128, 4, 1.55, 0.638}};
     const int KT = K / 64;
-    const auto rounds = [](long wgs) {
-        const long full = wgs / 256, rem = wgs - full * 256;
-        return (double)full + (rem ? 0.85 + 0.15 * (double)rem / 256.0 : 0.0);
-    };
-    const auto tiles = [&](const Cand& c) { return (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn); };
-    double least = 1e30;
-    const int whole = gemm_choose_tile(false, M, N, K).cfg;
-    if (whole != 16 && whole != 17 && whole != 18 && whole != 40 && whole != 34 && whole != 35) return best;   // rows enough for wide tiles
-    for (const Cand& c : cands)
-        if (c.cfg == whole || (whole == 18 && c.cfg == 16)) least = 4.7 + rounds(tiles(c)) * KT * (whole == 17 ? 0.33 : c.per_kt);
+    double least = gemm_choose_tile(false, M, N, K).us;
     for (const Cand& c : cands)
         for (int s = 2; s <= c.max_splits; s *= 2) {
-            if (KT % s != 0 || KT / s < 4 || tiles(c) * s > 256) continue;
-            const double bytes = 4.0 * s * M * N;
-            const double t = 4.7 + rounds(tiles(c) * s) * (KT / s) * c.per_kt + bytes / 5.0e6 + bytes / 6.2e6 +
-                             (layernorm_follows ? 0.0 : 1.5);
+            const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+            if (KT % s != 0 || KT / s < 4 || tiles * s > 256) continue;
+            const double t = 2.2 + tile_rounds(M, N, c.bm, c.bn, 256, s, 0.804, 0.156, 0.033, 0.214) * (c.fix + KT / s * c.per_kt) +
+                             4.0e-6 * s * M * N * 0.505 + 1.5 * meet;
             if (t < least) {
                 least = t;
                 best.splits = s;

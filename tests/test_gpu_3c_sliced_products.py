@@ -8,7 +8,7 @@ import torch
 from paper_2503_23367_amd import binding as fb
 from paper_2503_23367_amd import synth
 from gpu_util import DEV, empty_ws
-from tile_cases import TILES
+from tile_cases import SLICED_ALONE, SLICED_DIMS, SLICED_ROWS, TILES
 from test_gpu_4_block import check_block
 
 pytestmark = pytest.mark.gpu
@@ -29,13 +29,15 @@ def test_tiles(M, N, K, epi):
     assert err <= 2.0 ** -7, float(err)
 
 
-DIMS = [synth.BlockDims(D=448, H=7, dh=64, F=2048), synth.D16, synth.BlockDims(D=1088, H=17, dh=64, F=8192),
-        synth.BlockDims(D=4224, H=33, dh=128, F=4352)]
+def _dims(D, H, dh, F):
+    return synth.BlockDims(D=D, H=H, dh=dh, F=F)
 
 
-@pytest.mark.parametrize("dims", DIMS, ids=lambda d: f"D{d.D}")
-@pytest.mark.parametrize("B,h,w,k", [(1, 1, 17, 17), (1, 9, 9, 63), (1, 9, 9, 65), (3, 6, 8, 43), (1, 16, 17, 257), (2, 16, 16, 193),
-                                     (1, 25, 25, 577)])
+DIMS = [_dims(*d) for d in SLICED_DIMS]
+
+
+@pytest.mark.parametrize("dims,B,h,w,k", [(d, *r) for d in DIMS for r in SLICED_ROWS] + [(_dims(*SLICED_ALONE[0]), *SLICED_ALONE[1])],
+                         ids=lambda v: f"D{v.D}" if isinstance(v, synth.BlockDims) else str(v))
 def test_block(dims, B, h, w, k):
     check_block(f"slices_{dims.D}", dims, B, h, w, k, 21, (21 + k + 7) // 8 * 8 + 8, seed=31)
 

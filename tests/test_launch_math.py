@@ -7,7 +7,7 @@ import subprocess
 
 import pytest
 
-from tile_cases import TILES
+from tile_cases import SLICED_ALONE, SLICED_DIMS, SLICED_ROWS, TILES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -37,6 +37,12 @@ void prefetch(const long* bytes, int n, int idle, double us, int cut, long* out)
     out[1] = p.blocks;
 }
 int tile(int qkv, int M, int N, int K) { return fv::gemm_choose_tile(qkv, M, N, K).cfg; }
+long slices(int M, int N, int K, int meet, int* out) {
+    const fv::SplitKPlan p = fv::gemm_splitk_plan(M, N, K, static_cast<fv::SlicesMeet>(meet));
+    out[0] = p.cfg;
+    out[1] = p.splits;
+    return (long)p.bytes;
+}
 int few_rows_ln(int M, int N, int K) { return fv::few_rows_layernorm(M, N, K); }
 }
 """
@@ -146,6 +152,54 @@ def test_tiles_are_not_the_ones_measured_slower(math):
         for N in (8, 64, 1344, 6144, 24576, 32768):
             for K in (64, 448, 2048, 2112, 8192, 32768):
                 assert math.tile(0, M, N, K) in TILES and math.tile(1, M, N, K) in {12, *TILES} - {11}, (M, N, K)
+
+
+LAYERNORM, EITHER, LAUNCH = 0, 1, 2   # SlicesMeet
+
+
+def _slices(math, M, N, K, meet):
+    out = (C.c_int * 2)()
+    math.slices.restype = C.c_long
+    size = math.slices(M, N, K, meet, out)
+    return size, out[0], out[1]
+
+
+def test_slices_of_a_half_pay_for_their_own_launch(math):
+    """No LayerNorm follows the out-proj of an attention half on its own.  Cut there all the same, as in a whole block, its calls were 3 to
+    11 % slower than whole (us, cut / whole): 357 rows 2304 wide 56.1 / 51.0, 479 and 443 of the small model 30.5 / 27.4, 30.1 / 27.1,
+    226 of 1920 34.3 / 32.3, 271 of 2048 42.4 / 39.7."""
+    for M, D in [(357, 2304), (479, 1024), (443, 1024), (226, 1920), (190, 1920), (271, 2048), (254, 2048), (201, 1024)]:
+        assert _slices(math, M, D, D, LAUNCH)[2] == 1, (M, D)
+    # ... and seven tile rows of 128 or 160 in two slices (MLP half of 813 rows 82.9 / 78.8, 974 of 9216: 131 / 118)
+    for M, N, K in [(813, 1920, 7680), (825, 1920, 7680), (974, 2304, 9216), (1328, 2304, 9216)]:
+        _, cfg, splits = _slices(math, M, N, K, LAUNCH)
+        rows = {40: 128, 35: 160, 34: 192}.get(cfg, 64)
+        assert splits == 1 or -(-M // rows) != 7, (M, N, K, cfg, splits)
+    # where slices win by several us they are kept: MLP half of 545 / 395 rows 67.7 / 62.4, 60.1 / 49.5
+    for M, N, K in [(64, 2048, 8192), (256, 2048, 8192), (576, 2048, 8192), (395, 1920, 7680), (545, 1920, 7680)]:
+        assert _slices(math, M, N, K, LAUNCH)[2] > 1 and _slices(math, M, N, K, EITHER)[2] > 1, (M, N, K)
+
+
+def test_slices_fit_their_launch(math):
+    """At most a round of workgroups, whole K tiles in every slice, tiles and counts that the launches know, and scratch for them all."""
+    for M in list(range(1, 140)) + [191, 256, 257, 400, 576, 731, 960, 1152, 2241, 4096, 70000]:
+        for N, K in [(64, 64), (448, 2048), (1024, 1024), (1024, 4096), (1920, 7680), (2048, 8192), (2176, 2176), (2304, 9216), (8192, 32768)]:
+            for meet in (LAYERNORM, EITHER, LAUNCH):
+                size, cfg, splits = _slices(math, M, N, K, meet)
+                if splits == 1:
+                    assert size == 0
+                    continue
+                bm, bn = {16: (64, 64), 17: (128, 64), 40: (128, 128), 35: (160, 128), 34: (192, 128)}[cfg]
+                assert splits in (2, 4, 8) and K // 64 % splits == 0 and size == 4 * splits * M * N
+                assert -(-M // bm) * -(-N // bn) * splits <= 256
+                assert not math.few_rows(M, N, K, 1) or not (K >= 2048 and K // 64 % 2 == 0 and N <= 8192)
+
+
+def test_sliced_cases_reach_every_tile_of_slices(math):
+    reached = set()
+    for (D, _, _, F), (B, _, _, k) in [(d, r) for d in SLICED_DIMS for r in SLICED_ROWS] + [SLICED_ALONE]:
+        reached |= {_slices(math, B * k, D, D, LAYERNORM)[1:], _slices(math, B * k, D, F, EITHER)[1:]}
+    assert {cfg for cfg, splits in reached if splits > 1} == {16, 17, 34, 35, 40} and {splits for _, splits in reached} == {1, 2, 4, 8}
 
 
 def test_column_chunks_fit_the_scratch(math):

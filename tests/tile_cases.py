@@ -16,3 +16,8 @@ TILES = {
     32: [(577, 8200, 2048, BIAS_GELU), (772, 6648, 256, BIAS_RES), (735, 8768, 1024, BIAS_RES)],   # 256x128
     11: [(1537, 8192, 2048, BIAS_GELU), (1345, 8472, 64, BIAS_RES), (1348, 8224, 1024, BIAS_GELU)],   # 256x256
 }
+
+# blocks whose out-proj and FC2 are cut into slices, on every tile that takes them: (D, H, dh, F) and (B, h, w, k)
+SLICED_DIMS = [(448, 7, 64, 2048), (1024, 16, 64, 4096), (1088, 17, 64, 8192), (4224, 33, 128, 4352)]
+SLICED_ROWS = [(1, 1, 17, 17), (1, 9, 9, 63), (1, 9, 9, 65), (3, 6, 8, 43), (1, 16, 17, 257), (2, 16, 16, 193), (1, 25, 25, 577)]
+SLICED_ALONE = ((1472, 23, 64, 4096), (1, 18, 18, 321))   # 192x128
