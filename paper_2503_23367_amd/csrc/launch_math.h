@@ -231,6 +231,24 @@ FV_HOST_DEVICE PrefetchPlan prefetch_plan(const long* bytes, int n, int idle, do
     return p;
 }
 
+// Rows that a wave of the restoration takes, of maps of `rows` tokens in all, w wide, D columns.  Rank, taps and store of a row
+// wait for one another, so a wave a row while the chip has room for them all (us, a pair unrolled / one: 16x16 x 1024 3.8 / 2.7,
+// 53x37 x 2048 6.4 / 5.0, 64x64 x 2048 8.5 / 7.4, 640 rows x 1920 5.8 / 5.2, 440 x 4096 8.9 / 5.7).  Maps of more rows than that
+// have a queue of waves either way, and a pair has two rows' loads in flight (81x82 x 448 7.2 / 8.0, 100x104 x 1024 10.7 / 12.5,
+// 84x88 x 2048 15.1 / 15.5), except where one row a wave puts the lines of the map, whose taps are the same, on one XCD, as widths in
+// multiples of sixteen, and within one of them, do, and rows are wide enough for that to count (80x80 x 2048 15.3 / 11.5, 88x96 x 1280 11.7 / 10.1; 72x80 x
+// 1024 5.9 / 6.5), and for rows of 4096 columns, which fill a wave by themselves (6510 rows 28.4 / 20.6).  Beyond 2^25 elements two rows, one after the
+// other (90000 x 1920 155 / 134, 128x128 x 2048 one row 22.2, two 21.7).
+struct RestorePlan {
+    int rows;
+    bool pair;   // unrolled
+};
+FV_HOST_DEVICE RestorePlan restore_plan(long rows, int w, int D) {
+    if (rows * D >= 1L << 25) return RestorePlan{2, false};
+    if (rows < 4300 || D >= 4096 || ((w + 1) % 16 <= 2 && D >= 1280)) return RestorePlan{1, false};
+    return RestorePlan{2, true};
+}
+
 // Row chunks of the selection's column sums, of a map of N tokens and D columns: in powers of two, as few as give the
 // launch a workgroup per CU (64 columns each; 240 of the 256 count as all), none shorter than the 256 rows that a workgroup
 // has in flight.  A function of the map alone, so that a sample's scores have the same bits in every batch.

@@ -27,7 +27,8 @@ __global__ __launch_bounds__(256) void rank_from_idx_kernel(const int32_t* __res
     rank[(size_t)b * N + n] = (lo < k && row[lo] == n) ? lo : -1;
 }
 
-// grid (ceil(N / (4*rows_per_wave)), B), block 256.
+// grid (ceil(N / (4*rows_per_wave)), B), block 256.  PAIR: two rows a wave, unrolled, so that the loads of both are in flight.
+template <bool PAIR>
 __global__ __launch_bounds__(256) void restore_kernel(const bf16_t* __restrict__ y_kept,
                                                       const int32_t* __restrict__ rank, int k,
                                                       const bf16_t* __restrict__ cache_map, int hc, int wc,
@@ -38,8 +39,10 @@ __global__ __launch_bounds__(256) void restore_kernel(const bf16_t* __restrict__
     const int b = blockIdx.y;
     const int N = h * w;
     const int groups = (D + 511) >> 9;
-    for (int rr = 0; rr < rows_per_wave; ++rr) {
-        const int n = (blockIdx.x * 4 + wave) * rows_per_wave + rr;
+    const int rows = PAIR ? 2 : rows_per_wave;
+#pragma unroll(PAIR ? 2 : 1)
+    for (int rr = 0; rr < rows; ++rr) {
+        const int n = (blockIdx.x * 4 + wave) * rows + rr;
         if (n >= N) break;
         const int r = (k > 0) ? rank[(size_t)b * N + n] : -1;
         bf16_t* dst = y_out + ((size_t)b * N + n) * D;
@@ -107,13 +110,14 @@ void launch_rank_from_idx(const int32_t* idx, int32_t* rank, int B, int N, int k
 void launch_restore(const void* y_kept, const int32_t* rank, int B, int k, const void* cache_map, int hc,
                     int wc, int h, int w, int D, void* y_out, hipStream_t stream) {
     const int N = h * w;
-    // Rank, taps and store of a row wait for one another, so as many rows in flight as there are, a wave a row (two, one
-    // after the other / one: 16x16 x 1024 3.8 / 2.7 us, 53x37 x 2048 6.4 / 5.0, 64x64 x 2048 8.5 / 7.4), until a map has waves for
-    // several rounds of the chip (128x128 x 2048 21.7 / 22.2).
-    const int rows = (size_t)B * N * D >= (size_t)1 << 25 ? 2 : 1;
-    restore_kernel<<<dim3((N + 4 * rows - 1) / (4 * rows), B), 256, 0, stream>>>(
-        static_cast<const bf16_t*>(y_kept), rank, k, static_cast<const bf16_t*>(cache_map), hc, wc, h, w, D,
-        static_cast<bf16_t*>(y_out), rows);
+    const RestorePlan plan = restore_plan((long)B * N, w, D);
+    const dim3 grid((N + 4 * plan.rows - 1) / (4 * plan.rows), B);
+    const auto launch = [&](auto* kernel) {
+        kernel<<<grid, 256, 0, stream>>>(static_cast<const bf16_t*>(y_kept), rank, k, static_cast<const bf16_t*>(cache_map), hc,
+                                         wc, h, w, D, static_cast<bf16_t*>(y_out), plan.rows);
+    };
+    if (plan.pair) launch(&restore_kernel<true>);
+    else launch(&restore_kernel<false>);
 }
 
 void launch_residual_accumulate(const float* r_prev, int hp, int wp, const void* f_k, int h, int w, int B, int C,

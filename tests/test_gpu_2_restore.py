@@ -87,6 +87,13 @@ def test_restore_rebuilds_rank_from_idx(name, B, hc, wc, h, w, D, k):
     check(name, B, hc, wc, h, w, D, k, use_rank=False, seed=4)
 
 
+@pytest.mark.parametrize("B,hc,wc,h,w,D,k", [(1, 21, 40, 67, 65, 64, 1300), (3, 9, 21, 37, 41, 456, 700), (1, 30, 31, 70, 62, 1288, 4340),
+                                             (1, 17, 5, 4301, 1, 8, 0)])
+def test_restore_two_rows_a_wave(B, hc, wc, h, w, D, k):
+    """Maps of more rows than the chip has waves for: a pair a wave, an odd row and a part-filled workgroup at the end."""
+    check("pair", B, hc, wc, h, w, D, k, use_rank=True, seed=5)
+
+
 def test_restore_special_cases_exact():
     print("[restore] exact special cases", flush=True)
     # same size: identity on pruned slots; constant cache: constant; 2x of a bf16-exact ramp
