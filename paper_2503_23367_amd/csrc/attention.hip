@@ -50,7 +50,7 @@ struct AttnParams {
     int q_tiles, splits, keys_per_split, full_tiles, tail_tiles;
     float* part;   // [tail tile][split][1 + DB*QB*4 vectors][QG*64 lanes][4] fp32
     int* split_cnt;   // [tail tile][kCounterStride] arrival counters, zero between launches
-    int n_wg;         // plain kernel: workgroups of its own; those behind them prefetch
+    int n_wg;         // plain kernel with something to fetch: workgroups of its own; those behind them fetch
     Prefetch ahead;
     int* split_ready; // [tail tile][kCounterStride] ranges whose partial result is complete in memory, zero between launches
 };
@@ -83,7 +83,7 @@ constexpr int attn_waitcnt(int vm, bool lgkm) {
     return (vm & 0xF) | ((vm >> 4) << 14) | (0x7 << 4) | ((lgkm ? 0x0 : 0xF) << 8);
 }
 
-template <int DH, int QB, int QG, int KSPLIT>
+template <int DH, int QB, int QG, int KSPLIT, bool AHEAD>
 __global__ __launch_bounds__(QG * KSPLIT * 64, (QB == 1 ? 2 : 1)) void attention_kernel(const AttnParams p) {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
     constexpr int WAVES = QG * KSPLIT;
@@ -117,9 +117,12 @@ __global__ __launch_bounds__(QG * KSPLIT * 64, (QB == 1 ? 2 : 1)) void attention
     // round-robin to the 8 XCDs, each with its own L2; undo that so an XCD works on
     // a contiguous run of (head, query tile) pairs: the workgroups that stream the
     // same head's K / V then share one L2 instead of pulling it into all eight.
+    // AHEAD: workgroups behind the launch's own fetch weights.  Not in short launches with nothing to fetch: the workgroup
+    // count, and the way out, come from the arguments there, and the launch's own loads wait for a second and third round
+    // of those, 0.2 to 0.4 us (64 workgroups over 495 keys 10.2 -> 10.7 us).
     int wg = blockIdx.x;
-    const int n_wg = p.n_wg;
-    if (wg >= n_wg) {
+    const int n_wg = AHEAD ? p.n_wg : gridDim.x;
+    if (AHEAD && wg >= n_wg) {
         prefetch_lines(p.ahead, wg - n_wg);
         return;
     }
@@ -1236,8 +1239,6 @@ void launch_cfg(AttnParams& p, const AttnArgs& a, hipStream_t stream) {
     constexpr size_t tile_bytes = (size_t)2 * (64 * KSPLIT * (DH / 8) + DH * (8 * KSPLIT)) * 16;
     constexpr size_t merge_bytes = KSPLIT > 1 ? (size_t)QG * (DH / 32 * 16 + 2) * QB * 64 * 4 : 0;
     constexpr size_t smem = tile_bytes > merge_bytes ? tile_bytes : merge_bytes;
-    static std::once_flag once;
-    raise_lds_limit_once(once, &attention_kernel<DH, QB, QG, KSPLIT>, smem);
     const int per_wg = QG * 32 * QB;
     p.q_tiles = (p.k_tokens + per_wg - 1) / per_wg;
     p.n_wg = p.q_tiles * p.H * a.B;
@@ -1246,8 +1247,17 @@ void launch_cfg(AttnParams& p, const AttnArgs& a, hipStream_t stream) {
     if (p.n_wg <= 192)
         p.ahead = a.ahead.plan(256 - p.n_wg, 6.5 + (DH == 128 ? 1.45 : 0.6) * ((p.L + 64 * KSPLIT - 1) / (64 * KSPLIT)),
                                a.B * a.k_tokens <= kFewRowsMax);
-    attention_kernel<DH, QB, QG, KSPLIT>
-        <<<dim3(p.n_wg + p.ahead.blocks), QG * KSPLIT * 64, smem, stream>>>(p);
+    // (long launches take the other form with nothing to fetch: its start is nothing there, and 832 workgroups of dim 64 over
+    // 7263 keys, a part-filled round behind full ones, take 273 us in it and 302 in this one, others the same in both)
+    if (p.ahead.blocks > 0 || p.n_wg > 512) {
+        static std::once_flag once;
+        raise_lds_limit_once(once, &attention_kernel<DH, QB, QG, KSPLIT, true>, smem);
+        attention_kernel<DH, QB, QG, KSPLIT, true><<<dim3(p.n_wg + p.ahead.blocks), QG * KSPLIT * 64, smem, stream>>>(p);
+    } else {
+        static std::once_flag once;
+        raise_lds_limit_once(once, &attention_kernel<DH, QB, QG, KSPLIT, false>, smem);
+        attention_kernel<DH, QB, QG, KSPLIT, false><<<dim3(p.n_wg), QG * KSPLIT * 64, smem, stream>>>(p);
+    }
 }
 
 // Tuning builds only (-DFASTVAR_DEV_KNOBS, never the product library, which reads no environment and keeps
@@ -1277,8 +1287,8 @@ AttnSplitPlan attention_split_plan(int B, int H, int dh, int k_tokens, int L, si
     AttnSplitPlan sp{1, 0, false, 0, 0, 0, 0, 0};
     if (dh != 128 || L <= 256 || k_tokens <= 0) return sp;
     const long wg128 = (long)((k_tokens + 127) / 128) * H * B;
-    // With fewer than 128 workgroups of 128 queries the unsplit launch is the plain kernel's 64-query workgroups
-    // (keys split in two inside the workgroup), which the model below does not describe; over a short cache
+    // With fewer than 128 workgroups of 128 queries the unsplit launch is the plain kernel's workgroups of 64 queries, or 32
+    // (attention_cfg; keys split in two inside the workgroup), which the model below does not describe; over a short cache
     // they win (400 / 576 queries over 921 / 1497 keys: 22.3 / 29.3 us against 25.5 / 33.7 on two / three
     // ranges), over a long one the ranges do (410 queries over 6835 keys).
     if (wg128 < 128 && L < 2048) return sp;
@@ -1302,8 +1312,8 @@ AttnSplitPlan attention_split_plan(int B, int H, int dh, int k_tokens, int L, si
     double best = rounds(wg128) < kWide * rounds(wg256) ? rounds(wg128) : kWide * rounds(wg256);
     best *= 0.97;    // a split has to win by more than the model's noise
     for (int wide = 0; wide <= (attn_wide_enabled() ? 1 : 0); ++wide) {
-        // with fewer than 128 workgroups of 128 queries the unsplit launch is the plain kernel's 64-query
-        // workgroups, which the model above does not describe and 256-query workgroups do not beat
+        // with fewer than 128 workgroups of 128 queries the unsplit launch is the plain kernel's workgroups of 64 or 32
+        // queries, which the model above does not describe and 256-query workgroups do not beat
         if (wide && wg128 < 128) continue;
         const long wg = wide ? wg256 : wg128;
         for (int s = 2; s <= 4; ++s) {
@@ -1388,47 +1398,16 @@ void launch_attention(const AttnArgs& a, hipStream_t stream) {
             return;
         }
     }
-    // Head dim 128 and more than two key tiles: the software-pipelined kernel (64 queries per wave),
-    // with 128-query workgroups (two query groups x two key slices) or 256-query workgroups (four query
-    // groups), whichever needs less time for its rounds of workgroups.  The plain kernel (a wave per 32 queries) otherwise, on
-    // workgroups as small as still fit a round: there the launch waits for its keys, which more CUs then pull on, a block's time in us:
-    //   one tile of 64 keys: nothing to split, 128 queries (37.9 for one token of the large model, 40.0 with 128-key tiles);
-    //   head dim 128, up to 176 workgroups of 32 queries, keys split in two: 256 queries over 521 keys 79.7 (64 queries: 81.1),
-    //     300 over 1221 117.1 (118.9); 208 workgroups of them lose (400 over 921 104.5, 102.4);
-    //   up to 256 workgroups of 64 queries, keys split in two: small model, 576 over 1497 62.9, 1024 over 2624 88.3 (128 queries on
-    //     eight waves: 67.3, 92.3), 4 x 169 of the large model over 424 123.7 (pipelined: 130); 270 of them lose (576 over 1497 of
-    //     the 512 px model 129.8, 126.4);
-    //   more: with enough queries two 4-wave workgroups of 128 share a CU; with fewer an 8-wave workgroup splits the
-    //     keys of each tile between two waves per query group.
-    const long waves = (long)((a.k_tokens + 31) / 32) * a.H * a.B;
-    const long wg256 = (long)((a.k_tokens + 255) / 256) * a.H * a.B;
-    const long wg128 = (long)((a.k_tokens + 127) / 128) * a.H * a.B;
-    const long wg64 = (long)((a.k_tokens + 63) / 64) * a.H * a.B;
-    int cfg = waves >= 1800 ? 2 : 4;
-    if (a.L <= 64) cfg = 2;
-    else if (a.dh == 128 && waves <= 176) cfg = 7;
-    else if (wg64 <= 256 && (a.dh == 64 || wg128 < 128 || a.L <= 512)) cfg = 3;
-    else if (a.dh == 128 && a.L > 256) {
-        // rounds of workgroups on 256 CUs; a 256-query workgroup does twice the work about 7 % faster; too few queries for
-        // half the chip: 64-query workgroups
-        const long rounds128 = (wg128 + 255) / 256, rounds256 = (wg256 + 255) / 256;
-        if (wg128 < 128) cfg = 3;
-        else cfg = 1.86 * (double)rounds256 < (double)rounds128 ? 6 : 5;
-    }
-    if (a.dh == 64 && a.L >= 1024 && wg256 >= 128 && (a.k_tokens + 255) / 256 * 2 == (a.k_tokens + 127) / 128) {
-        // Head dim 64 is bound by the softmax, not the matrix pipe, and the pipelined kernel gains less:
-        // its 256-query workgroups win (by 5-20 % on 8 x 30 heads, 1024-3072 keys) where they pad the
-        // queries no further than 128-query workgroups would and the key loop is long enough to pay
-        // for the longer prologue; the plain kernel wins elsewhere.
-        cfg = 6;
-    }
+    int cfg = attention_cfg(a.B, a.H, a.dh, a.k_tokens, a.L);
     if (attn_cfg_override() >= 0) cfg = attn_cfg_override();
     // the software-pipelined kernel needs at least three key tiles
     if ((cfg == 5 || cfg == 6) && a.L <= 2 * (cfg == 5 ? 128 : 64)) cfg = 4;
     if (a.dh == 128) {
         switch (cfg) {
+#ifdef FASTVAR_DEV_KNOBS
             case 0: launch_cfg<128, 2, 4, 1>(p, a, stream); break;
             case 1: launch_cfg<128, 2, 2, 2>(p, a, stream); break;
+#endif
             case 2: launch_cfg<128, 1, 4, 1>(p, a, stream); break;
             case 3: launch_cfg<128, 1, 2, 2>(p, a, stream); break;
             case 5: launch_pipe<128, 2, 2>(p, a.B, stream); break;
@@ -1438,8 +1417,10 @@ void launch_attention(const AttnArgs& a, hipStream_t stream) {
         }
     } else {
         switch (cfg) {
+#ifdef FASTVAR_DEV_KNOBS
             case 0: launch_cfg<64, 2, 4, 1>(p, a, stream); break;
             case 1: launch_cfg<64, 2, 2, 2>(p, a, stream); break;
+#endif
             case 2: launch_cfg<64, 1, 4, 1>(p, a, stream); break;
             case 3: launch_cfg<64, 1, 2, 2>(p, a, stream); break;
             case 5: launch_pipe<64, 2, 2>(p, a.B, stream); break;

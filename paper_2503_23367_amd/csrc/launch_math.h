@@ -205,6 +205,41 @@ FV_HOST_DEVICE SplitKPlan gemm_splitk_plan(int M, int N, int K, SlicesMeet meet)
     return best;
 }
 
+// Attention without key ranges: which kernel and workgroups (attention.hip), of B samples, H heads of dim dh, k queries, L keys.
+// Head dim 128 and more than two key tiles: the software-pipelined kernel (64 queries per wave), with 128-query workgroups (5: two
+// query groups x two key slices) or 256-query workgroups (6: four query groups), whichever needs less time for its rounds
+// of workgroups on 256 CUs; a 256-query workgroup does twice the work about 7 % faster.  The plain kernel (a wave per 32 queries)
+// otherwise, on workgroups as small as still fit a round: there the launch waits for its keys, which more CUs then pull on, a block's
+// time in us:
+//   2: one tile of 64 keys: nothing to split, 128 queries (37.9 for one token of the large model, 40.0 with 128-key tiles);
+//   7: head dim 128, up to 176 workgroups of 32 queries, keys split in two: 256 queries over 521 keys 79.7 (64 queries: 81.1),
+//     300 over 1221 117.1 (118.9); 208 workgroups of them lose (400 over 921 104.5, 102.4).  Up to 32 queries there are as many
+//     workgroups of 64, whose second query group only loads, and two waves that load keys lose to four until the cache is long:
+//     the launch over 300 / 600 / 1200 / 2500 keys 9.4 / 12.0 / 17.5 / 28 us on two waves, 8.9 / 11.7 / 17.3 / 30 on four.
+//     Nor where workgroups of 64 divide evenly among the eight XCDs and those of 32 do not, so that every XCD pulls in every
+//     head's keys (18 heads, 222 over 1103 keys 18.8, 17.0 on 64);
+//   3: up to 256 workgroups of 64 queries, keys split in two: small model, 576 over 1497 62.9, 1024 over 2624 88.3 (128 queries on
+//     eight waves: 67.3, 92.3), 4 x 169 of the large model over 424 123.7 (pipelined: 130); 270 of them lose (576 over 1497 of
+//     the 512 px model 129.8, 126.4);
+//   more: with enough queries two 4-wave workgroups of 128 share a CU (2); with fewer an 8-wave workgroup splits the
+//     keys of each tile between two waves per query group (4).
+FV_HOST_DEVICE int attention_cfg(int B, int H, int dh, int k, int L) {
+    const auto groups = [&](int queries) { return (long)((k + queries - 1) / queries) * H * B; };
+    const long wg256 = groups(256), wg128 = groups(128), wg64 = groups(64), waves = groups(32);
+    // Head dim 64 is bound by the softmax, not the matrix pipe, and the pipelined kernel gains less: its 256-query workgroups
+    // win (by 5-20 % on 8 x 30 heads, 1024-3072 keys) where they pad the queries no further than 128-query workgroups would
+    // and the key loop is long enough to pay for the longer prologue; the plain kernel wins elsewhere.
+    if (dh == 64 && L >= 1024 && wg256 >= 128 && (k + 255) / 256 * 2 == (k + 127) / 128) return 6;
+    if (L <= 64) return 2;
+    if (dh == 128 && waves <= 176) return (k > 32 || L > 1536) && (waves % 8 == 0 || wg64 % 8 != 0) ? 7 : 3;
+    if (wg64 <= 256 && (dh == 64 || wg128 < 128 || L <= 512)) return 3;
+    if (dh == 128 && L > 256) {
+        const long rounds128 = (wg128 + 255) / 256, rounds256 = (wg256 + 255) / 256;
+        return 1.86 * (double)rounds256 < (double)rounds128 ? 6 : 5;
+    }
+    return waves >= 1800 ? 2 : 4;
+}
+
 // How much of a list of matrices (bytes[0], bytes[1], ..., in the order they are read) a launch of about `us` microseconds
 // fetches ahead on its `idle` CUs, and on how many of them.  Whole matrices, as many as come in while the launch runs: 45 KB a
 // microsecond and CU, 5.6 MB for the chip.  No more CUs than that takes: the launch's own loads wait behind the others.

@@ -47,6 +47,7 @@ int restore_rows(long rows, int w, int D) {
     const fv::RestorePlan p = fv::restore_plan(rows, w, D);
     return p.pair ? -p.rows : p.rows;
 }
+int attention(int B, int H, int dh, int k, int L) { return fv::attention_cfg(B, H, dh, k, L); }
 int few_rows_ln(int M, int N, int K) { return fv::few_rows_layernorm(M, N, K); }
 }
 """
@@ -204,6 +205,23 @@ def test_sliced_cases_reach_every_tile_of_slices(math):
     for (D, _, _, F), (B, _, _, k) in [(d, r) for d in SLICED_DIMS for r in SLICED_ROWS] + [SLICED_ALONE]:
         reached |= {_slices(math, B * k, D, D, LAYERNORM)[1:], _slices(math, B * k, D, F, EITHER)[1:]}
     assert {cfg for cfg, splits in reached if splits > 1} == {16, 17, 34, 35, 40} and {splits for _, splits in reached} == {1, 2, 4, 8}
+
+
+def test_attention_workgroups(math):
+    """Up to 32 queries workgroups of 32 have half the waves that load keys and no more workgroups: over 257 to 1200 keys the launch
+    was 1 to 6 % slower than on workgroups of 64."""
+    for H in (16, 18, 32):
+        for k in (1, 9, 31, 32):
+            for L in (65, 128, 300, 600, 1200, 1536):
+                assert math.attention(1, H, 128, k, L) == 3, (H, k, L)
+            assert math.attention(1, H, 128, k, 1537) == 7 and math.attention(1, H, 128, k, 64) == 2
+        assert math.attention(1, H, 128, 33, 300) == 7
+    # both sides of the other lines
+    for shape, cfg in [((1, 16, 128, 352, 521), 7), ((1, 16, 128, 353, 521), 3), ((4, 16, 128, 256, 512), 3), ((4, 16, 128, 256, 513), 5), ((3, 48, 128, 14, 575), 3), ((1, 18, 128, 222, 1103), 3),
+                       ((1, 18, 128, 256, 1103), 7), ((1, 18, 128, 64, 1103), 7),
+                       ((4, 16, 128, 257, 512), 5), ((4, 32, 128, 128, 513), 5), ((4, 32, 128, 128, 512), 3), ((1, 16, 64, 1024, 2624), 3),
+                       ((1, 16, 64, 1025, 2624), 4), ((8, 30, 64, 410, 1626), 6), ((8, 30, 64, 300, 1626), 2), ((1, 64, 128, 4096, 9000), 6)]:
+        assert math.attention(*shape) == cfg, (shape, cfg)
 
 
 def test_rows_of_a_restoring_wave(math):
