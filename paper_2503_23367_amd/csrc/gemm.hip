@@ -617,6 +617,12 @@ void launch_epi(GemmParams& p, hipStream_t stream) {
             if constexpr (is_qkv(EPI)) launch_cfg<256, 192, 64, 2, 4, 2, 1, EPI>(p, stream);
             else launch_cfg<256, 256, 64, 2, 2, 4, 1, EPI>(p, stream);
             break;
+        case 15:
+            if constexpr (is_qkv(EPI)) {
+                launch_cfg<64, 64, 64, 8, 2, 2, 1, EPI>(p, stream);
+                break;
+            }
+            [[fallthrough]];
         case 16: launch_cfg<64, 64, 64, 4, 2, 2, 1, EPI>(p, stream); break;
         case 17: launch_cfg<128, 64, 64, 6, 4, 2, 1, EPI>(p, stream); break;
         case 18: launch_cfg<64, 32, 64, 8, 2, 1, 2, EPI>(p, stream); break;

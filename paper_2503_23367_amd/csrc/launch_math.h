@@ -61,7 +61,7 @@ FV_HOST_DEVICE FewRowsPlan few_rows_plan(int N, int K, bool layernorm) {
 //     37.1 / 34.7, 38.8 / 38.2; K = 8192, 32768 of 1 / 8 rows 118 / 104, 119 / 115;
 //   several, part-filled: K = 2304, 12288 of 8 / 16 rows 19.6 / 17.0, 19.6 / 20.4, 16384 of 1 / 8 rows 20.4 / 17.9,
 //     20.5 / 21.9; K = 5120, 8192 of 16 rows 25.3 / 27.5;
-//   against a split K, up to 2048 columns (a workgroup per CU): 1024 of K = 4096, 1 / 16 rows 11.3 / 7.9, 11.8 / 10.7;
+//   against a split K, whose slices then met inside the product, up to 2048 columns (a workgroup per CU): 1024 of K = 4096, 1 / 16 rows 11.3 / 7.9, 11.8 / 10.7;
 //     1536 of 6144, 8 / 16 rows 13.2 / 12.0, 13.1 / 14.1;
 //   beyond, only where every CU has the same number of workgroups of sixteen columns: 4096 of K = 4096, 1 / 16 rows 14.1 / 11.8,
 //     14.4 / 13.9; 8192 of 8192, 4 / 8 rows 34.8 / 34.4, 35 / 38; but 2304 of 9216, 1 / 16 rows 17 / 26, 18 / 41, and 5120
@@ -76,7 +76,9 @@ FV_HOST_DEVICE bool few_rows_product(int M, int N, int K, bool split_k) {
     if (K < kFewRowsRound) return M == 1 || N <= (M <= 8 ? 16384 : 12288);
     return N <= (M == 1 ? 16384 : M <= 8 ? 12288 : 2048);
 }
-// The `split_k` of a block's products, which have scratch for slices.
+// The `split_k` of a block's products.  Out-proj and FC2 of these shapes are cut into slices where the tiled product takes them; QKV
+// and FC1 are not, but run on 64x32 tiles, one or two workgroups a CU, and beat this product as well: block of 1 / 4 / 8 rows, tiled
+// QKV / this one, 2304 wide 57.3 / 57.6, 59.5 / 60.4, 61.3 / 63.2 us, 2560 wide 56.1 / 55.7, 57.2 / 58.2, 57.5 / 60.5.
 FV_HOST_DEVICE bool few_rows_tiled_splits(int N, int K) { return K >= 2048 && K / 64 % 2 == 0 && N <= 8192; }
 // A LayerNorm over K columns fits in front: a wave holds its share of the rows in registers.
 FV_HOST_DEVICE bool few_rows_layernorm(int M, int N, int K) {
@@ -105,11 +107,12 @@ FV_HOST_DEVICE bool few_rows_layernorm(int M, int N, int K) {
 //    operand reuse of the larger ones: 128x64 tiles with eight waves and six stages (four waves and three stages: 256 x 6144 x
 //    2048 18.6 -> 16.6 us, 576 x 2048 x 2048 17.3 -> 14.0, 960 rows 18.3 -> 15.4), at most 64: 64x64 tiles with four stages, or
 //    64x32 ones with eight where these are at most a round (64 x 6144 x 2048 13.2 -> 11.2, 25 rows 11.4 -> 9.3; 128 rows, a
-//    round and a half, 13.1 -> 19.2) and K is more than eight tiles: up to there the sums of their two k-groups, which meet in LDS, cost
-//    what the finer split saves (24 products of K 320 to 512, weights in the cache, 1 % longer; of K 576 to 1024 5 %
-//    shorter, of 1088 to 2048 16 %, of longer ones 19 to 33 %).  64x64 tiles with eight stages, one workgroup a CU instead of two, and
-//    all of a ring's loads queued in front of the first product, take 6 % longer with weights in the cache (545 x 1024 x 1024
-//    6.5 / 7.1 us, 350 x 2048 x 2048 9.1 / 9.9), 2 to 5 % less with weights from memory and K above 1024: not kept.
+//    round and a half, 13.1 -> 19.2) and K is more than four tiles: up to there the sums of their two k-groups, which meet in LDS, cost
+//    more than the finer split saves (34 products 1 % longer; of K 320 to 512 3 % shorter with weights from memory, 1 % longer from
+//    the cache, of K 576 to 1024 5 to 12 % shorter, of longer ones 16 to 50 %).  64x64 tiles with eight stages, one workgroup a
+//    CU instead of two and all of a ring's loads queued in front of the first product, take 4 to 6 % longer with weights in the cache
+//    (545 x 1024 x 1024 6.5 / 7.1 us, 350 x 2048 x 2048 9.1 / 9.9), and of K above 1024 2 to 8 % less with weights from memory
+//    (68 x 5760 x 1920 12.5 / 11.5, 142 x 4096 x 4096 20.8 / 18.4): for QKV, whose weights no launch fetches ahead.
 // Beyond 128 tiles the choice is the candidate with the least modelled time (us): 2.05 to launch, and for every round of its
 // workgroups, a part-filled one counting 0.777 + 0.189 * fill, fix + K tiles * per_kt, where a K tile beyond the 32nd takes
 // `longer` more; tile counts that do not divide by eight are not dealt to the XCDs in contiguous runs, and cost 4 % more, with
@@ -135,7 +138,7 @@ FV_HOST_DEVICE TileChoice gemm_choose_tile(bool qkv, int M, int N, int K) {
     struct Cand { int cfg, bm, bn, slots; double fix, per_kt, longer; };
     const Cand cands[] = {
         {18, 64, 32, 256, 2.1, 0.170, 0.0},        // the first three by the rules above, their times for the K slices below
-        {16, 64, 64, 512, 2.7, 0.270, 0.0},
+        {qkv && KT > 16 ? 15 : 16, 64, 64, 512, 2.7, 0.270, 0.0},
         {17, 128, 64, 256, 3.4, 0.335, 0.0},
         {qkv ? 12 : 11, 256, qkv ? 192 : 256, 256, qkv ? 4.73 : 7.18, qkv ? 1.231 : 1.469, qkv ? -0.033 : -0.030},
         {32, 256, 128, 256, 4.81, 0.779, -0.042},
@@ -146,7 +149,7 @@ FV_HOST_DEVICE TileChoice gemm_choose_tile(bool qkv, int M, int N, int K) {
         {6, 128, 128, 512, 3.43, 1.001, -0.073},    // two workgroups per CU share its time
     };
     int from = 3, to = (int)(sizeof(cands) / sizeof(cands[0]));
-    if (tiles128 <= 64) from = (long)((M + 63) / 64) * ((N + 31) / 32) <= 256 && KT > 8 ? 0 : 1;
+    if (tiles128 <= 64) from = (long)((M + 63) / 64) * ((N + 31) / 32) <= 256 && KT > 4 ? 0 : 1;
     else if (tiles128 <= 128) from = 2;
     if (from < 3) to = from + 1;
     TileChoice best{6, 1e30};

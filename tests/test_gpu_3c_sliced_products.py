@@ -8,7 +8,8 @@ import torch
 from paper_2503_23367_amd import binding as fb
 from paper_2503_23367_amd import synth
 from gpu_util import DEV, empty_ws
-from tile_cases import SLICED_ALONE, SLICED_DIMS, SLICED_ROWS, TILES
+from tile_cases import QKV_TILES, SLICED_ALONE, SLICED_DIMS, SLICED_ROWS, TILES
+from test_gpu_3_components import test_qkv_gemm_appends_to_caches as check_qkv
 from test_gpu_4_block import check_block
 
 pytestmark = pytest.mark.gpu
@@ -27,6 +28,11 @@ def test_tiles(M, N, K, epi):
     assert out[M * N:].isnan().all()
     err = (out[:M * N].view(M, N).float() - ref).abs().max() / ref.abs().max()
     assert err <= 2.0 ** -7, float(err)
+
+
+@pytest.mark.parametrize("D,dh,B,k", list(QKV_TILES.values()))
+def test_qkv_tiles(D, dh, B, k):
+    check_qkv(_dims(D, D // dh, dh, D), B, k, 5, (5 + k + 7) // 8 * 8)
 
 
 def _dims(D, H, dh, F):

@@ -7,7 +7,7 @@ import subprocess
 
 import pytest
 
-from tile_cases import SLICED_ALONE, SLICED_DIMS, SLICED_ROWS, TILES
+from tile_cases import QKV_TILES, SLICED_ALONE, SLICED_DIMS, SLICED_ROWS, TILES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -137,26 +137,29 @@ def test_tile_cases_reach_their_tiles(math):
     for cfg, cases in TILES.items():
         for M, N, K, _ in cases:
             assert math.tile(0, M, N, K) == cfg, (M, N, K)
+    for cfg, (D, _, B, k) in QKV_TILES.items():
+        assert math.tile(1, B * k, 3 * D, D) == cfg, (B, k, D)
 
 
 # (qkv, M, N, K): the tile that was measured 6 % or more slower than the best one there, us
 SLOWER = [((0, 320, 6336, 192), 13), ((0, 1462, 4224, 640), 13),                       # 14.9 / 7.4, 17.5 / 14.7
           ((0, 3309, 4096, 16384), 35), ((0, 787, 4096, 16384), 35), ((0, 10418, 2560, 8192), 34),   # 453 / 392, 142 / 112, 455 / 401
           ((1, 4242, 6912, 2304), 34), ((1, 1095, 7680, 2560), 34),                    # 153 / 139, 59.4 / 54.2
-          ((0, 391, 256, 128), 18), ((0, 17, 560, 320), 18)]                           # 4.97 / 4.71, 5.12 / 4.75
+          ((0, 391, 256, 128), 18), ((0, 284, 1216, 192), 18),                         # 4.97 / 4.71, 4.96 / 4.55
+          ((1, 68, 5760, 1920), 16), ((1, 76, 6144, 2048), 16)]                        # 12.5 / 11.5, 12.7 / 11.5
 
 
 def test_tiles_are_not_the_ones_measured_slower(math):
     for shape, cfg in SLOWER:
         assert math.tile(*shape) != cfg, shape
     # where 64x32 tiles are at most a round and K is long enough for their two k-groups, and just past either
-    for M, N, K, cfg in [(64, 8192, 576, 18), (64, 8192, 512, 16), (128, 4096, 1024, 18), (128, 4104, 1024, 16), (129, 8192, 1024, 17)]:
+    for M, N, K, cfg in [(64, 8192, 320, 18), (64, 8192, 256, 16), (128, 4096, 1024, 18), (128, 4104, 1024, 16), (129, 8192, 1024, 17)]:
         assert math.tile(0, M, N, K) == cfg, (M, N, K)
     # every size has a tile that the launch knows
     for M in (17, 64, 65, 191, 193, 1000, 4097, 33000, 87381):
         for N in (8, 64, 1344, 6144, 24576, 32768):
             for K in (64, 448, 2048, 2112, 8192, 32768):
-                assert math.tile(0, M, N, K) in TILES and math.tile(1, M, N, K) in {12, *TILES} - {11}, (M, N, K)
+                assert math.tile(0, M, N, K) in TILES and math.tile(1, M, N, K) in {12, 15, *TILES} - {11}, (M, N, K)
 
 
 LAYERNORM, EITHER, LAUNCH = 0, 1, 2   # SlicesMeet

@@ -4,8 +4,8 @@ BIAS_RES, BIAS_GELU = 1, 2
 
 # tile configuration -> (M, N, K, epilogue): rows and columns that end inside a tile, K shorter than the ring and longer
 TILES = {
-    16: [(65, 2040, 64, BIAS_RES), (64, 1000, 512, BIAS_GELU), (160, 2832, 1024, BIAS_GELU)],      # 64x64
-    18: [(33, 8192, 2048, BIAS_GELU), (169, 80, 576, BIAS_RES), (177, 1272, 1024, BIAS_GELU)],     # 64x32
+    16: [(65, 2040, 64, BIAS_RES), (64, 1000, 256, BIAS_GELU), (160, 2832, 1024, BIAS_GELU)],      # 64x64
+    18: [(33, 8192, 2048, BIAS_GELU), (64, 1000, 512, BIAS_GELU), (169, 80, 576, BIAS_RES), (177, 1272, 1024, BIAS_GELU)],     # 64x32
     17: [(129, 6136, 448, BIAS_GELU), (257, 5000, 1024, BIAS_RES), (156, 4288, 64, BIAS_RES)],     # 128x64
     40: [(758, 4512, 256, BIAS_GELU), (151, 8376, 64, BIAS_RES), (1281, 2040, 4096, BIAS_RES)],    # 128x128
     6: [(577, 8200, 256, BIAS_GELU), (1500, 4104, 64, BIAS_GELU), (1154, 3488, 64, BIAS_RES)],     # 128x128, two a CU
@@ -16,6 +16,9 @@ TILES = {
     32: [(577, 8200, 2048, BIAS_GELU), (772, 6648, 256, BIAS_RES), (735, 8768, 1024, BIAS_RES)],   # 256x128
     11: [(1537, 8192, 2048, BIAS_GELU), (1345, 8472, 64, BIAS_RES), (1348, 8224, 1024, BIAS_GELU)],   # 256x256
 }
+
+# tiles of QKV alone -> (D, dh, B, k)
+QKV_TILES = {15: (1152, 128, 1, 131), 12: (1344, 64, 2, 1283)}   # 64x64 with eight stages, 256x192
 
 # blocks whose out-proj and FC2 are cut into slices, on every tile that takes them: (D, H, dh, F) and (B, h, w, k)
 SLICED_DIMS = [(448, 7, 64, 2048), (1024, 16, 64, 4096), (1088, 17, 64, 8192), (4224, 33, 128, 4352)]
