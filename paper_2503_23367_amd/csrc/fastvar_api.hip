@@ -284,15 +284,9 @@ fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k
     at.scale = d->softmax_scale;
     at.split_ws = bp.asplit_bytes ? base + bp.off_asplit : nullptr;
     at.split_ws_bytes = bp.asplit_bytes;
-    // (matrices under 16 MB only in a stack, and not for few rows: 16 blocks of the small model on 169 rows 775 -> 734 us with
-    // it, but its single step on 128 rows 55.8 -> 56.4 and eight blocks of it on 16 rows 241 -> 246)
-    if (2L * d->D * d->F >= 16L << 20 || (in_stack && M > fv::kFewRowsMax)) {
-        at.ahead.add(w->w_proj, 2L * d->D * d->D);
-        if (ffn_follows) {
-            at.ahead.add(w->w_fc1, 2L * d->D * d->F);
-            at.ahead.add(w->w_fc2, 2L * d->D * d->F);
-        }
-    }
+    const fv::AheadList list = fv::ahead_list(d->D, d->F, M, in_stack, ffn_follows);
+    const void* const ahead[] = {w->w_proj, w->w_fc1, w->w_fc2};
+    for (int i = 0; i < list.n; ++i) at.ahead.add(ahead[i], list.bytes[i]);
     fv::launch_attention(at, st);
     mark(st, FASTVAR_STAGE_ATTENTION);
     // h1 = x[idx] + o * Wp^T + bp

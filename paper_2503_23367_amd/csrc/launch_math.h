@@ -243,6 +243,19 @@ FV_HOST_DEVICE int attention_cfg(int B, int H, int dh, int k, int L) {
     return waves >= 1800 ? 2 : 4;
 }
 
+// Which matrices the attention launch of a call may fetch ahead: those that the call's later products read, in their order, and no
+// others; a call that does not go on to the MLP half may hold placeholders for its weights.  Matrices under 16 MB only in a
+// stack, and not for few rows (16 blocks of the small model on 169 rows 775 -> 734 us with it, but its single step on 128 rows
+// 55.8 -> 56.4 and eight blocks of it on 16 rows 241 -> 246).
+struct AheadList {
+    int n;           // of out-proj, FC1, FC2: the first n
+    long bytes[3];
+};
+FV_HOST_DEVICE AheadList ahead_list(int D, int F, int M, bool in_stack, bool ffn_follows) {
+    const AheadList all{ffn_follows ? 3 : 1, {2L * D * D, 2L * D * F, 2L * D * F}};
+    return all.bytes[1] >= 16L << 20 || (in_stack && M > kFewRowsMax) ? all : AheadList{0, {0, 0, 0}};
+}
+
 // How much of a list of matrices (bytes[0], bytes[1], ..., in the order they are read) a launch of about `us` microseconds
 // fetches ahead on its `idle` CUs, and on how many of them.  Whole matrices, as many as come in while the launch runs: 45 KB a
 // microsecond and CU, 5.6 MB for the chip.  No more CUs than that takes: the launch's own loads wait behind the others.

@@ -79,9 +79,9 @@ def test_step_scatters_the_rows_of_the_block(dims, B, h, w, k):
 
 
 @pytest.mark.parametrize("k", [1, 24, 130])
-def test_attention_half_reads_no_mlp_weights(k):
-    """The attention half of a model whose MLP weights are not in memory yet (placeholders of 256
-    bytes): the same bits as with the whole block's weights."""
+def test_attention_half_does_not_depend_on_mlp_weights(k):
+    """The attention half with MLP weights and with NaN in their place: the same bits.  (What the launch fetches ahead never
+    shows in its results; that nothing of the MLP half is on its list is checked in test_launch_math.py.)"""
     dims = synth.INF2B
     gen = torch.Generator(device=DEV)
     gen.manual_seed(k)
@@ -99,8 +99,7 @@ def test_attention_half_reads_no_mlp_weights(k):
     idx = torch.arange(k, dtype=torch.int32, device=DEV).view(1, k)
     ws = empty_ws(fb.fastvar_block_workspace_bytes(d, 1, k))
     out = []
-    for weights in (wt, dict(wt, w_fc1=torch.empty(128, dtype=torch.bfloat16, device=DEV),
-                             w_fc2=torch.empty(128, dtype=torch.bfloat16, device=DEV))):
+    for weights in (wt, dict(wt, w_fc1=torch.full_like(wt["w_fc1"], float("nan")), w_fc2=torch.full_like(wt["w_fc2"], float("nan")))):
         kc, vc, y = kc0.clone(), vc0.clone(), torch.full((1, k, D), float("nan"), dtype=torch.bfloat16, device=DEV)
         fb.fastvar_attn_forward_pruned(x, N, idx, 1, k, d, fb.make_weights(weights), kc, vc, L0, L_cap, y, ws)
         out.append((y, kc, vc))

@@ -47,6 +47,11 @@ int restore_rows(long rows, int w, int D) {
     const fv::RestorePlan p = fv::restore_plan(rows, w, D);
     return p.pair ? -p.rows : p.rows;
 }
+void ahead(int D, int F, int M, int in_stack, int ffn_follows, long* out) {
+    const fv::AheadList l = fv::ahead_list(D, F, M, in_stack, ffn_follows);
+    out[0] = l.n;
+    for (int i = 0; i < 3; ++i) out[1 + i] = l.bytes[i];
+}
 int attention(int B, int H, int dh, int k, int L) { return fv::attention_cfg(B, H, dh, k, L); }
 int few_rows_ln(int M, int N, int K) { return fv::few_rows_layernorm(M, N, K); }
 }
@@ -252,6 +257,21 @@ def test_column_chunks_fit_the_scratch(math):
             while -(-N // room) > 256:
                 room *= 2
             assert -(-N // rows) <= -(-N // room), (N, D)
+
+
+def test_attention_fetches_only_what_the_call_reads_later(math):
+    """An attention half on its own, or a sub-layer step that keeps nothing in its MLP half, once fetched FC1's and FC2's weights too,
+    past the end of whatever stood there for them."""
+    out = (C.c_long * 4)()
+    for D, F in [(64, 64), (1024, 4096), (1920, 7680), (2048, 8192), (2304, 6912), (4096, 16384)]:
+        for M in (1, 16, 17, 130, 576, 4096):
+            for in_stack in (0, 1):
+                math.ahead(D, F, M, in_stack, 0, out)
+                assert out[0] <= 1 and (out[0] == 0 or out[1] == 2 * D * D), (D, F, M, in_stack)
+                math.ahead(D, F, M, in_stack, 1, out)
+                large = 2 * D * F >= 16 << 20
+                assert out[0] == (3 if large or (in_stack and M > 16) else 0)
+                assert out[0] == 0 or tuple(out)[1:] == (2 * D * D, 2 * D * F, 2 * D * F)
 
 
 @pytest.mark.parametrize("cut", [0, 1])
