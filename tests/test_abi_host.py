@@ -37,6 +37,21 @@ def test_version_and_strerror():
     assert fb.strerror(-99) == "unknown error"
 
 
+@pytest.mark.parametrize("missing", [(), ("_cuda_getCurrentRawStream",), ("_cuda_getDevice",)])
+def test_stream_handle_without_torchs_own_functions(monkeypatch, missing):
+    """The current stream's handle, by torch's internal functions where the build has them and by its interface where not."""
+    torch = pytest.importorskip("torch")
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 77})())
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+    for name in missing:
+        monkeypatch.delattr(torch._C, name)
+    assert fb._stream() == (77 if missing else 103)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    assert fb._stream() == 77
+
+
 def test_keep_count_agrees_with_oracle_reading():
     for N in (0, 1, 7, 256, 576, 1024, 4096, 9216, 16384):
         for r in (0.0, 0.1, 0.25, 0.3, 0.4, 0.5, 0.6, 0.75, 1.0, 1.5, -0.5):
