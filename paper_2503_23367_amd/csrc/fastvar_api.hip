@@ -47,10 +47,10 @@ BlockPlan block_plan(const fastvar_dims* d, int B, int k) {
     // slices of out-proj and FC2 (few rows only): one area, used by one product at a time, as large as the largest, in a
     // whole block or in a half of one
     p.sk_bytes = 0;
-    for (const fv::SplitKPlan& sk : {fv::gemm_splitk_plan((int)M, d->D, d->D, fv::MEET_IN_LAYERNORM),
-                                     fv::gemm_splitk_plan((int)M, d->D, d->D, fv::MEET_IN_LAUNCH),
-                                     fv::gemm_splitk_plan((int)M, d->D, d->F, fv::MEET_IN_EITHER),
-                                     fv::gemm_splitk_plan((int)M, d->D, d->F, fv::MEET_IN_LAUNCH)})
+    for (const fv::SplitKPlan& sk : {fv::residual_product_plan((int)M, d->D, d->D, fv::MEET_IN_LAYERNORM),
+                                     fv::residual_product_plan((int)M, d->D, d->D, fv::MEET_IN_LAUNCH),
+                                     fv::residual_product_plan((int)M, d->D, d->F, fv::MEET_IN_EITHER),
+                                     fv::residual_product_plan((int)M, d->D, d->F, fv::MEET_IN_LAUNCH)})
         if (sk.bytes > p.sk_bytes) p.sk_bytes = sk.bytes;
     p.off_sk = off; off += round256(p.sk_bytes);
     p.bytes = off;
@@ -212,7 +212,7 @@ fv::SliceSum enqueue_residual_product(const fv::GemmArgs& g, hipStream_t st) {
     fv::launch_gemm(fv::EPI_BIAS_RES, g, st);
     fv::SliceSum s;
     if (!g.slice_ws) return s;
-    const fv::SplitKPlan sk = fv::gemm_splitk_plan(g.M, g.N, g.K, g.meet);
+    const fv::SplitKPlan sk = fv::residual_product_plan(g.M, g.N, g.K, g.meet);
     if (sk.splits == 1) return s;
     s.slices = static_cast<const float*>(g.slice_ws);
     s.splits = sk.splits; s.M = g.M; s.N = g.N;

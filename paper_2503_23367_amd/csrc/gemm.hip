@@ -592,7 +592,7 @@ void launch_cfg(GemmParams& p, hipStream_t stream) {
 
 // Tuning builds only (-DFASTVAR_DEV_KNOBS, never the product library, which reads no environment and keeps
 // no state): FASTVAR_GEMM_CFG (all epilogues) or FASTVAR_GEMM_CFG<e> (epilogue e = 0, 1, 2) forces a tile
-// configuration; unset means the heuristic below.
+// configuration, unsliced; unset means gemm_choose_tile and gemm_splitk_plan.
 int gemm_cfg_override(int epi) {
 #ifdef FASTVAR_DEV_KNOBS
     char name[32];
@@ -653,6 +653,10 @@ void launch_sliced(const SplitKPlan& sk, GemmParams& p, hipStream_t stream) {
 
 }  // namespace
 
+SplitKPlan residual_product_plan(int M, int N, int K, SlicesMeet meet) {
+    return gemm_cfg_override(EPI_BIAS_RES) >= 0 ? SplitKPlan{} : gemm_splitk_plan(M, N, K, meet);
+}
+
 void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {
     if (few_rows_product(a.M, a.N, a.K, a.slice_ws && few_rows_tiled_splits(a.N, a.K))) {
         launch_gemm_skinny(epi, a, stream);
@@ -676,7 +680,7 @@ void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {
     p.splits = 1;
     p.slices = static_cast<float*>(a.slice_ws);
     if (a.slice_ws && epi == EPI_BIAS_RES) {
-        const SplitKPlan sk = gemm_splitk_plan(a.M, a.N, a.K, a.meet);
+        const SplitKPlan sk = residual_product_plan(a.M, a.N, a.K, a.meet);
         if (sk.splits > 1) {
             launch_sliced(sk, p, stream);
             return;

@@ -104,7 +104,7 @@ struct GemmArgs {
     const float* rope_sin = nullptr;
     const int32_t* rope_rows = nullptr;
     int rope_N = 0;
-    // Optional scratch for the slices of a split K (EPI_BIAS_RES; gemm_splitk_plan says whether there are any and how
+    // Optional scratch for the slices of a split K (EPI_BIAS_RES; residual_product_plan says whether there are any and how
     // large they are).  Split, the launch leaves its slices there and touches neither `out` nor `residual`: the
     // launch of a SliceSum has to follow.
     void* slice_ws = nullptr;
@@ -121,6 +121,9 @@ void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream);
 // GEMMs of few rows (skinny.hip); launch_gemm routes there what few_rows_product (launch_math.h) gives it.
 void launch_gemm_skinny(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream);
 
+// The plan that launch_gemm follows for an out-proj or FC2 product (EPI_BIAS_RES): gemm_splitk_plan, and no slices where a tuning
+// build forces a tile.
+SplitKPlan residual_product_plan(int M, int N, int K, SlicesMeet meet);
 // What is left of a split product: out[row] = sum of the slices, in slice order, + residual (the bias is in the first slice).
 struct SliceSum {
     const float* slices = nullptr;   // [splits][M][N]; null: nothing is left to do
