@@ -20,6 +20,7 @@ constexpr int kMaxWidth = 8192;  // LayerNorm keeps a row in registers; score ke
 struct BlockPlan {
     size_t off_a, off_q, off_h1, off_u, off_rows, off_asplit, asplit_bytes, off_sk, sk_bytes, bytes;
     int asplit_counters;
+    fv::SplitKPlan proj, proj_half, fc2, fc2_half;   // out-proj and FC2, of a whole block and of a half of one
 };
 
 BlockPlan block_plan(const fastvar_dims* d, int B, int k) {
@@ -46,12 +47,13 @@ BlockPlan block_plan(const fastvar_dims* d, int B, int k) {
     p.off_asplit = off; off += round256(p.asplit_bytes);
     // slices of out-proj and FC2 (few rows only): one area, used by one product at a time, as large as the largest, in a
     // whole block or in a half of one
+    p.proj = fv::residual_product_plan((int)M, d->D, d->D, fv::MEET_IN_LAYERNORM);
+    p.proj_half = fv::residual_product_plan((int)M, d->D, d->D, fv::MEET_IN_LAUNCH);
+    p.fc2 = fv::residual_product_plan((int)M, d->D, d->F, fv::MEET_IN_EITHER);
+    p.fc2_half = fv::residual_product_plan((int)M, d->D, d->F, fv::MEET_IN_LAUNCH);
     p.sk_bytes = 0;
-    for (const fv::SplitKPlan& sk : {fv::residual_product_plan((int)M, d->D, d->D, fv::MEET_IN_LAYERNORM),
-                                     fv::residual_product_plan((int)M, d->D, d->D, fv::MEET_IN_LAUNCH),
-                                     fv::residual_product_plan((int)M, d->D, d->F, fv::MEET_IN_EITHER),
-                                     fv::residual_product_plan((int)M, d->D, d->F, fv::MEET_IN_LAUNCH)})
-        if (sk.bytes > p.sk_bytes) p.sk_bytes = sk.bytes;
+    for (const fv::SplitKPlan* sk : {&p.proj, &p.proj_half, &p.fc2, &p.fc2_half})
+        if (sk->bytes > p.sk_bytes) p.sk_bytes = sk->bytes;
     p.off_sk = off; off += round256(p.sk_bytes);
     p.bytes = off;
     return p;
@@ -96,7 +98,7 @@ int check_select(const void* x, int B, int h, int w, int D, int k, const int32_t
 
 int check_block(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* dims,
                 const fastvar_block_weights* wts, const void* kc, const void* vc, int L0, int L_cap,
-                const void* y, const void* ws, size_t ws_bytes) {
+                const void* y, const void* ws, size_t ws_bytes, const BlockPlan* bp = nullptr) {
     int rc = check_dims(dims);
     if (rc) return rc;
     rc = check_weights(wts);
@@ -111,7 +113,7 @@ int check_block(const void* x, int N, const int32_t* idx, int B, int k, const fa
     const double M = (double)B * k;
     const double widest = dims->F > 3 * dims->D ? dims->F : 3 * dims->D;
     if (M * widest >= 2147483648.0 || (double)widest * dims->F >= 2147483648.0) return FASTVAR_ECAPACITY;
-    if (k > 0 && (!ws || ws_bytes < fastvar_block_workspace_bytes(dims, B, k))) return FASTVAR_EWORKSPACE;
+    if (k > 0 && (!ws || ws_bytes < (bp ? bp->bytes : fastvar_block_workspace_bytes(dims, B, k)))) return FASTVAR_EWORKSPACE;
     return FASTVAR_OK;
 }
 
@@ -211,11 +213,9 @@ fv::ZeroCounters split_counters(void* ws, const BlockPlan& bp) {
 fv::SliceSum enqueue_residual_product(const fv::GemmArgs& g, hipStream_t st) {
     fv::launch_gemm(fv::EPI_BIAS_RES, g, st);
     fv::SliceSum s;
-    if (!g.slice_ws) return s;
-    const fv::SplitKPlan sk = fv::residual_product_plan(g.M, g.N, g.K, g.meet);
-    if (sk.splits == 1) return s;
+    if (g.slices.splits == 1) return s;
     s.slices = static_cast<const float*>(g.slice_ws);
-    s.splits = sk.splits; s.M = g.M; s.N = g.N;
+    s.splits = g.slices.splits; s.M = g.M; s.N = g.N;
     s.residual = g.residual; s.res_rows = g.res_rows;
     s.out = g.out; s.out_rows = g.out_rows;
     return s;
@@ -233,13 +233,12 @@ void finish(const fv::SliceSum& s, hipStream_t st) {
 // `before`: what is left of the product that x comes from (no index list).  Returns what is left of h1.
 // `ffn_follows`: the call goes on to the MLP half, whose weights may be fetched ahead; a call that does not touches
 // none of them.
-// `meet`: where the slices of a split out-proj meet; in a whole block its MLP half's LayerNorm reads h1 next.
-fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
+// `whole`: the half is part of a whole block, whose other half's LayerNorm reads h1 next and adds its slices up.
+fv::SliceSum enqueue_attn(const BlockPlan& bp, const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                   const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* h1_out, void* ws,
                   hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
                   const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false,
-                  bool ffn_follows = true, fv::SlicesMeet meet = fv::MEET_IN_LAUNCH) {
-    const BlockPlan bp = block_plan(d, B, k);
+                  bool ffn_follows = true, bool whole = false) {
     const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
     void* buf_a = base + bp.off_a;
@@ -294,7 +293,7 @@ fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k
     pj.A = buf_a; pj.W = w->w_proj; pj.bias = w->b_proj; pj.M = M; pj.N = d->D; pj.K = d->D;
     pj.out = h1_out; pj.residual = x; pj.res_rows = idx ? rows : nullptr; pj.k_tokens = k;
     pj.out_rows = (scatter && idx) ? rows : nullptr;
-    pj.slice_ws = sk; pj.meet = meet;
+    pj.slice_ws = sk; pj.slices = whole ? bp.proj : bp.proj_half;
     const fv::SliceSum left = enqueue_residual_product(pj, st);
     mark(st, FASTVAR_STAGE_PROJ);
     return left;
@@ -305,11 +304,10 @@ fv::SliceSum enqueue_attn(const void* x, int N, const int32_t* idx, int B, int k
 // `scatter_rows`: y is a [B, N, D] map and row m goes to row scatter_rows[m] of it (the absolute row of
 // the kept token, as left in the plan's row list by the gather).
 // `before`: what is left of the product that src comes from (no index list).  Returns what is left of y.
-fv::SliceSum enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
+fv::SliceSum enqueue_ffn(const BlockPlan& bp, const void* src, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                          const fastvar_block_weights* w, void* y, void* ws, hipStream_t st, bool clear,
                          bool scatter = false, const Fill* fill = nullptr, const fv::SliceSum& before = {},
-                         fv::SlicesMeet meet = fv::MEET_IN_LAUNCH) {
-    const BlockPlan bp = block_plan(d, B, k);
+                         bool whole = false) {
     const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
     void* buf_q = base + bp.off_q;
@@ -348,22 +346,21 @@ fv::SliceSum enqueue_ffn(const void* src, int N, const int32_t* idx, int B, int 
     f2.A = buf_u; f2.W = w->w_fc2; f2.bias = w->b_fc2; f2.M = M; f2.N = d->D; f2.K = d->F;
     f2.out = y; f2.residual = src; f2.res_rows = idx ? rows : nullptr; f2.k_tokens = k;
     f2.out_rows = scatter ? rows : nullptr;
-    f2.slice_ws = sk; f2.meet = meet;
+    f2.slice_ws = sk; f2.slices = whole ? bp.fc2 : bp.fc2_half;
     const fv::SliceSum left = enqueue_residual_product(f2, st);
     mark(st, FASTVAR_STAGE_FC2);
     return left;
 }
 
 // (`before` and what is returned as in the halves)
-fv::SliceSum enqueue_block(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
+fv::SliceSum enqueue_block(const BlockPlan& bp, const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                            const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* y, void* ws,
                            hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
                            const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false) {
-    void* buf_h1 = static_cast<char*>(ws) + block_plan(d, B, k).off_h1;
-    const fv::SliceSum h1 = enqueue_attn(x, N, idx, B, k, d, w, kc, vc, L0, L_cap, buf_h1, ws, st, clear, false,
-                                         idx ? fill : nullptr, rope, before, in_stack, true, fv::MEET_IN_LAYERNORM);
-    return enqueue_ffn(buf_h1, 0, nullptr, B, k, d, w, y, ws, st, false, scatter && idx, nullptr, h1,
-                       fv::MEET_IN_EITHER);
+    void* buf_h1 = static_cast<char*>(ws) + bp.off_h1;
+    const fv::SliceSum h1 = enqueue_attn(bp, x, N, idx, B, k, d, w, kc, vc, L0, L_cap, buf_h1, ws, st, clear, false,
+                                         idx ? fill : nullptr, rope, before, in_stack, true, true);
+    return enqueue_ffn(bp, buf_h1, 0, nullptr, B, k, d, w, y, ws, st, false, scatter && idx, nullptr, h1, true);
 }
 
 int check_ffn(const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* dims,
@@ -484,7 +481,7 @@ int fastvar_block_forward_pruned(const void* x, int N, const int32_t* idx, int B
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    finish(enqueue_block(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_kept_out, ws, st, true), st);
+    finish(enqueue_block(block_plan(dims, B, k), x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_kept_out, ws, st, true), st);
     return launch_status();
 }
 
@@ -510,7 +507,7 @@ int fastvar_block_forward_pruned_rope(const void* x, int N, const int32_t* idx, 
     if (k == 0) return FASTVAR_OK;
     const Rope rope{rope_cos, rope_sin};
     hipStream_t st = static_cast<hipStream_t>(stream);
-    finish(enqueue_block(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_kept_out, ws, st, true, false,
+    finish(enqueue_block(block_plan(dims, B, k), x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_kept_out, ws, st, true, false,
                          nullptr, &rope), st);
     return launch_status();
 }
@@ -572,11 +569,13 @@ int fastvar_step(const void* x, const int32_t* sched_h, const int32_t* sched_w, 
     const size_t blk_bytes = ws_bytes - sel_bytes - rank_bytes;
     // Stand-in for a kept-output buffer in the argument checks below (the block's last GEMM writes the
     // kept rows of y_out directly).
-    void* yk = k > 0 ? static_cast<void*>(ws_blk + block_plan(dims, B, k).off_q) : nullptr;
+    const BlockPlan bp = block_plan(dims, B, k);   // once: a plan takes the host about a microsecond
+    void* yk = k > 0 ? static_cast<void*>(ws_blk + bp.off_q) : nullptr;
 
     rc = check_select(x, B, h, w, D, k, idx_out, ws_sel, sel_bytes);
     if (rc) return rc;
-    rc = check_block(x, N, idx_out, B, k, dims, weights, k_cache, v_cache, L0, L_cap, yk, ws_blk, blk_bytes);
+    rc = check_block(x, N, idx_out, B, k, dims, weights, k_cache, v_cache, L0, L_cap, yk, ws_blk, blk_bytes,
+                     &bp);
     if (rc) return rc;
     rc = check_restore(yk, idx_out, rank, B, k, cache_map, hc, wc, h, w, D, y_out, nullptr, 0);
     if (rc) return rc;
@@ -590,7 +589,7 @@ int fastvar_step(const void* x, const int32_t* sched_h, const int32_t* sched_w, 
     // the step is the upsampled cache.
     const Fill fill{rank, cache_map, hc, wc, h, w, y_out};
     if (k > 0)
-        finish(enqueue_block(x, N, pruned ? idx_out : nullptr, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_out,
+        finish(enqueue_block(bp, x, N, pruned ? idx_out : nullptr, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_out,
                              ws_blk, st, true, true, &fill), st);
     else
         fv::launch_restore(nullptr, rank, B, k, cache_map, hc, wc, h, w, D, y_out, st);
@@ -632,7 +631,8 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h, const int32_t* sch
     int32_t* rank = reinterpret_cast<int32_t*>(base + sel_bytes);
     char* ws_blk = base + sel_bytes + rank_bytes;
     const size_t blk_bytes = ws_bytes - sel_bytes - rank_bytes;
-    void* yk = k > 0 ? static_cast<void*>(ws_blk + block_plan(dims, B, k).off_q) : nullptr;
+    const BlockPlan bp = block_plan(dims, B, k);   // once: a plan takes the host about a microsecond
+    void* yk = k > 0 ? static_cast<void*>(ws_blk + bp.off_q) : nullptr;
 
     // Every layer is checked before the first launch.  Output of layer l: its own cache map at the
     // capture step (the next layer reads it from there), else tmp / y_out alternating so that the last
@@ -650,12 +650,12 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h, const int32_t* sch
         if (!aligned16(dst) || dst == x) return FASTVAR_EINVAL;
         if (dense) {
             rc = check_block(src, N, nullptr, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk,
-                             blk_bytes);
+                             blk_bytes, &bp);
         } else {
             rc = check_select(src, B, h, w, D, k, idx_out, ws_sel, sel_bytes);
             if (!rc)
                 rc = check_block(src, N, idx_out, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, yk,
-                                 ws_blk, blk_bytes);
+                                 ws_blk, blk_bytes, &bp);
             if (!rc) rc = check_restore(yk, idx_out, rank, B, k, ly.cache_map, hc, wc, h, w, D, dst, nullptr, 0);
         }
         if (rc) return rc;
@@ -669,7 +669,7 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h, const int32_t* sch
         const void* src = l == 0 ? x : dst_of(l - 1);
         void* dst = dst_of(l);
         if (dense) {
-            left = enqueue_block(src, N, nullptr, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk,
+            left = enqueue_block(bp, src, N, nullptr, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst, ws_blk,
                                  st, l == 0, false, nullptr, nullptr, left, n_layers > 1);
         } else {
             fv::launch_select(src, B, N, D, k, idx_out, k > 0 ? rank : nullptr, nullptr, ws_sel, sp, st);
@@ -677,7 +677,7 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h, const int32_t* sch
             // restoration rides in the block's first launch (pruned rows) and its last (kept rows)
             const Fill fill{rank, ly.cache_map, hc, wc, h, w, dst};
             if (k > 0) {
-                finish(enqueue_block(src, N, idx_out, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst,
+                finish(enqueue_block(bp, src, N, idx_out, B, k, dims, ly.weights, ly.k_cache, ly.v_cache, L0, L_cap, dst,
                                      ws_blk, st, l == 0, true, &fill, nullptr, {}, n_layers > 1), st);
             } else {
                 fv::launch_restore(nullptr, rank, B, k, ly.cache_map, hc, wc, h, w, D, dst, st);
@@ -746,7 +746,7 @@ int fastvar_attn_forward_pruned(const void* x, int N, const int32_t* idx, int B,
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    finish(enqueue_attn(x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, h_kept_out, ws, st, true, false, nullptr,
+    finish(enqueue_attn(block_plan(dims, B, k), x, N, idx, B, k, dims, weights, k_cache, v_cache, L0, L_cap, h_kept_out, ws, st, true, false, nullptr,
                         nullptr, {}, false, false), st);
     return launch_status();
 }
@@ -758,7 +758,7 @@ int fastvar_ffn_forward_pruned(const void* x, int N, const int32_t* idx, int B, 
     if (rc) return rc;
     if (k == 0) return FASTVAR_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    finish(enqueue_ffn(x, N, idx, B, k, dims, weights, y_kept_out, ws, st, true), st);
+    finish(enqueue_ffn(block_plan(dims, B, k), x, N, idx, B, k, dims, weights, y_kept_out, ws, st, true), st);
     return launch_status();
 }
 
@@ -793,13 +793,14 @@ int fastvar_step_sublayer(const void* x, const int32_t* sched_h, const int32_t* 
     char* ws_blk = base + sel_bytes + rank_bytes;
     const size_t blk_bytes = ws_bytes - sel_bytes - rank_bytes;
     // Kept outputs of either half go to the h1 buffer of its own plan (neither half uses it).
-    void* hk = k_attn > 0 ? static_cast<void*>(ws_blk + block_plan(dims, B, k_attn).off_h1) : nullptr;
-    void* yk = k_ffn > 0 ? static_cast<void*>(ws_blk + block_plan(dims, B, k_ffn).off_h1) : nullptr;
+    const BlockPlan bp_a = block_plan(dims, B, k_attn), bp_f = block_plan(dims, B, k_ffn);
+    void* hk = k_attn > 0 ? static_cast<void*>(ws_blk + bp_a.off_h1) : nullptr;
+    void* yk = k_ffn > 0 ? static_cast<void*>(ws_blk + bp_f.off_h1) : nullptr;
 
     rc = check_select(x, B, h, w, D, k_attn, idx_attn_out, ws_sel, sel_bytes);
     if (rc) return rc;
     rc = check_block(x, N, idx_attn_out, B, k_attn, dims, weights, k_cache, v_cache, L0, L_cap, hk, ws_blk,
-                     blk_bytes);
+                     blk_bytes, &bp_a);
     if (rc) return rc;
     rc = check_restore(hk, idx_attn_out, rank, B, k_attn, cache_map_attn, hc, wc, h, w, D, x_mid, nullptr, 0);
     if (rc) return rc;
@@ -818,7 +819,7 @@ int fastvar_step_sublayer(const void* x, const int32_t* sched_h, const int32_t* 
     // each half's restoration rides in its own gather launch (pruned rows) and last GEMM (kept rows)
     const Fill fill_a{rank, cache_map_attn, hc, wc, h, w, x_mid};
     if (k_attn > 0)
-        finish(enqueue_attn(x, N, pruned_a ? idx_attn_out : nullptr, B, k_attn, dims, weights, k_cache, v_cache, L0,
+        finish(enqueue_attn(bp_a, x, N, pruned_a ? idx_attn_out : nullptr, B, k_attn, dims, weights, k_cache, v_cache, L0,
                             L_cap, x_mid, ws_blk, st, true, true, &fill_a, nullptr, {}, false, k_ffn > 0), st);
     else
         fv::launch_restore(nullptr, rank, B, k_attn, cache_map_attn, hc, wc, h, w, D, x_mid, st);
@@ -826,7 +827,7 @@ int fastvar_step_sublayer(const void* x, const int32_t* sched_h, const int32_t* 
     const Fill fill_f{rank, cache_map_ffn, hc, wc, h, w, y_out};
     if (k_ffn > 0)
         // (the halves lay the scratch out for their own k: its counters are cleared again)
-        finish(enqueue_ffn(x_mid, N, pruned_f ? idx_ffn_out : nullptr, B, k_ffn, dims, weights, y_out, ws_blk, st, true,
+        finish(enqueue_ffn(bp_f, x_mid, N, pruned_f ? idx_ffn_out : nullptr, B, k_ffn, dims, weights, y_out, ws_blk, st, true,
                            pruned_f, &fill_f), st);
     else
         fv::launch_restore(nullptr, rank, B, k_ffn, cache_map_ffn, hc, wc, h, w, D, y_out, st);

@@ -679,12 +679,9 @@ void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream) {
     p.tiles_m = p.tiles_n = 0;
     p.splits = 1;
     p.slices = static_cast<float*>(a.slice_ws);
-    if (a.slice_ws && epi == EPI_BIAS_RES) {
-        const SplitKPlan sk = residual_product_plan(a.M, a.N, a.K, a.meet);
-        if (sk.splits > 1) {
-            launch_sliced(sk, p, stream);
-            return;
-        }
+    if (epi == EPI_BIAS_RES && a.slices.splits > 1) {
+        launch_sliced(a.slices, p, stream);
+        return;
     }
     switch (epi) {
         case EPI_QKV:

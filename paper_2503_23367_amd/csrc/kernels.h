@@ -104,11 +104,11 @@ struct GemmArgs {
     const float* rope_sin = nullptr;
     const int32_t* rope_rows = nullptr;
     int rope_N = 0;
-    // Optional scratch for the slices of a split K (EPI_BIAS_RES; residual_product_plan says whether there are any and how
-    // large they are).  Split, the launch leaves its slices there and touches neither `out` nor `residual`: the
-    // launch of a SliceSum has to follow.
+    // Optional scratch of a block's products, and how K is cut (EPI_BIAS_RES; residual_product_plan, which also says how much of the
+    // scratch it takes).  Cut, the launch leaves its slices there and touches neither `out` nor `residual`: the launch of a
+    // SliceSum has to follow.
     void* slice_ws = nullptr;
-    SlicesMeet meet = MEET_IN_LAUNCH;
+    SplitKPlan slices;
     // Optional (EPI_QKV, EPI_BIAS_GELU; only where few_rows_layernorm says so): the rows of A are normalised on
     // the way in, and the call's arrival counters cleared, as the LayerNorm launch this replaces would.
     const void* ln_g = nullptr;
@@ -121,8 +121,8 @@ void launch_gemm(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream);
 // GEMMs of few rows (skinny.hip); launch_gemm routes there what few_rows_product (launch_math.h) gives it.
 void launch_gemm_skinny(GemmEpilogue epi, const GemmArgs& a, hipStream_t stream);
 
-// The plan that launch_gemm follows for an out-proj or FC2 product (EPI_BIAS_RES): gemm_splitk_plan, and no slices where a tuning
-// build forces a tile.
+// The plan of an out-proj or FC2 product (EPI_BIAS_RES) for GemmArgs: gemm_splitk_plan, and no slices where a tuning build forces
+// a tile.
 SplitKPlan residual_product_plan(int M, int N, int K, SlicesMeet meet);
 // What is left of a split product: out[row] = sum of the slices, in slice order, + residual (the bias is in the first slice).
 struct SliceSum {
