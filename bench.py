@@ -154,7 +154,9 @@ def kernel_table(wl, st, iters, block_ms, only=None):
     untimed step does not have; it is taken out again: the difference between the sum of the stage
     times and the untimed step's time per block (`block_ms`), spread evenly over the stages.  `ms_back_to_back`: the same launch through the component entry points, repeated
     back to back (operands cache resident; the stand-alone restore also copies the kept rows, which
-    inside the step the last GEMM writes in place)."""
+    inside the step the last GEMM writes in place).  Work and bytes are those of the named operation.  For few rows (up to
+    about 1500 at 2048 columns) out-proj and FC2 leave slices of K that the next launch adds up: the LayerNorm stages of
+    such a step hold that sum, its traffic and the residual too, and look slower than their bytes, the two products faster."""
     import torch
     from paper_2503_23367_amd import binding as fb
     dims = wl.dims

@@ -327,16 +327,19 @@ int fastvar_scale_step(const void* x, const int32_t* sched_h /* host */, const i
                        void* y_out, void* tmp, int32_t* idx_out,
                        void* ws, size_t ws_bytes, void* stream);
 
-/* Stages of a block inside the step entry points, for fastvar_scale_step_timed. */
+/* Stages of a block inside the step entry points, for fastvar_scale_step_timed.  Where the K of an out-proj or FC2
+ * product is cut into slices (few rows: up to about 1500 at 2048 columns), the launch leaves fp32 sums, and the
+ * launch that follows adds them up, with the residual: that part of PROJ is then in LN2, that of FC2 in the next
+ * block's LN1 (every token kept) or in FC2, as a second launch (the last block; pruned steps). */
 enum {
     FASTVAR_STAGE_SELECT = 0,    /* column sums, scores, top-k */
-    FASTVAR_STAGE_LN1 = 1,       /* gather + LayerNorm 1 */
+    FASTVAR_STAGE_LN1 = 1,       /* gather + LayerNorm 1 (+ the sum and residual of the block before, see above) */
     FASTVAR_STAGE_QKV = 2,       /* QKV GEMM + cache append */
     FASTVAR_STAGE_ATTENTION = 3,
-    FASTVAR_STAGE_PROJ = 4,      /* output projection + residual */
-    FASTVAR_STAGE_LN2 = 5,
+    FASTVAR_STAGE_PROJ = 4,      /* output projection + residual (sliced: see above) */
+    FASTVAR_STAGE_LN2 = 5,       /* LayerNorm 2 (sliced: PROJ's sum and residual too) */
     FASTVAR_STAGE_FC1 = 6,       /* FC1 + GELU */
-    FASTVAR_STAGE_FC2 = 7,       /* FC2 + residual */
+    FASTVAR_STAGE_FC2 = 7,       /* FC2 + residual (sliced: see above) */
     FASTVAR_STAGE_RESTORE = 8,
     FASTVAR_N_STAGES = 9
 };

@@ -257,8 +257,9 @@ FV_HOST_DEVICE AheadList ahead_list(int D, int F, int M, bool in_stack, bool ffn
 }
 
 // How much of a list of matrices (bytes[0], bytes[1], ..., in the order they are read) a launch of about `us` microseconds
-// fetches ahead on its `idle` CUs, and on how many of them.  Whole matrices, as many as come in while the launch runs: 45 KB a
-// microsecond and CU, 5.6 MB for the chip.  No more CUs than that takes: the launch's own loads wait behind the others.
+// fetches ahead on its `idle` CUs, and on how many of them.  Whole matrices, as many as pay: 45 KB a microsecond and
+// CU, 5.6 MB for the chip (fitted, not a bandwidth: a CU pulls in about 37, and what is still on its way when the launch
+// ends arrives while the next one starts).  No more CUs than that takes: the launch's own loads wait behind the others.
 // `cut`: products of few rows, whose columns are streamed by workgroups on their own, also gain from the first part of a matrix;
 // their launches are short, so less of it and from more CUs.  Eight blocks of the large model, without / with, us: one row
 // 327 / 318, 64 rows 473 / 450, 256 rows 707 / 675, 576 rows 1063 / 1005; one matrix more than this takes or one less: 64 rows

@@ -1,7 +1,8 @@
 // Weights that a later product of the call reads, brought into the memory-side cache by workgroups of a launch that leaves CUs
 // idle.  A product of a few hundred rows waits for its weights: a CU pulls in about 37 bytes a nanosecond of what comes
-// from memory and more of what the cache behind the L2s holds.  With the weights there (us, from memory / from the
-// cache): 256 x 6144 x 2048 16.6 / 12.6, FC2 of 256 and 576 rows 20 / 15.5, 30 / 25.  Half of a matrix is worth nothing to the tiled products,
+// from memory and more of what the cache behind the L2s holds.  With the weights there a product alone takes (us, from memory / from the
+// cache) 256 x 2048 x 8192 20 / 15.5, 576 x 2048 x 8192 30 / 25; inside eight blocks FC2 of 256 rows takes 18.1.  The launch
+// that fetches pays for it (24x24 25.5 -> 29.0 us, 18.2 -> 19.9 in a sub-layer step).  Half of a matrix is worth nothing to the tiled products,
 // whose slowest workgroups set the time, so they are fetched whole or not at all.
 #pragma once
 

@@ -111,9 +111,8 @@ CASES = [
     ("tiny128_keep_all_tile_edges", TINY128, 1, 16, 16, 256, 128, 384),
     ("d30_s24_b2", synth.D30, 2, 24, 24, 346, 640, 992),
     ("inf2b_s40_keep0.6", synth.INF2B, 1, 40, 40, 960, 2521, 3488),
-    # few rows at the large model's widths: every GEMM splits K between workgroups, with 64x64 tiles up
-    # to 64 rows and 128x128 tiles above; the four GEMMs of a block have different tile counts and share
-    # one scratch area (counters and partial tiles)
+    # few rows at the large model's widths: out-proj and FC2 leave slices of K in one scratch area, on tiles and in numbers that
+    # follow the rows
     ("inf2b_side1", synth.INF2B, 1, 1, 1, 1, 0, 8),
     ("inf2b_side6_keep_all", synth.INF2B, 1, 6, 6, 36, 21, 64),
     ("inf2b_side8_keep_all", synth.INF2B, 1, 8, 8, 64, 57, 128),

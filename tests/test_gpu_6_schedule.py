@@ -228,10 +228,10 @@ def test_stack_equals_single_block_calls_at_the_headline_size():
 
 @pytest.mark.parametrize("side", [2, 4, 5, 8, 12, 24])
 def test_structure_steps_of_the_large_model_across_layers(side):
-    """Structure steps of the 2B-class model.  From 25 rows on (side 5) GEMMs split K between workgroups, and the
-    GEMMs of a block (different tile counts) and the blocks of the stack reuse one scratch area whose arrival
-    counters are cleared once per call; of 16 rows (side 4) FC2 alone does, after products that split nothing
-    and carry the LayerNorm that clears the counters; of 4 rows (side 2) none does.  Three blocks through fastvar_scale_step must give the bits
+    """Structure steps of the 2B-class model.  From 25 rows on (side 5) out-proj and FC2 leave slices of K in one scratch
+    area, for the LayerNorm of the rows to add up: of their own block, or of the next one in the stack (the last block's
+    FC2 has a launch for it); of 16 rows (side 4) FC2 alone does, and what follows normalises its rows itself; of 4
+    rows (side 2) none does.  Three blocks through fastvar_scale_step must give the bits
     of three single-block calls; the first block is also checked against the oracle."""
     dims = synth.INF2B
     B, N, n_layers = 1, side * side, 3
@@ -413,11 +413,11 @@ def _two_block_case(case):
                                   "s48_fc2_two_k_slices"])
 def test_same_inputs_give_the_same_bits_every_run(case):
     """Same inputs, same bits: the stack step run 20 times.  The headline step merges two key ranges per
-    query tile in its attention; the keep 0.25 step three; the structure step (144 tokens at the large
-    model's widths) splits K between workgroups in all four GEMMs; the 48x48 step at keep 0.5 runs FC2 on
-    two K slices of 256x128 tiles whose last arriver waits for the other's partial tile.  All of them let the workgroup that
-    arrives last combine the partial results, so a result that depended on arrival order, or a partial
-    result read before it was complete, would show here as a changed bit.  Stops at the first difference."""
+    query tile in its attention; the keep 0.25 step three: there the workgroup that arrives last combines the partial
+    results.  The structure step (144 tokens at the large model's widths) cuts the K of out-proj and FC2 into slices, the
+    48x48 step at keep 0.5 that of FC2: slices are left in scratch, and the launch that follows adds them up in slice order.  A
+    result that depended on arrival order, or a partial result or slice read before it was complete, would show here as a
+    changed bit.  Stops at the first difference."""
     c = _two_block_case(case)
     print(f"[determinism] {case}: N={c['N']} k={c['k']} L0={c['L0']}, 2 blocks, 20 runs", flush=True)
     first = None
