@@ -17,7 +17,8 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libfastvar.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["fastvar_api.hip", "select.hip", "restore.hip", "layernorm.hip", "rope.hip", "gemm.hip", "skinny.hip",
+SOURCES = ["fastvar_api.hip", "select.hip", "restore.hip", "layernorm.hip", "rope.hip", "gemm.hip", "gemm_qkv.hip",
+           "gemm_rope.hip", "gemm_residual.hip", "gemm_gelu.hip", "gemm_sliced.hip", "skinny.hip",
            "attention.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

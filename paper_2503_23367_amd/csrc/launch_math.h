@@ -85,21 +85,13 @@ FV_HOST_DEVICE bool few_rows_layernorm(int M, int N, int K) {
     return K <= kFewRowsRound && few_rows_product(M, N, K, false);
 }
 
-// Tile choice.  What the measurements on the block's shapes say (inside the running step):
-//  * what a tile's loads need is time to land.  A ring refilled during the tile after the hand-over gives them
-//    STAGES-2 tiles and a fraction: nothing to speak of with two stages, which is all that 256x256 and 256x192
-//    tiles fit into 160 KB.  Those rings are therefore refilled at the hand-over itself (one whole tile ahead:
-//    256x192 at 2048 rows 60 -> 52 us, 256x256 68 -> 61 us); rings of three and four stages, which have the
-//    time anyway, lose 3-5 % to the burst of loads at the hand-over and keep the spread refill.
-//  * 256x128 tiles with eight waves of 64x64 and three stages are as fast per output element as the wide tiles
-//    and twice as fine grained; the same tile with two stages and the spread refill, or with 32-wide K tiles in
-//    four or six stages (twice the hand-overs), is 20-25 % slower; 128x128 with 128-wide K tiles in two stages
-//    20 % slower than with 64-wide ones in four.
-//  * 256x256 (QKV: 256x192, N = 3D divides evenly) wins where its tiles fill whole rounds of the 256 CUs, as
-//    at 2048 kept tokens; 128x128 tiles with eight waves of 64x32 and four stages where the wide tiles would
-//    leave CUs idle (N = D: out-proj, FC2).  Between them the tile count decides: 192x128 (eight waves of 96x32, three stages;
-//    four of 96x64 take 5-7 % longer: 960 x 6144 x 2048 29.5 -> 27.6 us), 160x128 (four waves of 160x32, four stages: 2300 x 2048 x
-//    8192 is 240 such tiles, the 2300-row step 438 -> 428) and 192x256 (two stages: 1152 x 8192 x 2048 52.9 -> 46.1).
+// Tile choice.  What the measurements on the block's shapes say:
+//  * large products are limited by power and by what a tile's waves read from LDS: tiles of 160x128 and up on four waves, one a SIMD,
+//    with the main loop's order written down (wide tiles in gemm_tiles.h).  Of the eight-wave tiles 128x128, 192x128 and 256x128 are
+//    left: as fast up to there, and their epilogues, two waves a SIMD, are shorter.
+//  * what is left is how evenly the tiles fill rounds of 256 workgroups; hence the many shapes.  The best of them beat the best of the
+//    seven shapes before (all on 32x32x16 instructions) by 9 % on average over 691 products; the picks by 8 %: 2048 x 8192 x 2048 61.9 -> 56.6 us,
+//    8192 x 2048 x 8192 222 -> 194, 2300 x 7680 x 1920 75 -> 65, 1200 x 7680 x 1920 48 -> 37, 2300 x 2048 x 8192 82.6 -> 73.2.
 //  * a part-filled last round costs less than a full one (fewer workgroups share the memory system and the
 //    power budget).
 //  * shapes that give at most 128 tiles of 128x128 (few rows) are bound by what a CU pulls in (about 37 bytes a
@@ -114,13 +106,16 @@ FV_HOST_DEVICE bool few_rows_layernorm(int M, int N, int K) {
 //    (545 x 1024 x 1024 6.5 / 7.1 us, 350 x 2048 x 2048 9.1 / 9.9), and of K above 1024 2 to 8 % less with weights from memory
 //    (68 x 5760 x 1920 12.5 / 11.5, 142 x 4096 x 4096 20.8 / 18.4): for QKV, whose weights no launch fetches ahead.
 // Beyond 128 tiles the choice is the candidate with the least modelled time (us): 2.05 to launch, and for every round of its
-// workgroups, a part-filled one counting 0.777 + 0.189 * fill, fix + K tiles * per_kt, where a K tile beyond the 32nd takes
+// workgroups, a part-filled one counting 0.684 + 0.311 * fill, fix + K tiles * per_kt, where a K tile beyond the 32nd takes
 // `longer` more; tile counts that do not divide by eight are not dealt to the XCDs in contiguous runs, and cost 4 % more, with
-// three, five or seven tile rows 10 % (there consecutive tiles of every XCD share neither operand).  The constants are a fit to 960
-// products (seven models' four products and generic ones; 100 to 16000 rows, K 64 to 16384; weights from memory and from the
-// cache) under each candidate, by the time that the picks lose: 0.4 % on the best candidate of every shape.  A fit to fifteen
-// workloads' products alone, short of K and of tile counts, cost 3 % more: 4242 x 6912 x 2304 153.1 us on 192x128 tiles, 139.3 on
-// 256x128; 3309 x 4096 x 16384 453 on 160x128, 392 on 256x256; 320 x 6336 x 192 14.9 on 192x256, 7.4 on 128x128.
+// three, five or seven tile rows 6 %.  The constants are a fit to 691 products (eight models' four products and generic ones; 65 to
+// 16000 rows, N 128 to 24576, K 64 to 16384; weights from memory and from the cache) under each candidate, by the time that the picks
+// lose: 1.3 % on the best of fifteen wide shapes and six others, of which these cost 0.7 % to have left out.
+enum Tile {   // (of gemm_tiles.h)
+    TILE_64x32 = 18, TILE_64x64 = 16, TILE_64x64_DEEP = 15, TILE_128x64 = 17, TILE_128x128 = 40, TILE_160x128 = 35, TILE_192x128 = 34,
+    TILE_192x192 = 14, TILE_192x256 = 13, TILE_224x128 = 36, TILE_224x192 = 37, TILE_224x256 = 38, TILE_256x128 = 32, TILE_256x192 = 12,
+    TILE_256x256 = 11
+};
 struct TileChoice {
     int cfg;
     double us;   // modelled
@@ -137,25 +132,29 @@ FV_HOST_DEVICE TileChoice gemm_choose_tile(bool qkv, int M, int N, int K) {
     const int KT = K / 64;
     struct Cand { int cfg, bm, bn, slots; double fix, per_kt, longer; };
     const Cand cands[] = {
-        {18, 64, 32, 256, 2.1, 0.170, 0.0},        // the first three by the rules above, their times for the K slices below
-        {qkv && KT > 16 ? 15 : 16, 64, 64, 512, 2.7, 0.270, 0.0},
-        {17, 128, 64, 256, 3.4, 0.335, 0.0},
-        {qkv ? 12 : 11, 256, qkv ? 192 : 256, 256, qkv ? 4.73 : 7.18, qkv ? 1.231 : 1.469, qkv ? -0.033 : -0.030},
-        {32, 256, 128, 256, 4.81, 0.779, -0.042},
-        {34, 192, 128, 256, 3.2, 0.660, -0.024},
-        {35, 160, 128, 256, 3.9, 0.654, -0.087},
-        {13, 192, 256, 256, 5.92, 1.239, -0.060},
-        {40, 128, 128, 256, 2.58, 0.526, -0.066},
-        {6, 128, 128, 512, 3.43, 1.001, -0.073},    // two workgroups per CU share its time
+        {TILE_64x32, 64, 32, 256, 2.1, 0.170, 0.0},        // the first three by the rules above, their times for the K slices below
+        {qkv && KT > 16 ? TILE_64x64_DEEP : TILE_64x64, 64, 64, 512, 2.7, 0.270, 0.0},
+        {TILE_128x64, 128, 64, 256, 3.4, 0.335, 0.0},
+        {TILE_128x128, 128, 128, 256, 3.33, 0.500, -0.023},
+        {TILE_160x128, 160, 128, 256, 4.50, 0.582, -0.016},
+        {TILE_192x128, 192, 128, 256, 3.94, 0.670, -0.002},
+        {TILE_192x192, 192, 192, 256, 6.51, 0.891, -0.048},
+        {TILE_192x256, 192, 256, 256, 9.22, 1.076, -0.045},
+        {TILE_224x128, 224, 128, 256, 6.42, 0.689, -0.021},
+        {TILE_224x192, 224, 192, 256, 8.80, 0.938, -0.027},
+        {TILE_224x256, 224, 256, 256, 10.46, 1.251, -0.018},
+        {TILE_256x128, 256, 128, 256, 5.15, 0.864, 0.008},
+        {TILE_256x192, 256, 192, 256, 8.69, 1.055, -0.013},
+        {TILE_256x256, 256, 256, 256, 11.57, 1.367, 0.034},
     };
     int from = 3, to = (int)(sizeof(cands) / sizeof(cands[0]));
     if (tiles128 <= 64) from = (long)((M + 63) / 64) * ((N + 31) / 32) <= 256 && KT > 4 ? 0 : 1;
     else if (tiles128 <= 128) from = 2;
     if (from < 3) to = from + 1;
-    TileChoice best{6, 1e30};
+    TileChoice best{TILE_128x128, 1e30};
     for (int i = from; i < to; ++i) {
         const Cand& c = cands[i];
-        const double rounds = tile_rounds(M, N, c.bm, c.bn, c.slots, 1, 0.777, 0.189, 0.037, 0.10);
+        const double rounds = tile_rounds(M, N, c.bm, c.bn, c.slots, 1, 0.684, 0.311, 0.041, 0.062);
         const double t = 2.05 + rounds * (c.fix + KT * c.per_kt + (KT > 32 ? (KT - 32) * c.longer : 0.0));
         if (t < best.us) best = TileChoice{c.cfg, t};
     }
@@ -188,8 +187,9 @@ FV_HOST_DEVICE SplitKPlan gemm_splitk_plan(int M, int N, int K, SlicesMeet meet)
     SplitKPlan best;
     if (few_rows_product(M, N, K, few_rows_tiled_splits(N, K))) return best;   // skinny.hip
     struct Cand { int cfg, bm, bn, max_splits; double fix, per_kt; };
-    const Cand cands[] = {{16, 64, 64, 8, 0.94, 0.244}, {17, 128, 64, 4, 2.07, 0.293}, {40, 128, 128, 4, 1.5, 0.492},
-                          {35, 160, 128, 2, 2.43, 0.555}, {34, 192, 128, 4, 1.55, 0.638}};
+    const Cand cands[] = {{TILE_64x64, 64, 64, 8, 0.94, 0.244}, {TILE_128x64, 128, 64, 4, 2.07, 0.293},
+                          {TILE_128x128, 128, 128, 4, 1.5, 0.492}, {TILE_160x128, 160, 128, 2, 2.43, 0.555},
+                          {TILE_192x128, 192, 128, 4, 1.55, 0.638}};
     const int KT = K / 64;
     double least = gemm_choose_tile(false, M, N, K).us;
     for (const Cand& c : cands)

@@ -164,7 +164,7 @@ def test_tiles_are_not_the_ones_measured_slower(math):
     for M in (17, 64, 65, 191, 193, 1000, 4097, 33000, 87381):
         for N in (8, 64, 1344, 6144, 24576, 32768):
             for K in (64, 448, 2048, 2112, 8192, 32768):
-                assert math.tile(0, M, N, K) in TILES and math.tile(1, M, N, K) in {12, 15, *TILES} - {11}, (M, N, K)
+                assert math.tile(0, M, N, K) in TILES and math.tile(1, M, N, K) in {15, *TILES}, (M, N, K)
 
 
 LAYERNORM, EITHER, LAUNCH = 0, 1, 2   # SlicesMeet
