@@ -131,6 +131,15 @@ __device__ __forceinline__ void layernorm_values(const uint4 (&raw)[CH], int D, 
     }
 }
 
+// 64 x 16 bytes from base + a lane's byte offset into 1 KB of LDS (lane l at lds + 16 l), through inline assembly: the compiler's own
+// model of this instruction makes it drain every outstanding LDS operation before the next operand use, which would
+// serialise the operand reads behind it.  Completion is tracked by hand (vmcnt before the barrier that publishes a tile).
+__device__ __forceinline__ void load16_to_lds(const void* base, uint32_t offset, uint32_t lds) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(offset), "s"(base) : "memory", "m0");
+#endif
+}
+
 // Compile-time loop: f(integral_constant<int, I>) for I in [Begin, End).
 // Used where an accumulator array must only ever be indexed by constants.
 template <int Begin, int End, class F>

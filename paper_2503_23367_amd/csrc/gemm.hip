@@ -4,15 +4,6 @@
 namespace fv {
 
 SplitKPlan residual_product_plan(int M, int N, int K, SlicesMeet meet) {
-#ifdef FASTVAR_DEV_KNOBS
-    if (const char* e = getenv("FASTVAR_SLICES")) {   // "tile:slices" of the product with FASTVAR_SLICES_K columns
-        const char* k = getenv("FASTVAR_SLICES_K");
-        SplitKPlan q;
-        if ((!k || atoi(k) == K) && sscanf(e, "%d:%d", &q.cfg, &q.splits) == 2 && q.splits > 1 && K / 64 % q.splits == 0) q.bytes = (size_t)q.splits * M * N * 4;
-        else q.splits = 1;
-        return q;
-    }
-#endif
     return gemm_cfg_override(EPI_BIAS_RES) >= 0 ? SplitKPlan{} : gemm_splitk_plan(M, N, K, meet);
 }
 

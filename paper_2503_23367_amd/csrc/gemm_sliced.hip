@@ -10,11 +10,6 @@ void launch_tiles_sliced(const SplitKPlan& sk, GemmParams& p, hipStream_t stream
         case TILE_128x64: launch_cfg<128, 64, 64, 6, 4, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
         case TILE_192x128: launch_cfg<192, 128, 64, 3, 2, 4, 1, EPI_BIAS_RES, true>(p, stream); break;
         case TILE_160x128: launch_cfg<160, 128, 64, 4, 2, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
-#ifdef FASTVAR_DEV_KNOBS
-        case 108: launch_cfg<192, 128, 64, 4, 2, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
-        case 114: launch_cfg<128, 128, 64, 4, 2, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
-        case 116: launch_cfg<64, 64, 64, 4, 2, 2, 1, EPI_BIAS_RES, true>(p, stream); break;
-#endif
         default: launch_cfg<128, 128, 64, 4, 2, 4, 1, EPI_BIAS_RES, true>(p, stream); break;   // TILE_128x128
     }
 }

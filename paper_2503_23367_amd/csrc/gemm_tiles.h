@@ -91,15 +91,6 @@ __device__ __forceinline__ int swz(int row) {
     return CPR == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3);
 }
 
-// 64 x 16 bytes from base + a lane's byte offset into 1 KB of LDS (lane l at lds + 16 l), through inline assembly: the compiler's own
-// model of this instruction makes it drain every outstanding LDS operation before the next operand use, which would
-// serialise the operand reads behind it.  Completion is tracked by hand (vmcnt before the barrier that publishes a tile).
-__device__ __forceinline__ void load16_to_lds(const void* base, uint32_t offset, uint32_t lds) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(offset), "s"(base) : "memory", "m0");
-#endif
-}
-
 // Slots from one load to the next, at most four, such that a K tile's loads find a slot each: of its last k-step those behind the
 // hand-over, of the others all.
 constexpr int load_slots(int slots, int before, int ksteps, int loads) {
@@ -122,8 +113,8 @@ __device__ __forceinline__ f32x4_t mfma(const bf16x8_t& a, const bf16x8_t& b, co
 // mostly the LayerNorm that reads the rows anyway.  The slices meeting inside this launch instead (partial tiles through
 // memory, the last workgroup of a tile adding them up) cost every such product 3 to 8 us: FC2 of the large model at
 // 64 / 256 / 576 / 1152 rows 13.3 / 25.2 / 43.2 / 60.2 us that way, 9.9 / 20.2 / 29.7 / 51.6 this way.
-template <int EPI, int KG, bool SLICED>
-constexpr bool kPersistent = !SLICED && KG == 1 && is_qkv(EPI);
+template <int EPI, int KG, bool SLICED, int BM, int BN>
+constexpr bool kPersistent = !SLICED && KG == 1 && (is_qkv(EPI) || (EPI == EPI_BIAS_GELU && BM * BN >= 224 * 256));
 
 // Wide tiles: 2 x 2 waves, one a SIMD, of at least 64x64 each.  A wave of 128x128 reads a third less from LDS per operation than
 // one of 128x64, and has the registers for it (256 accumulators); nothing else hides its latencies, so the order of its
@@ -182,9 +173,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     // a workgroup's tiles stay in its XCD's run).  What that buys is the overlap at the seam: the next
     // tile's first stages are fetched while this tile's epilogue runs, which needs no LDS.  It pays for the
     // QKV epilogue, the longest (2-byte stores into the transposed V cache): 3-4 % of the launch at 3072 to
-    // 6552 rows; the other epilogues are short enough that the hardware's own hand-over from a finished
-    // workgroup to the next does as well (measured: +-2 %), so they keep one workgroup per tile.
-    constexpr bool PERSIST = kPersistent<EPI, KG, SLICED>;
+    // 6552 rows; and for GELU on the widest tiles, one wave a SIMD, whose epilogue nothing else overlaps: 4096 x 8192 x 2048
+    // 111.4 -> 109.7 us, 3280 x 7680 x 1920 102.9 -> 99.8, 16384 x 8192 x 2048 429 -> 416.  The others are short enough
+    // that the hardware's own hand-over from a finished workgroup to the next does as well (+-2 %, GELU on 192x192 and
+    // 224x192 +-1 %), so they keep one workgroup per tile.
+    constexpr bool PERSIST = kPersistent<EPI, KG, SLICED, BM, BN>;
     const int n_tiles = p.tiles_m * p.tiles_n;
     int m0, n0;
 #define FV_TILE_COORDS(vpid_)                                                                   \
@@ -769,7 +762,7 @@ void launch_cfg(GemmParams& p, hipStream_t stream) {
     // one round of workgroups when there are more tiles than the chip holds at a time (the kernel then walks
     // the rest itself); as many workgroups per CU as fit into its 160 KB of LDS
     int grid = p.tiles_m * p.tiles_n;
-    if (kPersistent<EPI, KG, SLICED>) {
+    if (kPersistent<EPI, KG, SLICED, BM, BN>) {
         constexpr int per_cu = (int)((160u << 10) / smem) > 0 ? (int)((160u << 10) / smem) : 1;
         const int slots = compute_units() * per_cu;
         if (grid > slots && slots % 8 == 0) grid = slots;
