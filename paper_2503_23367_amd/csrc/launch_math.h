@@ -52,6 +52,19 @@ FV_HOST_DEVICE FewRowsPlan few_rows_plan(int N, int K, bool layernorm) {
     return p;
 }
 
+// Columns of a workgroup of a product with a LayerNorm in front: of sixteen and twelve, what leaves the busiest CU fewer weights to pull in.
+// Eight blocks of the large model, whose QKV is 384 workgroups of sixteen and 512 of twelve, 1 / 16 rows 278.3 / 272.2, 368.7 / 363.5 us, of the 512 px
+// model 268.1 / 262.8 (one row).
+FV_HOST_DEVICE int few_rows_columns(int N) {
+    const auto busiest = [&](int cols) { return ((N + cols - 1) / cols + 255) / 256 * cols; };
+    return busiest(12) < busiest(16) ? 12 : 16;
+}
+// The rows of a product without a LayerNorm in front go through LDS where all of them fit beside the sums (us, weights from memory,
+// without / with: 1 / 4 / 8 rows of 2048 x 8192 10.7 / 8.2, 11.5 / 9.3, 12.1 / 10.4, of 1920 x 7680 10.4 / 7.8, 11.1 / 8.9, 11.9 / 9.9; 1 / 16 of 1024 x 4096 5.7 /
+// 4.9, 8.5 / 7.1, of 2048 x 2048 4.4 / 4.1, 5.7 / 4.9, of 448 x 2048 4.2 / 3.8, 5.5 / 4.6; nothing in it at 448 x 448).
+constexpr int kFewRowsLds = 128 << 10;
+FV_HOST_DEVICE bool few_rows_in_lds(int M, int K) { return (long)M * K * 2 <= kFewRowsLds; }
+
 // Which product takes M rows: this one, or the tiled one of gemm.hip (split_k: which can split this K between
 // workgroups).  Every workgroup reads the rows' operands again, so the gain falls with the rows and with the number of
 // workgroups; and a K of several rounds waits for memory once a round, for longest where the last round is part-filled.

@@ -19,7 +19,8 @@
 // groups 660 against 474 us: every workgroup reads the rows' operands from L2, and they no longer fit beside the
 // weights in registers), hence kFewRowsMax; launch_math.h says which shapes of up to 16 rows come here.
 //
-// CW = 16 fills the operand with 16 weight rows.  CW = 8 (outputs of few columns: out-proj, FC2) gives half of the
+// CW = 16 fills the operand with 16 weight rows; 12 leaves a quarter of it to repetitions of the last one, for the sake of how many
+// workgroups there are (few_rows_columns).  CW = 8 (outputs of few columns: out-proj, FC2) gives half of the
 // operand's rows to a second K half of the same eight columns, which doubles the number of workgroups: the matrix
 // instructions, one per half, waste half of their rows, and have the time.
 #include "common.h"
@@ -50,7 +51,9 @@ __device__ __forceinline__ void lds_barrier() {
 // U: turns a wave has in flight.  Turns past the end load the last one and are skipped by a wave-uniform branch around
 // the MFMA, not around the load: with loads in branches the compiler can no longer count what is in flight, and waits for all.
 // Results: lane l holds columns n0 + 4 q + 0..3 of token row r.
-template <int EPI, bool LN, int CW, int NW, int U>
+// ROWS (no LN): the rows' operands come from LDS, where the workgroup has laid all of the rows; without it every lane of a wave loads its
+// own, sixteen rows' worth whatever M is, and a product of one row over K = 8192 spent more of its time on those than on its weights.
+template <int EPI, bool LN, int CW, int NW, int U, bool ROWS = false>
 __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
     constexpr int KH = CW == 8 ? 2 : 1;               // K halves side by side in the weight operand
     __shared__ f32x4_t red[NW][64];
@@ -68,7 +71,7 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
     // this lane's weight row, and the turn its K half starts at
     const int wh = KH == 2 ? r >> 3 : 0;
     const bf16_t* const wrow = static_cast<const bf16_t*>(p.W) +
-                               (size_t)min(n0 + (KH == 2 ? (r & 7) : r), p.N - 1) * p.K + 16 * q;
+                               (size_t)min(n0 + (KH == 2 ? (r & 7) : min(r, CW - 1)), p.N - 1) * p.K + 16 * q;
     // (rows past M repeat the last one; their results are dropped)
     const bf16_t* const arow = static_cast<const bf16_t*>(p.A) + (size_t)min(r, p.M - 1) * p.K + 16 * q;
 
@@ -89,7 +92,7 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
     for (int h = 0; h < KH; ++h) acc[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     if constexpr (LN) {
-        static_assert(!LN || (CW == 16 && 2 * 8 * NW * U <= 64 * NW), "one K range; gain and shift fit where the sums go");
+        static_assert(!LN || (CW != 8 && 2 * 8 * NW * U <= 64 * NW), "one K range; gain and shift fit where the sums go");
         // The rows are normalised as a LayerNorm launch does it, by the same code: a wave has one or two of them, in
         // registers, and leaves them in LDS, where the waves find their operands (16 bytes of padding a row: the sixteen
         // rows of an operand in different banks).  So a row has the same bits here as with an index list, whose gather is
@@ -144,13 +147,34 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
                 for (int c = 0; c < 2; ++c) acc[0] = mfma16(w[i][c], a[i][c], acc[0]);
             }
     } else {
-        for (int base = 0; base < half; base += NW * U) {
+        extern __shared__ __attribute__((aligned(16))) u32x4_t chunks_s[];
+        const int cpr = p.K >> 3;                     // 16-byte chunks of a row
+        if constexpr (ROWS) {
+            // straight into LDS, 64 chunks a load; chunk c of row m at c ^ (m % 8), so that an operand's rows are in different banks
+            typedef __attribute__((address_space(3))) void* lds_ptr_t;
+            const int total = p.M * cpr;
+            for (int s0 = wave * 64; s0 < total; s0 += NW * 64) {
+                const int s = min(s0 + lane, total - 1), row = s / cpr, c = s - row * cpr;
+                load16_to_lds(p.A, (uint32_t)(row * cpr + (c ^ (row & 7))) * 16u, (uint32_t)(uintptr_t)(lds_ptr_t)(chunks_s + s0));
+            }
+        }
+        const int am = min(r, p.M - 1);
+        const u32x4_t* const achunk = chunks_s + am * cpr;
+        auto round = [&](int base, bool first) __attribute__((always_inline)) {
             u32x4_t w[U][2], a[U][KH][2];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < U; ++i) {
                 const int t = min(base + wave + NW * i, half - 1);
 #pragma unroll
                 for (int c = 0; c < 2; ++c) w[i][c] = load16(wrow + min(t + wh * half, turns - 1) * 64 + 8 * c);
+            }
+            if (ROWS && first) {
+                // loads return in order: all but the 2 U of the weights behind the rows
+                __builtin_amdgcn_sched_barrier(0);
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * U) : "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
             }
 #pragma unroll
             for (int i = 0; i < U; ++i) {
@@ -158,8 +182,11 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
 #pragma unroll
                 for (int h = 0; h < KH; ++h)
 #pragma unroll
-                    for (int c = 0; c < 2; ++c)
-                        a[i][h][c] = load16(arow + min(t + h * half, turns - 1) * 64 + 8 * c);
+                    for (int c = 0; c < 2; ++c) {
+                        const int turn = min(t + h * half, turns - 1);
+                        if constexpr (ROWS) a[i][h][c] = achunk[turn * 8 + ((2 * q + c) ^ (am & 7))];
+                        else a[i][h][c] = load16(arow + turn * 64 + 8 * c);
+                    }
             }
 #pragma unroll
             for (int i = 0; i < U; ++i) {
@@ -171,7 +198,9 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
                         for (int c = 0; c < 2; ++c) acc[h] = mfma16(w[i][c], a[i][h][c], acc[h]);
                     }
             }
-        }
+        };
+        round(0, true);
+        for (int base = NW * U; base < half; base += NW * U) round(base, false);
     }
 
     if (KH == 2) {
@@ -182,7 +211,7 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
     }
     red[wave][lane] = acc[0];
     __syncthreads();
-    if (wave != 0 || m >= p.M || (KH == 2 && q >= 2) || n >= p.N) return;
+    if (wave != 0 || m >= p.M || 4 * q >= CW || n >= p.N) return;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
     if (p.bias) { v[0] = bf16_lo(bias.x); v[1] = bf16_hi(bias.x); v[2] = bf16_lo(bias.y); v[3] = bf16_hi(bias.y); }
     f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
@@ -230,13 +259,19 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const GemmArgs p) {
 
 template <int EPI, bool LN, int CW, int NW, int U>
 void launch(const GemmArgs& a, hipStream_t st) {
-    size_t rows_bytes = 0;
+    const int grid = (a.N + CW - 1) / CW;
     if constexpr (LN) {   // sixteen rows of 2048 columns: 74 KB with the sums, two workgroups in a CU's 160 KB
-        rows_bytes = (size_t)a.M * (a.K + 8) * sizeof(bf16_t);
         static std::once_flag once;
         raise_lds_limit_once(once, &skinny_kernel<EPI, LN, CW, NW, U>, kFewRowsMax * (512 * U + 8) * sizeof(bf16_t));
+        skinny_kernel<EPI, LN, CW, NW, U><<<grid, 64 * NW, (size_t)a.M * (a.K + 8) * sizeof(bf16_t), st>>>(a);
+    } else if (few_rows_in_lds(a.M, a.K)) {
+        static std::once_flag once;
+        raise_lds_limit_once(once, &skinny_kernel<EPI, LN, CW, NW, U, true>, kFewRowsLds);
+        const size_t rows_bytes = ((size_t)a.M * a.K * sizeof(bf16_t) + 1023) / 1024 * 1024;   // whole loads
+        skinny_kernel<EPI, LN, CW, NW, U, true><<<grid, 64 * NW, rows_bytes, st>>>(a);
+    } else {
+        skinny_kernel<EPI, LN, CW, NW, U><<<grid, 64 * NW, 0, st>>>(a);
     }
-    skinny_kernel<EPI, LN, CW, NW, U><<<(a.N + CW - 1) / CW, 64 * NW, rows_bytes, st>>>(a);
 }
 
 template <int EPI, bool LN, int CW, int NW, int U>
@@ -251,7 +286,8 @@ void launch_epi(const GemmArgs& a, hipStream_t st) {
     constexpr int W = kFewRowsWaves, U = kFewRowsTurns;
     const FewRowsPlan p = few_rows_plan(a.N, a.K, EPI != EPI_BIAS_RES);
     if constexpr (EPI != EPI_BIAS_RES)
-        if (a.ln_g) return launch_turns<EPI, true, 16, W, U>(p.turns, a, st);
+        if (a.ln_g) return few_rows_columns(a.N) == 12 ? launch_turns<EPI, true, 12, W, U>(p.turns, a, st)
+                                                       : launch_turns<EPI, true, 16, W, U>(p.turns, a, st);
     if (p.cols == 16) launch_turns<EPI, false, 16, W, U>(p.turns, a, st);
     else if (p.waves == W) launch_turns<EPI, false, 8, W, U>(p.turns, a, st);
     else launch_turns<EPI, false, 8, 2 * W, U>(p.turns, a, st);

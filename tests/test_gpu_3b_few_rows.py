@@ -139,3 +139,17 @@ def test_few_rows_over_a_long_cache(dims, B, N):
 def test_rope_without_an_index_list(name, dims, B, h, w, L0):
     """A token's slot is its row within its sample; with the LayerNorm in front of the product and, at 2176 columns, not."""
     check_block_rope(name, dims, B, h, w, h * w, L0, (L0 + h * w + 7) // 8 * 8, seed=27)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 72, 64), (3, 72, 192), (5, 72, 576), (16, 72, 4096), (16, 72, 4160), (8, 72, 8192), (9, 72, 8192),
+                                   (1, 72, 65536), (1, 72, 65600)])
+def test_rows_through_lds(M, N, K):
+    """Rows that are not whole loads of 64 chunks, the most that LDS takes (128 KB) and one turn or row more, one of them in many
+    rounds of weights."""
+    test_gemm_few_rows(M, N, K, fb.EPI_BIAS_RES)
+
+
+@pytest.mark.parametrize("B,N", [(1, 1), (1, 16), (3, 5)])
+def test_workgroups_of_twelve_columns(B, N):
+    """4160 columns behind the LayerNorm: 347 workgroups of twelve, the last of eight."""
+    test_block_all_tokens_kept_without_an_index_list(synth.BlockDims(D=128, H=2, dh=64, F=4160), B, N, 6)
