@@ -57,15 +57,15 @@ void launch_tiles_residual(GemmParams& p, hipStream_t stream);
 void launch_tiles_gelu(GemmParams& p, hipStream_t stream);
 void launch_tiles_sliced(const SplitKPlan& sk, GemmParams& p, hipStream_t stream);
 
-// Tuning builds only (-DFASTV4_DEV_KNOBS, never the product library, which reads no environment and keeps
-// no state): FASTV4_GEMM_CFG (all epilogues) or FASTV4_GEMM_CFG<e> (epilogue e = 0, 1, 2) forces a tile
+// Tuning builds only (-DFASTVAR_DEV_KNOBS, never the product library, which reads no environment and keeps
+// no state): FASTVAR_GEMM_CFG (all epilogues) or FASTVAR_GEMM_CFG<e> (epilogue e = 0, 1, 2) forces a tile
 // configuration, unsliced; unset means gemm_choose_tile and gemm_splitk_plan.
 inline int gemm_cfg_override(int epi) {
-#ifdef FASTV4_DEV_KNOBS
+#ifdef FASTVAR_DEV_KNOBS
     char name[32];
-    snprintf(name, sizeof(name), "FASTV4_GEMM_CFG%d", epi);
+    snprintf(name, sizeof(name), "FASTVAR_GEMM_CFG%d", epi);
     const char* e = getenv(name);
-    if (!e) e = getenv("FASTV4_GEMM_CFG");
+    if (!e) e = getenv("FASTVAR_GEMM_CFG");
     return e ? atoi(e) : -1;
 #else
     (void)epi;

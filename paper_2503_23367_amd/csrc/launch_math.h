@@ -296,21 +296,30 @@ FV_HOST_DEVICE PrefetchPlan prefetch_plan(const long* bytes, int n, int idle, do
     return p;
 }
 
+// Consecutive workgroups go to the eight XCDs in turn, each with its own L2.  Workgroup `block` of the xcd_blocks(n) that walk a
+// map takes share xcd_share(block, n) of its n: an XCD has a contiguous run of them, so the rows of a cached map that neighbouring
+// rows are blended from are fetched into one L2 and not into all.  A share of n or more is nothing to do.  Under eight shares an XCD
+// the runs are too short to matter, and a large batch of small maps is not padded.
+constexpr int kXcdShares = 64;
+FV_HOST_DEVICE int xcd_blocks(int n) { return n < kXcdShares ? n : (n + 7) / 8 * 8; }
+FV_HOST_DEVICE int xcd_share(int block, int n) { return n < kXcdShares ? block : (block & 7) * ((n + 7) / 8) + (block >> 3); }
+
 // Rows that a wave of the restoration takes, of maps of `rows` tokens in all, w wide, D columns.  Rank, taps and store of a row
-// wait for one another, so a wave a row while the chip has room for them all (us, a pair unrolled / one: 16x16 x 1024 3.8 / 2.7,
-// 53x37 x 2048 6.4 / 5.0, 64x64 x 2048 8.5 / 7.4, 640 rows x 1920 5.8 / 5.2, 440 x 4096 8.9 / 5.7).  Maps of more rows than that
-// have a queue of waves either way, and a pair has two rows' loads in flight (81x82 x 448 7.2 / 8.0, 100x104 x 1024 10.7 / 12.5,
-// 84x88 x 2048 15.1 / 15.5), except where one row a wave puts the lines of the map, whose taps are the same, on one XCD, as widths in
-// multiples of sixteen, and within one of them, do, and rows are wide enough for that to count (80x80 x 2048 15.3 / 11.5, 88x96 x 1280 11.7 / 10.1; 72x80 x
-// 1024 5.9 / 6.5), and for rows of 4096 columns, which fill a wave by themselves (6510 rows 28.4 / 20.6).  Beyond 2^25 elements two rows, one after the
-// other (90000 x 1920 155 / 134, 128x128 x 2048 one row 22.2, two 21.7).
+// wait for one another, so a wave a row while the chip has room for them all (us, a pair unrolled / one: 16x16 x 1024 5.5 / 4.9,
+// 53x37 x 2048 8.4 / 6.0, 64x64 x 2048 9.0 / 8.1, 4 x 33x31 x 1920 10.6 / 8.6, 40x44 x 4096 14.4 / 9.4), wide rows for longer (73x67 x 2048
+// 12.1 / 10.9, 8 x 24x24 x 1920 12.8 / 11.1, 75x70 x 1920 12.0 / 11.1).  Maps of more rows than that have a queue of waves either way, and a pair
+// has two rows' loads in flight (81x82 x 448 5.6 / 6.2, 100x104 x 1024 11.7 / 11.9, 72x80 x 1024 7.4 / 7.7, 2 x 90x77 x 1920 23.6 / 24.6), except
+// of widths near a multiple of sixteen (117x95 x 2048 21.5 / 20.5, 80x80 x 2048 12.7 / 12.6), and of 4096 columns, which fill a wave by themselves
+// (62x105 23.3 / 21.9).  Beyond 2^25 elements two rows, one after the other (90x90 x 8192 a pair 54.4, one row 52.7, two 51.4; 8 x 100x100 x 1920
+// 154.6, 145.0, 144.7).  All with shares in contiguous runs; dealt in turn, these plans' times were 2x90x77 x 1920 29.7 us (23.6 in
+// runs), 100x120 x 4096 47.9 (39.6), 90x90 x 8192 68.4 (51.4), 40x44 x 4096 10.6 (9.4), 64x64 x 2048 8.3 (8.2).
 struct RestorePlan {
     int rows;
     bool pair;   // unrolled
 };
 FV_HOST_DEVICE RestorePlan restore_plan(long rows, int w, int D) {
     if (rows * D >= 1L << 25) return RestorePlan{2, false};
-    if (rows < 4300 || D >= 4096 || ((w + 1) % 16 <= 2 && D >= 1280)) return RestorePlan{1, false};
+    if (rows < 4300 || D >= 4096 || (D >= 1280 && (rows < 6000 || (w + 1) % 16 <= 2))) return RestorePlan{1, false};
     return RestorePlan{2, true};
 }
 

@@ -71,14 +71,14 @@ __global__ __launch_bounds__(256) void layernorm_rows_kernel(const bf16_t* __res
 }
 
 // The same launch with the restoration's fill behind it: workgroups [0, ln_blocks) normalise the kept rows,
-// the others walk the token rows of the restored map (eight per workgroup, two per wave) and write the
-// pruned ones (rank < 0) from the cached map; kept rows are left to the block's last GEMM.
+// the others walk the token rows of the restored map (one a wave, each XCD a contiguous run of them; ln_blocks is a multiple
+// of eight) and write the pruned ones (rank < 0) from the cached map; kept rows are left to the block's last GEMM.
 struct FillParams {
     const int32_t* rank;      // [B, N]
     const bf16_t* cache_map;  // [B, hc*wc, D]
     bf16_t* y_out;            // [B, N, D]
     int hc, wc, h, w;
-    int blocks_per_sample;
+    int shares;   // of a sample, a wave a row
 };
 constexpr int kFillRowsPerWave = 1;
 
@@ -95,9 +95,9 @@ __global__ __launch_bounds__(256) void gather_layernorm_fill_kernel(const bf16_t
         layernorm_row<CH>(in, idx, N, k, M, D, gamma, beta, eps, rows_out, out, blockIdx.x * 4 + (threadIdx.x >> 6));
         return;
     }
-    const int fb = blockIdx.x - ln_blocks;
-    const int b = fb / f.blocks_per_sample;
-    const int blk = fb - b * f.blocks_per_sample;
+    const int per_sample = xcd_blocks(f.shares), fb = blockIdx.x - ln_blocks;
+    const int b = fb / per_sample;
+    const int blk = xcd_share(fb - b * per_sample, f.shares);   // (past the end: so are its rows)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int rr = 0; rr < kFillRowsPerWave; ++rr) {
@@ -227,14 +227,14 @@ void launch_gather_layernorm_fill(const void* x, const int32_t* idx, int B, int 
                                   const void* cache_map, int hc, int wc, int h, int w, void* y_out,
                                   const ZeroCounters& zc, hipStream_t stream) {
     const int M = B * k;
-    const int ln_blocks = (M + 3) / 4;
+    const int ln_blocks = (M + 31) / 32 * 8;
     FillParams f;
     f.rank = rank;
     f.cache_map = static_cast<const bf16_t*>(cache_map);
     f.y_out = static_cast<bf16_t*>(y_out);
     f.hc = hc; f.wc = wc; f.h = h; f.w = w;
-    f.blocks_per_sample = (N + 4 * kFillRowsPerWave - 1) / (4 * kFillRowsPerWave);
-    const dim3 grid(ln_blocks + B * f.blocks_per_sample), block(kClearThreads);
+    f.shares = (N + 4 * kFillRowsPerWave - 1) / (4 * kFillRowsPerWave);
+    const dim3 grid(ln_blocks + B * xcd_blocks(f.shares)), block(kClearThreads);
     const int ch = (D + 511) / 512;
     const auto launch = [&](auto kernel) {
         kernel<<<grid, block, 0, stream>>>(static_cast<const bf16_t*>(x), idx, N, k, M, D,

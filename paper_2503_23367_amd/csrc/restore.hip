@@ -5,6 +5,7 @@
 // 16-byte loads and stores; HBM bound (writes N*D bf16 once).
 #include "common.h"
 #include "kernels.h"
+#include "launch_math.h"
 #include "resample.h"
 
 namespace fv {
@@ -27,22 +28,24 @@ __global__ __launch_bounds__(256) void rank_from_idx_kernel(const int32_t* __res
     rank[(size_t)b * N + n] = (lo < k && row[lo] == n) ? lo : -1;
 }
 
-// grid (ceil(N / (4*rows_per_wave)), B), block 256.  PAIR: two rows a wave, unrolled, so that the loads of both are in flight.
+// grid (xcd_blocks(shares), B), block 256: the shares of a sample, ceil(N / (4*rows_per_wave)), in contiguous runs to the XCDs (see
+// xcd_share).  PAIR: two rows a wave, unrolled, so that the loads of both are in flight.
 template <bool PAIR>
 __global__ __launch_bounds__(256) void restore_kernel(const bf16_t* __restrict__ y_kept,
                                                       const int32_t* __restrict__ rank, int k,
                                                       const bf16_t* __restrict__ cache_map, int hc, int wc,
                                                       int h, int w, int D, bf16_t* __restrict__ y_out,
-                                                      int rows_per_wave) {
+                                                      int rows_per_wave, int shares) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int b = blockIdx.y;
+    const int share = xcd_share(blockIdx.x, shares);   // (past the end: so are its rows)
     const int N = h * w;
     const int groups = (D + 511) >> 9;
     const int rows = PAIR ? 2 : rows_per_wave;
 #pragma unroll(PAIR ? 2 : 1)
     for (int rr = 0; rr < rows; ++rr) {
-        const int n = (blockIdx.x * 4 + wave) * rows + rr;
+        const int n = (share * 4 + wave) * rows + rr;
         if (n >= N) break;
         const int r = (k > 0) ? rank[(size_t)b * N + n] : -1;
         bf16_t* dst = y_out + ((size_t)b * N + n) * D;
@@ -111,10 +114,11 @@ void launch_restore(const void* y_kept, const int32_t* rank, int B, int k, const
                     int wc, int h, int w, int D, void* y_out, hipStream_t stream) {
     const int N = h * w;
     const RestorePlan plan = restore_plan((long)B * N, w, D);
-    const dim3 grid((N + 4 * plan.rows - 1) / (4 * plan.rows), B);
+    const int shares = (N + 4 * plan.rows - 1) / (4 * plan.rows);
+    const dim3 grid(xcd_blocks(shares), B);
     const auto launch = [&](auto* kernel) {
         kernel<<<grid, 256, 0, stream>>>(static_cast<const bf16_t*>(y_kept), rank, k, static_cast<const bf16_t*>(cache_map), hc,
-                                         wc, h, w, D, static_cast<bf16_t*>(y_out), plan.rows);
+                                         wc, h, w, D, static_cast<bf16_t*>(y_out), plan.rows, shares);
     };
     if (plan.pair) launch(&restore_kernel<true>);
     else launch(&restore_kernel<false>);

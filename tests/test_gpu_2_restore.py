@@ -94,6 +94,14 @@ def test_restore_two_rows_a_wave(B, hc, wc, h, w, D, k):
     check("pair", B, hc, wc, h, w, D, k, use_rank=True, seed=5)
 
 
+@pytest.mark.parametrize("B,h,w", [(3, 1, 3), (9, 1, 1), (2, 18, 14), (2, 11, 23), (3, 16, 16), (2, 257, 1), (1, 75, 70), (1, 80, 86)])
+def test_restore_shares_around_the_xcds(B, h, w):
+    """Workgroups in numbers that eight does and does not divide, samples that end inside one; the last two on both sides of where wide
+    rows go from one to two a wave."""
+    D = 1288 if h > 40 else 72
+    check("shares", B, max(1, h // 2), max(1, w // 2), h, w, D, h * w // 3, use_rank=True, seed=6)
+
+
 def test_restore_special_cases_exact():
     print("[restore] exact special cases", flush=True)
     # same size: identity on pruned slots; constant cache: constant; 2x of a bf16-exact ramp

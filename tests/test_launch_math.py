@@ -30,6 +30,8 @@ void plan(int N, int K, int layernorm, int* out) {
     out[3] = fv::few_rows_share(K, p.cols);
 }
 int few_rows(int M, int N, int K, int split_k) { return fv::few_rows_product(M, N, K, split_k); }
+int xcd_share(int block, int n) { return fv::xcd_share(block, n); }
+int xcd_blocks(int n) { return fv::xcd_blocks(n); }
 int column_chunks(int N, int D) { return fv::column_chunks(N, D); }
 void prefetch(const long* bytes, int n, int idle, double us, int cut, long* out) {
     const fv::PrefetchPlan p = fv::prefetch_plan(bytes, n, idle, us, cut);
@@ -243,6 +245,20 @@ def test_rows_of_a_restoring_wave(math):
         assert math.restore_rows(C.c_long(h * w), w, D) == 1, (h, w, D)
     for rows, w, D in [(128 * 128, 128, 2048), (90000, 300, 1920), (1 << 22, 2048, 8)]:
         assert math.restore_rows(C.c_long(rows), w, D) == 2, (rows, w, D)
+
+
+@pytest.mark.parametrize("n", list(range(1, 20)) + list(range(60, 75)) + [1000, 4097, 8192])
+def test_shares_of_the_xcds(math, n):
+    """Every share is taken once, by workgroups of one XCD for a contiguous run of them; what is left over is past the end."""
+    blocks = math.xcd_blocks(n)
+    share = [math.xcd_share(i, n) for i in range(blocks)]
+    assert sorted(share) == list(range(blocks)) and n <= blocks < n + 8
+    if n < 64:
+        assert blocks == n
+        return
+    assert blocks % 8 == 0
+    for xcd in range(8):
+        assert share[xcd::8] == list(range(xcd * (blocks // 8), (xcd + 1) * (blocks // 8)))
 
 
 def test_column_chunks_fit_the_scratch(math):
