@@ -234,11 +234,13 @@ void finish(const fv::SliceSum& s, hipStream_t st) {
 // `ffn_follows`: the call goes on to the MLP half, whose weights may be fetched ahead; a call that does not touches
 // none of them.
 // `whole`: the half is part of a whole block, whose other half's LayerNorm reads h1 next and adds its slices up.
+// `all_idx`: the index list of a selection that keeps every token is still to be written (`idx` is NULL); the LayerNorm's launch does
+// it on the side, which takes 4 us off such a step.
 fv::SliceSum enqueue_attn(const BlockPlan& bp, const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                   const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* h1_out, void* ws,
                   hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
                   const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false,
-                  bool ffn_follows = true, bool whole = false) {
+                  bool ffn_follows = true, bool whole = false, int32_t* all_idx = nullptr) {
     const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
     void* buf_a = base + bp.off_a;
@@ -260,7 +262,8 @@ fv::SliceSum enqueue_attn(const BlockPlan& bp, const void* x, int N, const int32
     else if (before.slices)
         fv::launch_slice_sum_layernorm(before, w->ln1_g, w->ln1_b, d->ln_eps, buf_a, st);
     else
-        fv::launch_layernorm(x, M, d->D, w->ln1_g, w->ln1_b, d->ln_eps, buf_a, zc, st);
+        fv::launch_layernorm(x, M, d->D, w->ln1_g, w->ln1_b, d->ln_eps, buf_a, zc, st, all_idx, k);
+    if (all_idx && (ln_in_gemm || before.slices)) fv::launch_keep_all(all_idx, B, k, st);
     mark(st, FASTVAR_STAGE_LN1);
     // q | k | v = a1 * Wqkv^T + b ; k, v appended to the caches at [L0, L0+k)
     fv::GemmArgs g{};
@@ -307,7 +310,7 @@ fv::SliceSum enqueue_attn(const BlockPlan& bp, const void* x, int N, const int32
 fv::SliceSum enqueue_ffn(const BlockPlan& bp, const void* src, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                          const fastvar_block_weights* w, void* y, void* ws, hipStream_t st, bool clear,
                          bool scatter = false, const Fill* fill = nullptr, const fv::SliceSum& before = {},
-                         bool whole = false) {
+                         bool whole = false, int32_t* all_idx = nullptr) {
     const fv::ZeroCounters zc = clear ? split_counters(ws, bp) : fv::ZeroCounters{};
     char* base = static_cast<char*>(ws);
     void* buf_q = base + bp.off_q;
@@ -329,7 +332,8 @@ fv::SliceSum enqueue_ffn(const BlockPlan& bp, const void* src, int N, const int3
     else if (before.slices)
         fv::launch_slice_sum_layernorm(before, w->ln2_g, w->ln2_b, d->ln_eps, buf_q, st);
     else
-        fv::launch_layernorm(src, M, d->D, w->ln2_g, w->ln2_b, d->ln_eps, buf_q, zc, st);
+        fv::launch_layernorm(src, M, d->D, w->ln2_g, w->ln2_b, d->ln_eps, buf_q, zc, st, all_idx, k);
+    if (all_idx && (ln_in_gemm || before.slices)) fv::launch_keep_all(all_idx, B, k, st);
     mark(st, FASTVAR_STAGE_LN2);
     // u = gelu(a2 * W1^T + b1)
     fv::GemmArgs f1{};
@@ -352,14 +356,15 @@ fv::SliceSum enqueue_ffn(const BlockPlan& bp, const void* src, int N, const int3
     return left;
 }
 
-// (`before` and what is returned as in the halves)
+// (`before`, `all_idx` and what is returned as in the halves)
 fv::SliceSum enqueue_block(const BlockPlan& bp, const void* x, int N, const int32_t* idx, int B, int k, const fastvar_dims* d,
                            const fastvar_block_weights* w, void* kc, void* vc, int L0, int L_cap, void* y, void* ws,
                            hipStream_t st, bool clear, bool scatter = false, const Fill* fill = nullptr,
-                           const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false) {
+                           const Rope* rope = nullptr, const fv::SliceSum& before = {}, bool in_stack = false,
+                           int32_t* all_idx = nullptr) {
     void* buf_h1 = static_cast<char*>(ws) + bp.off_h1;
     const fv::SliceSum h1 = enqueue_attn(bp, x, N, idx, B, k, d, w, kc, vc, L0, L_cap, buf_h1, ws, st, clear, false,
-                                         idx ? fill : nullptr, rope, before, in_stack, true, true);
+                                         idx ? fill : nullptr, rope, before, in_stack, true, true, all_idx);
     return enqueue_ffn(bp, buf_h1, 0, nullptr, B, k, d, w, y, ws, st, false, scatter && idx, nullptr, h1, true);
 }
 
@@ -583,14 +588,14 @@ int fastvar_step(const void* x, const int32_t* sched_h, const int32_t* sched_w, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     // With every token kept (k == N) the block runs without an index list and its output is the map.
     const bool pruned = k > 0 && k < N;
-    fv::launch_select(x, B, N, D, k, idx_out, pruned ? rank : nullptr, nullptr, ws_sel, fv::select_plan(B, N, D), st);
+    if (pruned) fv::launch_select(x, B, N, D, k, idx_out, rank, nullptr, ws_sel, fv::select_plan(B, N, D), st);
     // Restoration has no launch of its own: the pruned rows of y_out are filled by extra workgroups of the
     // gather + LayerNorm launch, the kept rows are written by the block's last GEMM.  With nothing kept
     // the step is the upsampled cache.
     const Fill fill{rank, cache_map, hc, wc, h, w, y_out};
     if (k > 0)
         finish(enqueue_block(bp, x, N, pruned ? idx_out : nullptr, B, k, dims, weights, k_cache, v_cache, L0, L_cap, y_out,
-                             ws_blk, st, true, true, &fill), st);
+                             ws_blk, st, true, true, &fill, nullptr, {}, false, pruned ? nullptr : idx_out), st);
     else
         fv::launch_restore(nullptr, rank, B, k, cache_map, hc, wc, h, w, D, y_out, st);
     rc = launch_status();
@@ -815,20 +820,21 @@ int fastvar_step_sublayer(const void* x, const int32_t* sched_h, const int32_t* 
     const fv::SelectPlan sp = fv::select_plan(B, N, D);
     // (a half that keeps every token runs without an index list: its output is the map)
     const bool pruned_a = k_attn > 0 && k_attn < N, pruned_f = k_ffn > 0 && k_ffn < N;
-    fv::launch_select(x, B, N, D, k_attn, idx_attn_out, pruned_a ? rank : nullptr, nullptr, ws_sel, sp, st);
+    if (pruned_a) fv::launch_select(x, B, N, D, k_attn, idx_attn_out, rank, nullptr, ws_sel, sp, st);
     // each half's restoration rides in its own gather launch (pruned rows) and last GEMM (kept rows)
     const Fill fill_a{rank, cache_map_attn, hc, wc, h, w, x_mid};
     if (k_attn > 0)
         finish(enqueue_attn(bp_a, x, N, pruned_a ? idx_attn_out : nullptr, B, k_attn, dims, weights, k_cache, v_cache, L0,
-                            L_cap, x_mid, ws_blk, st, true, true, &fill_a, nullptr, {}, false, k_ffn > 0), st);
+                            L_cap, x_mid, ws_blk, st, true, true, &fill_a, nullptr, {}, false, k_ffn > 0,
+                            false, pruned_a ? nullptr : idx_attn_out), st);
     else
         fv::launch_restore(nullptr, rank, B, k_attn, cache_map_attn, hc, wc, h, w, D, x_mid, st);
-    fv::launch_select(x_mid, B, N, D, k_ffn, idx_ffn_out, pruned_f ? rank : nullptr, nullptr, ws_sel, sp, st);
+    if (pruned_f) fv::launch_select(x_mid, B, N, D, k_ffn, idx_ffn_out, rank, nullptr, ws_sel, sp, st);
     const Fill fill_f{rank, cache_map_ffn, hc, wc, h, w, y_out};
     if (k_ffn > 0)
         // (the halves lay the scratch out for their own k: its counters are cleared again)
         finish(enqueue_ffn(bp_f, x_mid, N, pruned_f ? idx_ffn_out : nullptr, B, k_ffn, dims, weights, y_out, ws_blk, st, true,
-                           pruned_f, &fill_f), st);
+                           pruned_f, &fill_f, {}, false, pruned_f ? nullptr : idx_ffn_out), st);
     else
         fv::launch_restore(nullptr, rank, B, k_ffn, cache_map_ffn, hc, wc, h, w, D, y_out, st);
     rc = launch_status();

@@ -38,6 +38,8 @@ SelectPlan select_plan(int B, int N, int D);
 // score_out, if asked for, is computed from it.
 void launch_select(const void* x, int B, int N, int D, int k, int32_t* idx, int32_t* rank,
                    float* score_out, void* ws, const SelectPlan& plan, hipStream_t stream);
+// The index list of a selection that keeps every token.
+void launch_keep_all(int32_t* idx, int B, int N, hipStream_t stream);
 
 // ---- restoration (Sec. 3.3, Eq. 6) ----
 void launch_rank_from_idx(const int32_t* idx, int32_t* rank, int B, int N, int k, hipStream_t stream);
@@ -69,9 +71,9 @@ void launch_gather_layernorm_fill(const void* x, const int32_t* idx, int B, int 
                                   const void* beta, float eps, int32_t* rows_out, void* a_out, const int32_t* rank,
                                   const void* cache_map, int hc, int wc, int h, int w, void* y_out,
                                   const ZeroCounters& zc, hipStream_t stream);
-// a = LayerNorm(rows of `in`), M rows.
+// a = LayerNorm(rows of `in`), M rows.  tokens_out [M] (optional): every row's token, m % N.
 void launch_layernorm(const void* in, int M, int D, const void* gamma, const void* beta, float eps,
-                      void* a_out, const ZeroCounters& zc, hipStream_t stream);
+                      void* a_out, const ZeroCounters& zc, hipStream_t stream, int32_t* tokens_out = nullptr, int N = 1);
 
 enum GemmEpilogue {
     EPI_QKV = 0,       // +bias; q -> q_out [M, D]; k, v -> caches at positions L0 + t

@@ -16,7 +16,7 @@ namespace {
 
 // CH = number of 512-column groups held in registers (D <= 512*CH).
 // Row m of the output reads input row (idx ? b*N + idx[m] : m), b = m / k; that
-// row index is also written to rows_out[m] when asked for.
+// row index is also written to rows_out[m] when asked for (without idx: the row's token, m % k).
 template <int CH>
 __device__ __forceinline__ void layernorm_row(const bf16_t* __restrict__ in, const int32_t* __restrict__ idx, int N,
                                               int k, int M, int D, const bf16_t* __restrict__ gamma,
@@ -29,7 +29,7 @@ __device__ __forceinline__ void layernorm_row(const bf16_t* __restrict__ in, con
     if (m >= M) return;
     size_t src_row = (size_t)m;
     if (idx) src_row = (size_t)(m / k) * N + idx[m];
-    if (rows_out && lane == 0) rows_out[m] = (int32_t)src_row;
+    if (rows_out && lane == 0) rows_out[m] = idx ? (int32_t)src_row : m % k;
     const bf16_t* src = in + src_row * D;
 
     // All of the row's loads and the gain / shift loads go out together: one memory
@@ -252,8 +252,8 @@ void launch_gather_layernorm_fill(const void* x, const int32_t* idx, int B, int 
 }
 
 void launch_layernorm(const void* in, int M, int D, const void* gamma, const void* beta, float eps, void* a_out,
-                      const ZeroCounters& zc, hipStream_t stream) {
-    dispatch(in, nullptr, 0, 1, M, D, gamma, beta, eps, nullptr, a_out, zc, stream);
+                      const ZeroCounters& zc, hipStream_t stream, int32_t* tokens_out, int N) {
+    dispatch(in, nullptr, 0, N, M, D, gamma, beta, eps, tokens_out, a_out, zc, stream);
 }
 
 void launch_slice_sum(const SliceSum& s, hipStream_t stream) {

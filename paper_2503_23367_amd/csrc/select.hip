@@ -346,6 +346,11 @@ SelectPlan select_plan(int B, int N, int D) {
     return p;
 }
 
+void launch_keep_all(int32_t* idx, int B, int N, hipStream_t stream) {
+    const long total = (long)B * N;
+    trivial_selection_kernel<<<(unsigned)((total + 255) / 256), 256, 0, stream>>>(N, total, true, idx, nullptr);
+}
+
 void launch_select(const void* x, int B, int N, int D, int k, int32_t* idx, int32_t* rank, float* score_out,
                    void* ws, const SelectPlan& plan, hipStream_t stream) {
     const bool trivial = k == 0 || k == N;

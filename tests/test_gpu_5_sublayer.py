@@ -166,6 +166,25 @@ def test_step_sublayer_batched_ragged_matches_oracle():
     check_step_sublayer("tiny64_b2", TINY64, (1, 2, 3, 4, 6, 9), 5, 2, 2, 33, 9, 61, 96, seed=23)
 
 
+@pytest.mark.parametrize("B,side", [(1, 2), (1, 4), (3, 3), (2, 7)])
+def test_steps_that_keep_every_token_write_the_index_list(B, side):
+    """By the LayerNorm's launch, or on its own where a product of up to 16 rows has the LayerNorm in front."""
+    sides, N, L_cap = (1, 2, side) if side > 2 else (1, side), side * side, 8 * ((side * side + 5 + 7) // 8)
+    step = len(sides) - 1
+    check_step_sublayer("keep_all", TINY128, sides, step, step - 1, B, N, N, 5, L_cap, seed=25)
+    W = synth.block_weights(25, TINY128)
+    wt, wstruct = upload_weights(W)
+    d = fb.make_dims(TINY128.D, TINY128.H, TINY128.dh, TINY128.F)
+    kc, vc = make_caches(*synth.kv_prior(25, B, 5, TINY128.H, TINY128.dh), L_cap)
+    x = to_dev_bf16(synth.token_map(25, B, side, side, TINY128.D))
+    cache = to_dev_bf16(synth.cached_map(25, B, sides[step - 1], sides[step - 1], TINY128.D))
+    y, idx = torch.empty_like(x), torch.full((B, N), -7, dtype=torch.int32, device=DEV)
+    fb.fastvar_step(x, list(sides), list(sides), step, step - 1, B, N, d, wstruct, kc, vc, 5, L_cap, cache, y, idx,
+                    empty_ws(fb.fastvar_step_workspace_bytes(d, B, N, N)))
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(idx.cpu().numpy(), np.tile(np.arange(N, dtype=np.int32), (B, 1)))
+
+
 def test_step_sublayer_headline_full_size():
     """1024 px last scale at keep 0.5 for both halves, the launch configuration of the benchmark."""
     wl = synth.WORKLOADS[synth.HEADLINE]
