@@ -18,7 +18,7 @@
 // MFMA: every K / V^T fragment read feeds two MFMAs).  A workgroup has
 // QG * KSPLIT waves: QG query groups, and KSPLIT waves per group that each take
 // a different 64-key slice of every (64*KSPLIT)-key tile and are merged at the
-// end (softmax partials combine exactly).  KSPLIT = 2 keeps all SIMDs busy when
+// end (softmax partials combine exactly).  KSPLIT = 2 or 4 keeps all SIMDs busy when
 // there are too few queries for one wave per SIMD.
 //
 // K and V^T tiles go global -> LDS directly (no register staging), double
@@ -70,13 +70,13 @@ __device__ __forceinline__ float other_half(float v) {
 
 // XOR key that spreads the 16-byte chunks of consecutive rows over all 64 LDS
 // banks (256 bytes): a 16-byte-per-lane read is served 16 lanes at a time, so 16
-// consecutive rows must land in 16 different chunk columns.  Rows of 256 bytes
-// (16 chunks) use the low 4 row bits; rows of 128 bytes (8 chunks, two rows per
+// consecutive rows must land in 16 different chunk columns.  Rows of 256 and 512 bytes
+// (16 and 32 chunks) use the low 4 row bits; rows of 128 bytes (8 chunks, two rows per
 // bank sweep) use row bits 1-3.
 template <int CPR>
 __device__ __forceinline__ int chunk_key(int row) {
-    static_assert(CPR == 8 || CPR == 16, "rows of 128 or 256 bytes");
-    return CPR == 16 ? (row & 15) : ((row >> 1) & 7);
+    static_assert(CPR == 8 || CPR == 16 || CPR == 32, "rows of 128, 256 or 512 bytes");
+    return CPR >= 16 ? (row & 15) : ((row >> 1) & 7);
 }
 
 constexpr int attn_waitcnt(int vm, bool lgkm) {
@@ -1243,9 +1243,9 @@ void launch_cfg(AttnParams& p, const AttnArgs& a, hipStream_t stream) {
     p.q_tiles = (p.k_tokens + per_wg - 1) / per_wg;
     p.n_wg = p.q_tiles * p.H * a.B;
     // A quarter of the CUs idle or more: they fetch the weights of the products behind this launch, which takes about
-    // 6.5 us and 1.45 (head dim 64: 0.6) for every tile of keys.
+    // 6.5 us and 1.45 (head dim 64: 0.6, of 256 keys 0.8) for every tile of keys.
     if (p.n_wg <= 192)
-        p.ahead = a.ahead.plan(256 - p.n_wg, 6.5 + (DH == 128 ? 1.45 : 0.6) * ((p.L + 64 * KSPLIT - 1) / (64 * KSPLIT)),
+        p.ahead = a.ahead.plan(256 - p.n_wg, 6.5 + (DH == 128 ? 1.45 : KSPLIT == 4 ? 0.8 : 0.6) * ((p.L + 64 * KSPLIT - 1) / (64 * KSPLIT)),
                                a.B * a.k_tokens <= kFewRowsMax);
     // (long launches take the other form with nothing to fetch: its start is nothing there, and 832 workgroups of dim 64 over
     // 7263 keys, a part-filled round behind full ones, take 273 us in it and 302 in this one, others the same in both)
@@ -1422,7 +1422,13 @@ void launch_attention(const AttnArgs& a, hipStream_t stream) {
             case 1: launch_cfg<64, 2, 2, 2>(p, a, stream); break;
 #endif
             case 2: launch_cfg<64, 1, 4, 1>(p, a, stream); break;
-            case 3: launch_cfg<64, 1, 2, 2>(p, a, stream); break;
+            case 3: {
+                const AttentionSlices sl = attention_slices(a.B, a.H, a.k_tokens, a.L);
+                if (sl.queries == 32) launch_cfg<64, 1, 1, 4>(p, a, stream);
+                else if (sl.slices == 4) launch_cfg<64, 1, 2, 4>(p, a, stream);
+                else launch_cfg<64, 1, 2, 2>(p, a, stream);
+                break;
+            }
             case 5: launch_pipe<64, 2, 2>(p, a.B, stream); break;
             case 6: launch_pipe<64, 4, 1>(p, a.B, stream); break;
             default: launch_cfg<64, 1, 4, 2>(p, a, stream); break;

@@ -256,6 +256,25 @@ FV_HOST_DEVICE int attention_cfg(int B, int H, int dh, int k, int L) {
     return waves >= 1800 ? 2 : 4;
 }
 
+// Head dim 64 on workgroups of 64 queries with a tile's keys split in two (3 above): over longer caches on what it runs instead.  Tiles
+// of 256 keys split between four waves halve the turns that a wave waits for its keys, and hold twice the keys in flight (128 KB a
+// workgroup; head dim 128 has no room for that).  us, two slices / four over 32 queries / four over 64, caches from memory, 16 heads: 100
+// queries over 300 / 500 / 600 / 700 / 1000 / 1300 / 2600 keys 6.6 / 8.9 / 9.9 / 10.4 / 13.6 / 16.7 / 24.5, 7.3 / 8.7 / 9.7 / 9.6 / 11.9 / 14.5 / 19.6, 8.2 / 9.3 / 10.7 / 10.6 / 12.6 / 15.8 /
+// 21.9; 60 queries of 30 heads over 5000 48.8, 39.2, 40.2.  So four slices over 32 queries from 640 keys on, where their workgroups are at
+// most half a round, which leaves CUs to fetch weights on, and divide among the XCDs if those of 64 do (200 of 30 heads over 1000 keys 13.5,
+// 14.4, 12.6); else over 64 queries where tiles of 256 waste little (800 / 1000 / 2200 / 3500 keys 11.5 / 13.4 / 22.8 / 31.1, 12.2 / 12.6 / 19.6 /
+// 25.8) and do not fall unevenly on the XCDs (320 of 30 heads over 1600 / 2200 keys 17.2 / 25.4, 17.9 / 22.7).  Not a matter of what
+// the launch fetches: a stack has the bits of its single blocks.
+struct AttentionSlices {
+    int queries, slices;
+};
+FV_HOST_DEVICE AttentionSlices attention_slices(int B, int H, int k, int L) {
+    const long wg32 = (long)((k + 31) / 32) * H * B, wg64 = (long)((k + 63) / 64) * H * B;
+    if (L > 640 && wg32 <= 128 && (wg32 % 8 == 0 || wg64 % 8 != 0)) return AttentionSlices{32, 4};
+    if (L > 7 * 128 && wg64 <= 256 && (wg64 % 8 == 0 || L > 2048)) return AttentionSlices{64, 4};
+    return AttentionSlices{64, 2};
+}
+
 // Which matrices the attention launch of a call may fetch ahead: those that the call's later products read, in their order, and no
 // others; a call that does not go on to the MLP half may hold placeholders for its weights.  Matrices under 16 MB only in a
 // stack, and not for few rows (16 blocks of the small model on 169 rows 775 -> 734 us with it, but its single step on 128 rows

@@ -15,3 +15,11 @@ pytestmark = pytest.mark.gpu
     (16, 4, 200, 300), (16, 4, 257, 512), (16, 2, 128, 513), (32, 2, 250, 140)])   # 256 workgroups of 64 queries and more
 def test_attention_few_queries(H, dh, B, k, L):
     check(H, dh, B, k, L, (L + 7) // 8 * 8)
+
+
+@pytest.mark.parametrize("H,B,k,L", [
+    (16, 1, 100, 641), (2, 1, 33, 768), (2, 2, 1, 769), (3, 1, 32, 1023),       # tiles of 256 keys over 32 queries
+    (16, 1, 257, 897), (16, 1, 300, 1024), (8, 2, 513, 1025), (30, 1, 270, 2055)])   # over 64
+def test_attention_key_tiles_in_four(H, B, k, L):
+    """Head dim 64, a tile's keys between four waves: last tiles of one key, of a slice and less, of all but one key, and whole."""
+    check(H, 64, B, k, L, (L + 7) // 8 * 8)

@@ -55,6 +55,10 @@ void ahead(int D, int F, int M, int in_stack, int ffn_follows, long* out) {
     for (int i = 0; i < 3; ++i) out[1 + i] = l.bytes[i];
 }
 int attention(int B, int H, int dh, int k, int L) { return fv::attention_cfg(B, H, dh, k, L); }
+int attention_slices(int B, int H, int k, int L) {
+    const fv::AttentionSlices s = fv::attention_slices(B, H, k, L);
+    return s.queries * 10 + s.slices;
+}
 int few_rows_ln(int M, int N, int K) { return fv::few_rows_layernorm(M, N, K); }
 }
 """
@@ -232,6 +236,13 @@ def test_attention_workgroups(math):
                        ((4, 16, 128, 257, 512), 5), ((4, 32, 128, 128, 513), 5), ((4, 32, 128, 128, 512), 3), ((1, 16, 64, 1024, 2624), 3),
                        ((1, 16, 64, 1025, 2624), 4), ((8, 30, 64, 410, 1626), 6), ((8, 30, 64, 300, 1626), 2), ((1, 64, 128, 4096, 9000), 6)]:
         assert math.attention(*shape) == cfg, (shape, cfg)
+
+
+def test_attention_slices_of_head_dim_64(math):
+    for shape, want in [((1, 16, 256, 641), 324), ((1, 16, 256, 640), 642), ((1, 16, 257, 897), 644), ((1, 16, 257, 896), 642), ((1, 16, 1024, 2624), 644),
+                        ((4, 16, 257, 2624), 642), ((1, 30, 128, 700), 324), ((1, 30, 200, 700), 642), ((1, 30, 100, 1000), 324),
+                        ((1, 30, 320, 2048), 642), ((1, 30, 320, 2049), 644), ((3, 7, 130, 1500), 324), ((1, 1, 1, 641), 324)]:
+        assert math.attention_slices(*shape) == want, (shape, want)
 
 
 def test_rows_of_a_restoring_wave(math):
