@@ -322,6 +322,11 @@ FV_HOST_DEVICE PrefetchPlan prefetch_plan(const long* bytes, int n, int idle, do
 constexpr int kXcdShares = 64;
 FV_HOST_DEVICE int xcd_blocks(int n) { return n < kXcdShares ? n : (n + 7) / 8 * 8; }
 FV_HOST_DEVICE int xcd_share(int block, int n) { return n < kXcdShares ? block : (block & 7) * ((n + 7) / 8) + (block >> 3); }
+// Widths near a multiple of sixteen: with shares of four tokens dealt in turn, the positions above and below one another are on one XCD already.
+FV_HOST_DEVICE bool columns_on_one_xcd(int w) { return (w + 1) % 16 <= 2; }
+// The fill of the pruned rows in runs, except of such widths: the kept tokens lie in clusters, which runs share out unevenly (steps, us,
+// in turn / in runs: 128x128 176.2 / 177.4, 64x64 127.0 / 127.3; 8 x 24x24 176.4 / 174.9, 73x67 144.0 / 143.2, 53x37 101.2 / 100.9).
+FV_HOST_DEVICE bool fill_in_runs(int w) { return !columns_on_one_xcd(w); }
 
 // Rows that a wave of the restoration takes, of maps of `rows` tokens in all, w wide, D columns.  Rank, taps and store of a row
 // wait for one another, so a wave a row while the chip has room for them all (us, a pair unrolled / one: 16x16 x 1024 5.5 / 4.9,
@@ -338,7 +343,7 @@ struct RestorePlan {
 };
 FV_HOST_DEVICE RestorePlan restore_plan(long rows, int w, int D) {
     if (rows * D >= 1L << 25) return RestorePlan{2, false};
-    if (rows < 4300 || D >= 4096 || (D >= 1280 && (rows < 6000 || (w + 1) % 16 <= 2))) return RestorePlan{1, false};
+    if (rows < 4300 || D >= 4096 || (D >= 1280 && (rows < 6000 || columns_on_one_xcd(w)))) return RestorePlan{1, false};
     return RestorePlan{2, true};
 }
 

@@ -71,14 +71,15 @@ __global__ __launch_bounds__(256) void layernorm_rows_kernel(const bf16_t* __res
 }
 
 // The same launch with the restoration's fill behind it: workgroups [0, ln_blocks) normalise the kept rows,
-// the others walk the token rows of the restored map (one a wave, each XCD a contiguous run of them; ln_blocks is a multiple
-// of eight) and write the pruned ones (rank < 0) from the cached map; kept rows are left to the block's last GEMM.
+// the others walk the token rows of the restored map (one a wave; each XCD a contiguous run of them where fill_in_runs, ln_blocks
+// is a multiple of eight) and write the pruned ones (rank < 0) from the cached map; kept rows are left to the block's last GEMM.
 struct FillParams {
     const int32_t* rank;      // [B, N]
     const bf16_t* cache_map;  // [B, hc*wc, D]
     bf16_t* y_out;            // [B, N, D]
     int hc, wc, h, w;
     int shares;   // of a sample, a wave a row
+    bool runs;    // in contiguous runs to the XCDs
 };
 constexpr int kFillRowsPerWave = 1;
 
@@ -97,7 +98,7 @@ __global__ __launch_bounds__(256) void gather_layernorm_fill_kernel(const bf16_t
     }
     const int per_sample = xcd_blocks(f.shares), fb = blockIdx.x - ln_blocks;
     const int b = fb / per_sample;
-    const int blk = xcd_share(fb - b * per_sample, f.shares);   // (past the end: so are its rows)
+    const int at = fb - b * per_sample, blk = f.runs ? xcd_share(at, f.shares) : at;   // (past the end: so are its rows)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int rr = 0; rr < kFillRowsPerWave; ++rr) {
@@ -234,6 +235,7 @@ void launch_gather_layernorm_fill(const void* x, const int32_t* idx, int B, int 
     f.y_out = static_cast<bf16_t*>(y_out);
     f.hc = hc; f.wc = wc; f.h = h; f.w = w;
     f.shares = (N + 4 * kFillRowsPerWave - 1) / (4 * kFillRowsPerWave);
+    f.runs = fill_in_runs(w);
     const dim3 grid(ln_blocks + B * xcd_blocks(f.shares)), block(kClearThreads);
     const int ch = (D + 511) / 512;
     const auto launch = [&](auto kernel) {
