@@ -91,14 +91,6 @@ __device__ __forceinline__ int swz(int row) {
     return CPR == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3);
 }
 
-// Slots from one load to the next, at most four, such that a K tile's loads find a slot each: of its last k-step those behind the
-// hand-over, of the others all.
-constexpr int load_slots(int slots, int before, int ksteps, int loads) {
-    for (int ls = 4; ls > 0; --ls)
-        if ((slots - before + ls - 1) / ls + (ksteps - 1) * slots / ls >= loads) return ls;
-    return 0;
-}
-
 __device__ __forceinline__ f32x4_t mfma(const bf16x8_t& a, const bf16x8_t& b, const f32x4_t& c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -124,7 +116,7 @@ constexpr bool kPersistent = !SLICED && KG == 1 && (is_qkv(EPI) || (EPI == EPI_B
 template <int BM, int BN, int WGM, int WGN, int KG>
 constexpr bool kWide = WGM == 2 && WGN == 2 && KG == 1 && BM * BN >= 128 * 128;
 template <int BM, int BN, int BK, int STAGES>
-constexpr int kStagesA = STAGES * (BM + BN) * BK * 2 <= (160 << 10) ? STAGES : 2;
+constexpr int kStagesA = wide_stages_a(BM, BN, BK, STAGES);
 
 template <int BM, int BN, int BK, int STAGES, int WGM, int WGN, int KG, int EPI, bool SLICED = false>
 __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const GemmParams p) {
@@ -301,7 +293,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     constexpr int SLOTS = MI * NI, SB = SLOTS >= 32 ? 4 : 2;             // slots of a k-step; those in front of the hand-over
     constexpr int RS = SLOTS - SB >= 2 * (MI + NI) ? 2 : 1;              // an operand read every RS slots
     constexpr int LS = WIDE ? load_slots(SLOTS, SB, KK, LPT) : 1;                 // a load every LS slots
-    constexpr int W3 = (SLOTS - SB + LS - 1) / LS < LPT ? (SLOTS - SB + LS - 1) / LS : LPT;
+    constexpr int W3 = handover_loads(SLOTS, SB, LS, LPT);
     static_assert(!WIDE || (LS > 0 && SLOTS - SB >= MI + NI && KK > 1), "a k-step has room for its reads, a K tile for its loads");
 #define FV_ISSUE_PROLOGUE()                                                                     \
     if constexpr (WIDE) {                                                                       \
@@ -318,7 +310,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
             _Pragma("unroll") for (int q = 0; q < (W3 < A_LD ? W3 : A_LD); ++q) FV_ISSUE_A(SA - 1, SA - 1, q); \
         }                                                                                       \
         if (STAGES - 1 < KT) {                                                                  \
-            _Pragma("unroll") for (int q = A_LD; q < (W3 < LPT ? W3 : LPT); ++q) FV_ISSUE_W(STAGES - 1, STAGES - 1, q - A_LD < 0 ? 0 : q - A_LD); \
+            _Pragma("unroll") for (int q = A_LD; q < W3; ++q) FV_ISSUE_W(STAGES - 1, STAGES - 1, q - A_LD < 0 ? 0 : q - A_LD); \
         }                                                                                       \
     } else {                                                                                    \
         _Pragma("unroll") for (int s = 0; s < AHEAD; ++s)                                       \
@@ -375,7 +367,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     // loads went out before the previous epilogue's stores and residual loads, and the counter says
     // nothing about the order in which loads and stores complete.)
     if (first_tile && KT >= (WIDE ? STAGES : AHEAD))
-        __builtin_amdgcn_s_waitcnt(waitcnt_imm(WIDE ? (SA - 2) * A_LD + (STAGES - 2) * W_LD + (W3 < LPT ? W3 : LPT) : (AHEAD - 1) * LPT, true));
+        __builtin_amdgcn_s_waitcnt(waitcnt_imm(WIDE ? wide_out_at_start(SA, STAGES, A_LD, W_LD, W3) : (AHEAD - 1) * LPT, true));
     else
         __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, true));
     asm volatile("" ::: "memory");
@@ -475,8 +467,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
                 constexpr int mi = s / NI, ni = s % NI, cur = kk & 1, nxt = cur ^ 1;
                 constexpr bool last = kk == KK - 1;
                 if constexpr (last && s == SB && R >= 1) {
-                    __builtin_amdgcn_s_waitcnt(waitcnt_imm((SA > 2 && R >= SA - 1 ? A_LD : 0) +
-                                                           (STAGES > 2 && R >= STAGES - 1 ? W_LD : 0), true));
+                    __builtin_amdgcn_s_waitcnt(waitcnt_imm(wide_out_at_handover(SA, STAGES, A_LD, W_LD, R), true));
                     asm volatile("" ::: "memory");
                     __builtin_amdgcn_s_barrier();
                     asm volatile("" ::: "memory");

@@ -98,6 +98,36 @@ FV_HOST_DEVICE bool few_rows_layernorm(int M, int N, int K) {
     return K <= kFewRowsRound && few_rows_product(M, N, K, false);
 }
 
+// The wide tiles' ring (gemm_tiles.h, main loop): a hand-over to tile kt + 1 waits for that tile's loads and opens the window in which the
+// A tile kt + sa and the W tile kt + stages are fetched, A's loads first; a window ends before the next hand-over.
+// Stages of A: as many as of W where 160 KB hold them, else two.
+constexpr int wide_stages_a(int bm, int bn, int bk, int stages) { return stages * (bm + bn) * bk * 2 <= (160 << 10) ? stages : 2; }
+// Slots from one load to the next, at most four, such that a K tile's loads find a slot each: of its last k-step those behind the
+// hand-over, of the others all.
+constexpr int load_slots(int slots, int before, int ksteps, int loads) {
+    for (int ls = 4; ls > 0; --ls)
+        if ((slots - before + ls - 1) / ls + (ksteps - 1) * slots / ls >= loads) return ls;
+    return 0;
+}
+// Loads of a window that the rest of the hand-over's own k-step issues.
+constexpr int handover_loads(int slots, int before, int ls, int loads) {
+    return (slots - before + ls - 1) / ls < loads ? (slots - before + ls - 1) / ls : loads;
+}
+// Loads that may still be out when the first tile is used: those of the other stages, and what the prologue issues of the first window.
+constexpr int wide_out_at_start(int sa, int stages, int a_ld, int w_ld, int first_window) {
+    return (sa - 2) * a_ld + (stages - 2) * w_ld + first_window;
+}
+// ... and at a hand-over with `left` tiles behind the current one: what was issued after the last load of the next tile.  With rings of
+// one depth these are whole tiles, stages - 2 of them; with a shorter A ring the next tile's A is in the latest windows, and of it
+// on W's loads of these may be out.
+constexpr int wide_out_at_handover(int sa, int stages, int a_ld, int w_ld, int left) {
+    const auto least = [](int a, int b) { return a < b ? a : b; };
+    if (left < 1) return 0;
+    if (sa == stages) return least(left - 1, stages - 2) * (a_ld + w_ld);
+    const int w_tiles = left - (stages - sa);   // W tiles that exist from the window of the next tile's A on
+    return least(left - 1, sa - 2) * a_ld + (w_tiles > 0 ? least(w_tiles, sa - 1) * w_ld : 0);
+}
+
 // Tile choice.  What the measurements on the block's shapes say:
 //  * large products are limited by power and by what a tile's waves read from LDS: tiles of 160x128 and up on four waves, one a SIMD,
 //    with the main loop's order written down (wide tiles in gemm_tiles.h).  Of the eight-wave tiles 128x128, 192x128 and 256x128 are

@@ -59,6 +59,11 @@ int attention_slices(int B, int H, int k, int L) {
     const fv::AttentionSlices s = fv::attention_slices(B, H, k, L);
     return s.queries * 10 + s.slices;
 }
+int wide_stages_a(int bm, int bn, int bk, int stages) { return fv::wide_stages_a(bm, bn, bk, stages); }
+int load_slots(int slots, int before, int ksteps, int loads) { return fv::load_slots(slots, before, ksteps, loads); }
+int handover_loads(int slots, int before, int ls, int loads) { return fv::handover_loads(slots, before, ls, loads); }
+int out_at_start(int sa, int stages, int a_ld, int w_ld, int window) { return fv::wide_out_at_start(sa, stages, a_ld, w_ld, window); }
+int out_at_handover(int sa, int stages, int a_ld, int w_ld, int left) { return fv::wide_out_at_handover(sa, stages, a_ld, w_ld, left); }
 int few_rows_ln(int M, int N, int K) { return fv::few_rows_layernorm(M, N, K); }
 }
 """
@@ -171,6 +176,53 @@ def test_tiles_are_not_the_ones_measured_slower(math):
         for N in (8, 64, 1344, 6144, 24576, 32768):
             for K in (64, 448, 2048, 2112, 8192, 32768):
                 assert math.tile(0, M, N, K) in TILES and math.tile(1, M, N, K) in {15, *TILES}, (M, N, K)
+
+
+# tiles on four waves, one a SIMD (rows, columns, stages of W), those of other rings that one may want, and rings of two
+WIDE = [(256, 256, 3), (256, 192, 3), (224, 256, 3), (224, 192, 3), (224, 128, 3), (192, 256, 3), (192, 192, 3), (160, 128, 4),
+        (128, 128, 3), (128, 128, 4), (128, 128, 5), (192, 192, 2), (256, 128, 3)]
+
+
+@pytest.mark.parametrize("bm,bn,stages", WIDE)
+def test_wide_tiles_wait_for_the_next_tile_and_no_more(math, bm, bn, stages):
+    """The main loop's order of loads, replayed: at every hand-over the loads that may still be out are those behind the next tile's last
+    one.  With four stages it once waited as with three, and the fourth bought nothing."""
+    sa = math.wide_stages_a(bm, bn, 64, stages)
+    a_ld, w_ld, ksteps = bm // 32, bn // 32, 2
+    slots, loads = (bm // 32) * (bn // 32), a_ld + w_ld
+    before = 4 if slots >= 32 else 2
+    every = math.load_slots(slots, before, ksteps, loads)
+    assert every > 0 and (stages - 1) * loads <= 63
+    first = math.handover_loads(slots, before, every, loads)
+    for tiles in list(range(1, 12)) + [32]:
+        order = []   # (operand, K tile) of every load, as issued
+
+        def window(a_tile, w_tile, lo, hi):
+            for q in range(lo, hi):
+                operand, tile = ("A", a_tile) if q < a_ld else ("W", w_tile)
+                if tile < tiles:
+                    order.append((operand, tile))
+
+        def check(tile, out):
+            last = max(i for i, (_, t) in enumerate(order) if t == tile)
+            assert {(o, t) for o, t in order if t == tile} == {("A", tile), ("W", tile)}
+            assert [order.count((o, tile)) for o in "AW"] == [a_ld, w_ld]
+            assert out == len(order) - 1 - last, (tiles, tile, out, order[last:])
+
+        for s in range(min(stages - 1, tiles)):
+            if s < sa - 1:
+                order += [("A", s)] * a_ld
+            order += [("W", s)] * w_ld
+        window(sa - 1, stages - 1, 0, first)
+        if tiles >= stages:
+            check(0, math.out_at_start(sa, stages, a_ld, w_ld, first))
+        for kt in range(tiles - 1):
+            # the rest of the window that the hand-over in front opened: in this tile's k-steps but the last
+            in_steps = sum(1 for i in range((ksteps - 1) * slots) if i % every == every // 2)
+            assert first + in_steps >= loads
+            window(kt + sa - 1, kt + stages - 1, first, loads)
+            check(kt + 1, math.out_at_handover(sa, stages, a_ld, w_ld, tiles - 1 - kt))
+            window(kt + sa, kt + stages, 0, first)
 
 
 LAYERNORM, EITHER, LAUNCH = 0, 1, 2   # SlicesMeet
