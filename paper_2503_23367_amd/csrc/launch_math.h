@@ -345,35 +345,44 @@ FV_HOST_DEVICE PrefetchPlan prefetch_plan(const long* bytes, int n, int idle, do
     return p;
 }
 
-// Consecutive workgroups go to the eight XCDs in turn, each with its own L2.  Workgroup `block` of the xcd_blocks(n) that walk a
-// map takes share xcd_share(block, n) of its n: an XCD has a contiguous run of them, so the rows of a cached map that neighbouring
-// rows are blended from are fetched into one L2 and not into all.  A share of n or more is nothing to do.  Under eight shares an XCD
-// the runs are too short to matter, and a large batch of small maps is not padded.
+// Consecutive workgroups go to the eight XCDs in turn, each with its own L2.  A map is walked in shares of four waves with `rows` token rows
+// each.  In runs, an XCD has a contiguous run of a sample's shares, so the rows of a cached map that neighbouring rows are blended from are
+// fetched into one L2 and not into all.  Which XCD has which run moves on by one a sample: the last run is the short one, and by always
+// the same XCD batches of small maps waited for the other seven (8 x 48x48 x 2048 32.6 -> 30.6 us, 8 x 13x20 x 4096 9.9 -> 9.7).
+// Dealt in turn, shares come round to an XCD every 32 * rows tokens: where the width is near a multiple of that, the positions above and below one another are
+// on one XCD already, and runs share clustered kept sets out unevenly (restoration, in turn / in runs: 64x95 x 2048 13.3 / 14.1 us, 96x96 17.1 / 17.6,
+// 128x128 26.6 / 27.3; but 80x80 14.45 / 14.54, 2 x 90x47 16.6 / 15.4, in pairs 96x96 x 1024 11.7 / 10.8; steps of the large model, whose fill this is,
+// 2 and 5 % of 96x96 tokens kept behind 11059 186.7 / 188.3, 220.8 / 221.9, of 128x96 behind 14745 213.8 / 215.3, 275.0 / 276.0; 15 % of 48x48 behind 2764 146.4 / 145.9,
+// 13 % of 80x80 behind 7680 246.4 / 245.2; nothing in it for the small models).  Under eight shares an XCD the runs are too short to matter.
 constexpr int kXcdShares = 64;
-FV_HOST_DEVICE int xcd_blocks(int n) { return n < kXcdShares ? n : (n + 7) / 8 * 8; }
-FV_HOST_DEVICE int xcd_share(int block, int n) { return n < kXcdShares ? block : (block & 7) * ((n + 7) / 8) + (block >> 3); }
-// Widths near a multiple of sixteen: with shares of four tokens dealt in turn, the positions above and below one another are on one XCD already.
-FV_HOST_DEVICE bool columns_on_one_xcd(int w) { return (w + 1) % 16 <= 2; }
-// The fill of the pruned rows in runs, except of such widths: the kept tokens lie in clusters, which runs share out unevenly (steps, us,
-// in turn / in runs: 128x128 176.2 / 177.4, 64x64 127.0 / 127.3; 8 x 24x24 176.4 / 174.9, 73x67 144.0 / 143.2, 53x37 101.2 / 100.9).
-FV_HOST_DEVICE bool fill_in_runs(int w) { return !columns_on_one_xcd(w); }
+FV_HOST_DEVICE bool columns_on_one_xcd(int w, int rows) {
+    const int period = 32 * rows, off = w % period;
+    return w > period / 2 && (off < 2 * rows || off > period - 2 * rows);
+}
+FV_HOST_DEVICE bool shares_in_runs(int shares, int w, int rows) { return shares >= kXcdShares && !columns_on_one_xcd(w, rows); }
+// Workgroups that walk a sample, and the share that workgroup `block` of them takes; a share past the last one is nothing to do.
+FV_HOST_DEVICE int xcd_blocks(int shares, bool runs) { return runs ? (shares + 7) / 8 * 8 : shares; }
+FV_HOST_DEVICE int xcd_share(int block, int shares, bool runs, int sample) {
+    return runs ? ((block + sample) & 7) * ((shares + 7) / 8) + (block >> 3) : block;
+}
 
 // Rows that a wave of the restoration takes, of maps of `rows` tokens in all, w wide, D columns.  Rank, taps and store of a row
 // wait for one another, so a wave a row while the chip has room for them all (us, a pair unrolled / one: 16x16 x 1024 5.5 / 4.9,
 // 53x37 x 2048 8.4 / 6.0, 64x64 x 2048 9.0 / 8.1, 4 x 33x31 x 1920 10.6 / 8.6, 40x44 x 4096 14.4 / 9.4), wide rows for longer (73x67 x 2048
 // 12.1 / 10.9, 8 x 24x24 x 1920 12.8 / 11.1, 75x70 x 1920 12.0 / 11.1).  Maps of more rows than that have a queue of waves either way, and a pair
 // has two rows' loads in flight (81x82 x 448 5.6 / 6.2, 100x104 x 1024 11.7 / 11.9, 72x80 x 1024 7.4 / 7.7, 2 x 90x77 x 1920 23.6 / 24.6), except
-// of widths near a multiple of sixteen (117x95 x 2048 21.5 / 20.5, 80x80 x 2048 12.7 / 12.6), and of 4096 columns, which fill a wave by themselves
-// (62x105 23.3 / 21.9).  Beyond 2^25 elements two rows, one after the other (90x90 x 8192 a pair 54.4, one row 52.7, two 51.4; 8 x 100x100 x 1920
-// 154.6, 145.0, 144.7).  All with shares in contiguous runs; dealt in turn, these plans' times were 2x90x77 x 1920 29.7 us (23.6 in
-// runs), 100x120 x 4096 47.9 (39.6), 90x90 x 8192 68.4 (51.4), 40x44 x 4096 10.6 (9.4), 64x64 x 2048 8.3 (8.2).
+// of 4096 columns, which fill a wave by themselves (62x105 23.3 / 21.9).  Wide rows gain from the pair while few of them are kept, whose
+// copies have no rank-to-taps wait to share (10 / 50 / 80 % kept: 85x88 x 2048 14.5 / 15.7, 15.6 / 14.9, 15.4 / 14.3; 120x112 24.0 / 25.2, 25.6 / 24.0,
+// 25.9 / 22.1; 80x80 10 / 60 % 14.0 / 14.5, 14.0 / 13.6): widths near a multiple of sixteen, those of most schedules, have a row a wave at every size.  Beyond 2^25 elements two rows, one after the other (90x90 x 8192 a pair 54.4, one row 52.7, two 51.4; 8 x 100x100 x 1920
+// 154.6, 145.0, 144.7).  All with shares in runs; dealt in turn, these plans' times were 2x90x77 x 1920 29.7 us (23.6 in
+// runs), 100x120 x 4096 47.9 (39.6), 90x90 x 8192 68.4 (51.4), 40x44 x 4096 10.6 (9.4).
 struct RestorePlan {
     int rows;
     bool pair;   // unrolled
 };
 FV_HOST_DEVICE RestorePlan restore_plan(long rows, int w, int D) {
     if (rows * D >= 1L << 25) return RestorePlan{2, false};
-    if (rows < 4300 || D >= 4096 || (D >= 1280 && (rows < 6000 || columns_on_one_xcd(w)))) return RestorePlan{1, false};
+    if (rows < 4300 || D >= 4096 || (D >= 1280 && (rows < 6000 || (w + 1) % 16 <= 2))) return RestorePlan{1, false};
     return RestorePlan{2, true};
 }
 

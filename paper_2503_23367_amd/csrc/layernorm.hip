@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256) void layernorm_rows_kernel(const bf16_t* __res
 }
 
 // The same launch with the restoration's fill behind it: workgroups [0, ln_blocks) normalise the kept rows,
-// the others walk the token rows of the restored map (one a wave; each XCD a contiguous run of them where fill_in_runs, ln_blocks
+// the others walk the token rows of the restored map (one a wave; to the XCDs in runs or in turn, see xcd_share; ln_blocks
 // is a multiple of eight) and write the pruned ones (rank < 0) from the cached map; kept rows are left to the block's last GEMM.
 struct FillParams {
     const int32_t* rank;      // [B, N]
@@ -96,9 +96,9 @@ __global__ __launch_bounds__(256) void gather_layernorm_fill_kernel(const bf16_t
         layernorm_row<CH>(in, idx, N, k, M, D, gamma, beta, eps, rows_out, out, blockIdx.x * 4 + (threadIdx.x >> 6));
         return;
     }
-    const int per_sample = xcd_blocks(f.shares), fb = blockIdx.x - ln_blocks;
+    const int per_sample = xcd_blocks(f.shares, f.runs), fb = blockIdx.x - ln_blocks;
     const int b = fb / per_sample;
-    const int at = fb - b * per_sample, blk = f.runs ? xcd_share(at, f.shares) : at;   // (past the end: so are its rows)
+    const int blk = xcd_share(fb - b * per_sample, f.shares, f.runs, b);   // (past the end: so are its rows)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int rr = 0; rr < kFillRowsPerWave; ++rr) {
@@ -235,8 +235,8 @@ void launch_gather_layernorm_fill(const void* x, const int32_t* idx, int B, int 
     f.y_out = static_cast<bf16_t*>(y_out);
     f.hc = hc; f.wc = wc; f.h = h; f.w = w;
     f.shares = (N + 4 * kFillRowsPerWave - 1) / (4 * kFillRowsPerWave);
-    f.runs = fill_in_runs(w);
-    const dim3 grid(ln_blocks + B * xcd_blocks(f.shares)), block(kClearThreads);
+    f.runs = shares_in_runs(f.shares, w, kFillRowsPerWave);
+    const dim3 grid(ln_blocks + B * xcd_blocks(f.shares, f.runs)), block(kClearThreads);
     const int ch = (D + 511) / 512;
     const auto launch = [&](auto kernel) {
         kernel<<<grid, block, 0, stream>>>(static_cast<const bf16_t*>(x), idx, N, k, M, D,

@@ -28,18 +28,18 @@ __global__ __launch_bounds__(256) void rank_from_idx_kernel(const int32_t* __res
     rank[(size_t)b * N + n] = (lo < k && row[lo] == n) ? lo : -1;
 }
 
-// grid (xcd_blocks(shares), B), block 256: the shares of a sample, ceil(N / (4*rows_per_wave)), in contiguous runs to the XCDs (see
-// xcd_share).  PAIR: two rows a wave, unrolled, so that the loads of both are in flight.
+// grid (xcd_blocks, B), block 256: the shares of a sample, ceil(N / (4*rows_per_wave)), to the XCDs in runs or in turn (xcd_share).
+// PAIR: two rows a wave, unrolled, so that the loads of both are in flight.
 template <bool PAIR>
 __global__ __launch_bounds__(256) void restore_kernel(const bf16_t* __restrict__ y_kept,
                                                       const int32_t* __restrict__ rank, int k,
                                                       const bf16_t* __restrict__ cache_map, int hc, int wc,
                                                       int h, int w, int D, bf16_t* __restrict__ y_out,
-                                                      int rows_per_wave, int shares) {
+                                                      int rows_per_wave, int shares, bool runs) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int b = blockIdx.y;
-    const int share = xcd_share(blockIdx.x, shares);   // (past the end: so are its rows)
+    const int share = xcd_share(blockIdx.x, shares, runs, b);   // (past the end: so are its rows)
     const int N = h * w;
     const int groups = (D + 511) >> 9;
     const int rows = PAIR ? 2 : rows_per_wave;
@@ -115,10 +115,11 @@ void launch_restore(const void* y_kept, const int32_t* rank, int B, int k, const
     const int N = h * w;
     const RestorePlan plan = restore_plan((long)B * N, w, D);
     const int shares = (N + 4 * plan.rows - 1) / (4 * plan.rows);
-    const dim3 grid(xcd_blocks(shares), B);
+    const bool runs = shares_in_runs(shares, w, plan.rows);
+    const dim3 grid(xcd_blocks(shares, runs), B);
     const auto launch = [&](auto* kernel) {
         kernel<<<grid, 256, 0, stream>>>(static_cast<const bf16_t*>(y_kept), rank, k, static_cast<const bf16_t*>(cache_map), hc,
-                                         wc, h, w, D, static_cast<bf16_t*>(y_out), plan.rows, shares);
+                                         wc, h, w, D, static_cast<bf16_t*>(y_out), plan.rows, shares, runs);
     };
     if (plan.pair) launch(&restore_kernel<true>);
     else launch(&restore_kernel<false>);

@@ -12,7 +12,7 @@ import torch
 from oracle import fastvar_oracle as O
 from paper_2503_23367_amd import binding as fb
 from paper_2503_23367_amd import synth
-from gpu_util import DEV, empty_ws, from_dev_bf16, max_rel, to_dev_bf16
+from gpu_util import DEV, empty_ws, from_dev_bf16, max_rel, to_dev_bf16, upload_weights
 
 pytestmark = pytest.mark.gpu
 
@@ -94,12 +94,34 @@ def test_restore_two_rows_a_wave(B, hc, wc, h, w, D, k):
     check("pair", B, hc, wc, h, w, D, k, use_rank=True, seed=5)
 
 
-@pytest.mark.parametrize("B,h,w", [(3, 1, 3), (9, 1, 1), (2, 18, 14), (2, 11, 23), (3, 16, 16), (2, 257, 1), (1, 75, 70), (1, 80, 86)])
+@pytest.mark.parametrize("B,h,w", [(3, 1, 3), (9, 1, 1), (2, 18, 14), (2, 11, 23), (3, 16, 16), (2, 257, 1), (1, 75, 70), (1, 80, 86),
+                                   (9, 13, 20), (3, 20, 33), (2, 70, 63), (1, 40, 128), (2, 39, 61)])
 def test_restore_shares_around_the_xcds(B, h, w):
-    """Workgroups in numbers that eight does and does not divide, samples that end inside one; the last two on both sides of where wide
-    rows go from one to two a wave."""
+    """Workgroups in numbers that eight does and does not divide, samples that end inside one; two on both sides of where wide rows go from
+    one to two a wave; runs that move on more than a round of samples, and shares dealt in turn, of one row a wave and of a pair."""
     D = 1288 if h > 40 else 72
     check("shares", B, max(1, h // 2), max(1, w // 2), h, w, D, h * w // 3, use_rank=True, seed=6)
+
+
+@pytest.mark.parametrize("B,h,w", [(9, 13, 20), (3, 16, 32), (2, 20, 33), (1, 24, 48), (1, 5, 65), (2, 3, 7)])
+def test_fill_of_a_step_equals_the_restoration(B, h, w):
+    """A step fills its pruned rows inside the gather's launch, by the restoration's code: the same map, bit for bit."""
+    dims, N, hc, wc = synth.BlockDims(D=64, H=1, dh=64, F=64), h * w, max(1, h // 2), max(1, w // 2)
+    k, L_cap = max(1, N // 3), (N // 3 + 15) // 8 * 8
+    print(f"[fill] B={B} map={h}x{w} k={k}", flush=True)
+    _, weights = upload_weights(synth.block_weights(3, dims))
+    cache, x = to_dev_bf16(synth.cached_map(3, B, hc, wc, 64)), to_dev_bf16(synth.token_map(3, B, h, w, 64))
+    kc, vc = (torch.zeros((B, 1, a, b), dtype=torch.bfloat16, device=DEV) for a, b in ((L_cap, 64), (64, L_cap)))
+    y = torch.full((B, N, 64), float("nan"), dtype=torch.bfloat16, device=DEV)
+    idx = torch.empty((B, k), dtype=torch.int32, device=DEV)
+    d = fb.make_dims(64, 1, 64, 64)
+    fb.fastvar_step(x, [hc, h], [wc, w], 1, 0, B, k, d, weights, kc, vc, 0, L_cap, cache, y, idx,
+                    empty_ws(fb.fastvar_step_workspace_bytes(d, B, N, k)))
+    kept = torch.gather(y, 1, idx.long()[..., None].expand(B, k, 64)).contiguous()
+    ref = torch.full_like(y, float("nan"))
+    fb.fastvar_restore(kept, idx, None, B, k, cache, hc, wc, h, w, 64, ref, empty_ws(fb.fastvar_restore_workspace_bytes(B, N)))
+    assert not torch.isnan(y).any()
+    assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
 
 
 def test_restore_special_cases_exact():

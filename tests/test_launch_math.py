@@ -30,8 +30,9 @@ void plan(int N, int K, int layernorm, int* out) {
     out[3] = fv::few_rows_share(K, p.cols);
 }
 int few_rows(int M, int N, int K, int split_k) { return fv::few_rows_product(M, N, K, split_k); }
-int xcd_share(int block, int n) { return fv::xcd_share(block, n); }
-int xcd_blocks(int n) { return fv::xcd_blocks(n); }
+int xcd_share(int block, int n, int runs, int sample) { return fv::xcd_share(block, n, runs, sample); }
+int xcd_blocks(int n, int runs) { return fv::xcd_blocks(n, runs); }
+int in_runs(int n, int w, int rows) { return fv::shares_in_runs(n, w, rows); }
 int column_chunks(int N, int D) { return fv::column_chunks(N, D); }
 void prefetch(const long* bytes, int n, int idle, double us, int cut, long* out) {
     const fv::PrefetchPlan p = fv::prefetch_plan(bytes, n, idle, us, cut);
@@ -312,16 +313,31 @@ def test_rows_of_a_restoring_wave(math):
 
 @pytest.mark.parametrize("n", list(range(1, 20)) + list(range(60, 75)) + [1000, 4097, 8192])
 def test_shares_of_the_xcds(math, n):
-    """Every share is taken once, by workgroups of one XCD for a contiguous run of them; what is left over is past the end."""
-    blocks = math.xcd_blocks(n)
-    share = [math.xcd_share(i, n) for i in range(blocks)]
-    assert sorted(share) == list(range(blocks)) and n <= blocks < n + 8
-    if n < 64:
-        assert blocks == n
-        return
-    assert blocks % 8 == 0
-    for xcd in range(8):
-        assert share[xcd::8] == list(range(xcd * (blocks // 8), (xcd + 1) * (blocks // 8)))
+    """Every share is taken once, in runs by workgroups of one XCD for a contiguous run of them; what is left over is past the end.  Over eight
+    samples every XCD has the same number of shares: the short run was always the same XCD's, and the others were waited for."""
+    assert [math.xcd_share(i, n, 0, 3) for i in range(math.xcd_blocks(n, 0))] == list(range(n))
+    assert not math.in_runs(n, 50, 1) if n < 64 else math.in_runs(n, 50, 1)
+    blocks = math.xcd_blocks(n, 1)
+    assert blocks % 8 == 0 and n <= blocks < n + 8
+    taken = [0] * 8
+    for sample in range(8):
+        share = [math.xcd_share(i, n, 1, sample) for i in range(blocks)]
+        assert sorted(share) == list(range(blocks))
+        for xcd in range(8):
+            first = share[xcd]
+            assert share[xcd::8] == list(range(first, first + blocks // 8))
+            taken[xcd] += sum(s < n for s in share[xcd::8])
+    assert taken == [n] * 8
+
+
+@pytest.mark.parametrize("rows", [1, 2])
+def test_shares_in_turn_where_columns_meet_on_an_xcd(math, rows):
+    """Shares dealt in turn are kept where most positions have the one below on their own XCD: widths near a multiple of 32 tokens a row of a
+    wave.  At 48, 80 and 112 columns a wave of one row has it four XCDs away."""
+    for w in range(1, 400):
+        same = sum(n // (4 * rows) % 8 == (n + w) // (4 * rows) % 8 for n in range(32 * rows)) / (32 * rows)
+        below = w > 16 * rows and same > 0.5   # (narrower: the next position is in the same share)
+        assert math.in_runs(1000, w, rows) == (not below), (w, same)
 
 
 def test_column_chunks_fit_the_scratch(math):
