@@ -61,9 +61,17 @@ FV_HOST_DEVICE int few_rows_columns(int N) {
 }
 // The rows of a product without a LayerNorm in front go through LDS where all of them fit beside the sums (us, weights from memory,
 // without / with: 1 / 4 / 8 rows of 2048 x 8192 10.7 / 8.2, 11.5 / 9.3, 12.1 / 10.4, of 1920 x 7680 10.4 / 7.8, 11.1 / 8.9, 11.9 / 9.9; 1 / 16 of 1024 x 4096 5.7 /
-// 4.9, 8.5 / 7.1, of 2048 x 2048 4.4 / 4.1, 5.7 / 4.9, of 448 x 2048 4.2 / 3.8, 5.5 / 4.6; nothing in it at 448 x 448).
+// 4.9, 8.5 / 7.1, of 2048 x 2048 4.4 / 4.1, 5.7 / 4.9, of 448 x 2048 4.2 / 3.8, 5.5 / 4.6; nothing in it at 448 x 448), whatever the number of
+// workgroups, also where 128 KB leave a CU one of them: QKV of 12 / 16 rows of 12288 x 4096 25.2 / 24.3, 27.1 / 25.2, 12 / 16 rows of 8192 x 4096 17.5 /
+// 16.4, 18.5 / 17.0, 12 of 16384 x 2048 17.1 / 15.0, 8 of 24576 x 2048 22.1 / 19.8, 1 / 8 of 16384 x 4096 24.3 / 23.4, 28.1 / 25.1, 1 of 8192 x 8192 30.4 /
+// 29.3.  The exception is one row over exactly a round of K in front of GELU or QKV, on as many workgroups a CU: there every load of a wave is out at
+// once, the row's behind the weights' (4096 / 12288 / 16384 / 24576 x 2048 5.4 / 5.65, 10.8 / 11.1, 13.3 / 13.8, 18.4 / 19.6; two rows 5.5 / 5.3, 11.0 / 10.7, 13.6 /
+// 13.3, 18.9 / 19.3; one of 6144 x 2048 7.7 / 7.6, of 12288 x 1984 10.5 / 9.8).
 constexpr int kFewRowsLds = 128 << 10;
-FV_HOST_DEVICE bool few_rows_in_lds(int M, int K) { return (long)M * K * 2 <= kFewRowsLds; }
+FV_HOST_DEVICE bool few_rows_in_lds(int M, int N, int K, bool layernorm) {
+    if (M == 1 && layernorm && K == kFewRowsRound && N % (16 * 256) == 0) return false;
+    return (long)M * K * 2 <= kFewRowsLds;
+}
 
 // Which product takes M rows: this one, or the tiled one of gemm.hip (split_k: which can split this K between
 // workgroups).  Every workgroup reads the rows' operands again, so the gain falls with the rows and with the number of

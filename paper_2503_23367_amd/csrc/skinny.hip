@@ -264,7 +264,7 @@ void launch(const GemmArgs& a, hipStream_t st) {
         static std::once_flag once;
         raise_lds_limit_once(once, &skinny_kernel<EPI, LN, CW, NW, U>, kFewRowsMax * (512 * U + 8) * sizeof(bf16_t));
         skinny_kernel<EPI, LN, CW, NW, U><<<grid, 64 * NW, (size_t)a.M * (a.K + 8) * sizeof(bf16_t), st>>>(a);
-    } else if (few_rows_in_lds(a.M, a.K)) {
+    } else if (few_rows_in_lds(a.M, a.N, a.K, EPI != EPI_BIAS_RES)) {
         static std::once_flag once;
         raise_lds_limit_once(once, &skinny_kernel<EPI, LN, CW, NW, U, true>, kFewRowsLds);
         const size_t rows_bytes = ((size_t)a.M * a.K * sizeof(bf16_t) + 1023) / 1024 * 1024;   // whole loads

@@ -142,11 +142,12 @@ def test_rope_without_an_index_list(name, dims, B, h, w, L0):
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 72, 64), (3, 72, 192), (5, 72, 576), (16, 72, 4096), (16, 72, 4160), (8, 72, 8192), (9, 72, 8192),
-                                   (1, 72, 65536), (1, 72, 65600)])
+                                   (1, 72, 65536), (1, 72, 65600), (1, 4096, 2048)])
 def test_rows_through_lds(M, N, K):
     """Rows that are not whole loads of 64 chunks, the most that LDS takes (128 KB) and one turn or row more, one of them in many
-    rounds of weights."""
+    rounds of weights; one row over a round of K, in LDS in front of a residual and not in front of GELU."""
     test_gemm_few_rows(M, N, K, fb.EPI_BIAS_RES)
+    test_gemm_few_rows(M, N, K, fb.EPI_BIAS_GELU)
 
 
 @pytest.mark.parametrize("B,N", [(1, 1), (1, 16), (3, 5)])
