@@ -607,6 +607,45 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     };
     if constexpr (RES && !ROWS_EARLY) load_rows(row_e);
     if constexpr (RES) static_for<0, RES_AHEAD>(load_residual);
+    // Rotary positions, wide tiles: the slots of the wave's rows are fetched together, then a row block's angles together, one row block ahead,
+    // both where registers are left, and without a branch (of columns past the keys any angle will do, it is not used).  Fetched where a run is turned,
+    // the one wave of a SIMD waited for memory once a run: over the plain epilogue a round of 256x256 tiles took 19 us, now 10, of 192x192 10 and
+    // 6, of 160x128 4.3 and 3.4 (QKV of 2048 / 4096 rows 2048 wide 56.5 -> 52.8, 110 -> 103, 3411 of 1536 64.0 -> 56.9, 7650 of 1024 74.4 -> 67.9).  Two waves
+    // a SIMD cover each other, and lose 0.3 to 1 us a round by fetching more than they use.
+    constexpr bool ROPE = EPI == EPI_QKV_ROPE, TURNS_EARLY = ROPE && WIDE;
+    constexpr int TURN_AHEAD = MI * NI <= 48 ? 1 : 0, TURNS = TURNS_EARLY ? TURN_AHEAD + 1 : 1;
+    constexpr bool SLOTS_EARLY = TURNS_EARLY && MI * NI <= 56;
+    int slots[SLOTS_EARLY ? MI : 1];
+    f32x2_t turn_cos[TURNS][NJ * RUNS], turn_sin[TURNS][NJ * RUNS];
+    const bool turns = TURNS_EARLY && n0e + wn * WTN < 2 * p.D;   // (wave uniform: some of its columns are queries or keys)
+    auto load_turn = [&](auto mi_c) {
+        constexpr int mi = decltype(mi_c)::value;
+        int slot = slots[SLOTS_EARLY ? mi : 0];
+        if constexpr (!SLOTS_EARLY) {
+            slot = min(m0e + wm * WTM + mi * 16 + row_e, p.M - 1);
+            slot = p.rope_rows ? p.rope_rows[slot] % p.rope_N : slot % p.k_tokens;
+        }
+        const size_t lane_at = (size_t)slot * (p.dh >> 1) + 2 * q_e;
+#pragma unroll
+        for (int i = 0; i < NJ * RUNS; ++i) {
+            const int first = ((n0e + wn * WTN + (i / RUNS) * 32) % p.dh + run_col(i % RUNS, 0)) / 2;
+            turn_cos[mi % TURNS][i] = *reinterpret_cast<const f32x2_t*>(p.rope_cos + lane_at + first);
+            turn_sin[mi % TURNS][i] = *reinterpret_cast<const f32x2_t*>(p.rope_sin + lane_at + first);
+        }
+    };
+    if constexpr (SLOTS_EARLY) {
+        if (turns) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) slots[mi] = min(m0e + wm * WTM + mi * 16 + row_e, p.M - 1);
+            if (p.rope_rows) {
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi) slots[mi] = p.rope_rows[slots[mi]];
+            }
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) slots[mi] = p.rope_rows ? slots[mi] % p.rope_N : slots[mi] % p.k_tokens;
+            if constexpr (TURN_AHEAD > 0) load_turn(std::integral_constant<int, 0>{});
+        }
+    }
     static_for<0, MI>([&](auto mi_c) {
         constexpr int mi = decltype(mi_c)::value;
         const int m = m0e + wm * WTM + mi * 16 + row_e;
@@ -621,8 +660,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
         const size_t orow = RES ? (size_t)out_row[RES ? mi : 0] : (size_t)mc;
         if constexpr (RES && mi + RES_AHEAD < MI) load_residual(std::integral_constant<int, mi + RES_AHEAD>{});
         bf16_t* const v_lane = p.v_cache + ((size_t)bq * p.H * p.dh + 4 * q_e) * p.L_cap + p.L0 + tq;
-        int slot = tq;   // rotary: the token's slot in its map
-        if (EPI == EPI_QKV_ROPE && p.rope_rows) slot = p.rope_rows[mc] % p.rope_N;
+        if constexpr (TURNS_EARLY && mi + TURN_AHEAD < MI) {
+            if (turns) load_turn(std::integral_constant<int, mi + TURN_AHEAD>{});
+        }
+        int slot = tq;   // the token's slot in its map
+        if (ROPE && !TURNS_EARLY && p.rope_rows) slot = p.rope_rows[mc] % p.rope_N;
         static_for<0, NJ>([&](auto nj_c) {
             constexpr int nj = decltype(nj_c)::value;
             const int nb = n0e + wn * WTN + nj * 32;      // first column of the block (wave uniform)
@@ -664,12 +706,14 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
                     v[0] += bf16_lo(rr.x); v[1] += bf16_hi(rr.x);
                     v[2] += bf16_lo(rr.y); v[3] += bf16_hi(rr.y);
                 }
-                if (EPI == EPI_QKV_ROPE) {
+                if constexpr (ROPE) {
                     // two interleaved pairs of one head, turned by the angles of the token's slot
-                    const int d = d0 + run_col(g, q_e);
-                    const size_t at = (size_t)slot * (p.dh >> 1) + (d >> 1);
-                    const f32x2_t cs = *reinterpret_cast<const f32x2_t*>(p.rope_cos + at);
-                    const f32x2_t sn = *reinterpret_cast<const f32x2_t*>(p.rope_sin + at);
+                    f32x2_t cs = turn_cos[mi % TURNS][nj * RUNS + g], sn = turn_sin[mi % TURNS][nj * RUNS + g];
+                    if constexpr (!TURNS_EARLY) {
+                        const size_t at = (size_t)slot * (p.dh >> 1) + ((d0 + run_col(g, q_e)) >> 1);
+                        cs = *reinterpret_cast<const f32x2_t*>(p.rope_cos + at);
+                        sn = *reinterpret_cast<const f32x2_t*>(p.rope_sin + at);
+                    }
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         const float a = v[2 * j], b = v[2 * j + 1];

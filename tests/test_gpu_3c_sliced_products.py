@@ -8,13 +8,13 @@ import torch
 from paper_2503_23367_amd import binding as fb
 from paper_2503_23367_amd import synth
 from gpu_util import DEV, empty_ws
-from tile_cases import QKV_TILES, SLICED_ALONE, SLICED_DIMS, SLICED_ROWS, TILES
+from tile_cases import QKV_SEAMS, QKV_TILES, ROPE_TILES, SEAMS, SLICED_ALONE, SLICED_DIMS, SLICED_ROWS, TILES
 from test_gpu_3_components import test_qkv_gemm_appends_to_caches as check_qkv
 from test_gpu_4_block import check_block
 
 pytestmark = pytest.mark.gpu
 
-@pytest.mark.parametrize("M,N,K,epi", [c for cases in TILES.values() for c in cases])
+@pytest.mark.parametrize("M,N,K,epi", [c for cases in [*TILES.values(), *SEAMS.values()] for c in cases])
 def test_tiles(M, N, K, epi):
     """Every tile shape (tile_cases.py), against fp32."""
     gen = torch.Generator(device=DEV)
@@ -33,6 +33,40 @@ def test_tiles(M, N, K, epi):
 @pytest.mark.parametrize("D,dh,B,k", list(QKV_TILES.values()))
 def test_qkv_tiles(D, dh, B, k):
     check_qkv(_dims(D, D // dh, dh, D), B, k, 5, (5 + k + 7) // 8 * 8)
+
+
+@pytest.mark.parametrize("rope", [False, True], ids=["plain", "rope"])
+@pytest.mark.parametrize("D,dh,B,k", [*QKV_SEAMS.values(), *ROPE_TILES.values()])
+def test_qkv_tiles_and_seams(D, dh, B, k, rope):
+    """Queries, keys and values of every tile and over the seams between a workgroup's tiles, against fp32; the kept slots of a larger map."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(D + k)
+    H, N, L0 = D // dh, k + 13, 5
+    L_cap = (L0 + k + 7) // 8 * 8 + 8
+    A, W, bias = (torch.randn(s, generator=gen, device=DEV).to(torch.bfloat16) for s in ((B * k, D), (3 * D, D), (3 * D,)))
+    W = (W * 0.2).contiguous()
+    idx = torch.stack([torch.randperm(N, generator=gen, device=DEV)[:k].sort().values for _ in range(B)]).to(torch.int32)
+    angle = torch.rand((N, dh // 2), generator=gen, device=DEV) * 6.3
+    cos, sin = angle.cos().contiguous(), angle.sin().contiguous()
+    q = torch.full((B, k, D), float("nan"), dtype=torch.bfloat16, device=DEV)
+    kc, vc = (torch.full((B, H, *s), float("nan"), dtype=torch.bfloat16, device=DEV) for s in ((L_cap, dh), (dh, L_cap)))
+    d = fb.make_dims(D, H, dh, D)
+    if rope:
+        fb.fastvar_qkv_gemm_rope(A, W, bias, idx, B, N, k, d, cos, sin, q, kc, vc, L0, L_cap)
+    else:
+        fb.fastvar_qkv_gemm(A, W, bias, B, k, d, q, kc, vc, L0, L_cap)
+    ref = torch.addmm(bias.float(), A.float(), W.float().T).view(B, k, 3, H, dh)
+    if rope:
+        c, s = (t[idx.long()].view(B, k, 1, dh // 2) for t in (cos, sin))
+        for part in (0, 1):
+            a, b = ref[:, :, part, :, 0::2].clone(), ref[:, :, part, :, 1::2].clone()
+            ref[:, :, part, :, 0::2], ref[:, :, part, :, 1::2] = a * c - b * s, a * s + b * c
+    got = (q.view(B, k, H, dh), kc[:, :, L0:L0 + k].permute(0, 2, 1, 3), vc[..., L0:L0 + k].permute(0, 3, 1, 2))
+    for part, g in enumerate(got):
+        err = (g.float() - ref[:, :, part]).abs().max() / ref[:, :, part].abs().max()
+        assert err <= 2.0 ** -7, (part, float(err))
+    for t, axis in ((kc, 2), (vc, 3)):
+        assert t.narrow(axis, 0, L0).isnan().all() and t.narrow(axis, L0 + k, L_cap - L0 - k).isnan().all()
 
 
 def _dims(D, H, dh, F):

@@ -7,7 +7,7 @@ import subprocess
 
 import pytest
 
-from tile_cases import QKV_TILES, SLICED_ALONE, SLICED_DIMS, SLICED_ROWS, TILES
+from tile_cases import QKV_SEAMS, QKV_TILES, ROPE_TILES, SEAMS, SLICED_ALONE, SLICED_DIMS, SLICED_ROWS, TILES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -165,8 +165,15 @@ def test_tile_cases_reach_their_tiles(math):
     for cfg, cases in TILES.items():
         for M, N, K, _ in cases:
             assert math.tile(0, M, N, K) == cfg, (M, N, K)
-    for cfg, (D, _, B, k) in QKV_TILES.items():
+    for cfg, (D, _, B, k) in [*QKV_TILES.items(), *QKV_SEAMS.items(), *ROPE_TILES.items()]:
         assert math.tile(1, B * k, 3 * D, D) == cfg, (B, k, D)
+    # a workgroup takes a second tile from 257 tiles on (one workgroup a CU)
+    sizes = {11: (256, 256), 38: (224, 256), 12: (256, 192), 37: (224, 192), 14: (192, 192), 13: (192, 256), 32: (256, 128)}
+    for cfg, cases in SEAMS.items():
+        for M, N, K, _ in cases:
+            assert math.tile(0, M, N, K) == cfg and -(-M // sizes[cfg][0]) * -(-N // sizes[cfg][1]) > 256, (M, N, K)
+    for cfg, (D, _, B, k) in QKV_SEAMS.items():
+        assert -(-B * k // sizes[cfg][0]) * -(-3 * D // sizes[cfg][1]) > 256, (B, k, D)
 
 
 # (qkv, M, N, K): the tile that was measured 6 % or more slower than the best one there, us

@@ -1,4 +1,4 @@
-"""Products of every tile shape of gemm.hip: the test on the GPU runs them, the one on the CPU checks that each reaches the tile
+"""Products of every tile shape of gemm_tiles.h: the test on the GPU runs them, the one on the CPU checks that each reaches the tile
 it is listed under, so that a change of the rule that picks tiles cannot leave one without a test."""
 BIAS_RES, BIAS_GELU = 1, 2
 
@@ -34,8 +34,21 @@ TILES = {
     11: [(2242, 5896, 192, BIAS_RES), (2244, 5904, 256, BIAS_GELU), (1573, 8224, 448, BIAS_RES)],   # 256x256
 }
 
-# tiles of QKV -> (D, dh, B, k): the one of its own, 64x64 with eight stages, and those whose workgroups walk several tiles
+# ... and those of GELU on the widest tiles, whose workgroups walk several tiles: more than a round of 256, in numbers that eight XCDs do and
+# do not share evenly, of K shorter than the ring, as long and longer
+SEAMS = {
+    11: [(2887, 10600, 192, BIAS_GELU), (2332, 11912, 448, BIAS_GELU), (5070, 6008, 1024, BIAS_GELU), (3516, 8632, 2048, BIAS_GELU)],
+    38: [(2517, 10600, 64, BIAS_GELU), (2147, 11256, 128, BIAS_GELU), (5810, 4696, 192, BIAS_GELU), (3331, 8304, 448, BIAS_GELU)],
+}
+
+# tiles of QKV -> (D, dh, B, k): the one of its own, 64x64 with eight stages, and some of the wide ones, with at most a round of tiles and more
 QKV_TILES = {15: (1152, 128, 1, 131), 37: (1344, 64, 2, 1283), 14: (1600, 64, 3, 1110), 13: (2368, 64, 3, 971)}
+# ... with more than a round of tiles each, plain and with rotary positions
+QKV_SEAMS = {11: (1152, 128, 2, 4315), 38: (1152, 64, 8, 911), 12: (1152, 64, 3, 2165), 37: (896, 128, 1, 7349), 14: (704, 64, 5, 1543),
+             13: (1344, 64, 3, 1799), 32: (704, 64, 3, 2409)}
+# ... and one of every other tile that rotary positions are turned on, within a round
+ROPE_TILES = {35: (2048, 128, 1, 679), 36: (1536, 128, 2, 688), 34: (1024, 64, 1, 1529), 40: (448, 64, 3, 538), 17: (448, 64, 3, 283),
+              16: (704, 64, 1, 237), 15: (1152, 128, 1, 135), 18: (448, 64, 3, 79)}
 
 # blocks whose out-proj and FC2 are cut into slices, on every tile that takes them: (D, H, dh, F) and (B, h, w, k)
 SLICED_DIMS = [(448, 7, 64, 2048), (1024, 16, 64, 4096), (1088, 17, 64, 8192), (4224, 33, 128, 4352)]
