@@ -183,7 +183,10 @@ FV_HOST_DEVICE TileChoice gemm_choose_tile(bool qkv, int M, int N, int K) {
     const int KT = K / 64;
     struct Cand { int cfg, bm, bn, slots; double fix, per_kt, longer; };
     const Cand cands[] = {
-        {TILE_64x32, 64, 32, 256, 2.1, 0.170, 0.0},        // the first three by the rules above, their times for the K slices below
+        // the first three by the rules above, their times for the K slices below, with round factors of their own: under those of the wide
+        // tiles they came out a microsecond short, and out-proj of 260 to 450 rows stayed whole (block of 259 / 286 rows 1920 wide 92.2 / 95.2 us,
+        // in two slices 90.8 / 94.0; stacks of eight blocks of 14x21 tokens 749 us 1920 wide, 761 whole, 874 and 890 2304 wide)
+        {TILE_64x32, 64, 32, 256, 2.1, 0.170, 0.0},
         {qkv && KT > 16 ? TILE_64x64_DEEP : TILE_64x64, 64, 64, 512, 2.7, 0.270, 0.0},
         {TILE_128x64, 128, 64, 256, 3.4, 0.335, 0.0},
         {TILE_128x128, 128, 128, 256, 3.33, 0.500, -0.023},
@@ -205,7 +208,8 @@ FV_HOST_DEVICE TileChoice gemm_choose_tile(bool qkv, int M, int N, int K) {
     TileChoice best{TILE_128x128, 1e30};
     for (int i = from; i < to; ++i) {
         const Cand& c = cands[i];
-        const double rounds = tile_rounds(M, N, c.bm, c.bn, c.slots, 1, 0.684, 0.311, 0.041, 0.062);
+        const double rounds = i < 3 ? tile_rounds(M, N, c.bm, c.bn, c.slots, 1, 0.777, 0.189, 0.037, 0.10)
+                                    : tile_rounds(M, N, c.bm, c.bn, c.slots, 1, 0.684, 0.311, 0.041, 0.062);
         const double t = 2.05 + rounds * (c.fix + KT * c.per_kt + (KT > 32 ? (KT - 32) * c.longer : 0.0));
         if (t < best.us) best = TileChoice{c.cfg, t};
     }
@@ -220,7 +224,7 @@ struct SplitKPlan {
     size_t bytes = 0;
 };
 // What the slices meet in.  A LayerNorm of the rows that follows anyway (out-proj of a whole block) adds them up for next to
-// nothing; where none does (a half of a block on its own), a launch of its own does, 3.0 us.  FC2 of a block has a LayerNorm
+// nothing; where none does (a half of a block on its own), a launch of its own does, 3.6 us.  FC2 of a block has a LayerNorm
 // behind it in a stack and none in a single step; both use one plan, so that a stack has the bits of its single blocks: half.
 enum SlicesMeet { MEET_IN_LAYERNORM = 0, MEET_IN_EITHER = 1, MEET_IN_LAUNCH = 2 };
 // Whether the K of such a product is cut, and on which tile.  Few output tiles leave CUs idle and make each of the others walk
@@ -228,12 +232,13 @@ enum SlicesMeet { MEET_IN_LAYERNORM = 0, MEET_IN_EITHER = 1, MEET_IN_LAUNCH = 2 
 // launch; a round of 256 workgroups at fix + K tiles of a slice * per_kt, a part-filled one 0.804 + 0.156 * fill, 3 % more where
 // the tiles do not divide evenly among the XCDs, 21 % with three, five or seven tile rows; 0.505 for every MB of slices; and the
 // meeting.  Against it the whole product at its tile's modelled time.  The constants are a fit to 480 products of seven models, 17 to 2600
-// rows, inside the calls that run them, by the time that the picks lose on the best candidate: 0.1 to 0.3 us a product.  A fit
+// rows, inside the calls that run them, on 32x32x16 instructions; on today's kernels, in 540 blocks and their halves (seven widths, the same rows), the
+// picks lose 0.05 (out-proj on its own) to 0.33 us (FC2 on its own) a product on the best candidate, with the meeting raised from 1.5 to 1.8.  A new fit of all
+// constants lost 0.05 to 0.31 and was up to 3 % slower on blocks that these pick right.  A fit
 // to 30 products of the large model lost 0.3 to 0.9, most of it in halves on their own, whose sum it took for free (attention
 // half of 357 rows 2304 wide 56.1 us, whole 51.0; of 443 rows of the small model 30.1 / 27.1), and at seven tile rows
-// (MLP half, 813 rows 1920 wide: two slices on 128x128 tiles 82.9, whole 78.8).  160x128 tiles in four slices are not taken: a full round of
-// them is slower than the model has it (576 x 2048 x 8192 5 us behind 192x128).  192x128 tiles run on four waves here, eight in whole products:
-// between them slices differ by -0.3 to 0.5 us.
+// (MLP half, 813 rows 1920 wide: two slices on 128x128 tiles 82.9, whole 78.8).  160x128 tiles in four slices are not offered: they win on 20 of 1002
+// products, around a full round (FC2 of 560 to 640 rows 1920 and 2048 wide, 1 to 8 us), and lose 4 us on the middle one.
 FV_HOST_DEVICE SplitKPlan gemm_splitk_plan(int M, int N, int K, SlicesMeet meet) {
     SplitKPlan best;
     if (few_rows_product(M, N, K, few_rows_tiled_splits(N, K))) return best;   // skinny.hip
@@ -248,7 +253,7 @@ FV_HOST_DEVICE SplitKPlan gemm_splitk_plan(int M, int N, int K, SlicesMeet meet)
             const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
             if (KT % s != 0 || KT / s < 4 || tiles * s > 256) continue;
             const double t = 2.2 + tile_rounds(M, N, c.bm, c.bn, 256, s, 0.804, 0.156, 0.033, 0.214) * (c.fix + KT / s * c.per_kt) +
-                             4.0e-6 * s * M * N * 0.505 + 1.5 * meet;
+                             4.0e-6 * s * M * N * 0.505 + 1.8 * meet;
             if (t < least) {
                 least = t;
                 best.splits = s;

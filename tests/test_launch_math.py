@@ -270,6 +270,16 @@ def test_slices_of_a_half_pay_for_their_own_launch(math):
         assert _slices(math, M, N, K, LAUNCH)[2] > 1 and _slices(math, M, N, K, EITHER)[2] > 1, (M, N, K)
 
 
+def test_slices_of_a_block_where_whole_small_tiles_are_slower(math):
+    """Out-proj inside a block, whose LayerNorm adds the slices up: whole, on 64x64 and 128x64 tiles that the model had a microsecond too
+    fast, stacks of 294 rows were 1.5 % slower (1920 wide 761 us for eight blocks, 749 in two slices; 2304 wide 890 / 874)."""
+    for M, D in [(259, 1920), (286, 1920), (294, 1920), (400, 1920), (294, 2304), (446, 2304)]:
+        assert _slices(math, M, D, D, LAYERNORM)[2] == 2, (M, D)
+    # ... but on their own the launch that adds up costs more than that (MLP half, slices / whole: 683 and 676 rows 2304 wide 73.8 / 65.9, 73.5 / 66.7)
+    for M, N, K in [(683, 2304, 6912), (676, 2304, 6912), (286, 1920, 1920)]:
+        assert _slices(math, M, N, K, LAUNCH)[2] == 1, (M, N, K)
+
+
 def test_slices_fit_their_launch(math):
     """At most a round of workgroups, whole K tiles in every slice, tiles and counts that the launches know, and scratch for them all."""
     for M in list(range(1, 140)) + [191, 256, 257, 400, 576, 731, 960, 1152, 2241, 4096, 70000]:
