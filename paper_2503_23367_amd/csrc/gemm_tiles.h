@@ -84,19 +84,15 @@ constexpr int waitcnt_imm(int vm, bool lgkm) {
 // XOR key that spreads the 16-byte chunks of consecutive rows over all 64 LDS
 // banks (256 bytes): a 16-byte-per-lane read is served 16 lanes at a time, so 16
 // consecutive rows must land in 16 different chunk columns.  Rows of 128 bytes
-// (8 chunks, two rows per bank sweep) use row bits 1-3; rows of 64 bytes (4
-// chunks, four rows per sweep) use row bits 2-3.
-template <int CPR>
-__device__ __forceinline__ int swz(int row) {
-    return CPR == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3);
-}
+// (8 chunks, two rows per bank sweep) use row bits 1-3.
+__device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 
 __device__ __forceinline__ f32x4_t mfma(const bf16x8_t& a, const bf16x8_t& b, const f32x4_t& c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
 // WGM x WGN waves tile the BM x BN block; KG such groups of waves split every K
-// tile between them (group g takes the g-th run of 16-wide k-steps) and are
+// tile between them (group g takes the g-th run of 32-wide k-steps) and are
 // summed through LDS at the end.  Eight waves (two per SIMD) cover each other's
 // barrier, load and LDS waits where the tile gives one wave per SIMD too little
 // independent work.
@@ -134,14 +130,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     constexpr int STAGE = A_TILE + W_TILE;
     static_assert(WTM % 16 == 0 && WTN % 32 == 0 && (BK / 32) % KG == 0, "wave tiles are made of pairs of 16x16x32 MFMAs");
     static_assert(A_LD * RPI * NW == BM && W_LD * RPI * NW == BN && NW % 2 == 0, "loads must tile the stage");
-    // When a stage is refilled.  EARLY: at the hand-over that frees it, all of the tile's loads at once (LPR
-    // after each operand read), so they have STAGES-1 whole tiles of matrix work to land in: what a ring of two
-    // stages needs, and all that there is room for where k-groups leave a wave few operand reads per tile.
-    // Otherwise spread over the k-steps of the following tile, one load per operand read: a
-    // quarter to three quarters of a tile later, which deeper rings can afford, and gentler on the hand-over.
-    constexpr int LPK = KK > 1 ? (LPT + KK - 2) / (KK - 1) : LPT;   // loads of a k-step
-    constexpr bool EARLY = STAGES <= 2 || KK == 1 || LPK > MI + NI;
-    constexpr int LPR = (LPT + MI + NI - 1) / (MI + NI);
+    // When a stage is refilled, one load per operand read.  EARLY, where k-groups leave a tile one k-step: at the hand-over that frees it.
+    // Otherwise during the first k-step of the following tile, half a tile later, which is gentler on the hand-over.  (Wide tiles have their
+    // own order, in the main loop.)
+    static_assert(CPR == 8 && KK <= 2, "rows of 128 bytes, at most two k-steps a tile");
+    constexpr bool EARLY = KK == 1;
     static_assert((STAGES - 1) * LPT <= 63, "vmcnt is 6 bits");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -205,7 +198,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
 #define FV_TILE_OFFSETS(lane_)                                                                  \
     {                                                                                           \
         const int ld_row_ = (lane_) / CPR;                                                      \
-        const int ld_chunk_ = ((lane_) % CPR) ^ swz<CPR>(wave * RPI + ld_row_);                 \
+        const int ld_chunk_ = ((lane_) % CPR) ^ swz(wave * RPI + ld_row_);                 \
         _Pragma("unroll") for (int j = 0; j < A_LD; ++j)                                        \
             a_off[j] = (uint32_t)(min(m0 + (wave + NW * j) * RPI + ld_row_, p.M - 1) * p.K + ld_chunk_ * 8) * 2u; \
         _Pragma("unroll") for (int j = 0; j < W_LD; ++j)                                        \
@@ -232,7 +225,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     const int frag_q = lane >> 4;
     const int a_row = wm * WTM + frag_row;  // + 16 mi
     const int w_row = wn * WTN + frag_row;  // + 16 ni
-    const int frag_sw = swz<CPR>(frag_row);
+    const int frag_sw = swz(frag_row);
 
 #define FV_LOAD_FRAGS(dst_a_, dst_w_, stage_, kk_)                                              \
     {                                                                                           \
@@ -244,8 +237,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
         _Pragma("unroll") for (int ni = 0; ni < NI; ++ni)                                       \
             dst_w_[ni] = *reinterpret_cast<const bf16x8_t*>(sw_ + (w_row + 16 * ni) * CPR + ch_); \
     }
-    // The same operand reads with the loads of a whole tile issued between them, LPR after each read
+    // The same operand reads with the loads of a whole tile issued between them, one after each read
     // (putting reads between the loads keeps the texture-address queue from filling up and stalling the wave).
+    static_assert(kWide<BM, BN, WGM, WGN, KG> || LPT <= MI + NI, "a load for every operand read at most");
 #define FV_LOAD_FRAGS_ISSUE(dst_a_, dst_w_, stage_, kk_, kt_, fill_)                            \
     {                                                                                           \
         const u32x4_t* sa_ = lds + (stage_) * STAGE;                                            \
@@ -258,26 +252,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
             else                                                                                \
                 dst_w_[g >= MI ? g - MI : 0] =                                                  \
                     *reinterpret_cast<const bf16x8_t*>(sw_ + (w_row + 16 * (g - MI)) * CPR + ch_); \
-            _Pragma("unroll") for (int u = 0; u < LPR; ++u)                                     \
-                if (g * LPR + u < LPT) FV_ISSUE_Q(kt_, fill_, g * LPR + u)                      \
-        }                                                                                       \
-    }
-
-    // ... and with slice part_ of nparts_ of a tile's loads, one load after each read.
-#define FV_LOAD_FRAGS_ISSUE_PART(dst_a_, dst_w_, stage_, kk_, kt_, fill_, part_, nparts_)       \
-    {                                                                                           \
-        const u32x4_t* sa_ = lds + (stage_) * STAGE;                                            \
-        const u32x4_t* sw_ = sa_ + A_TILE;                                                      \
-        const int ch_ = (4 * (kk0 + (kk_)) + frag_q) ^ frag_sw;                              \
-        const int q_lo_ = (part_) * LPT / (nparts_), q_hi_ = ((part_) + 1) * LPT / (nparts_); \
-        _Pragma("unroll") for (int g = 0; g < MI + NI; ++g) {                                   \
-            if (g < MI)                                                                         \
-                dst_a_[g < MI ? g : 0] =                                                        \
-                    *reinterpret_cast<const bf16x8_t*>(sa_ + (a_row + 16 * g) * CPR + ch_);     \
-            else                                                                                \
-                dst_w_[g >= MI ? g - MI : 0] =                                                  \
-                    *reinterpret_cast<const bf16x8_t*>(sw_ + (w_row + 16 * (g - MI)) * CPR + ch_); \
-            if (q_lo_ + g < q_hi_) FV_ISSUE_Q(kt_, fill_, q_lo_ + g)                            \
+            if (g < LPT) FV_ISSUE_Q(kt_, fill_, g)                                              \
         }                                                                                       \
     }
 
@@ -396,11 +371,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     _Pragma("unroll") for (int mi = (mi_lo_); mi < (mi_hi_); ++mi)                              \
         _Pragma("unroll") for (int ni = 0; ni < NI; ++ni)                                       \
             acc[mi][ni] = mfma(fw[cur_][ni], fa[cur_][mi], acc[mi][ni]);
-#define FV_INTERLEAVE(mfma_per_read_, with_dma_)                                                \
+#define FV_INTERLEAVE(mfma_per_read_)                                                           \
     _Pragma("unroll") for (int g = 0; g < MI + NI; ++g) {                                       \
         __builtin_amdgcn_sched_group_barrier(0x008, (mfma_per_read_), 0); /* MFMA */            \
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                /* DS read */         \
-        if (with_dma_) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0); /* direct-to-LDS load */ \
     }
     // One K tile.  Software pipeline inside the wave: the operand reads of the
     // next k-step are interleaved with the MFMAs of the current one (the
@@ -411,7 +385,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
     // this tile's stage is no longer being read) and preloads its first operands.
     // MORE_: a further tile is fetched, AHEAD tiles on: into the stage this tile
     // leaves, at its hand-over (EARLY), or into the stage the tile before it left,
-    // during its first k-steps.  The body is branch free on purpose: the
+    // during its first k-step.  The body is branch free on purpose: the
     // accumulators must stay in one register class across the loop.
 #define FV_TILE_BODY(MORE_, HANDOVER_, WAITN_)                                                  \
     {                                                                                           \
@@ -423,11 +397,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
             const int cur_ = kk & 1, nxt_ = cur_ ^ 1;                                           \
             if (kk + 1 < KK) {                                                                  \
                 if ((MORE_) && !EARLY)                                                          \
-                    FV_LOAD_FRAGS_ISSUE_PART(fa[nxt_], fw[nxt_], stage, kk + 1, kt + AHEAD, fill_, kk, KK - 1) \
+                    FV_LOAD_FRAGS_ISSUE(fa[nxt_], fw[nxt_], stage, kk + 1, kt + AHEAD, fill_) \
                 else                                                                            \
                     FV_LOAD_FRAGS(fa[nxt_], fw[nxt_], stage, kk + 1)                            \
                 FV_MFMA_ROWS(cur_, 0, MI)                                                       \
-                FV_INTERLEAVE((MI * NI) / (MI + NI), false)                                     \
+                FV_INTERLEAVE((MI * NI) / (MI + NI))                                            \
             } else if (HANDOVER_) {                                                             \
                 __builtin_amdgcn_s_waitcnt(waitcnt_imm((WAITN_), true));                        \
                 asm volatile("" ::: "memory");                                                  \
@@ -438,7 +412,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
                 else                                                                            \
                     FV_LOAD_FRAGS(fa[nxt_], fw[nxt_], next_stage_, 0)                           \
                 FV_MFMA_ROWS(cur_, 0, MI)                                                       \
-                FV_INTERLEAVE((MI * NI) / (MI + NI), false)                                     \
+                FV_INTERLEAVE((MI * NI) / (MI + NI))                                            \
             } else {                                                                            \
                 FV_MFMA_ROWS(cur_, 0, MI)                                                       \
             }                                                                                   \
@@ -478,7 +452,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
                     if constexpr (!last) FV_WIDE_READ(nxt, sa, sw, kk + 1, rd)
                     else if constexpr (R >= 1) FV_WIDE_READ(nxt, sa1, sw1, 0, rd)
                 }
-                // loads: a window opens at a hand-over, for the stages that it frees; every other slot
+                // loads: a window opens at a hand-over, for the stages that it frees; one every LS slots
                 constexpr int q = last ? (s >= SB && (s - SB) % LS == 0 ? (s - SB) / LS : -1)
                                        : ((kk * SLOTS + s) % LS == LS / 2 ? W3 + (kk * SLOTS + s) / LS : -1);
                 if constexpr (q >= 0 && q < A_LD) {
@@ -762,7 +736,6 @@ __global__ __launch_bounds__(64 * WGM * WGN * KG) void gemm_nt_kernel(const Gemm
 #undef FV_ISSUE_TILE
 #undef FV_ISSUE_Q
 #undef FV_DMA16
-#undef FV_LOAD_FRAGS_ISSUE_PART
 #undef FV_LOAD_FRAGS_ISSUE
 #undef FV_LOAD_FRAGS
 #undef FV_TILE_OFFSETS
