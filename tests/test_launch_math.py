@@ -176,12 +176,12 @@ def test_tile_cases_reach_their_tiles(math):
         assert -(-B * k // sizes[cfg][0]) * -(-3 * D // sizes[cfg][1]) > 256, (B, k, D)
 
 
-# (qkv, M, N, K): the tile that was measured 6 % or more slower than the best one there, us
-SLOWER = [((0, 320, 6336, 192), 13), ((0, 1462, 4224, 640), 13),                       # 14.9 / 7.4, 17.5 / 14.7
-          ((0, 3309, 4096, 16384), 35), ((0, 787, 4096, 16384), 35), ((0, 10418, 2560, 8192), 34),   # 453 / 392, 142 / 112, 455 / 401
-          ((1, 4242, 6912, 2304), 34), ((1, 1095, 7680, 2560), 34),                    # 153 / 139, 59.4 / 54.2
-          ((0, 391, 256, 128), 18), ((0, 284, 1216, 192), 18),                         # 4.97 / 4.71, 4.96 / 4.55
-          ((1, 68, 5760, 1920), 16), ((1, 76, 6144, 2048), 16)]                        # 12.5 / 11.5, 12.7 / 11.5
+# (qkv, M, N, K): a tile that is 3 to 50 % slower there than the one picked, us
+SLOWER = [((0, 320, 6336, 192), 13), ((0, 1462, 4224, 640), 13),                       # 11.2 / 5.6, 19.2 / 15.0
+          ((0, 3309, 4096, 16384), 35), ((0, 787, 4096, 16384), 35), ((0, 10418, 2560, 8192), 34),   # 399 / 314, 158 / 117, 429 / 328
+          ((1, 4242, 6912, 2304), 34), ((1, 1095, 7680, 2560), 34),                    # 152 / 116, 64 / 43
+          ((0, 391, 256, 128), 18), ((0, 284, 1216, 192), 18),                         # 4.40 / 4.02, 4.23 / 4.11
+          ((1, 68, 5760, 1920), 16), ((1, 76, 6144, 2048), 16)]                        # 11.9 / 10.7, 12.0 / 10.7
 
 
 def test_tiles_are_not_the_ones_measured_slower(math):
@@ -199,7 +199,7 @@ def test_tiles_are_not_the_ones_measured_slower(math):
 
 # tiles on four waves, one a SIMD (rows, columns, stages of W), those of other rings that one may want, and rings of two
 WIDE = [(256, 256, 3), (256, 192, 3), (224, 256, 3), (224, 192, 3), (224, 128, 3), (192, 256, 3), (192, 192, 3), (160, 128, 4),
-        (128, 128, 3), (128, 128, 4), (128, 128, 5), (192, 192, 2), (256, 128, 3)]
+        (128, 128, 3), (128, 128, 4), (128, 128, 5), (128, 64, 6), (192, 192, 2), (256, 128, 3)]
 
 
 @pytest.mark.parametrize("bm,bn,stages", WIDE)
