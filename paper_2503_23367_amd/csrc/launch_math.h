@@ -73,7 +73,7 @@ FV_HOST_DEVICE bool few_rows_in_lds(int M, int N, int K, bool layernorm) {
     return (long)M * K * 2 <= kFewRowsLds;
 }
 
-// Which product takes M rows: this one, or the tiled one of gemm.hip (split_k: which can split this K between
+// Which product takes M rows: this one, or the tiled one of gemm_tiles.h (split_k: which can split this K between
 // workgroups).  Every workgroup reads the rows' operands again, so the gain falls with the rows and with the number of
 // workgroups; and a K of several rounds waits for memory once a round, for longest where the last round is part-filled.
 // us, tiled / this one, weights from memory:
@@ -220,7 +220,7 @@ FV_HOST_DEVICE TileChoice gemm_choose_tile(bool qkv, int M, int N, int K) {
 // and leave fp32 sums [splits][M][N] in scratch; splits == 1: no scratch needed.
 struct SplitKPlan {
     int splits = 1;
-    int cfg = 0;        // tile of the slices (gemm.hip)
+    int cfg = 0;        // tile of the slices (gemm_sliced.hip)
     size_t bytes = 0;
 };
 // What the slices meet in.  A LayerNorm of the rows that follows anyway (out-proj of a whole block) adds them up for next to

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void gather_layernorm_fill_kernel(const bf16_t
     }
 }
 
-// What is left of a product whose K was cut into slices (gemm.hip): a workgroup adds up the slices of one row, wave w
+// What is left of a product whose K was cut into slices (gemm_sliced.hip): a workgroup adds up the slices of one row, wave w
 // the column groups w, w + WAVES, ... of 512, all loads of a group in flight at once, and the residual, and rounds once.  LN: the rows
 // meet in LDS and the first wave normalises them, by the LayerNorm launch's own code and from the same rounded values, so a
 // row has the bits that two launches would give it.  Bound by the slices' bytes (6.2 TB/s behind 3 us: 960 rows of 2048 columns

@@ -1,5 +1,5 @@
 // GEMMs of at most kFewRowsMax rows (the first scales of a schedule): C[m,n] = sum_k A[m,k] * W[n,k], with the
-// same fused epilogues as gemm.hip and, for the QKV and FC1 products, the LayerNorm of the rows in front.
+// same fused epilogues as gemm_tiles.h and, for the QKV and FC1 products, the LayerNorm of the rows in front.
 //
 // At these row counts a block is one pass over its weights (100 MB for the large model), and the time goes to what
 // surrounds that pass: a launch per LayerNorm, rings that fill and drain, partial tiles that travel through
